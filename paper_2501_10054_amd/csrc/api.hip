@@ -143,6 +143,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
         char* scratch = nullptr;
         L->prefill_chunk = env_int("TARDIS_PREFILL_CHUNK", 16384, 64, 32768);
         if (L->prefill_chunk > L->max_batch) L->prefill_chunk = (int32_t)L->max_batch;
+        TD_TRY(td_gemm_init());
         TD_TRY(dev_alloc(&scratch, td_prefill_scratch_bytes(L, L->prefill_chunk)));
         L->pf_scratch = scratch;
     }

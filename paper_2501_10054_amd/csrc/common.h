@@ -116,7 +116,7 @@ struct tardis_layer_s {
     bf16_t* bt_delta;              // 64 x h repair factors
     float* bt_partial;             // partial products of the scatter step
     int32_t use_batched;
-    void* pf_scratch;              // prompt path: int8 tokens, exponents, int32 sums, pre-activations, delta, fp32 y
+    void* pf_scratch;              // prompt path: int8 tokens, exponents, aligned tokens, repair factors, fp32 partial sums of y
     int32_t prefill_min_tokens;    // calls with at least this many tokens take the prompt path (if it has scratch)
     int32_t prefill_chunk;         // ... in chunks of at most this many tokens (what the scratch is sized for)
     int32_t* rec_count;            // two-kernel path: flagged neurons per predictor block,
@@ -239,22 +239,26 @@ tardis_status_t td_estimate_errors(const tardis_ffn_desc* desc, const void* X, i
 tardis_status_t td_assign_thresholds(const float* err, int64_t n, float t, float t_min, float t_max, float* out,
                                      hipStream_t s);
 tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s);
-// gemm.hip:  C[m][n] = sum_k A[m][k] * B[n][k]  (+ C if accumulate) (+ row_bias[m]); C fp32, ldc = N
-tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
-                           int32_t dtype, int accumulate, const void* row_bias, hipStream_t s);
-// exact int8 x int8 -> int32 product of the same form (K a multiple of 16, operands 16-byte aligned)
-tardis_status_t td_gemm_nt_i8(const int8_t* A, const int8_t* B, int32_t* C, int64_t M, int64_t N, int64_t K,
-                              int splits, hipStream_t s);
-// decode.hip
+// gemm.hip:  C[m][n] = sum_k A[m][k] * B[n][k] (+ the same of A2, B2 unless null) (+ row_bias[m]); C fp32, ldc = N
+tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
+                           int64_t K, int32_t dtype, const void* row_bias, hipStream_t s);
+// the products of calls with many tokens, each with the step that follows it (see gemm.hip)
+tardis_status_t td_gemm_predict(const int8_t* XQ, const int8_t* Q, const int32_t* e, const float* tlo, const float* thi,
+                                uint32_t* mask, int mask_words, int64_t n, int64_t h, int64_t d, hipStream_t s);
+tardis_status_t td_gemm_hidden(const void* X, const void* W1, const void* b1, const float* a, const float* c,
+                               const uint32_t* mask, int mask_words, int act, void* out, int64_t n, int64_t h, int64_t d,
+                               hipStream_t s);
+tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
+                               int64_t n, int64_t d, int64_t h, hipStream_t s);
+size_t td_gemm_part_floats(int64_t n, int64_t d);
+tardis_status_t td_gemm_init();
+// prefill.hip
 bool td_prefill_supported(const tardis_layer_s* L);
 size_t td_prefill_scratch_bytes(const tardis_layer_s* L, int64_t n);
 tardis_status_t td_forward_prefill(tardis_layer_s* L, const void* x, int64_t n, void* y, int norm_out, hipStream_t s);
 tardis_status_t td_dense_prefill(tardis_layer_s* L, const void* x, int64_t n, void* y, hipStream_t s);
 bool td_layer_is_live(const tardis_layer_s* L);
-tardis_status_t td_gemm_init();
-int td_gemm_tile_rows(int64_t M);
-tardis_status_t td_gemm_nt_split(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
-                                 int accumulate, const void* row_bias, int splits, hipStream_t s);
+// decode.hip
 tardis_status_t td_decode_init();
 bool td_decode_fused_supported(const tardis_layer_s* L);
 constexpr int kDecodeMaxTokens = 16;  // tokens one weight pass of the decode kernel can be shared between

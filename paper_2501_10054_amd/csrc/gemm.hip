@@ -6,10 +6,10 @@
 // calibration pre-activations Z^T = W1 . X_cal^T (Sec. "Non-linear Function
 // Approximation", step 2) with A = W1 (h x d) and B = X_cal (n x d).  Used online for calls with
 // many tokens (prompts), where every step of the method is a product of the token matrix with a
-// weight matrix: predictor sums Xq . Q^T (int8), pre-activations X . W1^T, folded product X . W'^T
-// and the down projection of the masked delta.
+// weight matrix: predictor sums Xq . Q^T (int8) and their range test, pre-activations X . W1^T and the
+// repair factors of the flagged ones, and the folded product together with the down projection of the
+// masked factors, [X | D] . [W' | W2]^T.
 #include <cstdlib>
-#include <type_traits>
 
 #include "common.h"
 
@@ -78,31 +78,38 @@ gemm_nt_generic_kernel(const T* __restrict__ A, const T* __restrict__ B, float* 
 
 
 // ------------------------------------------------------------------ MFMA (bf16 or int8)
-// 256x256 output tile per block of 4 wavefronts (2x2, 128x128 each = 4x4 MFMA 32x32 tiles, 256
-// accumulators per lane), K in slices of 128 bytes per row (64 bf16 or 128 int8: the byte
-// geometry of the two is the same, 16 bytes per lane and MFMA) staged through two LDS stages
-// (rows padded to 144 bytes) and two register sets.
+// One kernel for every product on the matrix cores, with the step that follows the product in its
+// epilogue.  Output tile TM x TN = (WM*NA*16) x ((8/WM)*NB*16), 8 wavefronts in a WM x (8/WM) grid, each
+// NA x NB tiles of v_mfma_f32_16x16x32_bf16 / v_mfma_i32_16x16x64_i8 (the byte geometry of the two is the
+// same: 16 bytes per lane and MFMA).  K runs in slices of 128 bytes per row.
 //
-// Schedule of one slice (four steps of 16 MFMAs each).  A wavefront issues in order and each SIMD
-// holds one wavefront here, so whatever is not an MFMA is placed BETWEEN the MFMAs of a step, a
-// few instructions after each, instead of after them where the matrix cores would idle:
-//   step 1-2 the register set that holds slice kt+1 -> the other LDS stage
-//   barrier
-//   step 3   reads the first fragments of that stage; loads of slice kt+3 -> the set just freed
-//            (they are written to LDS six steps later)
-// and every step reads the LDS fragments of the next one.  On MI355X this runs the fold at about
-// 1 PFLOP/s; what remains is the LDS traffic (each staged byte is written once and read by two
-// wavefronts: 1536 LDS cycles against 2048 MFMA cycles per slice) and the global-load path.
+// What bounds it.  With real (not constant) data the chip is power limited: the clock settles where the
+// energy per MFMA and per moved byte allows (a loop of nothing but 16x16x32 MFMAs on random data runs at
+// 1.95-2.0 PFLOP/s, of 32x32x16 ones at 1.75; with zeros 2.4), and every stall raises the clock it would
+// need.  Hence:
+//  * 16x16 MFMAs;
+//  * slices go from memory straight to LDS (buffer_load ... lds): no staging registers and no LDS writes by
+//    the wavefronts.  A load instruction covers 8 rows x 128 bytes; half lines (64 bytes per row) fetch
+//    every line twice from L2 (0.94 against 1.13 PFLOP/s);
+//  * a lane asks for the 16-byte piece (slot ^ row) of its row, so that the fragment reads below (16 rows,
+//    same piece) hit all banks: no padding, no conflicts;
+//  * A has SA and B has SB slice buffers, together up to 160 KB.  The loads that refill the buffers of
+//    slice kt are issued, between MFMAs, right after the barrier behind which nobody reads them any more,
+//    and are waited for SB-1 / SA-1 slices later (never for the newest ones);
+//  * fragments of the next half slice are read while the MFMAs of this one run.  The MFMAs are inline
+//    assembly because the compiler, given the builtins, moves accumulators between the two register files;
+//  * blocks start at different slices (rotated within a window of 8 between the blocks of an XCD, which
+//    share lines in its L2, and by an eighth of K from XCD to XCD): with all of them at the same column of
+//    K the requests crowd onto few memory channels (zeros: 358 -> 300 us at 4096 x 4096 x 16384).
+// 4096 x 4096 x 16384 in bf16 with random data: 390 us, 1.41 PFLOP/s (one wavefront per SIMD with staging
+// through registers, which was here before: 605 us, 0.91).
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int MT = 256;
-constexpr int MKB = 128;                             // bytes of one staged row slice
-constexpr int MSTRIDE = MKB + 16;                    // bytes per staged row (padded)
-constexpr int mfma_stage_bytes(int im) { return (64 * im + MT) * MSTRIDE; }   // A tile (64*im rows) + B tile
-constexpr int mfma_lds_bytes(int im) { return 2 * mfma_stage_bytes(im); }
+constexpr int kSliceBytes = 128;
+constexpr int kWavesPerTile = 8;
+constexpr int kLdsBytes = 160 * 1024;
 
 // Which block computes which tile.  Blocks b, b+8, b+16, ... run on one XCD and share its L2, so
 // each XCD gets a rectangle of rm x rn tiles (the 8 XCDs form a gm x gn grid over the tile grid,
@@ -111,229 +118,480 @@ constexpr int mfma_lds_bytes(int im) { return 2 * mfma_stage_bytes(im); }
 // other's slices of A and B from L2 instead of fetching them from HBM again.
 struct TileMap {
     int tiles_m, tiles_n;      // tile grid of C
-    int splits;                // K ranges (1, 2, 4 or 8); more than one: results are added atomically into C
+    int splits;                // K ranges (1, 2, 4 or 8)
     int gn;                    // XCD grid columns (rows = 8 / splits / gn)
     int rm, rn;                // tiles per XCD rectangle
     int group;                 // tile rows walked together
     int slices;                // K slices per range
 };
 
-TileMap make_tile_map(int64_t M, int64_t N, int64_t K, int es, int splits, int tile_rows) {
+TileMap make_tile_map(int64_t M, int64_t N, int tile_m, int tile_n, int slices, int splits) {
     TileMap t;
-    t.tiles_m = (int)((M + tile_rows - 1) / tile_rows);
-    t.tiles_n = (int)((N + 255) / 256);
+    t.tiles_m = (int)((M + tile_m - 1) / tile_m);
+    t.tiles_n = (int)((N + tile_n - 1) / tile_n);
     t.splits = splits;
     const int nx = 8 / splits;
     int best = 1 << 30, gm = nx;
     for (int cand = 1; cand <= nx; cand *= 2) {            // cand = XCD grid rows
         const int rm = (t.tiles_m + cand - 1) / cand, rn = (t.tiles_n + nx / cand - 1) / (nx / cand);
-        if (rm + rn < best) { best = rm + rn; gm = cand; }
+        const int cost = rm * rn * 4096 + rm * tile_m + rn * tile_n;   // fewest blocks, then least operand bytes
+        if (cost < best) { best = cost; gm = cand; }
     }
     t.gn = nx / gm;
     t.rm = (t.tiles_m + gm - 1) / gm;
     t.rn = (t.tiles_n + t.gn - 1) / t.gn;
     t.group = t.rm < 8 ? t.rm : 8;
-    const int nk = (int)((K * es + 127) / 128);
-    t.slices = (nk + splits - 1) / splits;
+    t.slices = (slices + splits - 1) / splits;
     return t;
 }
 
-// RAGGED: K is not a multiple of the slice; the last slice is then moved back to end at K and the
-// pieces it shares with the slice before it are zeroed on their way to LDS (costs four selects
-// per LDS write, so it is a variant of its own).
-// IM: 32-row MFMA tiles per wavefront along M - the output tile is (64*IM) x 256.  IM = 4 is the
-// square tile for large products; IM = 2 and 1 serve products with at most 128 / 64 rows (a few
-// dozen tokens against a weight matrix), which are bound by the stream of B, not by the MFMAs.
-template <bool I8, bool ATOMIC, bool RAGGED, int IM>
-__global__ void __launch_bounds__(256)
-gemm_nt_mfma_kernel(const unsigned char* __restrict__ A0, const unsigned char* __restrict__ B0, void* __restrict__ Cv,
-                    int64_t M, int64_t N, int64_t K0, int accumulate, const bf16_t* __restrict__ row_bias,
-                    TileMap tm) {
-    constexpr int ES = I8 ? 1 : 2;                   // bytes per element
-    constexpr int MK = MKB / ES;                     // elements per K slice
-    constexpr int PER = 16 / ES;                     // elements per 16-byte chunk
-    constexpr int MTA = 64 * IM;                     // rows of the A tile
-    constexpr int NLA = 2 * IM;                      // loads per thread and slice for A (8 for B)
-    constexpr int MSTAGE = mfma_stage_bytes(IM);
-    typedef typename std::conditional<I8, i32x16_t, f32x16_t>::type acc_t;
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+// C = A.B^T (+ A2.B2^T: a second pair of operands whose K follows the first's).  Rows of A are rows of
+// C (M of them), rows of B columns of C (N); k, k2: bytes of a row of the first / second pair.
+struct GemmArgs {
+    const unsigned char *A, *B, *A2, *B2;
+    int64_t M, N;
+    uint32_t k, k2;
+    // epilogues
+    float* C;                      // F32: M x N; PART: [split][M][N]
+    const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, DELTA: per column
+    bf16_t* out;                   // HIDDEN, DELTA: M x N
+    const float *lo, *hi;          // PRED: bounds per column;  DELTA: slope and intercept per column
+    const int32_t* e;              // PRED: exponent per row
+    uint32_t* mask;                // PRED: written, DELTA: read; M x mask_words
+    int mask_words;
+    int act;
+};
+
+enum { EPI_F32, EPI_PART, EPI_PRED, EPI_DELTA, EPI_HIDDEN };
+
+__device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    i32x4_t r;
+    r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r.y = __builtin_amdgcn_readfirstlane((int)((a >> 32) & 0xffffu));
+    r.z = __builtin_amdgcn_readfirstlane((int)bytes);
+    r.w = 0x00020000;
+    return r;
+}
+
+// 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
+// (m0 is set and used in the one statement; the compiler keeps nothing in it)
+__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
+}
+
+// round to nearest even, in one instruction
+__device__ __forceinline__ uint32_t to_bf16(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+
+template <bool I8> struct Mma;
+template <> struct Mma<false> {
+    typedef f32x4_t acc_t;
+    static __device__ __forceinline__ void go(acc_t& c, const td_u32x4& a, const td_u32x4& b) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+    }
+};
+template <> struct Mma<true> {
+    typedef i32x4_t acc_t;
+    static __device__ __forceinline__ void go(acc_t& c, const td_u32x4& a, const td_u32x4& b) {
+        asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+    }
+};
+
+// RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
+// slice start instead (in bounds) and the fragments that hold them are zeroed as they are read.
+template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
+struct GemmTile {
+    static constexpr int WN = kWavesPerTile / WM;
+    static constexpr int TM = WM * NA * 16, TN = WN * NB * 16;
+    static constexpr int UA = TM * kSliceBytes, UB = TN * kSliceBytes;      // bytes of one slice
+    static constexpr int LA = TM / 64, LB = TN / 64;                        // loads per wavefront and slice
+    // as many slices as fit; A one ahead of B where the two do not fit equally often
+    static constexpr int SB = kLdsBytes / (UA + UB) > 6 ? 6 : kLdsBytes / (UA + UB);
+    static constexpr int SA = SB < 6 && SB * (UA + UB) + UA <= kLdsBytes ? SB + 1 : SB;
+    static constexpr int kRing = SA * UA + SB * UB;
+    static constexpr int kPer = LA + LB;
+    // loads that may still be in flight when slice kt+2 has to be there (see the order in the kernel)
+    static constexpr int kWaitB = LA + (SB - 2) * kPer, kWaitA = (SA - 2) * kPer;
+    static constexpr int kWait = kWaitB < kWaitA ? kWaitB : kWaitA;
+    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_DELTA ? 10 : 4);   // LDS of a wavefront in the epilogue
+    static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_DELTA ? 3 * TN * 4 : 0);
+    static constexpr int kLds = kRing > kEpiLds ? kRing : kEpiLds;
+    static_assert(SB >= 2 && SA >= 2 && kWait + kPer <= 63 && kLds <= kLdsBytes, "slice buffers");
+};
+
+template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
+__global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) {
+    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
+    typedef typename Mma<I8>::acc_t acc_t;
+    constexpr int WN = G::WN, TM = G::TM, TN = G::TN, SA = G::SA, SB = G::SB, LA = G::LA, LB = G::LB;
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
 
     const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
     const int ks = xcd % tm.splits, xg = xcd / tm.splits;
     const int per_group = tm.group * tm.rn;
-    const int g = local / per_group, r = local % per_group;
-    const int gsz = min(tm.group, tm.rm - g * tm.group);
-    const int tile_m = (xg / tm.gn) * tm.rm + g * tm.group + r % gsz;
+    const int grp = local / per_group, r = local % per_group;
+    const int gsz = min(tm.group, tm.rm - grp * tm.group);
+    const int tile_m = (xg / tm.gn) * tm.rm + grp * tm.group + r % gsz;
     const int tile_n = (xg % tm.gn) * tm.rn + r / gsz;
     if (tile_m >= tm.tiles_m || tile_n >= tm.tiles_n) return;
-    const int64_t m0 = (int64_t)tile_m * MTA, n0 = (int64_t)tile_n * MT;
-    // this block's range of K: operands advanced to its start, K = what remains from there
-    const int64_t kskip = (int64_t)ks * tm.slices * MK;
-    if (kskip >= K0) return;
-    const int64_t K = K0 - kskip;
-    const int nk = min((int)((K + MK - 1) / MK), tm.slices);
+    const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
 
-    acc_t acc[IM][4];
-#pragma unroll
-    for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    // slices [s0, s0 + nk) of this block's range, starting at s0 + rot
+    const int nk1 = (int)((p.k + kSliceBytes - 1) / kSliceBytes), nk2 = (int)((p.k2 + kSliceBytes - 1) / kSliceBytes);
+    const int s0 = ks * tm.slices;
+    const int nk = max(0, min(tm.slices, nk1 + nk2 - s0));
+    const int rot = nk > 0 ? ((local & 7) + xcd * nk / 8) % nk : 0;
+    auto slice_of = [&](int kt) { const int s = kt + rot; return s0 + (s >= nk ? s - nk : s); };
 
-    // staging map: chunk c = tid + 256*i, i = 0..7 -> row c/8, 16-byte piece c%8.  The address of
-    // a load is a wave-uniform base (tile start + slice) plus one of eight lane offsets, the same
-    // for both operands (same row pitch).  Rows past the matrix read row 0 of the tile instead;
-    // they are not zeroed: they only reach output rows and columns that are never stored.
-    td_u32x4 ra0[NLA], rb0[8], ra1[NLA], rb1[8];
-    const int srow = tid >> 3, spiece = tid & 7;
-    unsigned offa[NLA], offb[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const unsigned off = (unsigned)(((32 * i + srow) * K0 + spiece * PER) * ES);
-        if (i < NLA) offa[i] = m0 + 32 * i + srow < M ? off : 0u;
-        offb[i] = n0 + 32 * i + srow < N ? off : 0u;
+    const uint32_t rows_a = (uint32_t)min((int64_t)TM, p.M - m0), rows_b = (uint32_t)min((int64_t)TN, p.N - n0);
+    const i32x4_t ra1 = buffer_of(p.A + (size_t)m0 * p.k, rows_a * p.k), rb1 = buffer_of(p.B + (size_t)n0 * p.k, rows_b * p.k);
+    const i32x4_t ra2 = buffer_of(p.A2 + (size_t)m0 * p.k2, rows_a * p.k2), rb2 = buffer_of(p.B2 + (size_t)n0 * p.k2, rows_b * p.k2);
+
+    // lane -> row lane/8 of the 8 rows of a load, slot lane%8; wavefront w loads rows [w*TM/8, (w+1)*TM/8) of A, of B alike
+    const int lrow = lane >> 3, piece = (lane & 7) ^ (lrow & 7);   // (row & 7 == lrow: blocks of 8 rows)
+    uint32_t lds_a, lds_b;
+    {
+        const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+        lds_a = __builtin_amdgcn_readfirstlane(base + wave * (G::UA / kWavesPerTile));
+        lds_b = __builtin_amdgcn_readfirstlane(base + SA * G::UA + wave * (G::UB / kWavesPerTile));
     }
-    const unsigned char* tileA = A0 + (m0 * K0 + kskip) * ES;
-    const unsigned char* tileB = B0 + (n0 * K0 + kskip) * ES;
-    // slices past the last one re-read slice 0 (never multiplied): every load below is issued
-    // unconditionally, so the number of loads in flight at each wait is known statically
-    auto fetch = [&](td_u32x4 (&ra)[NLA], td_u32x4 (&rb)[8], unsigned& keep, int kt) {
-        const int64_t k0 = (int64_t)kt * MK;
-        int64_t kb = kt < nk ? k0 : 0;
-        keep = 1u;
+    const uint32_t row_a = (uint32_t)(wave * (TM / 8) + lrow), row_b = (uint32_t)(wave * (TN / 8) + lrow);
+    auto load_one = [&](bool is_a, int i, uint32_t buf, int kt) {
+        const bool live = kt < nk;
+        const int s = live ? slice_of(kt) : 0;
+        const bool second = s >= nk1;
+        const uint32_t soff = (uint32_t)(second ? s - nk1 : s) * kSliceBytes;
+        const uint32_t pitch = second ? p.k2 : p.k;
+        i32x4_t rs = is_a ? (second ? ra2 : ra1) : (second ? rb2 : rb1);
+        rs.z = live ? rs.z : 0;                                     // past the last slice: an empty buffer
+        uint32_t pc = (uint32_t)piece * 16u;
+        if constexpr (RAGGED) pc = soff + pc < pitch ? pc : 0u;
+        const uint32_t voff = ((is_a ? row_a : row_b) + 8u * i) * pitch + pc;
+        load_to_lds(is_a ? lds_a + buf * G::UA + i * 1024u : lds_b + buf * G::UB + i * 1024u, voff, rs, soff);
+    };
+
+    acc_t acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[i][j][q] = 0;
+
+    // fragments: lane holds 16 bytes of row lane%16 at piece 4*half + lane/16
+    const int frow = lane & 15, fp = lane >> 4;
+    uint32_t fsw[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) fsw[s] = (uint32_t)(frow * kSliceBytes + (((s * 4 + fp) ^ (frow & 7)) * 16));
+    td_u32x4 fa[2][NA], fb[2][NB];
+    auto read_one = [&](int buf, int t, uint32_t ba, uint32_t bb, int s, int slice) {   // fa[0], all of fb, the rest of fa
+        td_u32x4 v;
+        if (t == 0 || t > NB)
+            v = *reinterpret_cast<const td_u32x4*>(lds + ba * G::UA + (wm * NA + (t == 0 ? 0 : t - NB)) * 2048 + fsw[s]);
+        else
+            v = *reinterpret_cast<const td_u32x4*>(lds + SA * G::UA + bb * G::UB + (wn * NB + t - 1) * 2048 + fsw[s]);
         if constexpr (RAGGED) {
-            if (kt < nk && k0 + MK > K) kb = K - MK;                  // the last slice, moved back
-            keep = kb + spiece * PER >= k0 ? 1u : 0u;
+            const bool second = slice >= nk1;
+            const uint32_t at = (uint32_t)(second ? slice - nk1 : slice) * kSliceBytes + (uint32_t)(s * 4 + fp) * 16u;
+            if (at >= (second ? p.k2 : p.k)) v = td_u32x4{0, 0, 0, 0};
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (i < NLA) ra[i] = *reinterpret_cast<const td_u32x4*>(tileA + kb * ES + offa[i]);
-            rb[i] = *reinterpret_cast<const td_u32x4*>(tileB + kb * ES + offb[i]);
-        }
+        if (t == 0 || t > NB) fa[buf][t == 0 ? 0 : t - NB] = v; else fb[buf][t - 1] = v;
     };
-    auto stash_rows = [&](auto& rr, unsigned keep, unsigned char* dst) {     // rr: NLA or 8 row groups
-        const td_u32x4 zero = {0, 0, 0, 0};
+    constexpr int NM = NA * NB, NR = NA + NB;
+    constexpr int kReadEvery = NM / NR > 2 ? 2 : (NM / NR > 0 ? NM / NR : 1), kReadsPer = (NR + NM - 1) / NM;
+    constexpr int kLoadEvery = NM / G::kPer > 0 ? NM / G::kPer : 1;
+    static_assert(kLoadEvery * G::kPer <= NM, "a slice's loads fit between its MFMAs");
+
+    // In period p (the half of slice p behind the barrier, and the first half of slice p+1) the loads of
+    // B(p+SB) and then of A(p+SA) are issued; the prologue issues those of periods -SB .. -1.
 #pragma unroll
-        for (int i = 0; i < (int)(sizeof(rr) / sizeof(rr[0])); ++i)
-            *reinterpret_cast<td_u32x4*>(dst + 32 * i * MSTRIDE) = (!RAGGED || keep) ? rr[i] : zero;
-    };
-    auto stash_a = [&](const td_u32x4 (&rr)[NLA], unsigned keep, int stage) {
-        stash_rows(rr, keep, lds + stage * MSTAGE + srow * MSTRIDE + spiece * 16);
-    };
-    auto stash_b = [&](const td_u32x4 (&rr)[8], unsigned keep, int stage) {
-        stash_rows(rr, keep, lds + stage * MSTAGE + MTA * MSTRIDE + srow * MSTRIDE + spiece * 16);
-    };
-    const int frow = lane & 31, fk = (lane >> 5) * 16;  // fragment row and byte offset of its 16 bytes of k
-    td_u32x4 fa[2][IM], fb[2][4];
-    auto read_frags = [&](td_u32x4 (&da)[IM], td_u32x4 (&db)[4], int stage, int kstep) {
-        const unsigned char* as = lds + stage * MSTAGE + (wm * 32 * IM + frow) * MSTRIDE + fk + kstep * 32;
-        const unsigned char* bs = lds + stage * MSTAGE + MTA * MSTRIDE + (wn * 128 + frow) * MSTRIDE + fk + kstep * 32;
+    for (int s = 0; s < SA - SB; ++s)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i < IM) da[i] = *reinterpret_cast<const td_u32x4*>(as + i * 32 * MSTRIDE);
-            db[i] = *reinterpret_cast<const td_u32x4*>(bs + i * 32 * MSTRIDE);
-        }
-    };
-    auto mfma16 = [&](const td_u32x4 (&ua)[IM], const td_u32x4 (&ub)[4]) {   // 4 * IM MFMAs
+        for (int i = 0; i < LA; ++i) load_one(true, i, s, s);
 #pragma unroll
-        for (int i = 0; i < IM; ++i)
+    for (int s = 0; s < SB; ++s) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (I8)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4_t, ua[i]),
-                                                                      __builtin_bit_cast(i32x4_t, ub[j]), acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ua[i]),
-                                                                        __builtin_bit_cast(bf16x8_t, ub[j]), acc[i][j], 0, 0, 0);
+        for (int i = 0; i < LB; ++i) load_one(false, i, s, s);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) load_one(true, i, s + SA - SB, s + SA - SB);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(G::kWait + G::kPer) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    uint32_t ba = 0, bb = 0;
+    if (nk > 0) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t) read_one(0, t, 0, 0, 0, slice_of(0));
+    }
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kt = 0; kt < nk; ++kt) {
+        const uint32_t na = ba + 1 == SA ? 0 : ba + 1, nb = bb + 1 == SB ? 0 : bb + 1;
+        const int cur = RAGGED ? slice_of(kt) : 0, nxt = RAGGED ? slice_of(kt + 1 < nk ? kt + 1 : kt) : 0;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+#pragma unroll
+            for (int u = 0; u < kReadsPer; ++u) {
+                const int t = (q / kReadEvery) * kReadsPer + u;
+                if (q % kReadEvery == 0 && t < NR) read_one(1, t, ba, bb, 1, cur);
             }
-    };
-    // the scheduler is told the order inside a step of the square tile: one MFMA, `alu` VALU/SALU
-    // instructions, and after every `every`-th MFMA one memory instruction of class `cls` (0x020
-    // load, 0x200 LDS write).  The short tiles have 4 or 8 MFMAs per step and are bound by the
-    // stream of B: the compiler's own order serves them.
-#define TD_GEMM_INTERLEAVE(alu, cls, every)                                          \
-    _Pragma("unroll") for (int q = 0; q < 16; ++q) {                                 \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                           \
-        __builtin_amdgcn_sched_group_barrier(0x006, alu, 0);                         \
-        if (q % every == every - 1) __builtin_amdgcn_sched_group_barrier(cls, 1, 0); \
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (RAGGED) asm volatile("s_nop 1");
+            Mma<I8>::go(acc[q / NB][q % NB], fb[0][q % NB], fa[0][q / NB]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // slice kt+1 has arrived (this wavefront's share; the barrier makes it everybody's) and the last
+        // fragments of slice kt are in registers
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G::kWait) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+#pragma unroll
+            for (int u = 0; u < kReadsPer; ++u) {
+                const int t = (q / kReadEvery) * kReadsPer + u;
+                if (q % kReadEvery == 0 && t < NR) read_one(0, t, na, nb, 0, nxt);
+            }
+            if (q % kLoadEvery == 0) {
+                const int t = q / kLoadEvery;
+                if (t < LB) load_one(false, t, bb, kt + SB);
+                else if (t < LB + LA) load_one(true, t - LB, ba, kt + SA);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (RAGGED) asm volatile("s_nop 1");
+            Mma<I8>::go(acc[q / NB][q % NB], fb[1][q % NB], fa[1][q / NB]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ba = na;
+        bb = nb;
     }
-    // `sa`/`sb` (holding slice kt+1) go to the other LDS stage in steps 1-2 and are reloaded with
-    // slice kt+3 in step 3; the other register set (slice kt+2) stays in flight through the phase
-    auto phase = [&](int stage, td_u32x4 (&sa)[NLA], td_u32x4 (&sb)[8], unsigned& skeep, int lkt) {
-        read_frags(fa[1], fb[1], stage, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma16(fa[0], fb[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(fa[0], fb[0], stage, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma16(fa[1], fb[1]);
-        stash_b(sb, skeep, stage ^ 1);
-        if constexpr (IM == 4) { TD_GEMM_INTERLEAVE(RAGGED ? 3 : 1, 0x200, 2) }
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(fa[1], fb[1], stage, 3);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma16(fa[0], fb[0]);
-        stash_a(sa, skeep, stage ^ 1);
-        if constexpr (IM == 4) { TD_GEMM_INTERLEAVE(RAGGED ? 3 : 1, 0x200, 2) }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        read_frags(fa[0], fb[0], stage ^ 1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma16(fa[1], fb[1]);
-        fetch(sa, sb, skeep, lkt);
-        if constexpr (IM == 4) { TD_GEMM_INTERLEAVE(2, 0x020, 1) }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-#undef TD_GEMM_INTERLEAVE
+    // (the products are in inline assembly: their results are waited for here)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 
-    unsigned keep0 = 1u, keep1 = 1u;
-    fetch(ra0, rb0, keep0, 0);
-    fetch(ra1, rb1, keep1, 1);
-    stash_a(ra0, keep0, 0);
-    stash_b(rb0, keep0, 0);
-    fetch(ra0, rb0, keep0, 2);
-    __syncthreads();
-    read_frags(fa[0], fb[0], 0, 0);
-    int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        phase(0, ra1, rb1, keep1, kt + 3);           // multiplies slice kt, stages slice kt+1
-        phase(1, ra0, rb0, keep0, kt + 4);           // multiplies slice kt+1, stages slice kt+2
-    }
-    if (kt < nk) phase(0, ra1, rb1, keep1, kt + 3);  // odd count: the last slice
-
-    // D layout of the 32x32 tile: column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4
+    // acc[i][j][q] = C[row m0 + (wm*NA + i)*16 + lane%16][column n0 + (wn*NB + j)*16 + 4*(lane/16) + q]
+    const int64_t mw = m0 + wm * NA * 16, nw = n0 + wn * NB * 16;   // this wavefront's corner
+    constexpr int CW = NB * 16;                                      // its columns
+    if constexpr (EPI == EPI_F32 || EPI == EPI_PART) {
+        // 16 rows at a time through LDS, so that a store covers whole lines of a row
+        float* chunk = reinterpret_cast<float*>(lds + wave * G::kEpiWave);
+        float* C = EPI == EPI_PART ? p.C + (size_t)ks * p.M * p.N : p.C;
 #pragma unroll
-    for (int i = 0; i < IM; ++i) {
+        for (int i = 0; i < NA; ++i) {
+            const int64_t m = mw + i * 16 + frow;
+            float rb = 0.0f;
+            if (EPI == EPI_F32 && p.bias && m < p.M) rb = td_bf16_to_f32(p.bias[m]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t m = m0 + wm * 32 * IM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (m >= M) continue;
+            for (int j = 0; j < NB; ++j) {
+                f32x4_t v;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t n = n0 + wn * 128 + j * 32 + (lane & 31);
-                if (n >= N) continue;
-                if constexpr (I8) {
-                    int32_t* C = static_cast<int32_t*>(Cv);
-                    if constexpr (ATOMIC)
-                        __hip_atomic_fetch_add(C + m * N + n, acc[i][j][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    else
-                        C[m * N + n] = acc[i][j][r];
-                } else {
-                    float* C = static_cast<float*>(Cv);
-                    float v = acc[i][j][r] + ((row_bias && ks == 0) ? td_bf16_to_f32(row_bias[m]) : 0.0f);
-                    if constexpr (ATOMIC) {
-                        __hip_atomic_fetch_add(C + m * N + n, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    } else {
-                        if (accumulate) v += C[m * N + n];
-                        C[m * N + n] = v;
-                    }
+                for (int q = 0; q < 4; ++q) v[q] = acc[i][j][q] + rb;
+                // (pieces of 16 bytes rotated by the row, against bank conflicts)
+                *reinterpret_cast<f32x4_t*>(chunk + frow * CW + (((j * 4 + fp) ^ (frow & (NB * 4 - 1))) * 4)) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < 16 * CW / 64; ++u) {
+                const int at = u * 64 + lane, row = at / CW, col = at % CW;
+                const float v = chunk[row * CW + (((col >> 2) ^ (row & (NB * 4 - 1))) * 4) + (col & 3)];
+                const int64_t mm = mw + i * 16 + row, nn = nw + col;
+                if (mm < p.M && nn < p.N) C[mm * p.N + nn] = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    } else if constexpr (EPI == EPI_PRED) {
+        // range test; the four lanes of a row and (where the tile holds them) two tile columns make a word of 32 bits
+        f32x4_t lo[NB], hi[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int64_t n = nw + j * 16 + 4 * fp;                  // N % 4 == 0: all four or none
+            lo[j] = n < p.N ? *reinterpret_cast<const f32x4_t*>(p.lo + n) : f32x4_t{0, 0, 0, 0};
+            hi[j] = n < p.N ? *reinterpret_cast<const f32x4_t*>(p.hi + n) : f32x4_t{0, 0, 0, 0};
+        }
+        int ex[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) ex[i] = mw + i * 16 + frow < p.M ? p.e[mw + i * 16 + frow] : 0;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int64_t m = mw + i * 16 + frow;
+            const int e = ex[i];
+            uint32_t word[(NB + 1) / 2];
+#pragma unroll
+            for (int w = 0; w < (NB + 1) / 2; ++w) word[w] = 0u;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                uint32_t nib = 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = ldexpf((float)acc[i][j][q], e);
+                    if (!((v >= lo[j][q]) && (v < hi[j][q]))) nib |= 1u << q;
+                }
+                if (nw + j * 16 + 4 * fp >= p.N) nib = 0u;
+                word[j / 2] |= nib << (4 * fp + 16 * (j & 1));
+            }
+#pragma unroll
+            for (int w = 0; w < (NB + 1) / 2; ++w) {
+                word[w] |= __shfl_xor(word[w], 16);
+                word[w] |= __shfl_xor(word[w], 32);
+                const int64_t n = nw + w * 32;
+                if (fp == 0 && m < p.M && n < p.N) {
+                    uint32_t* row = p.mask + (size_t)m * p.mask_words;
+                    if constexpr (NB >= 2) row[n >> 5] = word[w];
+                    else reinterpret_cast<uint16_t*>(row)[n >> 4] = (uint16_t)word[w];
                 }
             }
+            if constexpr (NB == 1) {                                 // the upper half of a last word nobody else writes
+                if (fp == 0 && m < p.M && nw < p.N && nw + 16 >= p.N && ((nw >> 4) & 1) == 0)
+                    reinterpret_cast<uint16_t*>(p.mask + (size_t)m * p.mask_words)[(nw >> 4) + 1] = 0;
+            }
+        }
+    } else {
+        // DELTA: D = sigma(z) - (a z + c) where the mask has a bit, else 0.  The flagged elements (few) of 16
+        // rows are listed in LDS first and then evaluated 64 at a time: evaluating all 128 accumulators of a
+        // lane would run sigma 128 times per wavefront, the list needs about (share flagged) x 128 runs.
+        // HIDDEN: sigma(z + b) of every element.
+        bf16_t* chunk = reinterpret_cast<bf16_t*>(lds + wave * G::kEpiWave);
+        uint2* list = reinterpret_cast<uint2*>(lds + wave * G::kEpiWave + 16 * CW * 2);
+        float* par = reinterpret_cast<float*>(lds + kWavesPerTile * G::kEpiWave);
+        uint32_t bits[EPI == EPI_DELTA ? NA : 1];                        // bit 4j + q of this lane's elements
+        if constexpr (EPI == EPI_DELTA) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                const int64_t m = mw + i * 16 + frow;
+                bits[i] = 0u;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const int64_t n = nw + j * 16 + 4 * fp;
+                    if (m < p.M && n < p.N)
+                        bits[i] |= ((p.mask[(size_t)m * p.mask_words + (n >> 5)] >> (n & 31)) & 15u) << (4 * j);
+                }
+            }
+            for (int c = tid; c < TN; c += 512) {
+                const int64_t n = n0 + c < p.N ? n0 + c : p.N - 1;
+                par[c] = td_bf16_to_f32(p.bias[n]);
+                par[TN + c] = p.lo[n];
+                par[2 * TN + c] = p.hi[n];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            if constexpr (EPI == EPI_DELTA) {
+                const td_u32x4 zero = {0, 0, 0, 0};
+                for (int v = lane; v < 16 * CW / 8; v += 64) reinterpret_cast<td_u32x4*>(chunk)[v] = zero;
+                __builtin_amdgcn_wave_barrier();
+                int total = 0;
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const bool flagged = (bits[i] >> (4 * j + q)) & 1u;
+                        const unsigned long long all = __ballot(flagged);
+                        if (flagged) {
+                            const int at = total + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32),
+                                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
+                            list[at] = make_uint2(__float_as_uint((float)acc[i][j][q]), (uint32_t)(frow * CW + j * 16 + 4 * fp + q));
+                        }
+                        total += __popcll(all);
+                    }
+                __builtin_amdgcn_wave_barrier();
+                for (int t = lane; t < total; t += 64) {
+                    const uint2 en = list[t];
+                    const int c = wn * CW + (int)(en.y % CW);
+                    const float z = __uint_as_float(en.x) + par[c];
+                    chunk[en.y] = td_f32_to_bf16(td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]));
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const int64_t n = nw + j * 16 + 4 * fp;
+                    uint2 b = make_uint2(0u, 0u);
+                    if (n < p.N) b = *reinterpret_cast<const uint2*>(p.bias + n);
+                    const float bv[4] = {__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u),
+                                         __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
+                    uint32_t o[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[q] = to_bf16(td_act((float)acc[i][j][q] + bv[q], p.act));
+                    *reinterpret_cast<uint2*>(chunk + frow * CW + j * 16 + 4 * fp) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (int v = lane; v < 16 * CW / 8; v += 64) {           // N % 8 == 0: whole 16-byte vectors
+                const int row = v / (CW / 8), col = (v % (CW / 8)) * 8;
+                const int64_t mm = mw + i * 16 + row, nn = nw + col;
+                if (mm < p.M && nn < p.N)
+                    *reinterpret_cast<td_u32x4*>(p.out + mm * p.N + nn) = reinterpret_cast<const td_u32x4*>(chunk)[v];
+            }
+            __builtin_amdgcn_wave_barrier();
         }
     }
+}
+
+// The tile for a product: the one whose rounds over 256 CUs cost least.  A block spends per slice either the
+// cycles of its MFMAs or those in which its share of L2 bandwidth (about 34 bytes per cycle and CU, measured
+// above) delivers the two operand slices.  `splittable`: K may be cut into 2, 4 or 8 ranges (each then adds
+// the partial tile's bytes, written and read again; at most kPartRows rows of partial sums are kept).
+constexpr int64_t kPartRows = 4096;
+struct TileChoice { int shape, splits; };
+constexpr int kShapeM[] = {256, 192, 256, 192, 128, 128}, kShapeN[] = {256, 256, 128, 128, 128, 64};
+
+TileChoice choose_tile(int64_t M, int64_t N, int64_t slices, bool splittable, bool store_f32) {
+    TileChoice best{0, 1};
+    double best_cost = 1e300;
+    for (int s = 0; s < 6; ++s)
+        for (int sp = 1; sp <= (splittable ? 8 : 1); sp *= 2) {
+            if (sp > 1 && (slices / sp < 8 || sp * M > kPartRows)) break;
+            const TileMap t = make_tile_map(M, N, kShapeM[s], kShapeN[s], (int)slices, sp);
+            const int64_t per_xcd = (int64_t)t.rm * t.rn;              // blocks of one XCD (of one range): 32 at once
+            const double mfma = 2100.0 * kShapeM[s] * kShapeN[s] / 65536.0, feed = (kShapeM[s] + kShapeN[s]) * 128.0 / 34.0;
+            const double tail = 3000.0 + (store_f32 ? 0.12 : 0.06) * kShapeM[s] * kShapeN[s];
+            const double cost = (double)((per_xcd + 31) / 32) * ((double)t.slices * (mfma > feed ? mfma : feed) + tail) +
+                                (splittable ? sp * (double)M * (double)N * 8.0 / 2000.0 : 0.0);   // partial sums, about 2 KB a cycle
+            if (cost < best_cost) { best_cost = cost; best = {s, sp}; }
+        }
+    return best;
+}
+
+template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
+void launch_shape(const GemmArgs& p, int splits, hipStream_t s) {
+    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
+    const int slices = (int)((p.k + 127) / 128 + (p.k2 + 127) / 128);
+    const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, splits);
+    hipLaunchKernelGGL((gemm_tile_kernel<I8, EPI, RAGGED, WM, NA, NB>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
+}
+
+template <bool I8, int EPI, bool RAGGED>
+void launch_tile(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
+    switch (c.shape) {
+        case 0: launch_shape<I8, EPI, RAGGED, 2, 8, 4>(p, c.splits, s); break;
+        case 1: launch_shape<I8, EPI, RAGGED, 2, 6, 4>(p, c.splits, s); break;
+        case 2: launch_shape<I8, EPI, RAGGED, 2, 8, 2>(p, c.splits, s); break;
+        case 3: launch_shape<I8, EPI, RAGGED, 2, 6, 2>(p, c.splits, s); break;
+        case 4: launch_shape<I8, EPI, RAGGED, 2, 4, 2>(p, c.splits, s); break;
+        default: launch_shape<I8, EPI, RAGGED, 2, 4, 1>(p, c.splits, s); break;
+    }
+}
+
+template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB> tardis_status_t raise_shape() {
+    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
+    TD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<I8, EPI, RAGGED, WM, NA, NB>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds));
+    return TARDIS_OK;
+}
+
+template <bool I8, int EPI, bool RAGGED> tardis_status_t raise_lds() {
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 8, 4>()));
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 6, 4>()));
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 8, 2>()));
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 6, 2>()));
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 4, 2>()));
+    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 4, 1>()));
+    return TARDIS_OK;
 }
 
 template <typename T>
@@ -344,31 +602,14 @@ void launch_generic(const void* A, const void* B, float* C, int64_t M, int64_t N
                        static_cast<const T*>(B), C, M, N, K, accumulate, static_cast<const T*>(row_bias));
 }
 
-__global__ void __launch_bounds__(256) gemm_zero_kernel(uint32_t* __restrict__ p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0u;
-}
-
-// The kernels that add atomically (K cut into ranges, and every short-tile variant) need C to
-// hold the value they add onto: zeros unless the caller accumulates.
-void zero_result(void* C, int64_t M, int64_t N, hipStream_t s) {
-    const size_t n = (size_t)M * (size_t)N;
-    const unsigned blocks = (unsigned)((n / 4 + 255) / 256 < 4096 ? (n / 4 + 255) / 256 + 1 : 4096);
-    hipLaunchKernelGGL(gemm_zero_kernel, dim3(blocks), dim3(256), 0, s, static_cast<uint32_t*>(C), n);
-}
-
-template <bool I8, bool ATOMIC, bool RAGGED, int IM>
-void launch_mfma(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int accumulate,
-                 const void* row_bias, const TileMap& tm, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_nt_mfma_kernel<I8, ATOMIC, RAGGED, IM>), dim3(8 * tm.rm * tm.rn), dim3(256),
-                       mfma_lds_bytes(IM), s, static_cast<const unsigned char*>(A),
-                       static_cast<const unsigned char*>(B), C, M, N, K, accumulate,
-                       static_cast<const bf16_t*>(row_bias), tm);
-}
-
 bool gemm_force_generic() {
     const char* v = std::getenv("TARDIS_GEMM_GENERIC");
     return v && v[0] == '1';
 }
+
+const unsigned char* bytes_of(const void* p) { return static_cast<const unsigned char*>(p); }
+bool is_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+int64_t slices_of(int64_t bytes) { return (bytes + kSliceBytes - 1) / kSliceBytes; }
 
 }  // namespace
 
@@ -376,79 +617,120 @@ bool gemm_force_generic() {
 tardis_status_t td_gemm_init() {
     static td_once once;
     return once.run([]() -> tardis_status_t {
-        struct { const void* fn; int lds; } kernels[] = {
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<false, false, false, 4>), mfma_lds_bytes(4)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<false, false, true, 4>), mfma_lds_bytes(4)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<false, true, false, 4>), mfma_lds_bytes(4)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<true, false, false, 4>), mfma_lds_bytes(4)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<true, true, false, 4>), mfma_lds_bytes(4)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<false, true, false, 2>), mfma_lds_bytes(2)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<true, true, false, 2>), mfma_lds_bytes(2)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<false, true, false, 1>), mfma_lds_bytes(1)},
-            {reinterpret_cast<const void*>(gemm_nt_mfma_kernel<true, true, false, 1>), mfma_lds_bytes(1)}};
-        for (const auto& k : kernels)
-            TD_HIP(hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds));
+        TD_TRY((raise_lds<false, EPI_F32, false>()));
+        TD_TRY((raise_lds<false, EPI_F32, true>()));
+        TD_TRY((raise_lds<false, EPI_PART, false>()));
+        TD_TRY((raise_lds<false, EPI_PART, true>()));
+        TD_TRY((raise_lds<true, EPI_PRED, false>()));
+        TD_TRY((raise_lds<false, EPI_DELTA, false>()));
+        TD_TRY((raise_lds<false, EPI_HIDDEN, false>()));
         return TARDIS_OK;
     });
 }
 
-// rows of the output tile the matrix-core kernel uses for a product with M rows
-int td_gemm_tile_rows(int64_t M) { return M <= 64 ? 64 : (M <= 128 ? 128 : 256); }
-
-tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
-                           int accumulate, const void* row_bias, hipStream_t s) {
-    return td_gemm_nt_split(A, B, C, M, N, K, dtype, accumulate, row_bias, 1, s);
-}
-
-// the same with K cut into `splits` ranges (1, 2, 4, 8) that run as separate blocks - for products
-// whose tile grid alone would leave most of the chip idle.  The ranges add their partial sums into C
-// atomically (C is zeroed first unless `accumulate`); so do the short-tile variants (M <= 128).
-tardis_status_t td_gemm_nt_split(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
-                                 int32_t dtype, int accumulate, const void* row_bias, int splits, hipStream_t s) {
+// C = A.B^T + A2.B2^T (A2, B2 null: the first product alone; both pairs have rows of K elements)
+tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
+                           int64_t K, int32_t dtype, const void* row_bias, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return TARDIS_ERR_SHAPE;
     if ((M + GT - 1) / GT > 65535) return TARDIS_ERR_SHAPE;
-    if (splits != 1 && splits != 2 && splits != 4 && splits != 8) return TARDIS_ERR_INVALID_ARG;
     // (any M, N work on the matrix cores; small products are not worth it)
-    if (dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 &&
-        (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0 && K % 8 == 0 &&
-        !gemm_force_generic()) {
+    if (dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 && is_aligned16(A) && is_aligned16(B) &&
+        is_aligned16(A2) && is_aligned16(B2) && K % 8 == 0 && !gemm_force_generic()) {
         TD_TRY(td_gemm_init());
-        if (K % 64 != 0) {       // a ragged K runs unsplit on the square tile: plain stores
-            launch_mfma<false, false, true, 4>(A, B, C, M, N, K, accumulate, row_bias, make_tile_map(M, N, K, 2, 1, 256), s);
-        } else {
-            const int rows = td_gemm_tile_rows(M);
-            const TileMap tm = make_tile_map(M, N, K, 2, splits, rows);
-            const bool atomic = splits > 1 || rows < 256;
-            if (atomic && !accumulate) zero_result(C, M, N, s);
-            if (rows == 64) launch_mfma<false, true, false, 1>(A, B, C, M, N, K, 1, row_bias, tm, s);
-            else if (rows == 128) launch_mfma<false, true, false, 2>(A, B, C, M, N, K, 1, row_bias, tm, s);
-            else if (atomic) launch_mfma<false, true, false, 4>(A, B, C, M, N, K, 1, row_bias, tm, s);
-            else launch_mfma<false, false, false, 4>(A, B, C, M, N, K, accumulate, row_bias, tm, s);
+        GemmArgs p{};
+        p.A = bytes_of(A);
+        p.B = bytes_of(B);
+        p.A2 = A2 ? bytes_of(A2) : p.A;
+        p.B2 = B2 ? bytes_of(B2) : p.B;
+        p.M = M;
+        p.N = N;
+        p.k = (uint32_t)(K * 2);
+        p.k2 = A2 ? p.k : 0u;
+        p.C = C;
+        p.bias = static_cast<const bf16_t*>(row_bias);
+        const TileChoice c = choose_tile(M, N, slices_of(p.k) + slices_of(p.k2), false, true);
+        if (K % 64 != 0) launch_tile<false, EPI_F32, true>(p, c, s);
+        else launch_tile<false, EPI_F32, false>(p, c, s);
+    } else {
+        for (int part = 0; part < (A2 ? 2 : 1); ++part) {
+            if (dtype == TARDIS_BF16)
+                launch_generic<bf16_t>(part ? A2 : A, part ? B2 : B, C, M, N, K, part, part ? nullptr : row_bias, s);
+            else
+                launch_generic<float>(part ? A2 : A, part ? B2 : B, C, M, N, K, part, part ? nullptr : row_bias, s);
         }
-    } else if (dtype == TARDIS_BF16)
-        launch_generic<bf16_t>(A, B, C, M, N, K, accumulate, row_bias, s);
-    else
-        launch_generic<float>(A, B, C, M, N, K, accumulate, row_bias, s);
+    }
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
 
-// C (int32, M x N) = A (int8, M x K) . B (int8, N x K)^T, exact.  16-byte aligned operands, K % 128 == 0.
-// splits: K ranges as above (integer adds, so the result is the same exact sum).
-tardis_status_t td_gemm_nt_i8(const int8_t* A, const int8_t* B, int32_t* C, int64_t M, int64_t N, int64_t K,
-                              int splits, hipStream_t s) {
-    if (M <= 0 || N <= 0 || K <= 0 || K % 128 != 0) return TARDIS_ERR_SHAPE;
-    if (splits != 1 && splits != 2 && splits != 4 && splits != 8) return TARDIS_ERR_INVALID_ARG;
-    if ((reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(B) & 15)) return TARDIS_ERR_INVALID_ARG;
-    TD_TRY(td_gemm_init());
-    const int rows = td_gemm_tile_rows(M);
-    const TileMap tm = make_tile_map(M, N, K, 1, splits, rows);
-    const bool atomic = splits > 1 || rows < 256;
-    if (atomic) zero_result(C, M, N, s);
-    if (rows == 64) launch_mfma<true, true, false, 1>(A, B, C, M, N, K, 0, nullptr, tm, s);
-    else if (rows == 128) launch_mfma<true, true, false, 2>(A, B, C, M, N, K, 0, nullptr, tm, s);
-    else if (atomic) launch_mfma<true, true, false, 4>(A, B, C, M, N, K, 0, nullptr, tm, s);
-    else launch_mfma<true, false, false, 4>(A, B, C, M, N, K, 0, nullptr, tm, s);
+// The products of calls with many tokens (bf16 layers, d % 128 == 0, h % 8 == 0, 16-byte aligned operands).
+// mask[t] = range test of Xq . Q^T (exact int32 sums)
+tardis_status_t td_gemm_predict(const int8_t* XQ, const int8_t* Q, const int32_t* e, const float* tlo, const float* thi,
+                                uint32_t* mask, int mask_words, int64_t n, int64_t h, int64_t d, hipStream_t s) {
+    GemmArgs p{};
+    p.A = p.A2 = bytes_of(XQ);
+    p.B = p.B2 = bytes_of(Q);
+    p.M = n;
+    p.N = h;
+    p.k = (uint32_t)d;
+    p.e = e;
+    p.lo = tlo;
+    p.hi = thi;
+    p.mask = mask;
+    p.mask_words = mask_words;
+    launch_tile<true, EPI_PRED, false>(p, choose_tile(n, h, slices_of(p.k), false, false), s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
+}
+
+// out[t] = sigma(z) - (a z + c) at the bits of mask[t], else 0; z = X . W1^T + b1.  mask null: out = sigma(z)
+tardis_status_t td_gemm_hidden(const void* X, const void* W1, const void* b1, const float* a, const float* c,
+                               const uint32_t* mask, int mask_words, int act, void* out, int64_t n, int64_t h, int64_t d,
+                               hipStream_t s) {
+    GemmArgs p{};
+    p.A = p.A2 = bytes_of(X);
+    p.B = p.B2 = bytes_of(W1);
+    p.M = n;
+    p.N = h;
+    p.k = (uint32_t)(d * 2);
+    p.bias = static_cast<const bf16_t*>(b1);
+    p.lo = a;
+    p.hi = c;
+    p.mask = const_cast<uint32_t*>(mask);
+    p.mask_words = mask_words;
+    p.act = act;
+    p.out = static_cast<bf16_t*>(out);
+    const TileChoice t = choose_tile(n, h, slices_of(p.k), false, false);
+    if (mask) launch_tile<false, EPI_DELTA, false>(p, t, s);
+    else launch_tile<false, EPI_HIDDEN, false>(p, t, s);
+    TD_HIP(hipGetLastError());
+    return TARDIS_OK;
+}
+
+// part[0 .. *parts)[n][d] = partial sums of X . Wp^T + H . W2^T (X, Wp null: the second product alone); the caller
+// adds them up.  At most 8 of them.
+tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
+                               int64_t n, int64_t d, int64_t h, hipStream_t s) {
+    GemmArgs p{};
+    p.A = bytes_of(X ? X : H);
+    p.B = bytes_of(X ? Wp : W2);
+    p.A2 = bytes_of(H);
+    p.B2 = bytes_of(W2);
+    p.M = n;
+    p.N = d;
+    p.k = (uint32_t)((X ? d : h) * 2);
+    p.k2 = X ? (uint32_t)(h * 2) : 0u;
+    p.C = part;
+    const TileChoice c = choose_tile(n, d, slices_of(p.k) + slices_of(p.k2), true, true);
+    *parts = c.splits;
+    if (h % 64 != 0) launch_tile<false, EPI_PART, true>(p, c, s);
+    else launch_tile<false, EPI_PART, false>(p, c, s);
+    TD_HIP(hipGetLastError());
+    return TARDIS_OK;
+}
+
+// floats that `part` of td_gemm_output has to hold for calls of up to n tokens (grows with n)
+size_t td_gemm_part_floats(int64_t n, int64_t d) {
+    const int64_t rows = n > kPartRows ? n : (8 * n < kPartRows ? 8 * n : kPartRows);
+    return (size_t)rows * (size_t)d;
 }

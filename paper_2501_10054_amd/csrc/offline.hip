@@ -787,7 +787,7 @@ tardis_status_t td_estimate_errors(const tardis_ffn_desc* desc, const void* X, i
     DevBuf zt, cn;
     TD_TRY(zt.alloc((size_t)h * n * 4));
     TD_TRY(cn.alloc((size_t)h * 4));
-    TD_TRY(td_gemm_nt(desc->W1, X, static_cast<float*>(zt.p), h, n, d, desc->dtype, 0, desc->b1, s));
+    TD_TRY(td_gemm_nt(desc->W1, X, nullptr, nullptr, static_cast<float*>(zt.p), h, n, d, desc->dtype, desc->b1, s));
     const dim3 cgrid((unsigned)((h + kBlock - 1) / kBlock));
     if (desc->dtype == TARDIS_BF16)
         hipLaunchKernelGGL(col_norm_kernel<bf16_t>, cgrid, dim3(kBlock), 0, s, static_cast<const bf16_t*>(desc->W2), d, h,
@@ -877,8 +877,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
         hipLaunchKernelGGL(scale_transpose_bf16_kernel, tile_grid(d, h), dim3(256), 0, s,
                            static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(phi.p),
                            static_cast<bf16_t*>(plo.p), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, phi.p, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 0, nullptr, s));
-        TD_TRY(td_gemm_nt(desc->W2, plo.p, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 1, nullptr, s));
+        TD_TRY(td_gemm_nt(desc->W2, phi.p, desc->W2, plo.p, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, nullptr, s));
         const int64_t n = d * d;
         if (Wp8)
             hipLaunchKernelGGL(wp_to_fp8_kernel, dim3((unsigned)d), dim3(kBlock), 0, s, static_cast<const float*>(acc.p),
@@ -896,7 +895,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
         TD_TRY(p.alloc((size_t)d * h * 4));
         hipLaunchKernelGGL(scale_transpose_f32_kernel, tile_grid(d, h), dim3(256), 0, s,
                            static_cast<const float*>(desc->W1), a, static_cast<float*>(p.p), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, p.p, static_cast<float*>(Wp), d, d, h, TARDIS_F32, 0, nullptr, s));
+        TD_TRY(td_gemm_nt(desc->W2, p.p, nullptr, nullptr, static_cast<float*>(Wp), d, d, h, TARDIS_F32, nullptr, s));
         hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)d), dim3(kBlock), 0, s,
                            static_cast<const float*>(desc->W2), static_cast<const float*>(desc->b1),
                            static_cast<const float*>(desc->b2), a, c, bp, d, h);
@@ -912,7 +911,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
     const int64_t d = desc->d, h = desc->h;
     DevBuf zt;
     TD_TRY(zt.alloc((size_t)h * n * 4));
-    TD_TRY(td_gemm_nt(desc->W1, X, static_cast<float*>(zt.p), h, n, d, desc->dtype, 0, desc->b1, s));
+    TD_TRY(td_gemm_nt(desc->W1, X, nullptr, nullptr, static_cast<float*>(zt.p), h, n, d, desc->dtype, desc->b1, s));
     int npad = 2;
     while (npad < n) npad <<= 1;
     if (step > 0.0f) {   // greedy range search instead of central quantiles
