@@ -711,6 +711,30 @@ def test_calibrate_many_samples_uses_large_lds():
     assert np.abs(a.cpu().numpy() - oa).max() < 1e-3 and np.abs(c.cpu().numpy() - oc).max() < 1e-3
 
 
+@pytest.mark.parametrize("kind", ["normal", "outlier", "repeated"])
+@pytest.mark.parametrize("n", [2, 3, 255, 256, 257, 1024, 1025, 4096, 4097, 8193])
+def test_calibrate_sample_counts_and_crowded_samples(n, kind):
+    """Edges of the samples a thread holds; one far outlier (all other samples in one cell of the histogram:
+    the sort); every token four times (equal samples: membership by value)."""
+    seed = synth.workload_seed(9, 40)
+    layer = synth.make_layer(48, 72, "f32", seed, w1_std=0.2, w2_std=0.05, with_bias=True)
+    X = synth.make_tokens(n, 48, "f32", seed, synth.STREAM_CAL)
+    if kind == "outlier":
+        X[n // 2] *= 1e4
+    if kind == "repeated":
+        X = np.repeat(X[:(n + 3) // 4], 4, axis=0)[:n].copy()
+    lo, hi, a, c = (t.cpu().numpy() for t in T.tardis_calibrate(make_ffn(layer), dev(X, "f32"), 0.9))
+    olo, ohi, oa, oc = O.calibrate(layer.W1, layer.b1, X, 0.9)
+    scale = max(1.0, float(np.abs(olo).max()), float(np.abs(ohi).max()))
+    assert np.abs(lo - olo).max() <= 2e-6 * scale and np.abs(hi - ohi).max() <= 2e-6 * scale
+    if n < 255:          # two or three samples: a line through what lies inside, whose sums have no averaging
+        assert np.abs(a - oa).max() <= 0.1
+        return
+    # fp32 pre-activations (2e-6 off) against the checker's; equal samples may be split by their rounding (1/n each)
+    tol = 1e-5 * scale if kind == "normal" else 1e-5 * scale + 20.0 / n
+    assert np.abs(a - oa).max() <= tol and np.abs(c - oc).max() <= tol
+
+
 def test_fused_kernel_with_ragged_hidden_width_and_bias():
     # d = 2048 takes the single-launch kernel; h = 1000 is neither a multiple of 32 nor of the
     # per-block neuron count, and the layer has biases
