@@ -5,6 +5,7 @@
 #include <mutex>
 #include <new>
 #include <unordered_set>
+#include <vector>
 
 #include "common.h"
 
@@ -35,17 +36,35 @@ tardis_status_t check_desc(const tardis_ffn_desc* desc) {
     return TARDIS_OK;
 }
 
-template <typename P> tardis_status_t dev_alloc(P** p, size_t bytes) {
-    void* v = nullptr;
-    hipError_t e = hipMalloc(&v, bytes ? bytes : 16);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        *p = nullptr;
-        return e == hipErrorOutOfMemory ? TARDIS_ERR_OOM : TARDIS_ERR_HIP;
+// A layer's device memory is one allocation: its parts are asked for first and placed together.  (A
+// hipMalloc / hipFree pair of 128 MiB or more costs 0.3 ms here, and up to several in a process that holds
+// much memory; a layer has about thirty parts, three of them that large.)
+class Arena {
+   public:
+    template <typename P> void reserve(P** p, size_t bytes) {
+        parts_.push_back({reinterpret_cast<void**>(p), total_});
+        total_ += ((bytes ? bytes : 16) + 255) / 256 * 256;
     }
-    *p = static_cast<P*>(v);
-    return TARDIS_OK;
-}
+    tardis_status_t commit(void** base) {
+        void* v = nullptr;
+        const hipError_t e = hipMalloc(&v, total_ ? total_ : 256);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e == hipErrorOutOfMemory ? TARDIS_ERR_OOM : TARDIS_ERR_HIP;
+        }
+        *base = v;
+        for (const Part& q : parts_) *q.at = static_cast<char*>(v) + q.offset;
+        return TARDIS_OK;
+    }
+
+   private:
+    struct Part {
+        void** at;
+        size_t offset;
+    };
+    std::vector<Part> parts_;
+    size_t total_ = 0;
+};
 
 // integer tuning knob from the environment (read when a layer is folded)
 int env_int(const char* name, int fallback, int lo, int hi) {
@@ -57,11 +76,7 @@ int env_int(const char* name, int fallback, int lo, int hi) {
 
 void free_layer(tardis_layer_s* L) {
     if (!L) return;
-    void* owned[] = {L->W2T, L->W2, L->Wp, L->Wp8, L->wp8_scale, L->bp, L->Q, L->Q4, L->M4, L->tlo, L->thi, L->a, L->c,
-                     L->yacc, L->mask, L->counts, L->list, L->hidden, L->sync, L->yfix, L->fx_bound, L->stack_desc, L->zeros_h, L->xnext, L->rec_count, L->rec_jb, L->rec_tb, L->rec_delta, L->pf_scratch,
-                     L->bt_xq, L->bt_e, L->bt_tokmask, L->bt_ulist, L->bt_ucount, L->bt_delta, L->bt_partial};
-    for (void* p : owned)
-        if (p) (void)hipFree(p);
+    if (L->memory) (void)hipFree(L->memory);
     delete L;
 }
 
@@ -82,25 +97,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     L->b2 = desc->b2;
     L->last_n = 0;
     const size_t nb = (size_t)L->max_batch;
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->W2T), (size_t)h * d * es));
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->W2), (size_t)h * d * es));
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->Wp), (size_t)d * d * es));
-    TD_TRY(dev_alloc(&L->bp, (size_t)d * 4));
-    TD_TRY(dev_alloc(&L->tlo, (size_t)h * 4));
-    TD_TRY(dev_alloc(&L->thi, (size_t)h * 4));
-    TD_TRY(dev_alloc(&L->a, (size_t)h * 4));
-    TD_TRY(dev_alloc(&L->c, (size_t)h * 4));
-    // (16 rows of slack: a partially filled group of tokens writes its empty slots there)
-    TD_TRY(dev_alloc(&L->yacc, (nb + kDecodeMaxTokens) * d * 4));
-    TD_TRY(dev_alloc(&L->mask, (nb + kDecodeMaxTokens) * L->mask_words * 4));
-    TD_TRY(dev_alloc(&L->counts, nb * 4));
-    TD_TRY(dev_alloc(&L->list, nb * h * 4));
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->hidden), nb * h * es));
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->zeros_h), (size_t)h * es));
-    TD_HIP(hipMemsetAsync(L->zeros_h, 0, (size_t)h * es, s));
-    TD_TRY(dev_alloc(reinterpret_cast<char**>(&L->xnext), nb * d * es));
-    TD_TRY(dev_alloc(&L->sync, 256));
-    TD_HIP(hipMemsetAsync(L->sync, 0, 256, s));
+    const bool fp8 = opts && opts->folded_dtype == TARDIS_FP8_E4M3;
     L->dec_threads = env_int("TARDIS_DECODE_THREADS", 1024, 512, 1024) == 512 ? 512 : 1024;
     L->dec_blocks = env_int("TARDIS_DECODE_BLOCKS", L->dec_threads == 512 ? 512 : 256, 1, 4096);
     L->dec_copies = env_int("TARDIS_DECODE_COPIES", 2, 1, 4);
@@ -109,21 +106,8 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // what a finished block of the single-token kernel requests of the next layer, in sixteenths of prefetch_bytes:
     // the first block to finish / the last one (linear in between)
     L->prefetch_shape = env_int("TARDIS_PREFETCH_FIRST16", 32, 0, 255) | (env_int("TARDIS_PREFETCH_LAST16", 0, 0, 255) << 8);
-    // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)
-    const size_t yfix_bytes = (size_t)(L->dec_copies < 2 ? 2 : L->dec_copies) * kDecodeMaxTokens * d * 4;
-    TD_TRY(dev_alloc(&L->yfix, yfix_bytes));
-    TD_HIP(hipMemsetAsync(L->yfix, 0, yfix_bytes, s));
     L->use_fused = env_int("TARDIS_DECODE_FUSED", 1, 0, 1) && td_decode_fused_supported(L);
     L->defer_min_tokens = env_int("TARDIS_DEFER_MIN", 4, 4, 99);
-    if (L->use_fused) {
-        TD_TRY(td_decode_init());
-        TD_TRY(td_static_scratch_setup());   // for tardis_ffn_forward_static on this device
-        const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;
-        TD_TRY(dev_alloc(&L->rec_count, (size_t)L->dec_blocks * 4));
-        TD_TRY(dev_alloc(&L->rec_jb, (size_t)L->dec_blocks * npb * 4));
-        TD_TRY(dev_alloc(&L->rec_tb, (size_t)L->dec_blocks * npb * 4));
-        TD_TRY(dev_alloc(&L->rec_delta, (size_t)L->dec_blocks * npb * kDecodeMaxTokens * 4));
-    }
     // counted fixed-point repair accumulators: asked for by opts->deterministic, or by the knob
     L->deterministic = opts ? opts->deterministic : 0;
     L->fx = (L->deterministic || env_int("TARDIS_FIXED_POINT", 0, 0, 1)) && L->use_fused && L->dec_threads == 1024 &&
@@ -135,27 +119,73 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // reads one-byte effective codes, kept only where such a path can run
     const bool packed4 = L->sketch_bits < 8 && L->use_fused && (d == 2048 || d == 4096);
     const bool byte_codes = !packed4 || (L->use_batched && L->max_batch > L->batched_min_tokens);
-    if (byte_codes) TD_TRY(dev_alloc(&L->Q, (size_t)h * d));
-    if (packed4) TD_TRY(dev_alloc(&L->Q4, (size_t)h * d / 2));
-    if (L->sketch_bits < 8) TD_TRY(dev_alloc(&L->M4, (size_t)h * ((d + 31) / 32)));
     L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", 65, 33, 1 << 20);
-    if (L->max_batch >= L->prefill_min_tokens && td_prefill_supported(L)) {
-        char* scratch = nullptr;
+    const bool prefill = L->max_batch >= L->prefill_min_tokens && byte_codes && td_prefill_supported(L);
+    const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
+    const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
+    // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)
+    const size_t yfix_bytes = (size_t)(L->dec_copies < 2 ? 2 : L->dec_copies) * kDecodeMaxTokens * d * 4;
+
+    Arena mem;
+    mem.reserve(&L->W2T, (size_t)h * d * es);
+    mem.reserve(&L->W2, (size_t)h * d * es);
+    mem.reserve(&L->Wp, (size_t)d * d * es);
+    mem.reserve(&L->bp, (size_t)d * 4);
+    mem.reserve(&L->tlo, (size_t)h * 4);
+    mem.reserve(&L->thi, (size_t)h * 4);
+    mem.reserve(&L->a, (size_t)h * 4);
+    mem.reserve(&L->c, (size_t)h * 4);
+    // (16 rows of slack: a partially filled group of tokens writes its empty slots there)
+    mem.reserve(&L->yacc, (nb + kDecodeMaxTokens) * d * 4);
+    mem.reserve(&L->mask, (nb + kDecodeMaxTokens) * L->mask_words * 4);
+    mem.reserve(&L->counts, nb * 4);
+    mem.reserve(&L->list, nb * h * 4);
+    mem.reserve(&L->hidden, nb * h * es);
+    mem.reserve(&L->zeros_h, (size_t)h * es);
+    mem.reserve(&L->xnext, nb * d * es);
+    mem.reserve(&L->sync, 256);
+    mem.reserve(&L->yfix, yfix_bytes);
+    if (L->use_fused) {
+        mem.reserve(&L->rec_count, (size_t)L->dec_blocks * 4);
+        mem.reserve(&L->rec_jb, (size_t)L->dec_blocks * npb * 4);
+        mem.reserve(&L->rec_tb, (size_t)L->dec_blocks * npb * 4);
+        mem.reserve(&L->rec_delta, (size_t)L->dec_blocks * npb * kDecodeMaxTokens * 4);
+    }
+    if (byte_codes) mem.reserve(&L->Q, (size_t)h * d);
+    if (packed4) mem.reserve(&L->Q4, (size_t)h * d / 2);
+    if (L->sketch_bits < 8) mem.reserve(&L->M4, (size_t)h * ((d + 31) / 32));
+    if (prefill) {
         L->prefill_chunk = env_int("TARDIS_PREFILL_CHUNK", 16384, 64, 32768);
         if (L->prefill_chunk > L->max_batch) L->prefill_chunk = (int32_t)L->max_batch;
-        TD_TRY(td_gemm_init());
-        TD_TRY(dev_alloc(&scratch, td_prefill_scratch_bytes(L, L->prefill_chunk)));
-        L->pf_scratch = scratch;
+        mem.reserve(&L->pf_scratch, td_prefill_scratch_bytes(L, L->prefill_chunk));
     }
     if (L->use_batched) {
+        mem.reserve(&L->bt_xq, (size_t)64 * d);
+        mem.reserve(&L->bt_e, 64 * 4);
+        mem.reserve(&L->bt_tokmask, (size_t)h * 8);
+        mem.reserve(&L->bt_ulist, (size_t)h * 4);
+        mem.reserve(&L->bt_ucount, 16);
+        mem.reserve(&L->bt_delta, (size_t)64 * h * 2);
+        mem.reserve(&L->bt_partial, td_batched_partial_floats(L) * 4);
+    }
+    if (fp8) {
+        mem.reserve(&L->Wp8, (size_t)d * d);
+        mem.reserve(&L->wp8_scale, (size_t)d * 4);
+    }
+    if (stack_entry) mem.reserve(&L->stack_desc, sizeof(td_stack_layer_dev));
+    if (L->fx) mem.reserve(&L->fx_bound, 8);
+    TD_TRY(mem.commit(&L->memory));
+
+    if (L->use_fused) {
+        TD_TRY(td_decode_init());
+        TD_TRY(td_static_scratch_setup());   // for tardis_ffn_forward_static on this device
+    }
+    if (prefill) TD_TRY(td_gemm_init());
+    TD_HIP(hipMemsetAsync(L->zeros_h, 0, (size_t)h * es, s));
+    TD_HIP(hipMemsetAsync(L->sync, 0, 256, s));
+    TD_HIP(hipMemsetAsync(L->yfix, 0, yfix_bytes, s));
+    if (L->use_batched) {
         TD_TRY(td_batched_init());
-        TD_TRY(dev_alloc(&L->bt_xq, (size_t)64 * d));
-        TD_TRY(dev_alloc(&L->bt_e, 64 * 4));
-        TD_TRY(dev_alloc(&L->bt_tokmask, (size_t)h * 8));
-        TD_TRY(dev_alloc(&L->bt_ulist, (size_t)h * 4));
-        TD_TRY(dev_alloc(&L->bt_ucount, 16));
-        TD_TRY(dev_alloc(&L->bt_delta, (size_t)64 * h * 2));
-        TD_TRY(dev_alloc(&L->bt_partial, td_batched_partial_floats(L) * 4));
         TD_HIP(hipMemsetAsync(L->bt_delta, 0, (size_t)64 * h * 2, s));
         TD_HIP(hipMemsetAsync(L->bt_ucount, 0, 16, s));
     }
@@ -164,33 +194,25 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     TD_HIP(hipMemsetAsync(L->yacc, 0, nb * d * 4, s));
     TD_HIP(hipMemcpyAsync(L->a, a, (size_t)h * 4, hipMemcpyDeviceToDevice, s));
     TD_HIP(hipMemcpyAsync(L->c, c, (size_t)h * 4, hipMemcpyDeviceToDevice, s));
+    // (the fold first: the two copies of W2 hold its operands until they are filled)
+    TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, L->W2T, L->W2, s));
     TD_HIP(hipMemcpyAsync(L->W2, desc->W2, (size_t)h * d * es, hipMemcpyDeviceToDevice, s));
     TD_TRY(td_transpose(desc->W2, L->W2T, d, h, desc->dtype, s));
     TD_TRY(td_build_sketch(desc->W1, desc->b1, lo, hi, h, d, desc->dtype, L->sketch_bits, L->margin, L->Q, L->Q4, L->M4, L->tlo,
                            L->thi, s));
-    if (opts && opts->folded_dtype == TARDIS_FP8_E4M3) {
-        TD_TRY(dev_alloc(&L->Wp8, (size_t)d * d));
-        TD_TRY(dev_alloc(&L->wp8_scale, (size_t)d * 4));
-    }
-    TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, s));
     L->stack_fused = env_int("TARDIS_STACK_FUSED", 0, 0, 2);   // 2: refuse a one-token stack the single launch cannot serve
     L->stack_spin_limit = env_int("TARDIS_STACK_SPIN_LIMIT", 1 << 22, 1, 1 << 30);
-    if (L->use_fused && L->dtype == TARDIS_BF16 && L->Q) {   // this layer's entry for the single-launch stack kernel
-        const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;
+    if (stack_entry) {   // this layer's entry for the single-launch stack kernel
         const td_stack_layer_dev hd{static_cast<const bf16_t*>(L->Wp), L->bp, L->Q, L->tlo, L->thi,
                                     static_cast<const bf16_t*>(L->W1),
                                     static_cast<const bf16_t*>(L->b1 ? L->b1 : L->zeros_h),
                                     static_cast<const bf16_t*>(L->W2T), L->a, L->c, L->mask,
                                     static_cast<bf16_t*>(L->xnext), L->yfix, L->sync, (int32_t)h, (int32_t)npb, L->act, 0};
         TD_TRY(td_stack_init());
-        TD_TRY(dev_alloc(&L->stack_desc, sizeof(hd)));
         TD_HIP(hipMemcpyAsync(L->stack_desc, &hd, sizeof(hd), hipMemcpyHostToDevice, s));
         TD_HIP(hipStreamSynchronize(s));   // (hd lives on this stack frame)
     }
-    if (L->fx) {
-        TD_TRY(dev_alloc(&L->fx_bound, 8));
-        TD_TRY(td_fx_bounds(L, L->fx_bound, s));
-    }
+    if (L->fx) TD_TRY(td_fx_bounds(L, L->fx_bound, s));
     TD_HIP(hipStreamSynchronize(s));
     return TARDIS_OK;
 }

@@ -73,7 +73,8 @@ struct tardis_layer_s {
     const void* W1;  // h x d
     const void* b1;  // h or null
     const void* b2;  // d or null
-    // owned
+    // owned: `memory` is the one allocation everything below lies in
+    void* memory;
     void* W2T;     // h x d, neuron-major copy of W2
     void* W2;      // d x h, copy of W2 as given (dense baseline)
     void* Wp;      // d x d folded matrix
@@ -227,8 +228,9 @@ tardis_status_t td_unpack_sketch4(const uint8_t* Q4, const uint8_t* M4, int64_t 
                                   hipStream_t s);
 // Wp8 / wp8_scale non-null (bf16 layers): W' is stored as e4m3 codes with a power-of-two scale per row, and Wp
 // receives the same values as bf16
+// work1, work2: h x d elements of the layer dtype each, overwritten
 tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float* c, void* Wp, float* bp,
-                        uint8_t* Wp8, float* wp8_scale, hipStream_t s);
+                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, hipStream_t s);
 // step > 0: greedy range search with that increment; step <= 0: central quantile ranges
 tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t n, float coverage,
                              const float* cov_pn, float step, float* lo, float* hi, float* a, float* c,

@@ -1154,19 +1154,17 @@ tardis_status_t td_unpack_sketch4(const uint8_t* Q4, const uint8_t* M4, int64_t 
 }
 
 tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float* c, void* Wp, float* bp,
-                        uint8_t* Wp8, float* wp8_scale, hipStream_t s) {
+                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, hipStream_t s) {
     if (Wp8 && desc->dtype != TARDIS_BF16) return TARDIS_ERR_DTYPE;
     const int64_t d = desc->d, h = desc->h;
     if ((h + 31) / 32 > 65535 || (d + 31) / 32 > 65535) return TARDIS_ERR_SHAPE;
     if (desc->dtype == TARDIS_BF16) {
-        DevBuf phi, plo, acc;
-        TD_TRY(phi.alloc((size_t)d * h * 2));
-        TD_TRY(plo.alloc((size_t)d * h * 2));
+        DevBuf acc;
         TD_TRY(acc.alloc((size_t)d * d * 4));
         hipLaunchKernelGGL(scale_transpose_bf16_kernel, tile_grid(d, h), dim3(256), 0, s,
-                           static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(phi.p),
-                           static_cast<bf16_t*>(plo.p), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, phi.p, desc->W2, plo.p, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, nullptr, s));
+                           static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(work1),
+                           static_cast<bf16_t*>(work2), h, d);
+        TD_TRY(td_gemm_nt(desc->W2, work1, desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, nullptr, s));
         const int64_t n = d * d;
         if (Wp8)
             hipLaunchKernelGGL(wp_to_fp8_kernel, dim3((unsigned)d), dim3(kBlock), 0, s, static_cast<const float*>(acc.p),
@@ -1180,11 +1178,9 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
         TD_HIP(hipGetLastError());
         TD_HIP(hipStreamSynchronize(s));  // temporaries are freed on return
     } else {
-        DevBuf p;
-        TD_TRY(p.alloc((size_t)d * h * 4));
         hipLaunchKernelGGL(scale_transpose_f32_kernel, tile_grid(d, h), dim3(256), 0, s,
-                           static_cast<const float*>(desc->W1), a, static_cast<float*>(p.p), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, p.p, nullptr, nullptr, static_cast<float*>(Wp), d, d, h, TARDIS_F32, nullptr, s));
+                           static_cast<const float*>(desc->W1), a, static_cast<float*>(work1), h, d);
+        TD_TRY(td_gemm_nt(desc->W2, work1, nullptr, nullptr, static_cast<float*>(Wp), d, d, h, TARDIS_F32, nullptr, s));
         hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)d), dim3(kBlock), 0, s,
                            static_cast<const float*>(desc->W2), static_cast<const float*>(desc->b1),
                            static_cast<const float*>(desc->b2), a, c, bp, d, h);
@@ -1199,34 +1195,50 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
                              hipStream_t s) {
     const int64_t d = desc->d, h = desc->h;
     DevBuf zt;
+    if (step <= 0.0f) {
+        // The pre-activations of a chunk of neurons at a time: 64 MiB of them make one round of 256 x 256 tiles
+        // over the 256 CUs, are still in the last-level cache when the fit reads them, and are the largest
+        // buffer the runtime keeps for the next call instead of mapping and unmapping it (0.3 ms and more).
+        int64_t rows = (int64_t)(64 << 20) / (4 * n) / 256 * 256;
+        rows = rows < 256 ? 256 : (rows > h ? h : rows);
+        TD_TRY(zt.alloc((size_t)rows * n * 4));
+        const size_t es = td_elem_size(desc->dtype);
+        for (int64_t j0 = 0; j0 < h; j0 += rows) {
+            tardis_ffn_desc part = *desc;                 // the neurons [j0, j0 + part.h)
+            part.h = h - j0 < rows ? h - j0 : rows;
+            part.W1 = static_cast<const char*>(desc->W1) + (size_t)j0 * d * es;
+            part.b1 = desc->b1 ? static_cast<const char*>(desc->b1) + (size_t)j0 * es : nullptr;
+            float* z = static_cast<float*>(zt.p);
+            TD_TRY(td_gemm_nt(part.W1, X, nullptr, nullptr, z, part.h, n, d, desc->dtype, part.b1, s));
+            const float* cov = cov_pn ? cov_pn + j0 : nullptr;
+            if (desc->dtype == TARDIS_BF16)
+                TD_TRY(launch_calibrate<bf16_t>(&part, z, X, (int)n, coverage, cov, lo + j0, hi + j0, a + j0, c + j0, s));
+            else
+                TD_TRY(launch_calibrate<float>(&part, z, X, (int)n, coverage, cov, lo + j0, hi + j0, a + j0, c + j0, s));
+        }
+        TD_HIP(hipStreamSynchronize(s));
+        return TARDIS_OK;
+    }
     TD_TRY(zt.alloc((size_t)h * n * 4));
     TD_TRY(td_gemm_nt(desc->W1, X, nullptr, nullptr, static_cast<float*>(zt.p), h, n, d, desc->dtype, desc->b1, s));
     int npad = 2;
     while (npad < n) npad <<= 1;
-    if (step > 0.0f) {   // greedy range search instead of central quantiles
-        const size_t lds = (size_t)((n + 1) & ~(int64_t)1) * sizeof(double) + (size_t)npad * sizeof(float);
-        if (lds > 48 * 1024)
-            TD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(range_search_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        DevBuf capped;
-        TD_TRY(capped.alloc(sizeof(int)));
-        TD_HIP(hipMemsetAsync(capped.p, 0, sizeof(int), s));
-        hipLaunchKernelGGL(range_search_kernel, dim3((unsigned)h), dim3(kBlock), lds, s,
-                           static_cast<const float*>(zt.p), (int)n, npad, coverage, cov_pn, step, (int)desc->act, lo,
-                           hi, a, c, static_cast<int*>(capped.p));
-        TD_HIP(hipGetLastError());
-        int n_capped = 0;
-        TD_HIP(hipMemcpyAsync(&n_capped, capped.p, sizeof(int), hipMemcpyDeviceToHost, s));
-        TD_HIP(hipStreamSynchronize(s));
-        // Algorithm 1 has no limit on the number of growth steps; the kernel's guard (4096) is only
-        // reached when `step` is absurdly small against a neuron's spread of inputs: refuse, do not
-        // substitute another range
-        return n_capped > 0 ? TARDIS_ERR_INVALID_ARG : TARDIS_OK;
-    }
-    if (desc->dtype == TARDIS_BF16)
-        TD_TRY(launch_calibrate<bf16_t>(desc, static_cast<const float*>(zt.p), X, (int)n, coverage, cov_pn, lo, hi, a, c, s));
-    else
-        TD_TRY(launch_calibrate<float>(desc, static_cast<const float*>(zt.p), X, (int)n, coverage, cov_pn, lo, hi, a, c, s));
+    const size_t lds = (size_t)((n + 1) & ~(int64_t)1) * sizeof(double) + (size_t)npad * sizeof(float);
+    if (lds > 48 * 1024)
+        TD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(range_search_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    DevBuf capped;
+    TD_TRY(capped.alloc(sizeof(int)));
+    TD_HIP(hipMemsetAsync(capped.p, 0, sizeof(int), s));
+    hipLaunchKernelGGL(range_search_kernel, dim3((unsigned)h), dim3(kBlock), lds, s,
+                       static_cast<const float*>(zt.p), (int)n, npad, coverage, cov_pn, step, (int)desc->act, lo,
+                       hi, a, c, static_cast<int*>(capped.p));
+    TD_HIP(hipGetLastError());
+    int n_capped = 0;
+    TD_HIP(hipMemcpyAsync(&n_capped, capped.p, sizeof(int), hipMemcpyDeviceToHost, s));
     TD_HIP(hipStreamSynchronize(s));
-    return TARDIS_OK;
+    // Algorithm 1 has no limit on the number of growth steps; the kernel's guard (4096) is only
+    // reached when `step` is absurdly small against a neuron's spread of inputs: refuse, do not
+    // substitute another range
+    return n_capped > 0 ? TARDIS_ERR_INVALID_ARG : TARDIS_OK;
 }

@@ -179,8 +179,9 @@ void finish(const PromptScratch& w, int parts, const float* bias32, const bf16_t
 
 }  // namespace
 
+// (and the layer keeps one-byte codes)
 bool td_prefill_supported(const tardis_layer_s* L) {
-    return L->dtype == TARDIS_BF16 && L->d % 128 == 0 && L->h >= 128 && L->h % 8 == 0 && L->Q != nullptr;
+    return L->dtype == TARDIS_BF16 && L->d % 128 == 0 && L->h >= 128 && L->h % 8 == 0;
 }
 
 size_t td_prefill_scratch_bytes(const tardis_layer_s* L, int64_t n) { return PromptScratch(nullptr, n, L->d, L->h).bytes; }
