@@ -27,12 +27,69 @@ transpose_kernel(const E* __restrict__ src, E* __restrict__ dst, int64_t rows, i
     }
 }
 
+// The same for 2-byte elements with rows and cols multiples of 8 and 16-byte aligned arrays: 64 x 64 tiles, 16 bytes
+// a thread on both sides (the 32 x 32 form moves 64 bytes of a row at a time).  Two source rows share a word
+// of the LDS tile; a thread collects eight of them for one destination row.
+// SPLIT: the fold's operands instead of a copy: p = a[row] * src, its bf16 head to dst and the bf16 remainder to
+// dst_lo, so that the folded matrix is accumulated from ~16 significant bits instead of 8 (the paper's
+// Sec. "Precision Effects on Reordering FFN" finds bf16 intermediates visibly worse than fp32).
+// Bound: HBM.  16384 x 4096: copy 127 -> 46 us, split 217 -> 76 us (32 x 32 tiles before).
+template <bool SPLIT>
+__global__ void __launch_bounds__(256)
+transpose16_kernel(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, bf16_t* __restrict__ dst_lo,
+                   const float* __restrict__ a, int64_t rows, int64_t cols) {
+    constexpr int PITCH = 65;                                    // words: column c of source rows 2r, 2r+1 at [r][c]
+    __shared__ uint32_t hi[32 * PITCH], lo[SPLIT ? 32 * PITCH : 1];
+    const int64_t c0 = (int64_t)blockIdx.x * 64, r0 = (int64_t)blockIdx.y * 64;
+    {
+        const int pr = threadIdx.x >> 3, pc = (threadIdx.x & 7) * 8;   // row pair, first of 8 columns
+        const int64_t r = r0 + 2 * pr, c = c0 + pc;
+        td_u32x4 v[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+        float s[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (r + u < rows && c < cols) {
+                v[u] = *reinterpret_cast<const td_u32x4*>(src + (r + u) * cols + c);
+                if constexpr (SPLIT) s[u] = a[r + u];
+            }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            uint32_t e[2], rest[2] = {0u, 0u};
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                e[u] = (v[u][k >> 1] >> (16 * (k & 1))) & 0xffffu;
+                if constexpr (SPLIT) {
+                    const float p = s[u] * td_bf16_to_f32((bf16_t)e[u]);
+                    const bf16_t head = td_f32_to_bf16(p);
+                    e[u] = head;
+                    rest[u] = td_f32_to_bf16(p - td_bf16_to_f32(head));
+                }
+            }
+            hi[pr * PITCH + pc + k] = e[0] | (e[1] << 16);
+            if constexpr (SPLIT) lo[pr * PITCH + pc + k] = rest[0] | (rest[1] << 16);
+        }
+    }
+    __syncthreads();
+    // thread -> destination row (source column) and 8 source rows
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int cc = u * 32 + (threadIdx.x >> 3), rr = (threadIdx.x & 7) * 4;   // column; first of 4 row pairs
+        const int64_t c = c0 + cc, r = r0 + 2 * rr;
+        if (c >= cols || r >= rows) continue;                    // rows % 8 == 0: all eight or none
+        td_u32x4 o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = hi[(rr + k) * PITCH + cc];
+        *reinterpret_cast<td_u32x4*>(dst + c * rows + r) = o;
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = lo[(rr + k) * PITCH + cc];
+            *reinterpret_cast<td_u32x4*>(dst_lo + c * rows + r) = o;
+        }
+    }
+}
+
 // ------------------------------------------------------- scaled transpose (fold)
-// P = diag(a) W1 (h x d) written transposed (d x h).  For bf16 storage the fp32
-// product is split into a bf16 head and a bf16 remainder so that the folded
-// matrix is accumulated from ~16 significant bits instead of 8 (the paper's
-// Sec. "Precision Effects on Reordering FFN" finds bf16 intermediates visibly
-// worse than fp32).
+// P = diag(a) W1 (h x d) written transposed (d x h) as head and remainder (see above), any sizes.
 __global__ void __launch_bounds__(256)
 scale_transpose_bf16_kernel(const bf16_t* __restrict__ W1, const float* __restrict__ a, bf16_t* __restrict__ Phi,
                             bf16_t* __restrict__ Plo, int64_t h, int64_t d) {
@@ -82,20 +139,35 @@ f32_to_bf16_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, int6
     if (i < n) dst[i] = td_f32_to_bf16(src[i]);
 }
 
-// b'[r] = sum_j W2[r][j] * (c_j + a_j b1_j) + b2[r]; one block per output row,
-// fp64 accumulation.
+// k_j = c_j + a_j b1_j, the vector that the folded bias multiplies W2 with
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
-fold_bias_kernel(const T* __restrict__ W2, const T* __restrict__ b1, const T* __restrict__ b2,
-                 const float* __restrict__ a, const float* __restrict__ c, float* __restrict__ bp, int64_t d,
-                 int64_t h) {
+fold_bias_terms_kernel(const T* __restrict__ b1, const float* __restrict__ a, const float* __restrict__ c,
+                       double* __restrict__ k, int64_t h) {
+    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (j < h) k[j] = (double)c[j] + (b1 ? (double)a[j] * (double)td_load<T>(b1 + j) : 0.0);
+}
+
+// b'[r] = sum_j W2[r][j] * k_j + b2[r]; one block per output row, fp64 accumulation.  Bound: HBM (W2 once, 16
+// bytes a load where rows are whole vectors): d=4096, h=16384: 92 -> 45 us.
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+fold_bias_kernel(const T* __restrict__ W2, const double* __restrict__ k, const T* __restrict__ b2, float* __restrict__ bp,
+                 int64_t d, int64_t h) {
     __shared__ double red[kBlock / TD_WAVE];
+    constexpr int V = 16 / (int)sizeof(T);
     const int64_t r = blockIdx.x;
+    const T* row = W2 + r * h;
     double acc = 0.0;
-    for (int64_t j = threadIdx.x; j < h; j += kBlock) {
-        double kj = (double)c[j];
-        if (b1) kj += (double)a[j] * (double)td_load<T>(b1 + j);
-        acc += (double)td_load<T>(W2 + r * h + j) * kj;
+    if (h % V == 0) {
+        for (int64_t v = threadIdx.x; v < h / V; v += kBlock) {
+            const td_u32x4 w = td_load_stream16(reinterpret_cast<const td_u32x4*>(row) + v);
+            const T* wt = reinterpret_cast<const T*>(&w);
+#pragma unroll
+            for (int u = 0; u < V; ++u) acc += (double)td_load<T>(wt + u) * k[v * V + u];
+        }
+    } else {
+        for (int64_t j = threadIdx.x; j < h; j += kBlock) acc += (double)td_load<T>(row + j) * k[j];
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
@@ -126,16 +198,47 @@ __device__ __forceinline__ void predictor_range(double lo, double hi, double mar
     }
 }
 
+// rint(w / s) clamped to [-127, 127], the quotient as IEEE division gives it.  w * (1/s) is within 3 units in the
+// last place of it, i.e. (|quotient| <= 127) within 1e-13; only where that could reach another integer - the
+// quotient is that close to a half - the division itself is done.
+__device__ __forceinline__ int sketch_code(float w, double s, double inv) {
+    double q = (double)w * inv;
+    const double n = rint(q);
+    if (fabs(fabs(q - n) - 0.5) < 1e-9) q = (double)w / s;
+    return (int)fmin(fmax(rint(q), -127.0), 127.0);
+}
+
+// Bound: HBM (W1 once, a byte per weight out).  16384 x 4096: 140 -> 79 us (a 64-bit division per weight and
+// 2-byte loads before).
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
               const float* __restrict__ hi, int64_t d, int8_t* __restrict__ Q, float* __restrict__ tlo,
               float* __restrict__ thi, float margin) {
     __shared__ float red[kBlock / TD_WAVE];
+    constexpr int V = 16 / (int)sizeof(T);
+    constexpr int kKeep = 2;                         // vectors a thread keeps between the two passes
     const int64_t j = blockIdx.x;
     const T* row = W1 + j * d;
+    const bool vec = d % V == 0;                     // (W1 is 16-byte aligned: so is every row)
+    const int64_t nv = vec ? d / V : 0;
+    td_u32x4 keep[kKeep];
     float m = 0.0f;
-    for (int64_t k = threadIdx.x; k < d; k += kBlock) m = fmaxf(m, fabsf(td_load<T>(row + k)));
+    auto vmax = [&](const td_u32x4& w) {
+        const T* wt = reinterpret_cast<const T*>(&w);
+#pragma unroll
+        for (int u = 0; u < V; ++u) m = fmaxf(m, fabsf(td_load<T>(wt + u)));
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int64_t v = i * kBlock + threadIdx.x;
+        if (v < nv) {
+            keep[i] = reinterpret_cast<const td_u32x4*>(row)[v];
+            vmax(keep[i]);
+        }
+    }
+    for (int64_t v = kKeep * kBlock + threadIdx.x; v < nv; v += kBlock) vmax(reinterpret_cast<const td_u32x4*>(row)[v]);
+    for (int64_t k = nv * V + threadIdx.x; k < d; k += kBlock) m = fmaxf(m, fabsf(td_load<T>(row + k)));
     m = td_wave_max(m);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = m;
     __syncthreads();
@@ -146,19 +249,30 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
     const double bj = b1 ? (double)td_load<T>(b1 + j) : 0.0;
     double rl, rh;
     predictor_range((double)lo[j], (double)hi[j], (double)margin, rl, rh);
-    if (m > 0.0f) {
-        for (int64_t k = threadIdx.x; k < d; k += kBlock) {
-            double q = rint((double)td_load<T>(row + k) / s);
-            q = fmin(fmax(q, -127.0), 127.0);
-            Q[j * d + k] = (int8_t)(int)q;
-        }
-        if (threadIdx.x == 0) {
+    const bool live = m > 0.0f;
+    const double inv = live ? 1.0 / s : 0.0;
+    auto code = [&](float w) { return live ? sketch_code(w, s, inv) : 0; };
+    auto put = [&](int64_t v, const td_u32x4& w) {
+        const T* wt = reinterpret_cast<const T*>(&w);
+        uint32_t o[2] = {0u, 0u};
+#pragma unroll
+        for (int u = 0; u < V; ++u) o[u >> 2] |= (uint32_t)(uint8_t)(int8_t)code(td_load<T>(wt + u)) << (8 * (u & 3));
+        int8_t* dst = Q + j * d + v * V;             // V-byte aligned: d % V == 0
+        if constexpr (V == 8) *reinterpret_cast<uint2*>(dst) = make_uint2(o[0], o[1]);
+        else *reinterpret_cast<uint32_t*>(dst) = o[0];
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int64_t v = i * kBlock + threadIdx.x;
+        if (v < nv) put(v, keep[i]);
+    }
+    for (int64_t v = kKeep * kBlock + threadIdx.x; v < nv; v += kBlock) put(v, reinterpret_cast<const td_u32x4*>(row)[v]);
+    for (int64_t k = nv * V + threadIdx.x; k < d; k += kBlock) Q[j * d + k] = (int8_t)code(td_load<T>(row + k));
+    if (threadIdx.x == 0) {
+        if (live) {
             tlo[j] = (float)((rl - bj) / s);
             thi[j] = (float)((rh - bj) / s);
-        }
-    } else {
-        for (int64_t k = threadIdx.x; k < d; k += kBlock) Q[j * d + k] = 0;
-        if (threadIdx.x == 0) {
+        } else {
             const bool inside = (rl <= bj) && (bj < rh);
             tlo[j] = inside ? -INFINITY : INFINITY;
             thi[j] = INFINITY;
@@ -1043,7 +1157,9 @@ struct DevBuf {  // frees on scope exit
     }
 };
 
-dim3 tile_grid(int64_t cols, int64_t rows) { return dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32)); }
+dim3 tile_grid(int64_t cols, int64_t rows, int64_t side = 32) {
+    return dim3((unsigned)((cols + side - 1) / side), (unsigned)((rows + side - 1) / side));
+}
 
 }  // namespace
 
@@ -1107,7 +1223,11 @@ tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s
 
 tardis_status_t td_transpose(const void* src, void* dst, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s) {
     if ((rows + 31) / 32 > 65535) return TARDIS_ERR_SHAPE;
-    if (dtype == TARDIS_BF16)
+    const bool whole = rows % 8 == 0 && cols % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    if (dtype == TARDIS_BF16 && whole)
+        hipLaunchKernelGGL(transpose16_kernel<false>, tile_grid(cols, rows, 64), dim3(256), 0, s,
+                           static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), nullptr, nullptr, rows, cols);
+    else if (dtype == TARDIS_BF16)
         hipLaunchKernelGGL(transpose_kernel<uint16_t>, tile_grid(cols, rows), dim3(256), 0, s,
                            static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst), rows, cols);
     else
@@ -1158,12 +1278,19 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
     if (Wp8 && desc->dtype != TARDIS_BF16) return TARDIS_ERR_DTYPE;
     const int64_t d = desc->d, h = desc->h;
     if ((h + 31) / 32 > 65535 || (d + 31) / 32 > 65535) return TARDIS_ERR_SHAPE;
+    DevBuf kk;
+    TD_TRY(kk.alloc((size_t)h * 8));
     if (desc->dtype == TARDIS_BF16) {
         DevBuf acc;
         TD_TRY(acc.alloc((size_t)d * d * 4));
-        hipLaunchKernelGGL(scale_transpose_bf16_kernel, tile_grid(d, h), dim3(256), 0, s,
-                           static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(work1),
-                           static_cast<bf16_t*>(work2), h, d);
+        if (d % 8 == 0 && h % 8 == 0)
+            hipLaunchKernelGGL(transpose16_kernel<true>, tile_grid(d, h, 64), dim3(256), 0, s,
+                               static_cast<const bf16_t*>(desc->W1), static_cast<bf16_t*>(work1),
+                               static_cast<bf16_t*>(work2), a, h, d);
+        else
+            hipLaunchKernelGGL(scale_transpose_bf16_kernel, tile_grid(d, h), dim3(256), 0, s,
+                               static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(work1),
+                               static_cast<bf16_t*>(work2), h, d);
         TD_TRY(td_gemm_nt(desc->W2, work1, desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, nullptr, s));
         const int64_t n = d * d;
         if (Wp8)
@@ -1172,18 +1299,22 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
         else
             hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                                static_cast<const float*>(acc.p), static_cast<bf16_t*>(Wp), n);
+        hipLaunchKernelGGL(fold_bias_terms_kernel<bf16_t>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                           static_cast<const bf16_t*>(desc->b1), a, c, static_cast<double*>(kk.p), h);
         hipLaunchKernelGGL(fold_bias_kernel<bf16_t>, dim3((unsigned)d), dim3(kBlock), 0, s,
-                           static_cast<const bf16_t*>(desc->W2), static_cast<const bf16_t*>(desc->b1),
-                           static_cast<const bf16_t*>(desc->b2), a, c, bp, d, h);
+                           static_cast<const bf16_t*>(desc->W2), static_cast<const double*>(kk.p),
+                           static_cast<const bf16_t*>(desc->b2), bp, d, h);
         TD_HIP(hipGetLastError());
         TD_HIP(hipStreamSynchronize(s));  // temporaries are freed on return
     } else {
         hipLaunchKernelGGL(scale_transpose_f32_kernel, tile_grid(d, h), dim3(256), 0, s,
                            static_cast<const float*>(desc->W1), a, static_cast<float*>(work1), h, d);
         TD_TRY(td_gemm_nt(desc->W2, work1, nullptr, nullptr, static_cast<float*>(Wp), d, d, h, TARDIS_F32, nullptr, s));
+        hipLaunchKernelGGL(fold_bias_terms_kernel<float>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                           static_cast<const float*>(desc->b1), a, c, static_cast<double*>(kk.p), h);
         hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)d), dim3(kBlock), 0, s,
-                           static_cast<const float*>(desc->W2), static_cast<const float*>(desc->b1),
-                           static_cast<const float*>(desc->b2), a, c, bp, d, h);
+                           static_cast<const float*>(desc->W2), static_cast<const double*>(kk.p),
+                           static_cast<const float*>(desc->b2), bp, d, h);
         TD_HIP(hipGetLastError());
         TD_HIP(hipStreamSynchronize(s));
     }

@@ -251,6 +251,46 @@ def test_prompt_path_many_tokens(d, h, n, bits):
     run_case(w.layer, w.X_cal, w.X_test, 0.9, batched=True, check_calibrate=False, sketch_bits=bits)
 
 
+@pytest.mark.parametrize("d,h,n", [(128, 8192, 2048), (128, 8192, 1500), (128, 8200, 1025), (256, 1000, 65),
+                                   (256, 1000, 130), (384, 4104, 333), (128, 2000, 700)])
+def test_prompt_path_tiles(d, h, n):
+    """Every tile shape of the matrix-core products at its edges: a K of one or two slices, K that is not whole
+    slices (h % 64 != 0), ragged rows and columns, words of the mask cut by the tile."""
+    seed = synth.workload_seed(9, 50 + n % 7)
+    layer = custom_layer(d, h, "bf16", seed, 0.1, True)
+    r = run_case(layer, synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL),
+                 synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST), 0.93, batched=True)
+    assert r["rate"] > 0
+
+
+def test_prompt_path_takes_tokens_at_any_address():
+    """Tokens and outputs that are not 16-byte aligned (a slice of a larger buffer) give the same bits."""
+    seed = synth.workload_seed(9, 58)
+    layer = custom_layer(256, 1024, "bf16", seed, 0.1, False)
+    ffn = make_ffn(layer)
+    L = T.tardis_fold(ffn, *T.tardis_calibrate(ffn, dev(synth.make_tokens(256, 256, "bf16", seed, synth.STREAM_CAL), "bf16"), 0.9),
+                      max_batch=80)
+    x = dev(synth.make_tokens(80, 256, "bf16", seed, synth.STREAM_TEST), "bf16")
+    for call in (T.tardis_ffn_forward_batched, T.tardis_dense_forward):
+        want = call(L, x)
+        buf = torch.zeros(80 * 256 + 1, dtype=torch.bfloat16, device=DEV)
+        out = torch.zeros_like(buf)
+        buf[1:] = x.flatten()
+        got = call(L, buf[1:].view(80, 256), out[1:].view(80, 256))
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    L.close()
+
+
+@pytest.mark.parametrize("d,h", [(64, 128), (72, 136), (136, 72), (75, 130), (520, 1032)])
+def test_fold_tile_edges(d, h):
+    """Whole and partial 64 x 64 tiles of the transposes, rows that are and are not whole 16-byte vectors."""
+    seed = synth.workload_seed(9, 60)
+    layer = custom_layer(d, h, "bf16", seed, 0.1, True)
+    run_case(layer, synth.make_tokens(128, d, "bf16", seed, synth.STREAM_CAL),
+             synth.make_tokens(2, d, "bf16", seed, synth.STREAM_TEST), 0.9)
+
+
 def test_prompt_path_with_bias_and_relu():
     seed = synth.workload_seed(3, 11)
     layer = synth.make_layer(512, 2048, "bf16", seed, w1_std=0.05, w2_std=0.05, heavy_frac=0.01, with_bias=True)
