@@ -113,14 +113,17 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     L->fx = (L->deterministic || env_int("TARDIS_FIXED_POINT", 0, 0, 1)) && L->use_fused && L->dec_threads == 1024 &&
             (d + L->dec_blocks - 1) / L->dec_blocks <= 64 && L->dec_blocks <= 65535;
     if (L->deterministic && !L->fx) return TARDIS_ERR_SHAPE;   // only the fused decode kernels have the ordered path
-    L->use_batched = env_int("TARDIS_BATCHED", 1, 0, 1) && td_batched_supported(L);
-    L->batched_min_tokens = env_int("TARDIS_BATCHED_MIN", L->use_fused ? 17 : 1, 1, 64);
+    // calls with at least this many tokens run as matrix products (prefill.hip).  Against decode groups at
+    // d=4096, h=16384 and 1 / 5 / 15 % fallback: 16 tokens 52 / 68 / 99 us in groups, 84 as products whatever the rate;
+    // 17 tokens (16 + 1) 73 / 93 / 129 against 84; from 18 on two full groups, 104 / 136 / 201 at 32 tokens, 85.  (d=2048: 16
+    // tokens 27 / 32 / 40 against 42; d=1024: 21 / 25 / 31 against 28.)  A layer without those kernels has only a launch
+    // sequence per token to compare with: from 2 tokens on.
+    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", L->use_fused ? 18 : 2, 2, 1 << 20);
+    const bool products = L->max_batch >= 2 && td_prefill_supported(L);   // (the dense FFN takes them from 2 tokens on)
     // 4-bit sketch: the decode kernel reads the packed form (d = 2048, 4096); every other path
     // reads one-byte effective codes, kept only where such a path can run
     const bool packed4 = L->sketch_bits < 8 && L->use_fused && (d == 2048 || d == 4096);
-    const bool byte_codes = !packed4 || (L->use_batched && L->max_batch > L->batched_min_tokens);
-    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", 65, 33, 1 << 20);
-    const bool prefill = L->max_batch >= L->prefill_min_tokens && byte_codes && td_prefill_supported(L);
+    const bool byte_codes = !packed4 || (products && L->max_batch >= L->prefill_min_tokens);
     const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
     // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)
@@ -154,19 +157,10 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     if (byte_codes) mem.reserve(&L->Q, (size_t)h * d);
     if (packed4) mem.reserve(&L->Q4, (size_t)h * d / 2);
     if (L->sketch_bits < 8) mem.reserve(&L->M4, (size_t)h * ((d + 31) / 32));
-    if (prefill) {
+    if (products) {
         L->prefill_chunk = env_int("TARDIS_PREFILL_CHUNK", 16384, 64, 32768);
         if (L->prefill_chunk > L->max_batch) L->prefill_chunk = (int32_t)L->max_batch;
         mem.reserve(&L->pf_scratch, td_prefill_scratch_bytes(L, L->prefill_chunk));
-    }
-    if (L->use_batched) {
-        mem.reserve(&L->bt_xq, (size_t)64 * d);
-        mem.reserve(&L->bt_e, 64 * 4);
-        mem.reserve(&L->bt_tokmask, (size_t)h * 8);
-        mem.reserve(&L->bt_ulist, (size_t)h * 4);
-        mem.reserve(&L->bt_ucount, 16);
-        mem.reserve(&L->bt_delta, (size_t)64 * h * 2);
-        mem.reserve(&L->bt_partial, td_batched_partial_floats(L) * 4);
     }
     if (fp8) {
         mem.reserve(&L->Wp8, (size_t)d * d);
@@ -180,15 +174,10 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
         TD_TRY(td_decode_init());
         TD_TRY(td_static_scratch_setup());   // for tardis_ffn_forward_static on this device
     }
-    if (prefill) TD_TRY(td_gemm_init());
+    if (products) TD_TRY(td_gemm_init());
     TD_HIP(hipMemsetAsync(L->zeros_h, 0, (size_t)h * es, s));
     TD_HIP(hipMemsetAsync(L->sync, 0, 256, s));
     TD_HIP(hipMemsetAsync(L->yfix, 0, yfix_bytes, s));
-    if (L->use_batched) {
-        TD_TRY(td_batched_init());
-        TD_HIP(hipMemsetAsync(L->bt_delta, 0, (size_t)64 * h * 2, s));
-        TD_HIP(hipMemsetAsync(L->bt_ucount, 0, 16, s));
-    }
     TD_HIP(hipMemsetAsync(L->counts, 0, nb * 4, s));
     TD_HIP(hipMemsetAsync(L->mask, 0, nb * L->mask_words * 4, s));
     TD_HIP(hipMemsetAsync(L->yacc, 0, nb * d * 4, s));

@@ -108,24 +108,14 @@ struct tardis_layer_s {
     int32_t dec_threads;  // block size of the fused decode kernel (512 or 1024)
     int32_t dec_copies;   // number of repair accumulator copies
     int32_t use_fused;    // fused single-launch decode path available for this layer
-    // working memory of the batched path (one pass of up to 64 tokens); null if unused
-    int8_t* bt_xq;                 // 64 x d int8 token codes
-    int32_t* bt_e;                 // 64 token exponents
-    unsigned long long* bt_tokmask;  // h: which tokens of the pass flagged each neuron
-    int32_t* bt_ulist;             // h: neurons flagged by at least one token
-    int32_t* bt_ucount;            // 1
-    bf16_t* bt_delta;              // 64 x h repair factors
-    float* bt_partial;             // partial products of the scatter step
-    int32_t use_batched;
-    void* pf_scratch;              // prompt path: int8 tokens, exponents, aligned tokens, repair factors, fp32 partial sums of y
-    int32_t prefill_min_tokens;    // calls with at least this many tokens take the prompt path (if it has scratch)
+    void* pf_scratch;              // matrix products: int8 tokens, exponents, aligned tokens, repair factors, fp32 partial sums of y
+    int32_t prefill_min_tokens;    // calls with at least this many tokens run as matrix products (if there is scratch)
     int32_t prefill_chunk;         // ... in chunks of at most this many tokens (what the scratch is sized for)
     int32_t* rec_count;            // two-kernel path: flagged neurons per predictor block,
     uint32_t* rec_jb;              //   neuron index and
     uint32_t* rec_tb;              //   token bits of each record (dec_blocks x neurons per block),
     float* rec_delta;              //   and kDecodeMaxTokens deltas per record
     int32_t defer_min_tokens;      // groups of at least this many tokens take the two-kernel path (4, 8; 99 = never)
-    int32_t batched_min_tokens;    // token counts up to this go through the single-token path
     int64_t last_n;    // token count of the most recent online call
     int32_t fx;        // decode kernels accumulate the repair in counted fixed-point words (deterministic results)
     int32_t deterministic;   // every online call runs as decode groups on those accumulators
@@ -245,11 +235,9 @@ tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s
 tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
                            int64_t K, int32_t dtype, const void* row_bias, hipStream_t s);
 // the products of calls with many tokens, each with the step that follows it (see gemm.hip)
-tardis_status_t td_gemm_predict(const int8_t* XQ, const int8_t* Q, const int32_t* e, const float* tlo, const float* thi,
-                                uint32_t* mask, int mask_words, int64_t n, int64_t h, int64_t d, hipStream_t s);
-tardis_status_t td_gemm_hidden(const void* X, const void* W1, const void* b1, const float* a, const float* c,
-                               const uint32_t* mask, int mask_words, int act, void* out, int64_t n, int64_t h, int64_t d,
-                               hipStream_t s);
+tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
+                               uint32_t* mask, void* out, int64_t n, hipStream_t s);
+tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const void* b1, void* out, int64_t n, hipStream_t s);
 tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
                                int64_t n, int64_t d, int64_t h, hipStream_t s);
 size_t td_gemm_part_floats(int64_t n, int64_t d);
@@ -276,11 +264,6 @@ tardis_status_t td_mask_to_list(const tardis_layer_s* L, int64_t n, int32_t* cou
 tardis_status_t td_stack_init();
 bool td_stack_decode_supported(const tardis_layer_s* L);
 tardis_status_t td_stack_decode(tardis_layer_s* const* layers, int n_layers, const void* x, void* y, hipStream_t s);
-// batched.hip
-bool td_batched_supported(const tardis_layer_s* L);
-size_t td_batched_partial_floats(const tardis_layer_s* L);
-tardis_status_t td_batched_init();
-tardis_status_t td_forward_batched(tardis_layer_s* L, const void* x, int64_t n, void* y, int norm_out, hipStream_t s);
 // forward.hip
 // norm_out != 0: the output is y / sqrt(mean(y^2) + kRmsEps) per token (glue between stacked layers)
 tardis_status_t td_forward(tardis_layer_s* L, const void* x, int64_t n, void* y, int norm_out, hipStream_t s);

@@ -10,6 +10,7 @@
 // repair factors of the flagged ones, and the folded product together with the down projection of the
 // masked factors, [X | D] . [W' | W2]^T.
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 
@@ -153,16 +154,22 @@ struct GemmArgs {
     uint32_t k, k2;
     // epilogues
     float* C;                      // F32: M x N; PART: [split][M][N]
-    const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, DELTA: per column
-    bf16_t* out;                   // HIDDEN, DELTA: M x N
-    const float *lo, *hi;          // PRED: bounds per column;  DELTA: slope and intercept per column
-    const int32_t* e;              // PRED: exponent per row
-    uint32_t* mask;                // PRED: written, DELTA: read; M x mask_words
+    const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, REPAIR: per column
+    bf16_t* out;                   // HIDDEN, REPAIR: M x N
+    const float *lo, *hi;          // REPAIR: bounds of the range test per column,
+    const float *slope, *icept;    //   line per column,
+    const int32_t* e;              //   exponent per row (readable to the next multiple of 16 bytes),
+    uint32_t* mask;                //   flags, M x mask_words, written
     int mask_words;
     int act;
 };
 
-enum { EPI_F32, EPI_PART, EPI_PRED, EPI_DELTA, EPI_HIDDEN };
+// F32: C = product (+ bias).  PART: one range of K's share of C.  HIDDEN: out = sigma(product + bias).
+// REPAIR: the first pair of operands is int8 (token codes and predictor codes), the second bf16 (tokens and
+// W1): the sums of the first give the flags, those of the second z, and out = sigma(z) - (slope z + icept) at
+// the flagged places, 0 elsewhere.  Neither the sums nor z leave the block, and the stream of slices goes on
+// from the one product to the other.
+enum { EPI_F32, EPI_PART, EPI_HIDDEN, EPI_REPAIR };
 
 __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);
@@ -176,54 +183,54 @@ __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
 
 // 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
 // (m0 is set and used in the one statement; the compiler keeps nothing in it)
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
 }
 
 // round to nearest even, in one instruction
 __device__ __forceinline__ uint32_t to_bf16(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 
-template <bool I8> struct Mma;
-template <> struct Mma<false> {
-    typedef f32x4_t acc_t;
-    static __device__ __forceinline__ void go(acc_t& c, const td_u32x4& a, const td_u32x4& b) {
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-    }
-};
-template <> struct Mma<true> {
-    typedef i32x4_t acc_t;
-    static __device__ __forceinline__ void go(acc_t& c, const td_u32x4& a, const td_u32x4& b) {
-        asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-    }
-};
+// (the accumulator of the int8 form holds integers)
+template <bool I8> __device__ __forceinline__ void mma16(f32x4_t& c, const td_u32x4& a, const td_u32x4& b) {
+    if constexpr (I8) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
 
 // RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
 // slice start instead (in bounds) and the fragments that hold them are zeroed as they are read.
-template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
+template <int EPI, bool RAGGED, int WM, int NA, int NB>
 struct GemmTile {
     static constexpr int WN = kWavesPerTile / WM;
     static constexpr int TM = WM * NA * 16, TN = WN * NB * 16;
     static constexpr int UA = TM * kSliceBytes, UB = TN * kSliceBytes;      // bytes of one slice
+    static constexpr bool kOnce = TM == 64;                                 // one row of tiles: B is read by one block
     static constexpr int LA = TM / 64, LB = TN / 64;                        // loads per wavefront and slice
+    // REPAIR: bounds and exponents wait in LDS for the range test (the largest tile has no room and reads them then)
+    static constexpr int kPar = EPI == EPI_REPAIR && TM * TN < 256 * 256 ? 3 * 1024 : 0;
     // as many slices as fit; A one ahead of B where the two do not fit equally often
-    static constexpr int SB = kLdsBytes / (UA + UB) > 6 ? 6 : kLdsBytes / (UA + UB);
-    static constexpr int SA = SB < 6 && SB * (UA + UB) + UA <= kLdsBytes ? SB + 1 : SB;
+    static constexpr int kRoom = kLdsBytes - kPar;
+    static constexpr int SB = kRoom / (UA + UB) > 10 ? 10 : kRoom / (UA + UB);
+    static constexpr int SA = SB < 10 && SB * (UA + UB) + UA <= kRoom ? SB + 1 : SB;
     static constexpr int kRing = SA * UA + SB * UB;
     static constexpr int kPer = LA + LB;
     // loads that may still be in flight when slice kt+2 has to be there (see the order in the kernel)
     static constexpr int kWaitB = LA + (SB - 2) * kPer, kWaitA = (SA - 2) * kPer;
     static constexpr int kWait = kWaitB < kWaitA ? kWaitB : kWaitA;
-    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_DELTA ? 10 : 4);   // LDS of a wavefront in the epilogue
-    static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_DELTA ? 3 * TN * 4 : 0);
-    static constexpr int kLds = kRing > kEpiLds ? kRing : kEpiLds;
+    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_REPAIR ? 10 : 4);   // LDS of a wavefront in the epilogue
+    static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_REPAIR ? 3 * TN * 4 : 0);
+    static constexpr int kLds = kRing + kPar > kEpiLds ? kRing + kPar : kEpiLds;
     static_assert(SB >= 2 && SA >= 2 && kWait + kPer <= 63 && kLds <= kLdsBytes, "slice buffers");
 };
 
-template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
+template <int EPI, bool RAGGED, int WM, int NA, int NB>
 __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) {
-    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
-    typedef typename Mma<I8>::acc_t acc_t;
+    typedef GemmTile<EPI, RAGGED, WM, NA, NB> G;
     constexpr int WN = G::WN, TM = G::TM, TN = G::TN, SA = G::SA, SB = G::SB, LA = G::LA, LB = G::LB;
     extern __shared__ __align__(1024) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -239,12 +246,21 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     if (tile_m >= tm.tiles_m || tile_n >= tm.tiles_n) return;
     const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
 
-    // slices [s0, s0 + nk) of this block's range, starting at s0 + rot
+    // slices [s0, s0 + nk) of this block's range, from a starting point of its own (REPAIR: of either product)
     const int nk1 = (int)((p.k + kSliceBytes - 1) / kSliceBytes), nk2 = (int)((p.k2 + kSliceBytes - 1) / kSliceBytes);
     const int s0 = ks * tm.slices;
     const int nk = max(0, min(tm.slices, nk1 + nk2 - s0));
-    const int rot = nk > 0 ? ((local & 7) + xcd * nk / 8) % nk : 0;
-    auto slice_of = [&](int kt) { const int s = kt + rot; return s0 + (s >= nk ? s - nk : s); };
+    auto start = [&](int len) { return len > 0 ? ((local & 7) + xcd * len / 8) % len : 0; };
+    const int rot = start(EPI == EPI_REPAIR ? nk1 : nk), rot2 = EPI == EPI_REPAIR ? start(nk2) : 0;
+    auto slice_of = [&](int kt) {
+        if constexpr (EPI == EPI_REPAIR) {
+            const bool second = kt >= nk1;
+            const int s = second ? kt + rot2 : kt + rot;
+            return s - (second ? (s >= nk1 + nk2 ? nk2 : 0) : (s >= nk1 ? nk1 : 0));
+        }
+        const int s = kt + rot;
+        return s0 + (s >= nk ? s - nk : s);
+    };
 
     const uint32_t rows_a = (uint32_t)min((int64_t)TM, p.M - m0), rows_b = (uint32_t)min((int64_t)TN, p.N - n0);
     const i32x4_t ra1 = buffer_of(p.A + (size_t)m0 * p.k, rows_a * p.k), rb1 = buffer_of(p.B + (size_t)n0 * p.k, rows_b * p.k);
@@ -259,21 +275,33 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
         lds_b = __builtin_amdgcn_readfirstlane(base + SA * G::UA + wave * (G::UB / kWavesPerTile));
     }
     const uint32_t row_a = (uint32_t)(wave * (TM / 8) + lrow), row_b = (uint32_t)(wave * (TN / 8) + lrow);
-    auto load_one = [&](bool is_a, int i, uint32_t buf, int kt) {
-        const bool live = kt < nk;
+    struct Source {                                   // one operand's slice (uniform)
+        i32x4_t rs;
+        uint32_t soff, pitch;
+    };
+    auto source = [&](bool is_a, int kt) {
+        const bool live = kt < nk;                                  // past the last slice: an empty buffer
         const int s = live ? slice_of(kt) : 0;
         const bool second = s >= nk1;
-        const uint32_t soff = (uint32_t)(second ? s - nk1 : s) * kSliceBytes;
-        const uint32_t pitch = second ? p.k2 : p.k;
-        i32x4_t rs = is_a ? (second ? ra2 : ra1) : (second ? rb2 : rb1);
-        rs.z = live ? rs.z : 0;                                     // past the last slice: an empty buffer
+        Source o;
+        const i32x4_t r1 = is_a ? ra1 : rb1, r2 = is_a ? ra2 : rb2;
+        o.rs.x = second ? r2.x : r1.x;
+        o.rs.y = second ? r2.y : r1.y;
+        o.rs.z = live ? (second ? r2.z : r1.z) : 0;
+        o.rs.w = r1.w;
+        o.soff = (uint32_t)(second ? s - nk1 : s) * kSliceBytes;
+        o.pitch = second ? p.k2 : p.k;
+        return o;
+    };
+    auto load_one = [&](bool is_a, int i, uint32_t buf, const Source& o) {
         uint32_t pc = (uint32_t)piece * 16u;
-        if constexpr (RAGGED) pc = soff + pc < pitch ? pc : 0u;
-        const uint32_t voff = ((is_a ? row_a : row_b) + 8u * i) * pitch + pc;
-        load_to_lds(is_a ? lds_a + buf * G::UA + i * 1024u : lds_b + buf * G::UB + i * 1024u, voff, rs, soff);
+        if constexpr (RAGGED) pc = o.soff + pc < o.pitch ? pc : 0u;
+        const uint32_t voff = ((is_a ? row_a : row_b) + 8u * i) * o.pitch + pc;
+        if (is_a) load_to_lds(lds_a + buf * G::UA + i * 1024u, voff, o.rs, o.soff);
+        else load_to_lds<G::kOnce>(lds_b + buf * G::UB + i * 1024u, voff, o.rs, o.soff);
     };
 
-    acc_t acc[NA][NB];
+    f32x4_t acc[NA][NB];
 #pragma unroll
     for (int i = 0; i < NA; ++i)
 #pragma unroll
@@ -305,18 +333,28 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     constexpr int kLoadEvery = NM / G::kPer > 0 ? NM / G::kPer : 1;
     static_assert(kLoadEvery * G::kPer <= NM, "a slice's loads fit between its MFMAs");
 
+    if constexpr (G::kPar > 0) {
+        const uint32_t at = __builtin_amdgcn_readfirstlane(
+            (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + G::kRing + wave * 1024);
+        if (wave == 0) load_to_lds(at, lane * 16, buffer_of(p.lo + n0, rows_b * 4), 0u);
+        if (wave == 1) load_to_lds(at, lane * 16, buffer_of(p.hi + n0, rows_b * 4), 0u);
+        if (wave == 2) load_to_lds(at, lane * 16, buffer_of(p.e + m0, (rows_a * 4 + 15u) & ~15u), 0u);
+    }
     // In period p (the half of slice p behind the barrier, and the first half of slice p+1) the loads of
     // B(p+SB) and then of A(p+SA) are issued; the prologue issues those of periods -SB .. -1.
 #pragma unroll
-    for (int s = 0; s < SA - SB; ++s)
+    for (int s = 0; s < SA - SB; ++s) {
+        const Source o = source(true, s);
 #pragma unroll
-        for (int i = 0; i < LA; ++i) load_one(true, i, s, s);
+        for (int i = 0; i < LA; ++i) load_one(true, i, s, o);
+    }
 #pragma unroll
     for (int s = 0; s < SB; ++s) {
+        const Source ob = source(false, s), oa = source(true, s + SA - SB);
 #pragma unroll
-        for (int i = 0; i < LB; ++i) load_one(false, i, s, s);
+        for (int i = 0; i < LB; ++i) load_one(false, i, s, ob);
 #pragma unroll
-        for (int i = 0; i < LA; ++i) load_one(true, i, s + SA - SB, s + SA - SB);
+        for (int i = 0; i < LA; ++i) load_one(true, i, s + SA - SB, oa);
     }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(G::kWait + G::kPer) : "memory");
     __builtin_amdgcn_s_barrier();
@@ -328,45 +366,96 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     }
     asm volatile("s_nop 7" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const uint32_t na = ba + 1 == SA ? 0 : ba + 1, nb = bb + 1 == SB ? 0 : bb + 1;
-        const int cur = RAGGED ? slice_of(kt) : 0, nxt = RAGGED ? slice_of(kt + 1 < nk ? kt + 1 : kt) : 0;
+    auto multiply = [&](auto i8, int from, int to) {
+        for (int kt = from; kt < to; ++kt) {
+            const Source ob = source(false, kt + SB), oa = source(true, kt + SA);
+            const uint32_t na = ba + 1 == SA ? 0 : ba + 1, nb = bb + 1 == SB ? 0 : bb + 1;
+            const int cur = RAGGED ? slice_of(kt) : 0, nxt = RAGGED ? slice_of(kt + 1 < nk ? kt + 1 : kt) : 0;
 #pragma unroll
-        for (int q = 0; q < NM; ++q) {
+            for (int q = 0; q < NM; ++q) {
 #pragma unroll
-            for (int u = 0; u < kReadsPer; ++u) {
-                const int t = (q / kReadEvery) * kReadsPer + u;
-                if (q % kReadEvery == 0 && t < NR) read_one(1, t, ba, bb, 1, cur);
+                for (int u = 0; u < kReadsPer; ++u) {
+                    const int t = (q / kReadEvery) * kReadsPer + u;
+                    if (q % kReadEvery == 0 && t < NR) read_one(1, t, ba, bb, 1, cur);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (RAGGED) asm volatile("s_nop 1");
+                mma16<decltype(i8)::value>(acc[q / NB][q % NB], fb[0][q % NB], fa[0][q / NB]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (RAGGED) asm volatile("s_nop 1");
-            Mma<I8>::go(acc[q / NB][q % NB], fb[0][q % NB], fa[0][q / NB]);
-            __builtin_amdgcn_sched_barrier(0);
+            // slice kt+1 has arrived (this wavefront's share; the barrier makes it everybody's) and the last
+            // fragments of slice kt are in registers
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G::kWait) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+#pragma unroll
+                for (int u = 0; u < kReadsPer; ++u) {
+                    const int t = (q / kReadEvery) * kReadsPer + u;
+                    if (q % kReadEvery == 0 && t < NR) read_one(0, t, na, nb, 0, nxt);
+                }
+                if (q % kLoadEvery == 0) {
+                    const int t = q / kLoadEvery;
+                    if (t < LB) load_one(false, t, bb, ob);
+                    else if (t < LB + LA) load_one(true, t - LB, ba, oa);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (RAGGED) asm volatile("s_nop 1");
+                mma16<decltype(i8)::value>(acc[q / NB][q % NB], fb[1][q % NB], fa[1][q / NB]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ba = na;
+            bb = nb;
         }
-        // slice kt+1 has arrived (this wavefront's share; the barrier makes it everybody's) and the last
-        // fragments of slice kt are in registers
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G::kWait) : "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+    };
+    [[maybe_unused]] uint32_t bits[NA];               // REPAIR: bit 4j + q: the element acc[i][j][q] is flagged
+    if constexpr (EPI == EPI_REPAIR) {
+        multiply(std::true_type{}, 0, nk1);
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // (the products are in inline assembly: their results are waited for here)
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4_t lo[NB], hi[NB];
+        int ex[NA];
+        const float* par = reinterpret_cast<const float*>(lds + G::kRing);
+        const int nc = wn * NB * 16 + 4 * fp, mr = wm * NA * 16 + frow;   // first column, row of this lane in the tile
+        const f32x4_t none = {0, 0, 0, 0};
 #pragma unroll
-        for (int q = 0; q < NM; ++q) {
-#pragma unroll
-            for (int u = 0; u < kReadsPer; ++u) {
-                const int t = (q / kReadEvery) * kReadsPer + u;
-                if (q % kReadEvery == 0 && t < NR) read_one(0, t, na, nb, 0, nxt);
+        for (int j = 0; j < NB; ++j) {                // N % 8 == 0: four columns or none
+            const bool in = n0 + nc + j * 16 < p.N;
+            if constexpr (G::kPar > 0) {
+                lo[j] = *reinterpret_cast<const f32x4_t*>(par + nc + j * 16);
+                hi[j] = *reinterpret_cast<const f32x4_t*>(par + 256 + nc + j * 16);
+            } else {
+                lo[j] = in ? *reinterpret_cast<const f32x4_t*>(p.lo + n0 + nc + j * 16) : none;
+                hi[j] = in ? *reinterpret_cast<const f32x4_t*>(p.hi + n0 + nc + j * 16) : none;
             }
-            if (q % kLoadEvery == 0) {
-                const int t = q / kLoadEvery;
-                if (t < LB) load_one(false, t, bb, kt + SB);
-                else if (t < LB + LA) load_one(true, t - LB, ba, kt + SA);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (RAGGED) asm volatile("s_nop 1");
-            Mma<I8>::go(acc[q / NB][q % NB], fb[1][q % NB], fa[1][q / NB]);
-            __builtin_amdgcn_sched_barrier(0);
         }
-        ba = na;
-        bb = nb;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            if constexpr (G::kPar > 0) ex[i] = reinterpret_cast<const int*>(par)[512 + mr + i * 16];
+            else ex[i] = m0 + mr + i * 16 < p.M ? p.e[m0 + mr + i * 16] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            bits[i] = 0u;
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = ldexpf((float)__float_as_int(acc[i][j][q]), ex[i]);
+                    const bool inside = (v >= lo[j][q]) && (v < hi[j][q]);
+                    if (!inside && n0 + nc + j * 16 < p.N && m0 + mr + i * 16 < p.M) bits[i] |= 1u << (4 * j + q);
+                    acc[i][j][q] = 0.0f;
+                }
+            __builtin_amdgcn_sched_barrier(0);        // (one row block at a time: fewer live registers)
+        }
+        asm volatile("s_nop 7" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(std::false_type{}, nk1, nk);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(bits[i]));   // (nothing derived from them is kept through the loop)
+    } else {
+        multiply(std::false_type{}, 0, nk);
     }
     // (the products are in inline assembly: their results are waited for here)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
@@ -404,84 +493,46 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
             }
             __builtin_amdgcn_wave_barrier();
         }
-    } else if constexpr (EPI == EPI_PRED) {
-        // range test; the four lanes of a row and (where the tile holds them) two tile columns make a word of 32 bits
-        f32x4_t lo[NB], hi[NB];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int64_t n = nw + j * 16 + 4 * fp;                  // N % 4 == 0: all four or none
-            lo[j] = n < p.N ? *reinterpret_cast<const f32x4_t*>(p.lo + n) : f32x4_t{0, 0, 0, 0};
-            hi[j] = n < p.N ? *reinterpret_cast<const f32x4_t*>(p.hi + n) : f32x4_t{0, 0, 0, 0};
-        }
-        int ex[NA];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) ex[i] = mw + i * 16 + frow < p.M ? p.e[mw + i * 16 + frow] : 0;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int64_t m = mw + i * 16 + frow;
-            const int e = ex[i];
-            uint32_t word[(NB + 1) / 2];
-#pragma unroll
-            for (int w = 0; w < (NB + 1) / 2; ++w) word[w] = 0u;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                uint32_t nib = 0u;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float v = ldexpf((float)acc[i][j][q], e);
-                    if (!((v >= lo[j][q]) && (v < hi[j][q]))) nib |= 1u << q;
-                }
-                if (nw + j * 16 + 4 * fp >= p.N) nib = 0u;
-                word[j / 2] |= nib << (4 * fp + 16 * (j & 1));
-            }
-#pragma unroll
-            for (int w = 0; w < (NB + 1) / 2; ++w) {
-                word[w] |= __shfl_xor(word[w], 16);
-                word[w] |= __shfl_xor(word[w], 32);
-                const int64_t n = nw + w * 32;
-                if (fp == 0 && m < p.M && n < p.N) {
-                    uint32_t* row = p.mask + (size_t)m * p.mask_words;
-                    if constexpr (NB >= 2) row[n >> 5] = word[w];
-                    else reinterpret_cast<uint16_t*>(row)[n >> 4] = (uint16_t)word[w];
-                }
-            }
-            if constexpr (NB == 1) {                                 // the upper half of a last word nobody else writes
-                if (fp == 0 && m < p.M && nw < p.N && nw + 16 >= p.N && ((nw >> 4) & 1) == 0)
-                    reinterpret_cast<uint16_t*>(p.mask + (size_t)m * p.mask_words)[(nw >> 4) + 1] = 0;
-            }
-        }
     } else {
-        // DELTA: D = sigma(z) - (a z + c) where the mask has a bit, else 0.  The flagged elements (few) of 16
-        // rows are listed in LDS first and then evaluated 64 at a time: evaluating all 128 accumulators of a
-        // lane would run sigma 128 times per wavefront, the list needs about (share flagged) x 128 runs.
+        // REPAIR: the flagged elements (few) of 16 rows are listed in LDS first and then evaluated 64 at a time:
+        // evaluating all accumulators of a lane would run sigma 128 times per wavefront in the largest tile, the
+        // list needs about (share flagged) x 128 runs.
         // HIDDEN: sigma(z + b) of every element.
         bf16_t* chunk = reinterpret_cast<bf16_t*>(lds + wave * G::kEpiWave);
         uint2* list = reinterpret_cast<uint2*>(lds + wave * G::kEpiWave + 16 * CW * 2);
         float* par = reinterpret_cast<float*>(lds + kWavesPerTile * G::kEpiWave);
-        uint32_t bits[EPI == EPI_DELTA ? NA : 1];                        // bit 4j + q of this lane's elements
-        if constexpr (EPI == EPI_DELTA) {
-#pragma unroll
-            for (int i = 0; i < NA; ++i) {
-                const int64_t m = mw + i * 16 + frow;
-                bits[i] = 0u;
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const int64_t n = nw + j * 16 + 4 * fp;
-                    if (m < p.M && n < p.N)
-                        bits[i] |= ((p.mask[(size_t)m * p.mask_words + (n >> 5)] >> (n & 31)) & 15u) << (4 * j);
-                }
-            }
+        if constexpr (EPI == EPI_REPAIR) {
             for (int c = tid; c < TN; c += 512) {
                 const int64_t n = n0 + c < p.N ? n0 + c : p.N - 1;
                 par[c] = td_bf16_to_f32(p.bias[n]);
-                par[TN + c] = p.lo[n];
-                par[2 * TN + c] = p.hi[n];
+                par[TN + c] = p.slope[n];
+                par[2 * TN + c] = p.icept[n];
             }
             __syncthreads();
         }
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            if constexpr (EPI == EPI_DELTA) {
+            if constexpr (EPI == EPI_REPAIR) {
+                // mask: the four lanes of a row and (where the tile holds them) two tile columns make a word of 32 bits
+                const int64_t m = mw + i * 16 + frow;
+#pragma unroll
+                for (int w = 0; w < (NB + 1) / 2; ++w) {
+                    uint32_t word = ((bits[i] >> (8 * w)) & 15u) << (4 * fp);
+                    if constexpr (NB >= 2) word |= ((bits[i] >> (8 * w + 4)) & 15u) << (4 * fp + 16);
+                    word |= __shfl_xor(word, 16);
+                    word |= __shfl_xor(word, 32);
+                    const int64_t n = nw + w * 32;
+                    if (fp == 0 && m < p.M && n < p.N) {
+                        uint32_t* row = p.mask + (size_t)m * p.mask_words;
+                        if constexpr (NB >= 2) {
+                            row[n >> 5] = word;
+                        } else {
+                            uint16_t* half = reinterpret_cast<uint16_t*>(row) + (n >> 4);
+                            half[0] = (uint16_t)word;
+                            if (n + 16 >= p.N && ((n >> 4) & 1) == 0) half[1] = 0;   // the rest of a last word
+                        }
+                    }
+                }
                 const td_u32x4 zero = {0, 0, 0, 0};
                 for (int v = lane; v < 16 * CW / 8; v += 64) reinterpret_cast<td_u32x4*>(chunk)[v] = zero;
                 __builtin_amdgcn_wave_barrier();
@@ -495,7 +546,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                         if (flagged) {
                             const int at = total + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32),
                                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
-                            list[at] = make_uint2(__float_as_uint((float)acc[i][j][q]), (uint32_t)(frow * CW + j * 16 + 4 * fp + q));
+                            list[at] = make_uint2(__float_as_uint(acc[i][j][q]), (uint32_t)(frow * CW + j * 16 + 4 * fp + q));
                         }
                         total += __popcll(all);
                     }
@@ -504,7 +555,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                     const uint2 en = list[t];
                     const int c = wn * CW + (int)(en.y % CW);
                     const float z = __uint_as_float(en.x) + par[c];
-                    chunk[en.y] = td_f32_to_bf16(td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]));
+                    chunk[en.y] = (bf16_t)to_bf16(td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]));
                 }
             } else {
 #pragma unroll
@@ -516,7 +567,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                                          __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
                     uint32_t o[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = to_bf16(td_act((float)acc[i][j][q] + bv[q], p.act));
+                    for (int q = 0; q < 4; ++q) o[q] = to_bf16(td_act(acc[i][j][q] + bv[q], p.act));
                     *reinterpret_cast<uint2*>(chunk + frow * CW + j * 16 + 4 * fp) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
                 }
             }
@@ -538,12 +589,13 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 // the partial tile's bytes, written and read again; at most kPartRows rows of partial sums are kept).
 constexpr int64_t kPartRows = 4096;
 struct TileChoice { int shape, splits; };
-constexpr int kShapeM[] = {256, 192, 256, 192, 128, 128}, kShapeN[] = {256, 256, 128, 128, 128, 64};
+constexpr int kShapes = 7;
+constexpr int kShapeM[kShapes] = {256, 192, 256, 192, 128, 128, 64}, kShapeN[kShapes] = {256, 256, 128, 128, 128, 64, 64};
 
 TileChoice choose_tile(int64_t M, int64_t N, int64_t slices, bool splittable, bool store_f32) {
     TileChoice best{0, 1};
     double best_cost = 1e300;
-    for (int s = 0; s < 6; ++s)
+    for (int s = 0; s < kShapes; ++s)
         for (int sp = 1; sp <= (splittable ? 8 : 1); sp *= 2) {
             if (sp > 1 && (slices / sp < 8 || sp * M > kPartRows)) break;
             const TileMap t = make_tile_map(M, N, kShapeM[s], kShapeN[s], (int)slices, sp);
@@ -557,41 +609,44 @@ TileChoice choose_tile(int64_t M, int64_t N, int64_t slices, bool splittable, bo
     return best;
 }
 
-template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB>
-void launch_shape(const GemmArgs& p, int splits, hipStream_t s) {
-    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
-    const int slices = (int)((p.k + 127) / 128 + (p.k2 + 127) / 128);
-    const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, splits);
-    hipLaunchKernelGGL((gemm_tile_kernel<I8, EPI, RAGGED, WM, NA, NB>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
-}
-
-template <bool I8, int EPI, bool RAGGED>
-void launch_tile(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
-    switch (c.shape) {
-        case 0: launch_shape<I8, EPI, RAGGED, 2, 8, 4>(p, c.splits, s); break;
-        case 1: launch_shape<I8, EPI, RAGGED, 2, 6, 4>(p, c.splits, s); break;
-        case 2: launch_shape<I8, EPI, RAGGED, 2, 8, 2>(p, c.splits, s); break;
-        case 3: launch_shape<I8, EPI, RAGGED, 2, 6, 2>(p, c.splits, s); break;
-        case 4: launch_shape<I8, EPI, RAGGED, 2, 4, 2>(p, c.splits, s); break;
-        default: launch_shape<I8, EPI, RAGGED, 2, 4, 1>(p, c.splits, s); break;
+// f(wm, na, nb) with the constants of a shape
+template <typename F> void for_shape(int shape, F f) {
+    using std::integral_constant;
+    typedef integral_constant<int, 1> c1;
+    typedef integral_constant<int, 2> c2;
+    typedef integral_constant<int, 4> c4;
+    typedef integral_constant<int, 6> c6;
+    typedef integral_constant<int, 8> c8;
+    switch (shape) {
+        case 0: f(c2{}, c8{}, c4{}); break;
+        case 1: f(c2{}, c6{}, c4{}); break;
+        case 2: f(c2{}, c8{}, c2{}); break;
+        case 3: f(c2{}, c6{}, c2{}); break;
+        case 4: f(c2{}, c4{}, c2{}); break;
+        case 5: f(c2{}, c4{}, c1{}); break;
+        default: f(c2{}, c2{}, c1{}); break;
     }
 }
 
-template <bool I8, int EPI, bool RAGGED, int WM, int NA, int NB> tardis_status_t raise_shape() {
-    typedef GemmTile<I8, EPI, RAGGED, WM, NA, NB> G;
-    TD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<I8, EPI, RAGGED, WM, NA, NB>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds));
-    return TARDIS_OK;
+template <int EPI, bool RAGGED> void launch_tile(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
+    for_shape(c.shape, [&](auto wm, auto na, auto nb) {
+        typedef GemmTile<EPI, RAGGED, wm, na, nb> G;
+        const int slices = (int)((p.k + 127) / 128 + (p.k2 + 127) / 128);
+        const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, c.splits);
+        hipLaunchKernelGGL((gemm_tile_kernel<EPI, RAGGED, wm, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
+    });
 }
 
-template <bool I8, int EPI, bool RAGGED> tardis_status_t raise_lds() {
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 8, 4>()));
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 6, 4>()));
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 8, 2>()));
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 6, 2>()));
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 4, 2>()));
-    TD_TRY((raise_shape<I8, EPI, RAGGED, 2, 4, 1>()));
-    return TARDIS_OK;
+template <int EPI, bool RAGGED> tardis_status_t raise_lds() {
+    tardis_status_t st = TARDIS_OK;
+    for (int shape = 0; shape < kShapes; ++shape)
+        for_shape(shape, [&](auto wm, auto na, auto nb) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<EPI, RAGGED, wm, na, nb>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     GemmTile<EPI, RAGGED, wm, na, nb>::kLds);
+            if (e != hipSuccess) st = TARDIS_ERR_HIP;
+        });
+    return st;
 }
 
 template <typename T>
@@ -617,13 +672,12 @@ int64_t slices_of(int64_t bytes) { return (bytes + kSliceBytes - 1) / kSliceByte
 tardis_status_t td_gemm_init() {
     static td_once once;
     return once.run([]() -> tardis_status_t {
-        TD_TRY((raise_lds<false, EPI_F32, false>()));
-        TD_TRY((raise_lds<false, EPI_F32, true>()));
-        TD_TRY((raise_lds<false, EPI_PART, false>()));
-        TD_TRY((raise_lds<false, EPI_PART, true>()));
-        TD_TRY((raise_lds<true, EPI_PRED, false>()));
-        TD_TRY((raise_lds<false, EPI_DELTA, false>()));
-        TD_TRY((raise_lds<false, EPI_HIDDEN, false>()));
+        TD_TRY((raise_lds<EPI_F32, false>()));
+        TD_TRY((raise_lds<EPI_F32, true>()));
+        TD_TRY((raise_lds<EPI_PART, false>()));
+        TD_TRY((raise_lds<EPI_PART, true>()));
+        TD_TRY((raise_lds<EPI_HIDDEN, false>()));
+        TD_TRY((raise_lds<EPI_REPAIR, false>()));
         return TARDIS_OK;
     });
 }
@@ -649,8 +703,8 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const v
         p.C = C;
         p.bias = static_cast<const bf16_t*>(row_bias);
         const TileChoice c = choose_tile(M, N, slices_of(p.k) + slices_of(p.k2), false, true);
-        if (K % 64 != 0) launch_tile<false, EPI_F32, true>(p, c, s);
-        else launch_tile<false, EPI_F32, false>(p, c, s);
+        if (K % 64 != 0) launch_tile<EPI_F32, true>(p, c, s);
+        else launch_tile<EPI_F32, false>(p, c, s);
     } else {
         for (int part = 0; part < (A2 ? 2 : 1); ++part) {
             if (dtype == TARDIS_BF16)
@@ -664,45 +718,45 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const v
 }
 
 // The products of calls with many tokens (bf16 layers, d % 128 == 0, h % 8 == 0, 16-byte aligned operands).
-// mask[t] = range test of Xq . Q^T (exact int32 sums)
-tardis_status_t td_gemm_predict(const int8_t* XQ, const int8_t* Q, const int32_t* e, const float* tlo, const float* thi,
-                                uint32_t* mask, int mask_words, int64_t n, int64_t h, int64_t d, hipStream_t s) {
+// mask[t] = range test of Xq . Q^T (exact int32 sums), out[t] = sigma(z) - (a z + c) at its bits, else 0, z = X . W1^T + b1
+tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
+                               uint32_t* mask, void* out, int64_t n, hipStream_t s) {
     GemmArgs p{};
-    p.A = p.A2 = bytes_of(XQ);
-    p.B = p.B2 = bytes_of(Q);
+    p.A = bytes_of(XQ);
+    p.B = bytes_of(L->Q);
+    p.A2 = bytes_of(X);
+    p.B2 = bytes_of(L->W1);
     p.M = n;
-    p.N = h;
-    p.k = (uint32_t)d;
+    p.N = L->h;
+    p.k = (uint32_t)L->d;
+    p.k2 = (uint32_t)(L->d * 2);
+    p.bias = static_cast<const bf16_t*>(b1);
+    p.out = static_cast<bf16_t*>(out);
+    p.lo = L->tlo;
+    p.hi = L->thi;
+    p.slope = L->a;
+    p.icept = L->c;
     p.e = e;
-    p.lo = tlo;
-    p.hi = thi;
     p.mask = mask;
-    p.mask_words = mask_words;
-    launch_tile<true, EPI_PRED, false>(p, choose_tile(n, h, slices_of(p.k), false, false), s);
+    p.mask_words = (int)L->mask_words;
+    p.act = L->act;
+    launch_tile<EPI_REPAIR, false>(p, choose_tile(n, L->h, slices_of(p.k) + slices_of(p.k2), false, false), s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
 
-// out[t] = sigma(z) - (a z + c) at the bits of mask[t], else 0; z = X . W1^T + b1.  mask null: out = sigma(z)
-tardis_status_t td_gemm_hidden(const void* X, const void* W1, const void* b1, const float* a, const float* c,
-                               const uint32_t* mask, int mask_words, int act, void* out, int64_t n, int64_t h, int64_t d,
-                               hipStream_t s) {
+// out[t] = sigma(X . W1^T + b1), the dense FFN's hidden activations
+tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const void* b1, void* out, int64_t n, hipStream_t s) {
     GemmArgs p{};
     p.A = p.A2 = bytes_of(X);
-    p.B = p.B2 = bytes_of(W1);
+    p.B = p.B2 = bytes_of(L->W1);
     p.M = n;
-    p.N = h;
-    p.k = (uint32_t)(d * 2);
+    p.N = L->h;
+    p.k = (uint32_t)(L->d * 2);
     p.bias = static_cast<const bf16_t*>(b1);
-    p.lo = a;
-    p.hi = c;
-    p.mask = const_cast<uint32_t*>(mask);
-    p.mask_words = mask_words;
-    p.act = act;
+    p.act = L->act;
     p.out = static_cast<bf16_t*>(out);
-    const TileChoice t = choose_tile(n, h, slices_of(p.k), false, false);
-    if (mask) launch_tile<false, EPI_DELTA, false>(p, t, s);
-    else launch_tile<false, EPI_HIDDEN, false>(p, t, s);
+    launch_tile<EPI_HIDDEN, false>(p, choose_tile(n, L->h, slices_of(p.k), false, false), s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
@@ -723,8 +777,8 @@ tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, con
     p.C = part;
     const TileChoice c = choose_tile(n, d, slices_of(p.k) + slices_of(p.k2), true, true);
     *parts = c.splits;
-    if (h % 64 != 0) launch_tile<false, EPI_PART, true>(p, c, s);
-    else launch_tile<false, EPI_PART, false>(p, c, s);
+    if (h % 64 != 0) launch_tile<EPI_PART, true>(p, c, s);
+    else launch_tile<EPI_PART, false>(p, c, s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }

@@ -87,7 +87,8 @@ quantize_rows_kernel(const bf16_t* __restrict__ X, int d, int8_t* __restrict__ X
     if (threadIdx.x == 0) E[t] = e;
 }
 
-// y[t] = sum over the parts of Y[t] + bias (optionally RMS-normalised), one block per token; d % 4 == 0.
+// y[t] = sum over the parts of Y[t] + bias (optionally RMS-normalised); d % 4 == 0.  One block per token with the
+// norm, which needs whole rows; gridDim.y blocks of 1024 columns each per token without (64 tokens: 7.3 -> 4.6 us).
 // bias: fp32 (b') or bf16 (b2), or neither.
 __global__ void __launch_bounds__(256)
 finish_rows_kernel(const float* __restrict__ Y, int parts, size_t part_stride, const float* __restrict__ bias32,
@@ -131,7 +132,7 @@ finish_rows_kernel(const float* __restrict__ Y, int parts, size_t part_stride, c
         __syncthreads();
         scale = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
     }
-    for (int v = threadIdx.x; v < d / 4; v += 256) {
+    for (int v = (int)blockIdx.y * 256 + (int)threadIdx.x; v < d / 4; v += (int)gridDim.y * 256) {
         const float4 s = value(v);
         const bf16_t o[4] = {td_f32_to_bf16(s.x * scale), td_f32_to_bf16(s.y * scale), td_f32_to_bf16(s.z * scale),
                              td_f32_to_bf16(s.w * scale)};
@@ -173,7 +174,7 @@ bool aligned(const void* p, uintptr_t to) { return (reinterpret_cast<uintptr_t>(
 
 void finish(const PromptScratch& w, int parts, const float* bias32, const bf16_t* bias16, int64_t n, int64_t d, bf16_t* y,
             int norm_out, hipStream_t s) {
-    hipLaunchKernelGGL(finish_rows_kernel, dim3((unsigned)n), dim3(256), 0, s, w.part, parts, (size_t)n * d, bias32, bias16,
+    hipLaunchKernelGGL(finish_rows_kernel, dim3((unsigned)n, norm_out ? 1u : (unsigned)((d + 1023) / 1024)), dim3(256), 0, s, w.part, parts, (size_t)n * d, bias32, bias16,
                        (int)d, y, aligned(y, 8) ? 1 : 0, norm_out, kRmsEps);
 }
 
@@ -197,9 +198,7 @@ static tardis_status_t prefill_chunk(tardis_layer_s* L, const bf16_t* x, int64_t
         hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)n), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
         x = w.x;
     }
-    const int words = (int)L->mask_words;
-    TD_TRY(td_gemm_predict(w.xq, L->Q, w.e, L->tlo, L->thi, mask, words, n, h, d, s));
-    TD_TRY(td_gemm_hidden(x, L->W1, L->b1 ? L->b1 : L->zeros_h, L->a, L->c, mask, words, (int)L->act, w.hid, n, h, d, s));
+    TD_TRY(td_gemm_repair(L, w.xq, w.e, x, L->b1 ? L->b1 : L->zeros_h, mask, w.hid, n, s));
     int parts = 1;
     TD_TRY(td_gemm_output(x, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
     finish(w, parts, L->bp, nullptr, n, d, y, norm_out, s);
@@ -233,8 +232,7 @@ tardis_status_t td_dense_prefill(tardis_layer_s* L, const void* xv, int64_t n, v
             hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)nc), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
             x = w.x;
         }
-        TD_TRY(td_gemm_hidden(x, L->W1, L->b1 ? L->b1 : L->zeros_h, nullptr, nullptr, nullptr, 0, (int)L->act, w.hid, nc, h,
-                              d, s));
+        TD_TRY(td_gemm_hidden(L, x, L->b1 ? L->b1 : L->zeros_h, w.hid, nc, s));
         int parts = 1;
         TD_TRY(td_gemm_output(nullptr, nullptr, w.hid, L->W2, w.part, &parts, nc, d, h, s));
         finish(w, parts, nullptr, static_cast<const bf16_t*>(L->b2), nc, d, static_cast<bf16_t*>(yv) + t0 * d, 0, s);
