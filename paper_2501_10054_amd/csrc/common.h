@@ -93,7 +93,7 @@ struct tardis_layer_s {
     // working memory of the online calls (sized by max_batch)
     float* yacc;       // max_batch x d fp32 accumulator
     uint32_t* mask;    // max_batch x mask_words
-    int32_t* counts;   // max_batch flagged-neuron counters
+    int32_t* counts;   // max_batch flagged-neuron counters (zero between calls)
     int32_t* list;     // max_batch x h flagged indices
     float* hidden;     // max_batch x h activations for the dense baseline
     int32_t* sync;     // small block of device counters (zero between calls)

@@ -282,6 +282,19 @@ def test_prompt_path_takes_tokens_at_any_address():
     L.close()
 
 
+@pytest.mark.parametrize("d,h,dtype", [(1, 33, "f32"), (5, 40, "f32"), (128, 512, "f32"), (129, 500, "f32"),
+                                       (1030, 20, "bf16"), (128, 512, "bf16"), (180, 1100, "bf16")])
+def test_layers_of_one_block_a_token(d, h, dtype):
+    """Around the size up to which a token is one block (128 KB of W' and predictor rows): rows shorter than a
+    vector, more columns than threads, sizes just above and below; several tokens in a call and one each."""
+    seed = synth.workload_seed(9, 70)
+    layer = custom_layer(d, h, dtype, seed, 0.3, True)
+    X_cal = synth.make_tokens(200, d, dtype, seed, synth.STREAM_CAL)
+    X = synth.make_tokens(5, d, dtype, seed, synth.STREAM_TEST)
+    run_case(layer, X_cal, X, 0.85, check_calibrate=False)
+    run_case(layer, X_cal, X, 0.85, batched=True, check_calibrate=False)
+
+
 @pytest.mark.parametrize("d,h", [(64, 128), (72, 136), (136, 72), (75, 130), (520, 1032)])
 def test_fold_tile_edges(d, h):
     """Whole and partial 64 x 64 tiles of the transposes, rows that are and are not whole 16-byte vectors."""
