@@ -108,7 +108,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kSliceBytes = 128;
 constexpr int kWavesPerTile = 8;
 constexpr int kLdsBytes = 160 * 1024;
 
@@ -204,13 +203,15 @@ template <bool I8> __device__ __forceinline__ void mma16(f32x4_t& c, const td_u3
 
 // RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
 // slice start instead (in bounds) and the fragments that hold them are zeroed as they are read.
-template <int EPI, bool RAGGED, int WM, int NA, int NB>
+template <int EPI, bool RAGGED, int SL, int WM, int NA, int NB>
 struct GemmTile {
     static constexpr int WN = kWavesPerTile / WM;
     static constexpr int TM = WM * NA * 16, TN = WN * NB * 16;
-    static constexpr int UA = TM * kSliceBytes, UB = TN * kSliceBytes;      // bytes of one slice
-    static constexpr bool kOnce = TM == 64;                                 // one row of tiles: B is read by one block
-    static constexpr int LA = TM / 64, LB = TN / 64;                        // loads per wavefront and slice
+    static constexpr int UA = TM * SL, UB = TN * SL;      // bytes of one slice
+// one row of tiles: a row of B is read by one block, so its lines are not kept (64 tokens: 40.6 -> 38.8 us; the
+    // output product, whose blocks share lines between K ranges, loses by it: 31.7 -> 35.5 us)
+    static constexpr bool kOnce = TM == 64 && EPI == EPI_REPAIR;
+    static constexpr int LA = UA / 8192, LB = UB / 8192;                        // loads per wavefront and slice
     // REPAIR: bounds and exponents wait in LDS for the range test (the largest tile has no room and reads them then)
     static constexpr int kPar = EPI == EPI_REPAIR && TM * TN < 256 * 256 ? 3 * 1024 : 0;
     // as many slices as fit; A one ahead of B where the two do not fit equally often
@@ -225,12 +226,13 @@ struct GemmTile {
     static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_REPAIR ? 10 : 4);   // LDS of a wavefront in the epilogue
     static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_REPAIR ? 3 * TN * 4 : 0);
     static constexpr int kLds = kRing + kPar > kEpiLds ? kRing + kPar : kEpiLds;
+    static_assert(SL % 128 == 0 && UA % 8192 == 0 && UB % 8192 == 0, "whole loads of 1 KB for 8 wavefronts");
     static_assert(SB >= 2 && SA >= 2 && kWait + kPer <= 63 && kLds <= kLdsBytes, "slice buffers");
 };
 
-template <int EPI, bool RAGGED, int WM, int NA, int NB>
+template <int EPI, bool RAGGED, int SL, int WM, int NA, int NB>
 __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) {
-    typedef GemmTile<EPI, RAGGED, WM, NA, NB> G;
+    typedef GemmTile<EPI, RAGGED, SL, WM, NA, NB> G;
     constexpr int WN = G::WN, TM = G::TM, TN = G::TN, SA = G::SA, SB = G::SB, LA = G::LA, LB = G::LB;
     extern __shared__ __align__(1024) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,7 +249,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
 
     // slices [s0, s0 + nk) of this block's range, from a starting point of its own (REPAIR: of either product)
-    const int nk1 = (int)((p.k + kSliceBytes - 1) / kSliceBytes), nk2 = (int)((p.k2 + kSliceBytes - 1) / kSliceBytes);
+    const int nk1 = (int)((p.k + SL - 1) / SL), nk2 = (int)((p.k2 + SL - 1) / SL);
     const int s0 = ks * tm.slices;
     const int nk = max(0, min(tm.slices, nk1 + nk2 - s0));
     auto start = [&](int len) { return len > 0 ? ((local & 7) + xcd * len / 8) % len : 0; };
@@ -266,8 +268,10 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     const i32x4_t ra1 = buffer_of(p.A + (size_t)m0 * p.k, rows_a * p.k), rb1 = buffer_of(p.B + (size_t)n0 * p.k, rows_b * p.k);
     const i32x4_t ra2 = buffer_of(p.A2 + (size_t)m0 * p.k2, rows_a * p.k2), rb2 = buffer_of(p.B2 + (size_t)n0 * p.k2, rows_b * p.k2);
 
-    // lane -> row lane/8 of the 8 rows of a load, slot lane%8; wavefront w loads rows [w*TM/8, (w+1)*TM/8) of A, of B alike
-    const int lrow = lane >> 3, piece = (lane & 7) ^ (lrow & 7);   // (row & 7 == lrow: blocks of 8 rows)
+    // a load is 1024 / SL rows, lane -> row lane / (pieces of a row), slot lane % (pieces of a row); wavefront w
+    // loads rows [w*TM/8, (w+1)*TM/8) of A, of B alike
+    constexpr int PS = SL / 16, RPL = 1024 / SL, SWZ = PS < 16 ? PS - 1 : 15;
+    const int lrow = lane / PS, lslot = lane % PS;
     uint32_t lds_a, lds_b;
     {
         const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
@@ -289,14 +293,15 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
         o.rs.y = second ? r2.y : r1.y;
         o.rs.z = live ? (second ? r2.z : r1.z) : 0;
         o.rs.w = r1.w;
-        o.soff = (uint32_t)(second ? s - nk1 : s) * kSliceBytes;
+        o.soff = (uint32_t)(second ? s - nk1 : s) * SL;
         o.pitch = second ? p.k2 : p.k;
         return o;
     };
     auto load_one = [&](bool is_a, int i, uint32_t buf, const Source& o) {
-        uint32_t pc = (uint32_t)piece * 16u;
+        const uint32_t row = (is_a ? row_a : row_b) + (uint32_t)(RPL * i);
+        uint32_t pc = ((uint32_t)lslot ^ (row & SWZ)) * 16u;
         if constexpr (RAGGED) pc = o.soff + pc < o.pitch ? pc : 0u;
-        const uint32_t voff = ((is_a ? row_a : row_b) + 8u * i) * o.pitch + pc;
+        const uint32_t voff = row * o.pitch + pc;
         if (is_a) load_to_lds(lds_a + buf * G::UA + i * 1024u, voff, o.rs, o.soff);
         else load_to_lds<G::kOnce>(lds_b + buf * G::UB + i * 1024u, voff, o.rs, o.soff);
     };
@@ -309,29 +314,29 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[i][j][q] = 0;
 
-    // fragments: lane holds 16 bytes of row lane%16 at piece 4*half + lane/16
+    // fragments: lane holds 16 bytes of row lane%16 at piece 4*step + lane/16
+    constexpr int KS = SL / 64;                       // steps (MFMA depths) of a slice
     const int frow = lane & 15, fp = lane >> 4;
-    uint32_t fsw[2];
+    uint32_t fsw[KS];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) fsw[s] = (uint32_t)(frow * kSliceBytes + (((s * 4 + fp) ^ (frow & 7)) * 16));
+    for (int s = 0; s < KS; ++s) fsw[s] = (uint32_t)(frow * SL + (((s * 4 + fp) ^ (frow & SWZ)) * 16));
     td_u32x4 fa[2][NA], fb[2][NB];
     auto read_one = [&](int buf, int t, uint32_t ba, uint32_t bb, int s, int slice) {   // fa[0], all of fb, the rest of fa
         td_u32x4 v;
         if (t == 0 || t > NB)
-            v = *reinterpret_cast<const td_u32x4*>(lds + ba * G::UA + (wm * NA + (t == 0 ? 0 : t - NB)) * 2048 + fsw[s]);
+            v = *reinterpret_cast<const td_u32x4*>(lds + ba * G::UA + (wm * NA + (t == 0 ? 0 : t - NB)) * (16 * SL) + fsw[s]);
         else
-            v = *reinterpret_cast<const td_u32x4*>(lds + SA * G::UA + bb * G::UB + (wn * NB + t - 1) * 2048 + fsw[s]);
+            v = *reinterpret_cast<const td_u32x4*>(lds + SA * G::UA + bb * G::UB + (wn * NB + t - 1) * (16 * SL) + fsw[s]);
         if constexpr (RAGGED) {
             const bool second = slice >= nk1;
-            const uint32_t at = (uint32_t)(second ? slice - nk1 : slice) * kSliceBytes + (uint32_t)(s * 4 + fp) * 16u;
+            const uint32_t at = (uint32_t)(second ? slice - nk1 : slice) * SL + (uint32_t)(s * 4 + fp) * 16u;
             if (at >= (second ? p.k2 : p.k)) v = td_u32x4{0, 0, 0, 0};
         }
         if (t == 0 || t > NB) fa[buf][t == 0 ? 0 : t - NB] = v; else fb[buf][t - 1] = v;
     };
     constexpr int NM = NA * NB, NR = NA + NB;
     constexpr int kReadEvery = NM / NR > 2 ? 2 : (NM / NR > 0 ? NM / NR : 1), kReadsPer = (NR + NM - 1) / NM;
-    constexpr int kLoadEvery = NM / G::kPer > 0 ? NM / G::kPer : 1;
-    static_assert(kLoadEvery * G::kPer <= NM, "a slice's loads fit between its MFMAs");
+    constexpr int kLoadEvery = NM / G::kPer > 0 ? NM / G::kPer : 1, kLoadsPer = (G::kPer + NM - 1) / NM;
 
     if constexpr (G::kPar > 0) {
         const uint32_t at = __builtin_amdgcn_readfirstlane(
@@ -372,17 +377,19 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
             const uint32_t na = ba + 1 == SA ? 0 : ba + 1, nb = bb + 1 == SB ? 0 : bb + 1;
             const int cur = RAGGED ? slice_of(kt) : 0, nxt = RAGGED ? slice_of(kt + 1 < nk ? kt + 1 : kt) : 0;
 #pragma unroll
-            for (int q = 0; q < NM; ++q) {
+            for (int st = 0; st < KS - 1; ++st)
 #pragma unroll
-                for (int u = 0; u < kReadsPer; ++u) {
-                    const int t = (q / kReadEvery) * kReadsPer + u;
-                    if (q % kReadEvery == 0 && t < NR) read_one(1, t, ba, bb, 1, cur);
+                for (int q = 0; q < NM; ++q) {
+#pragma unroll
+                    for (int u = 0; u < kReadsPer; ++u) {
+                        const int t = (q / kReadEvery) * kReadsPer + u;
+                        if (q % kReadEvery == 0 && t < NR) read_one((st + 1) & 1, t, ba, bb, st + 1, cur);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (RAGGED) asm volatile("s_nop 1");
+                    mma16<decltype(i8)::value>(acc[q / NB][q % NB], fb[st & 1][q % NB], fa[st & 1][q / NB]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (RAGGED) asm volatile("s_nop 1");
-                mma16<decltype(i8)::value>(acc[q / NB][q % NB], fb[0][q % NB], fa[0][q / NB]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
             // slice kt+1 has arrived (this wavefront's share; the barrier makes it everybody's) and the last
             // fragments of slice kt are in registers
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G::kWait) : "memory");
@@ -395,8 +402,10 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                     const int t = (q / kReadEvery) * kReadsPer + u;
                     if (q % kReadEvery == 0 && t < NR) read_one(0, t, na, nb, 0, nxt);
                 }
-                if (q % kLoadEvery == 0) {
-                    const int t = q / kLoadEvery;
+#pragma unroll
+                for (int u = 0; u < kLoadsPer; ++u) {
+                    const int t = (q / kLoadEvery) * kLoadsPer + u;
+                    if (q % kLoadEvery != 0) continue;
                     if (t < LB) load_one(false, t, bb, ob);
                     else if (t < LB + LA) load_one(true, t - LB, ba, oa);
                 }
@@ -589,61 +598,84 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 // the partial tile's bytes, written and read again; at most kPartRows rows of partial sums are kept).
 constexpr int64_t kPartRows = 4096;
 struct TileChoice { int shape, splits; };
-constexpr int kShapes = 7;
-constexpr int kShapeM[kShapes] = {256, 192, 256, 192, 128, 128, 64}, kShapeN[kShapes] = {256, 256, 128, 128, 128, 64, 64};
+constexpr int kShapes = 10;
+constexpr int kShapeM[kShapes] = {256, 192, 256, 192, 128, 128, 64, 64, 64, 64},
+              kShapeN[kShapes] = {256, 256, 128, 128, 128, 64, 64, 64, 32, 128},
+              kShapeSlice[kShapes] = {128, 128, 128, 128, 128, 128, 128, 256, 256, 128};
 
-TileChoice choose_tile(int64_t M, int64_t N, int64_t slices, bool splittable, bool store_f32) {
+// whole: K has to be whole slices (of both products); else a ragged K is allowed
+TileChoice choose_tile(const GemmArgs& p, bool splittable, bool store_f32, bool whole) {
     TileChoice best{0, 1};
     double best_cost = 1e300;
-    for (int s = 0; s < kShapes; ++s)
+    const int64_t M = p.M, N = p.N;
+    for (int s = 0; s < kShapes; ++s) {
+        const int SL = kShapeSlice[s], TM = kShapeM[s], TN = kShapeN[s];
+        if (whole && (p.k % SL != 0 || p.k2 % SL != 0)) continue;
+        if (TM == 64 && M > 64) continue;
+        const int64_t slices = (p.k + SL - 1) / SL + (p.k2 + SL - 1) / SL;
         for (int sp = 1; sp <= (splittable ? 8 : 1); sp *= 2) {
-            if (sp > 1 && (slices / sp < 8 || sp * M > kPartRows)) break;
-            const TileMap t = make_tile_map(M, N, kShapeM[s], kShapeN[s], (int)slices, sp);
+            if (sp > 1 && (slices * SL / sp < 1024 || sp * M > kPartRows)) break;
+            const TileMap t = make_tile_map(M, N, TM, TN, (int)slices, sp);
             const int64_t per_xcd = (int64_t)t.rm * t.rn;              // blocks of one XCD (of one range): 32 at once
-            const double mfma = 2100.0 * kShapeM[s] * kShapeN[s] / 65536.0, feed = (kShapeM[s] + kShapeN[s]) * 128.0 / 34.0;
-            const double tail = 3000.0 + (store_f32 ? 0.12 : 0.06) * kShapeM[s] * kShapeN[s];
+            const double mfma = 2100.0 / 128.0 * SL * TM * TN / 65536.0;
+            const double feed = ((M < TM ? M : TM) + TN) * (double)SL / (SL > 128 ? 34.5 : 34.0);
+            const double tail = 3000.0 + (store_f32 ? 0.12 : 0.06) * TM * TN;
             const double cost = (double)((per_xcd + 31) / 32) * ((double)t.slices * (mfma > feed ? mfma : feed) + tail) +
                                 (splittable ? sp * (double)M * (double)N * 8.0 / 2000.0 : 0.0);   // partial sums, about 2 KB a cycle
             if (cost < best_cost) { best_cost = cost; best = {s, sp}; }
         }
+    }
     return best;
 }
 
-// f(wm, na, nb) with the constants of a shape
+// f(slice bytes, wm, na, nb) with the constants of a shape
+template <int V> using num = std::integral_constant<int, V>;
 template <typename F> void for_shape(int shape, F f) {
-    using std::integral_constant;
-    typedef integral_constant<int, 1> c1;
-    typedef integral_constant<int, 2> c2;
-    typedef integral_constant<int, 4> c4;
-    typedef integral_constant<int, 6> c6;
-    typedef integral_constant<int, 8> c8;
     switch (shape) {
-        case 0: f(c2{}, c8{}, c4{}); break;
-        case 1: f(c2{}, c6{}, c4{}); break;
-        case 2: f(c2{}, c8{}, c2{}); break;
-        case 3: f(c2{}, c6{}, c2{}); break;
-        case 4: f(c2{}, c4{}, c2{}); break;
-        case 5: f(c2{}, c4{}, c1{}); break;
-        default: f(c2{}, c2{}, c1{}); break;
+        case 0: f(num<128>{}, num<2>{}, num<8>{}, num<4>{}); break;
+        case 1: f(num<128>{}, num<2>{}, num<6>{}, num<4>{}); break;
+        case 2: f(num<128>{}, num<2>{}, num<8>{}, num<2>{}); break;
+        case 3: f(num<128>{}, num<2>{}, num<6>{}, num<2>{}); break;
+        case 4: f(num<128>{}, num<2>{}, num<4>{}, num<2>{}); break;
+        case 5: f(num<128>{}, num<2>{}, num<4>{}, num<1>{}); break;
+        case 6: f(num<128>{}, num<2>{}, num<2>{}, num<1>{}); break;
+        case 7: f(num<256>{}, num<2>{}, num<2>{}, num<1>{}); break;
+        case 8: f(num<256>{}, num<4>{}, num<1>{}, num<1>{}); break;
+        default: f(num<128>{}, num<2>{}, num<2>{}, num<2>{}); break;
     }
 }
 
-template <int EPI, bool RAGGED> void launch_tile(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
-    for_shape(c.shape, [&](auto wm, auto na, auto nb) {
-        typedef GemmTile<EPI, RAGGED, wm, na, nb> G;
-        const int slices = (int)((p.k + 127) / 128 + (p.k2 + 127) / 128);
+template <int EPI, bool RAGGED> void launch_ragged(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
+    for_shape(c.shape, [&](auto sl, auto wm, auto na, auto nb) {
+        typedef GemmTile<EPI, RAGGED, sl, wm, na, nb> G;
+        const int slices = (int)((p.k + sl - 1) / sl + (p.k2 + sl - 1) / sl);
         const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, c.splits);
-        hipLaunchKernelGGL((gemm_tile_kernel<EPI, RAGGED, wm, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
+        hipLaunchKernelGGL((gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
     });
+}
+
+// EPI_F32 and EPI_PART take any K that is whole 16-byte pieces
+template <int EPI> TileChoice launch_tile(const GemmArgs& p, hipStream_t s) {
+    constexpr bool may_be_ragged = EPI == EPI_F32 || EPI == EPI_PART;
+    const TileChoice c = choose_tile(p, EPI == EPI_PART, may_be_ragged, !may_be_ragged);
+    const int sl = kShapeSlice[c.shape];
+    if constexpr (may_be_ragged) {
+        if (p.k % sl != 0 || p.k2 % sl != 0) {
+            launch_ragged<EPI, true>(p, c, s);
+            return c;
+        }
+    }
+    launch_ragged<EPI, false>(p, c, s);
+    return c;
 }
 
 template <int EPI, bool RAGGED> tardis_status_t raise_lds() {
     tardis_status_t st = TARDIS_OK;
     for (int shape = 0; shape < kShapes; ++shape)
-        for_shape(shape, [&](auto wm, auto na, auto nb) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<EPI, RAGGED, wm, na, nb>),
+        for_shape(shape, [&](auto sl, auto wm, auto na, auto nb) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     GemmTile<EPI, RAGGED, wm, na, nb>::kLds);
+                                                     GemmTile<EPI, RAGGED, sl, wm, na, nb>::kLds);
             if (e != hipSuccess) st = TARDIS_ERR_HIP;
         });
     return st;
@@ -664,7 +696,6 @@ bool gemm_force_generic() {
 
 const unsigned char* bytes_of(const void* p) { return static_cast<const unsigned char*>(p); }
 bool is_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-int64_t slices_of(int64_t bytes) { return (bytes + kSliceBytes - 1) / kSliceBytes; }
 
 }  // namespace
 
@@ -702,9 +733,7 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const v
         p.k2 = A2 ? p.k : 0u;
         p.C = C;
         p.bias = static_cast<const bf16_t*>(row_bias);
-        const TileChoice c = choose_tile(M, N, slices_of(p.k) + slices_of(p.k2), false, true);
-        if (K % 64 != 0) launch_tile<EPI_F32, true>(p, c, s);
-        else launch_tile<EPI_F32, false>(p, c, s);
+        launch_tile<EPI_F32>(p, s);
     } else {
         for (int part = 0; part < (A2 ? 2 : 1); ++part) {
             if (dtype == TARDIS_BF16)
@@ -740,7 +769,7 @@ tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const 
     p.mask = mask;
     p.mask_words = (int)L->mask_words;
     p.act = L->act;
-    launch_tile<EPI_REPAIR, false>(p, choose_tile(n, L->h, slices_of(p.k) + slices_of(p.k2), false, false), s);
+    launch_tile<EPI_REPAIR>(p, s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
@@ -756,7 +785,7 @@ tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const voi
     p.bias = static_cast<const bf16_t*>(b1);
     p.act = L->act;
     p.out = static_cast<bf16_t*>(out);
-    launch_tile<EPI_HIDDEN, false>(p, choose_tile(n, L->h, slices_of(p.k), false, false), s);
+    launch_tile<EPI_HIDDEN>(p, s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
@@ -775,10 +804,7 @@ tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, con
     p.k = (uint32_t)((X ? d : h) * 2);
     p.k2 = X ? (uint32_t)(h * 2) : 0u;
     p.C = part;
-    const TileChoice c = choose_tile(n, d, slices_of(p.k) + slices_of(p.k2), true, true);
-    *parts = c.splits;
-    if (h % 64 != 0) launch_tile<EPI_PART, true>(p, c, s);
-    else launch_tile<EPI_PART, false>(p, c, s);
+    *parts = launch_tile<EPI_PART>(p, s).splits;
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }

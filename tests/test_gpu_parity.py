@@ -252,7 +252,8 @@ def test_prompt_path_many_tokens(d, h, n, bits):
 
 
 @pytest.mark.parametrize("d,h,n", [(128, 8192, 2048), (128, 8192, 1500), (128, 8200, 1025), (256, 1000, 65),
-                                   (256, 1000, 130), (384, 4104, 333), (128, 2000, 700)])
+                                   (256, 1000, 130), (384, 4104, 333), (128, 2000, 700), (128, 1000, 2), (384, 4104, 23),
+                                   (1024, 4096, 18), (512, 8200, 64), (1536, 2000, 33)])
 def test_prompt_path_tiles(d, h, n):
     """Every tile shape of the matrix-core products at its edges: a K of one or two slices, K that is not whole
     slices (h % 64 != 0), ragged rows and columns, words of the mask cut by the tile."""
