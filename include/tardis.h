@@ -101,8 +101,9 @@ typedef struct {
                               folded result - outside the 1e-2 this library otherwise keeps, which is
                               why it is an option */
     int64_t max_batch;     /* largest n accepted by the batched online calls (1 .. 4096; longer prompts are
-                              the caller's to cut); from 65 on the layer
-                              also holds scratch for the prompt path, about n * (5 d + 10 h) bytes */
+                              the caller's to cut); from 2 on the layer
+                              also holds scratch for the matrix products, about n * (3 d + 2 h) bytes and
+                              at most max(n, 4096) * 4 d of partial sums */
     int32_t deterministic; /* 0, or 1: results that are bit-identical from run to run.  Every online call on
                               the layer then runs as groups of up to 16 tokens whose repair is accumulated
                               in counted fixed-point words (integer adds commute; a word's unit comes from
@@ -240,7 +241,7 @@ tardis_status_t tardis_ffn_forward(tardis_handle_t L, const void* x, void* y, vo
 /* n tokens (1 <= n <= max_batch), strictly per token: token t is repaired only
  * for the neurons its own predictor pass flagged.  x, y: n x d.
  * How the tokens are processed depends on n (groups of up to 16 tokens per
- * launch; passes of up to 64; from 65 tokens four dense matrix products, as the
+ * launch; from 18 tokens on three dense matrix products, as the
  * paper's remark on prompt processing suggests) and never on their values; the
  * masks are the same bits on every path, y agrees to rounding. */
 tardis_status_t tardis_ffn_forward_batched(tardis_handle_t L, const void* x, int64_t n, void* y,
@@ -299,7 +300,7 @@ tardis_status_t tardis_stack_forward(const tardis_handle_t* layers, int32_t n_la
 tardis_status_t tardis_set_next_layer(tardis_handle_t L, tardis_handle_t next);
 
 /* The unmodified FFN, y = W2 sigma(W1 x + b1) + b2, on the same streaming
- * kernels: the dense baseline the folded path is measured against (from 65
+ * kernels: the dense baseline the folded path is measured against (from 2
  * tokens on, two matrix-core products, as for the folded path's prompts).
  * 1 <= n <= max_batch.  x, y: n x d. */
 tardis_status_t tardis_dense_forward(tardis_handle_t L, const void* x, int64_t n, void* y,

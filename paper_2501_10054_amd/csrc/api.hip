@@ -5,7 +5,6 @@
 #include <mutex>
 #include <new>
 #include <unordered_set>
-#include <vector>
 
 #include "common.h"
 
@@ -42,10 +41,12 @@ tardis_status_t check_desc(const tardis_ffn_desc* desc) {
 class Arena {
    public:
     template <typename P> void reserve(P** p, size_t bytes) {
-        parts_.push_back({reinterpret_cast<void**>(p), total_});
+        if (n_ < kMaxParts) parts_[n_] = {reinterpret_cast<void**>(p), total_};
+        ++n_;
         total_ += ((bytes ? bytes : 16) + 255) / 256 * 256;
     }
     tardis_status_t commit(void** base) {
+        if (n_ > kMaxParts) return TARDIS_ERR_SHAPE;
         void* v = nullptr;
         const hipError_t e = hipMalloc(&v, total_ ? total_ : 256);
         if (e != hipSuccess) {
@@ -53,7 +54,7 @@ class Arena {
             return e == hipErrorOutOfMemory ? TARDIS_ERR_OOM : TARDIS_ERR_HIP;
         }
         *base = v;
-        for (const Part& q : parts_) *q.at = static_cast<char*>(v) + q.offset;
+        for (int i = 0; i < n_; ++i) *parts_[i].at = static_cast<char*>(v) + parts_[i].offset;
         return TARDIS_OK;
     }
 
@@ -62,7 +63,9 @@ class Arena {
         void** at;
         size_t offset;
     };
-    std::vector<Part> parts_;
+    static constexpr int kMaxParts = 48;   // (a fixed array: nothing here throws through the C boundary)
+    Part parts_[kMaxParts];
+    int n_ = 0;
     size_t total_ = 0;
 };
 
