@@ -181,15 +181,15 @@ __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
 }
 
 // 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
-// (m0 is set and used in the one statement; the compiler keeps nothing in it)
+// (m0 is set and used in the one statement)
 template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
     if constexpr (ONCE)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "m0");
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "m0");
 }
 
 // round to nearest even, in one instruction
@@ -199,6 +199,17 @@ __device__ __forceinline__ uint32_t to_bf16(float v) { return __builtin_bit_cast
 template <bool I8> __device__ __forceinline__ void mma16(f32x4_t& c, const td_u32x4& a, const td_u32x4& b) {
     if constexpr (I8) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+
+// The compiler does not know how long those take.  Every use of the accumulators from here on (of their new values, for
+// the compiler) comes behind the statements before this, a wait among them, and every definition before it: without it
+// plain arithmetic on them may be moved in front of the wait.
+template <int NA, int NB> __device__ __forceinline__ void fence(f32x4_t (&acc)[NA][NB]) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[i][j])::"memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
@@ -369,6 +380,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 #pragma unroll
         for (int t = 0; t < NR; ++t) read_one(0, t, 0, 0, 0, slice_of(0));
     }
+    fence(acc);
     asm volatile("s_nop 7" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     auto multiply = [&](auto i8, int from, int to) {
@@ -422,7 +434,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     if constexpr (EPI == EPI_REPAIR) {
         multiply(std::true_type{}, 0, nk1);
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // (the products are in inline assembly: their results are waited for here)
-        __builtin_amdgcn_sched_barrier(0);
+        fence(acc);
         f32x4_t lo[NB], hi[NB];
         int ex[NA];
         const float* par = reinterpret_cast<const float*>(lds + G::kRing);
@@ -458,6 +470,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                 }
             __builtin_amdgcn_sched_barrier(0);        // (one row block at a time: fewer live registers)
         }
+        fence(acc);
         asm volatile("s_nop 7" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         multiply(std::false_type{}, nk1, nk);
@@ -469,8 +482,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     // (the products are in inline assembly: their results are waited for here)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
+    fence(acc);
 
     // acc[i][j][q] = C[row m0 + (wm*NA + i)*16 + lane%16][column n0 + (wn*NB + j)*16 + 4*(lane/16) + q]
     const int64_t mw = m0 + wm * NA * 16, nw = n0 + wn * NB * 16;   // this wavefront's corner
