@@ -181,15 +181,16 @@ __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
 }
 
 // 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
-// (m0 is set and used in the one statement)
+// (m0 is set and used in the one statement.  It is a reserved register, which the compiler does not take as a clobber; it
+// uses it nowhere else in these kernels, and the listing's test holds it to that)
 template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
     if constexpr (ONCE)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "m0");
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "m0");
+                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
 }
 
 // round to nearest even, in one instruction

@@ -118,3 +118,12 @@ def test_results_of_matrix_instructions_are_waited_for(listings, packed):
         if found:
             bad[name] = (len(found), found[0])
     assert not bad, bad
+
+
+def test_m0_belongs_to_the_loads_to_lds(listings):
+    """m0 is written by the statement that loads to LDS and cannot be declared as overwritten: nothing else may use it."""
+    for name, (code, _) in _kernels(listings[False]).items():
+        for i, (op, rest) in enumerate(code):
+            if re.search(r"\bm0\b", rest):
+                assert op == "s_mov_b32" and rest.startswith("m0, s"), (name, op, rest)
+                assert [code[i + 1][0], code[i + 2][0]] == ["s_nop", "buffer_load_dwordx4"] and "lds" in code[i + 2][1], name
