@@ -469,7 +469,12 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                     if (!inside && n0 + nc + j * 16 < p.N && m0 + mr + i * 16 < p.M) bits[i] |= 1u << (4 * j + q);
                     acc[i][j][q] = 0.0f;
                 }
-            __builtin_amdgcn_sched_barrier(0);        // (one row block at a time: fewer live registers)
+            // (one row block at a time, and its cleared accumulators made here: the compiler otherwise prepares all of the
+            // second product's beside the first one's, and the 256 x 128 tile spills: 256 -> 172 registers)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[i][j]));
+            asm volatile("" : "+v"(bits[i]));
+            __builtin_amdgcn_sched_barrier(0);
         }
         fence(acc);
         asm volatile("s_nop 7" ::: "memory");

@@ -127,3 +127,15 @@ def test_m0_belongs_to_the_loads_to_lds(listings):
             if re.search(r"\bm0\b", rest):
                 assert op == "s_mov_b32" and rest.startswith("m0, s"), (name, op, rest)
                 assert [code[i + 1][0], code[i + 2][0]] == ["s_nop", "buffer_load_dwordx4"] and "lds" in code[i + 2][1], name
+
+
+def test_no_product_kernel_spills_vector_registers(listings):
+    """A spill could store an accumulator that an MFMA is still writing, and costs trips to memory in the loop."""
+    spills = {}
+    for packed, text in listings.items():
+        for part in re.split(r"\n  - \.agpr_count", text[text.index("amdhsa.kernels:"):])[1:]:
+            name = re.search(r"\.name:\s+(\S+)", part)[1]
+            if "gemm_tile_kernel" in name:
+                spills[packed, name] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", part)[1])
+    assert len(spills) >= 100
+    assert not any(spills.values()), {n: c for n, c in spills.items() if c}
