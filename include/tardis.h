@@ -103,7 +103,8 @@ typedef struct {
     int64_t max_batch;     /* largest n accepted by the batched online calls (1 .. 4096; longer prompts are
                               the caller's to cut); from 2 on the layer
                               also holds scratch for the matrix products, about n * (3 d + 2 h) bytes and
-                              at most max(n, 4096) * 4 d of partial sums */
+                              at most max(n, 4096) * 4 d of partial sums (twice the 2 h and the sums where
+                              repair factors are two bf16 numbers, see tardis_ffn_forward_batched) */
     int32_t deterministic; /* 0, or 1: results that are bit-identical from run to run.  Every online call on
                               the layer then runs as groups of up to 16 tokens whose repair is accumulated
                               in counted fixed-point words (integer adds commute; a word's unit comes from
@@ -241,9 +242,13 @@ tardis_status_t tardis_ffn_forward(tardis_handle_t L, const void* x, void* y, vo
 /* n tokens (1 <= n <= max_batch), strictly per token: token t is repaired only
  * for the neurons its own predictor pass flagged.  x, y: n x d.
  * How the tokens are processed depends on n (groups of up to 16 tokens per
- * launch; from 18 tokens on three dense matrix products, as the
- * paper's remark on prompt processing suggests) and never on their values; the
- * masks are the same bits on every path, y agrees to rounding. */
+ * launch; from 18 or 19 tokens on - from 2 where no kernel groups tokens - three
+ * dense matrix products, as the paper's remark on prompt processing suggests)
+ * and never on their values; the masks are the same bits on every path, y agrees
+ * to rounding.  The products take each repair factor rounded to bf16, in calls
+ * of at least 65 tokens and for layers with d % 512 == 0, d <= 8192 and
+ * h % 2048 == 0; elsewhere, and at every size for sketches below 8 bits with
+ * d = 2048 or 4096 and another h, as the sum of two bf16 numbers. */
 tardis_status_t tardis_ffn_forward_batched(tardis_handle_t L, const void* x, int64_t n, void* y,
                                            void* stream);
 

@@ -120,12 +120,23 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // d=4096, h=16384 and 1 / 5 / 15 % fallback: 16 tokens 52 / 68 / 99 us in groups, 84 as products whatever the rate;
     // 17 tokens (16 + 1) 73 / 93 / 129 against 84; from 18 on two full groups, 104 / 136 / 201 at 32 tokens, 85.  (d=2048: 16
     // tokens 27 / 32 / 40 against 42; d=1024: 21 / 25 / 31 against 28.)  A layer without those kernels has only a launch
-    // sequence per token to compare with: from 2 tokens on.
-    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", L->use_fused ? 18 : 2, 2, 1 << 20);
+    // sequence per token to compare with: from 2 tokens on.  (With fine factors, see below: from 19 on; 18 tokens at 5 % take 38 / 47 / 90 us in
+    // groups and 37 / 51 / 82 as products at d = 1024 / 2048 / 4096 and h = 3000 / 5000 / 11008, 19 a third group.)
     const bool products = L->max_batch >= 2 && td_prefill_supported(L);   // (the dense FFN takes them from 2 tokens on)
     // 4-bit sketch: the decode kernel reads the packed form (d = 2048, 4096); every other path
     // reads one-byte effective codes, kept only where such a path can run
     const bool packed4 = L->sketch_bits < 8 && L->use_fused && (d == 2048 || d == 4096);
+    // Up to which number of tokens the products carry the repair factors with 16 significant bits instead of 8.  One bf16 a
+    // factor adds an error of about the size of the output's own rounding (against 64 bits, 15 % fallback: d = 768,
+    // h = 3072, 64 tokens 2.29e-3, with 16 bits or 32 2.17e-3; d = 4096, h = 11008 2.21e-3 against 2.09e-3), and up to 64
+    // tokens the kernels that would serve these calls otherwise - decode groups, launches over tokens - multiply by
+    // factors of 32 bits.  The `coarse` layers (rows of whole 512-byte pieces, a hidden width of whole 2048s) take one
+    // bf16 at every size, the others from 65 tokens on, and packed sketches without coarse rows never: their calls of
+    // more tokens were decode groups too.  What it costs, 64 tokens: d = 768, h = 3072 25 -> 31 us, d = 2048, h = 5000
+    // 38 -> 52, d = 4096, h = 11008 69 -> 92 (the second product reads W2 once more).
+    const bool coarse = d % 512 == 0 && d <= 8192 && h % 2048 == 0;
+    L->fine_max_tokens = coarse ? 0 : packed4 ? INT32_MAX : 64;
+    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse || packed4 ? 18 : 19, 2, 1 << 20);
     const bool byte_codes = !packed4 || (products && L->max_batch >= L->prefill_min_tokens);
     const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
@@ -163,7 +174,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     if (products) {
         L->prefill_chunk = env_int("TARDIS_PREFILL_CHUNK", 16384, 64, 32768);
         if (L->prefill_chunk > L->max_batch) L->prefill_chunk = (int32_t)L->max_batch;
-        mem.reserve(&L->pf_scratch, td_prefill_scratch_bytes(L, L->prefill_chunk));
+        mem.reserve(&L->pf_scratch, td_prefill_scratch_bytes(L));
     }
     if (fp8) {
         mem.reserve(&L->Wp8, (size_t)d * d);

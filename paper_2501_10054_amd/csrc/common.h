@@ -111,6 +111,7 @@ struct tardis_layer_s {
     void* pf_scratch;              // matrix products: int8 tokens, exponents, aligned tokens, repair factors, fp32 partial sums of y
     int32_t prefill_min_tokens;    // calls with at least this many tokens run as matrix products (if there is scratch)
     int32_t prefill_chunk;         // ... in chunks of at most this many tokens (what the scratch is sized for)
+    int32_t fine_max_tokens;       // ... and those with at most this many carry the repair factors as head and remainder
     int32_t* rec_count;            // two-kernel path: flagged neurons per predictor block,
     uint32_t* rec_jb;              //   neuron index and
     uint32_t* rec_tb;              //   token bits of each record (dec_blocks x neurons per block),
@@ -236,7 +237,7 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const v
                            int64_t K, int32_t dtype, const void* row_bias, hipStream_t s);
 // the products of calls with many tokens, each with the step that follows it (see gemm.hip)
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
-                               uint32_t* mask, void* out, int64_t n, hipStream_t s);
+                               uint32_t* mask, void* out, void* rest, int64_t n, hipStream_t s);
 tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const void* b1, void* out, int64_t n, hipStream_t s);
 tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
                                int64_t n, int64_t d, int64_t h, hipStream_t s);
@@ -244,7 +245,7 @@ size_t td_gemm_part_floats(int64_t n, int64_t d);
 tardis_status_t td_gemm_init();
 // prefill.hip
 bool td_prefill_supported(const tardis_layer_s* L);
-size_t td_prefill_scratch_bytes(const tardis_layer_s* L, int64_t n);
+size_t td_prefill_scratch_bytes(const tardis_layer_s* L);   // for calls of any size, in chunks of prefill_chunk
 tardis_status_t td_forward_prefill(tardis_layer_s* L, const void* x, int64_t n, void* y, int norm_out, hipStream_t s);
 tardis_status_t td_dense_prefill(tardis_layer_s* L, const void* x, int64_t n, void* y, hipStream_t s);
 bool td_layer_is_live(const tardis_layer_s* L);

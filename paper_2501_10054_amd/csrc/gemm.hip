@@ -155,6 +155,7 @@ struct GemmArgs {
     float* C;                      // F32: M x N; PART: [split][M][N]
     const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, REPAIR: per column
     bf16_t* out;                   // HIDDEN, REPAIR: M x N
+    bf16_t* rest;                  // REPAIR: what the rounding of `out` to bf16 left, M x N (or null)
     const float *lo, *hi;          // REPAIR: bounds of the range test per column,
     const float *slope, *icept;    //   line per column,
     const int32_t* e;              //   exponent per row (readable to the next multiple of 16 bytes),
@@ -166,8 +167,8 @@ struct GemmArgs {
 // F32: C = product (+ bias).  PART: one range of K's share of C.  HIDDEN: out = sigma(product + bias).
 // REPAIR: the first pair of operands is int8 (token codes and predictor codes), the second bf16 (tokens and
 // W1): the sums of the first give the flags, those of the second z, and out = sigma(z) - (slope z + icept) at
-// the flagged places, 0 elsewhere.  Neither the sums nor z leave the block, and the stream of slices goes on
-// from the one product to the other.
+// the flagged places, 0 elsewhere (with `rest`: as bf16 head and bf16 remainder, 16 significant bits together).  Neither
+// the sums nor z leave the block, and the stream of slices goes on from the one product to the other.
 enum { EPI_F32, EPI_PART, EPI_HIDDEN, EPI_REPAIR };
 
 __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
@@ -235,7 +236,7 @@ struct GemmTile {
     // loads that may still be in flight when slice kt+2 has to be there (see the order in the kernel)
     static constexpr int kWaitB = LA + (SB - 2) * kPer, kWaitA = (SA - 2) * kPer;
     static constexpr int kWait = kWaitB < kWaitA ? kWaitB : kWaitA;
-    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_REPAIR ? 10 : 4);   // LDS of a wavefront in the epilogue
+    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_REPAIR ? 12 : 4);   // LDS of a wavefront in the epilogue
     static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_REPAIR ? 3 * TN * 4 : 0);
     static constexpr int kLds = kRing + kPar > kEpiLds ? kRing + kPar : kEpiLds;
     static_assert(SL % 128 == 0 && UA % 8192 == 0 && UB % 8192 == 0, "whole loads of 1 KB for 8 wavefronts");
@@ -526,7 +527,8 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
         // list needs about (share flagged) x 128 runs.
         // HIDDEN: sigma(z + b) of every element.
         bf16_t* chunk = reinterpret_cast<bf16_t*>(lds + wave * G::kEpiWave);
-        uint2* list = reinterpret_cast<uint2*>(lds + wave * G::kEpiWave + 16 * CW * 2);
+        bf16_t* chunk2 = chunk + 16 * CW;                            // REPAIR: the remainders
+        uint2* list = reinterpret_cast<uint2*>(lds + wave * G::kEpiWave + 16 * CW * 4);
         float* par = reinterpret_cast<float*>(lds + kWavesPerTile * G::kEpiWave);
         if constexpr (EPI == EPI_REPAIR) {
             for (int c = tid; c < TN; c += 512) {
@@ -561,7 +563,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                     }
                 }
                 const td_u32x4 zero = {0, 0, 0, 0};
-                for (int v = lane; v < 16 * CW / 8; v += 64) reinterpret_cast<td_u32x4*>(chunk)[v] = zero;
+                for (int v = lane; v < (p.rest ? 2 : 1) * 16 * CW / 8; v += 64) reinterpret_cast<td_u32x4*>(chunk)[v] = zero;
                 __builtin_amdgcn_wave_barrier();
                 int total = 0;
 #pragma unroll
@@ -582,7 +584,13 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                     const uint2 en = list[t];
                     const int c = wn * CW + (int)(en.y % CW);
                     const float z = __uint_as_float(en.x) + par[c];
-                    chunk[en.y] = (bf16_t)to_bf16(td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]));
+                    const float factor = td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]);
+                    const uint32_t head = to_bf16(factor);
+                    chunk[en.y] = (bf16_t)head;
+                    if (p.rest) {                                     // (infinite and NaN factors are all in the head)
+                        const float rest = factor - td_bf16_to_f32((bf16_t)head);
+                        chunk2[en.y] = (bf16_t)(fabsf(rest) < INFINITY ? to_bf16(rest) : 0u);
+                    }
                 }
             } else {
 #pragma unroll
@@ -602,8 +610,11 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
             for (int v = lane; v < 16 * CW / 8; v += 64) {           // N % 8 == 0: whole 16-byte vectors
                 const int row = v / (CW / 8), col = (v % (CW / 8)) * 8;
                 const int64_t mm = mw + i * 16 + row, nn = nw + col;
-                if (mm < p.M && nn < p.N)
+                if (mm < p.M && nn < p.N) {
                     *reinterpret_cast<td_u32x4*>(p.out + mm * p.N + nn) = reinterpret_cast<const td_u32x4*>(chunk)[v];
+                    if (EPI == EPI_REPAIR && p.rest)
+                        *reinterpret_cast<td_u32x4*>(p.rest + mm * p.N + nn) = reinterpret_cast<const td_u32x4*>(chunk2)[v];
+                }
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -765,9 +776,10 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const v
 }
 
 // The products of calls with many tokens (bf16 layers, d % 128 == 0, h % 8 == 0, 16-byte aligned operands).
-// mask[t] = range test of Xq . Q^T (exact int32 sums), out[t] = sigma(z) - (a z + c) at its bits, else 0, z = X . W1^T + b1
+// mask[t] = range test of Xq . Q^T (exact int32 sums), out[t] = sigma(z) - (a z + c) at its bits, else 0, z = X . W1^T + b1;
+// rest (or null) = what `out` lost when it was rounded to bf16, in bf16
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
-                               uint32_t* mask, void* out, int64_t n, hipStream_t s) {
+                               uint32_t* mask, void* out, void* rest, int64_t n, hipStream_t s) {
     GemmArgs p{};
     p.A = bytes_of(XQ);
     p.B = bytes_of(L->Q);
@@ -779,6 +791,7 @@ tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const 
     p.k2 = (uint32_t)(L->d * 2);
     p.bias = static_cast<const bf16_t*>(b1);
     p.out = static_cast<bf16_t*>(out);
+    p.rest = static_cast<bf16_t*>(rest);
     p.lo = L->tlo;
     p.hi = L->thi;
     p.slope = L->a;

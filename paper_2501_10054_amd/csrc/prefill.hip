@@ -9,6 +9,8 @@
 //                             where token t flagged neuron j, else 0, rounded to bf16
 //     Y   = [X | D] [W' | W2]^T   one product over d + h columns, in up to 8 ranges whose fp32 sums the
 //                             finishing kernel adds: y = Y + b' (then the optional RMS norm and the conversion)
+// Calls with few tokens on some layers (fine_max_tokens) keep what the rounding of D left as well and add its product
+// with W2^T: the kernels that serve fewer tokens multiply factors of 32 bits.
 // Neither the sums nor the pre-activations (n x h, 4 bytes each) reach memory.  Masks are bit-exact with
 // the per-token path (same integer sums, same range test).
 #include "common.h"
@@ -152,9 +154,10 @@ struct PromptScratch {
     int32_t* e;
     bf16_t* x;          // aligned copy of the tokens (used when the caller's are not 16-byte aligned)
     bf16_t* hid;        // repair factors D, or the dense hidden activations (n x h)
-    float* part;        // partial sums of the output
+    bf16_t* rest;       // fine: remainders of D (n x h)
+    float* part;        // partial sums of the output (fine: of both products)
     size_t bytes;
-    PromptScratch(void* base, int64_t n, int64_t d, int64_t h) {
+    PromptScratch(void* base, int64_t n, int64_t d, int64_t h, bool fine) {
         unsigned char* p = static_cast<unsigned char*>(base);
         auto take = [&](size_t b) {
             unsigned char* at = p;
@@ -165,7 +168,8 @@ struct PromptScratch {
         e = reinterpret_cast<int32_t*>(take((size_t)n * 4));
         x = reinterpret_cast<bf16_t*>(take((size_t)n * d * 2));
         hid = reinterpret_cast<bf16_t*>(take((size_t)n * h * 2));
-        part = reinterpret_cast<float*>(take(td_gemm_part_floats(n, d) * 4));
+        rest = reinterpret_cast<bf16_t*>(take(fine ? (size_t)n * h * 2 : 0));
+        part = reinterpret_cast<float*>(take((fine ? 2 : 1) * td_gemm_part_floats(n, d) * 4));
         bytes = (size_t)(p - static_cast<unsigned char*>(base));
     }
 };
@@ -180,27 +184,33 @@ void finish(const PromptScratch& w, int parts, const float* bias32, const bf16_t
 
 }  // namespace
 
-// (and the layer keeps one-byte codes)
 bool td_prefill_supported(const tardis_layer_s* L) {
     return L->dtype == TARDIS_BF16 && L->d % 128 == 0 && L->h >= 128 && L->h % 8 == 0;
 }
 
-size_t td_prefill_scratch_bytes(const tardis_layer_s* L, int64_t n) { return PromptScratch(nullptr, n, L->d, L->h).bytes; }
+size_t td_prefill_scratch_bytes(const tardis_layer_s* L) {
+    const int64_t chunk = L->prefill_chunk, fine = L->fine_max_tokens < chunk ? L->fine_max_tokens : chunk;
+    const size_t all = PromptScratch(nullptr, chunk, L->d, L->h, false).bytes;
+    const size_t few = fine > 0 ? PromptScratch(nullptr, fine, L->d, L->h, true).bytes : 0;
+    return all > few ? all : few;                    // (either grows with its number of tokens)
+}
 
 // one chunk of at most L->prefill_chunk tokens (the scratch is sized for that many)
 static tardis_status_t prefill_chunk(tardis_layer_s* L, const bf16_t* x, int64_t n, bf16_t* y, uint32_t* mask,
-                                     int norm_out, hipStream_t s) {
+                                     bool fine, int norm_out, hipStream_t s) {
     const int64_t d = L->d, h = L->h;
-    const PromptScratch w(L->pf_scratch, n, d, h);
+    const PromptScratch w(L->pf_scratch, n, d, h, fine);
     if (aligned(x, 16)) {
         hipLaunchKernelGGL(quantize_rows_kernel<false>, dim3((unsigned)n), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
     } else {
         hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)n), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
         x = w.x;
     }
-    TD_TRY(td_gemm_repair(L, w.xq, w.e, x, L->b1 ? L->b1 : L->zeros_h, mask, w.hid, n, s));
-    int parts = 1;
+    TD_TRY(td_gemm_repair(L, w.xq, w.e, x, L->b1 ? L->b1 : L->zeros_h, mask, w.hid, fine ? w.rest : nullptr, n, s));
+    int parts = 1, more = 0;
     TD_TRY(td_gemm_output(x, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
+    if (fine) TD_TRY(td_gemm_output(nullptr, nullptr, w.rest, L->W2, w.part + (size_t)parts * n * d, &more, n, d, h, s));
+    parts += more;
     finish(w, parts, L->bp, nullptr, n, d, y, norm_out, s);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
@@ -214,7 +224,7 @@ tardis_status_t td_forward_prefill(tardis_layer_s* L, const void* xv, int64_t n,
     bf16_t* y = static_cast<bf16_t*>(yv);
     for (int64_t t0 = 0; t0 < n; t0 += L->prefill_chunk) {
         const int64_t nc = n - t0 < L->prefill_chunk ? n - t0 : L->prefill_chunk;
-        TD_TRY(prefill_chunk(L, x + t0 * L->d, nc, y + t0 * L->d, L->mask + t0 * L->mask_words, norm_out, s));
+        TD_TRY(prefill_chunk(L, x + t0 * L->d, nc, y + t0 * L->d, L->mask + t0 * L->mask_words, n <= L->fine_max_tokens, norm_out, s));
     }
     L->last_n = n;
     return TARDIS_OK;
@@ -226,7 +236,7 @@ tardis_status_t td_dense_prefill(tardis_layer_s* L, const void* xv, int64_t n, v
     const int64_t d = L->d, h = L->h;
     for (int64_t t0 = 0; t0 < n; t0 += L->prefill_chunk) {
         const int64_t nc = n - t0 < L->prefill_chunk ? n - t0 : L->prefill_chunk;
-        const PromptScratch w(L->pf_scratch, nc, d, h);
+        const PromptScratch w(L->pf_scratch, nc, d, h, false);
         const bf16_t* x = static_cast<const bf16_t*>(xv) + t0 * d;
         if (!aligned(x, 16)) {
             hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)nc), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);

@@ -305,6 +305,26 @@ def test_fold_tile_edges(d, h):
              synth.make_tokens(2, d, "bf16", seed, synth.STREAM_TEST), 0.9)
 
 
+@pytest.mark.parametrize("d,h,n,bits", [(768, 3072, 2, 8), (768, 3072, 64, 8), (512, 1000, 33, 8), (1024, 3000, 18, 8),
+                                        (1024, 4104, 64, 8), (2048, 1000, 64, 4), (2048, 1000, 90, 4)])
+def test_repair_factors_are_not_rounded_to_one_bf16(d, h, n, bits, monkeypatch):
+    """Slope 0, intercept 16 and empty ranges: every factor is sigma(z) - 16 and has to cancel against b' = 16 W2 1.
+    The output's own rounding is 2^-9 at most (relative); a factor of 16 significant bits is off by 16 * 2^-17, against
+    a sigma(z) of about 0.6 (r.m.s.), 2e-4 together.  One bf16 a factor (16 * 2^-9 at most) makes 2 to 6 %.  (90
+    tokens: two chunks.)"""
+    monkeypatch.setenv("TARDIS_PREFILL_CHUNK", "64")
+    seed = synth.workload_seed(9, 80)
+    layer = synth.make_layer(d, h, "bf16", seed, w1_std=d ** -0.5, w2_std=0.05, heavy_frac=0.0, with_bias=False)
+    full = lambda v: torch.full((h,), v, dtype=torch.float32, device=DEV)
+    L = T.tardis_fold(make_ffn(layer), full(0.0), full(0.0), full(0.0), full(16.0), max_batch=n, sketch_bits=bits)
+    X = synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST)
+    got = host(T.tardis_ffn_forward_batched(L, dev(X, "bf16")))
+    z = torch.from_numpy(X).double() @ torch.from_numpy(layer.W1).double().T
+    want = (torch.nn.functional.gelu(z) @ torch.from_numpy(layer.W2).double().T).numpy()
+    L.close()
+    assert rel_l2(got, want) <= 3e-3
+
+
 def test_prompt_path_with_bias_and_relu():
     seed = synth.workload_seed(3, 11)
     layer = synth.make_layer(512, 2048, "bf16", seed, w1_std=0.05, w2_std=0.05, heavy_frac=0.01, with_bias=True)
