@@ -809,6 +809,51 @@ def test_calibrate_sample_counts_and_crowded_samples(n, kind):
     assert np.abs(a - oa).max() <= tol and np.abs(c - oc).max() <= tol
 
 
+def bitonic(z):
+    """What a bitonic network that swaps where (x > y) == ascending makes of z, NaN or not."""
+    n = len(z)
+    npad = 1 << max(1, (n - 1).bit_length())
+    v = np.full(npad, np.inf)
+    v[:n] = z
+    t = np.arange(npad // 2)
+    k = 2
+    while k <= npad:
+        s = k // 2
+        while s:
+            i = 2 * t - (t & (s - 1))
+            x, y = v[i], v[i + s]
+            swap = (x > y) == ((i & k) == 0)
+            v[i], v[i + s] = np.where(swap, y, x), np.where(swap, x, y)
+            s //= 2
+        k *= 2
+    return v
+
+
+@pytest.mark.parametrize("bad", [(np.nan,), (np.nan, np.nan, np.nan), (np.inf,), (np.inf, np.nan)])
+@pytest.mark.parametrize("n,coverage", [(5, 0.9), (300, 1.0), (300, 0.9), (4500, 0.85)])
+def test_calibrate_samples_that_are_not_finite(n, coverage, bad):
+    """Tokens with a NaN or an infinity: no order statistic is right then, but the answer is the sorting network's, the
+    same in every run."""
+    seed = synth.workload_seed(9, 41)
+    layer = synth.make_layer(48, 72, "f32", seed, w1_std=0.2, w2_std=0.05, with_bias=True)
+    X = synth.make_tokens(n, 48, "f32", seed, synth.STREAM_CAL)
+    for i, v in enumerate(bad):
+        X[(i + 1) * n // (len(bad) + 1), 7 + i] = v
+    with np.errstate(invalid="ignore"):
+        z = X.astype(np.float64) @ layer.W1.astype(np.float64).T + layer.b1
+        ends = np.empty((2, 72))
+        for j in range(72):
+            v = bitonic(z[:, j])
+            for q, share in enumerate(((1 - coverage) / 2, (1 + coverage) / 2)):
+                pos = float(share) * (n - 1)
+                i = min(max(int(np.floor(pos)), 0), n - 1)
+                ends[q, j] = v[i] + (pos - i) * (v[min(i + 1, n - 1)] - v[i])
+    for _ in range(3):
+        got = [t.cpu().numpy() for t in T.tardis_calibrate(make_ffn(layer), dev(X, "f32"), coverage)]
+        for q in range(2):
+            np.testing.assert_allclose(got[q], ends[q], rtol=2e-5, atol=2e-5)
+
+
 def test_fused_kernel_with_ragged_hidden_width_and_bias():
     # d = 2048 takes the single-launch kernel; h = 1000 is neither a multiple of 32 nor of the
     # per-block neuron count, and the layer has biases
