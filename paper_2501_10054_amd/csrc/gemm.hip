@@ -742,11 +742,14 @@ tardis_status_t td_gemm_init() {
     });
 }
 
+// more rows than the grid of the kernel for any shape counts
+bool td_gemm_refuses_rows(int64_t M) { return (M + GT - 1) / GT > 65535; }
+
 // C = A.B^T + A2.B2^T (A2, B2 null: the first product alone; both pairs have rows of K elements)
 tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
                            int64_t K, int32_t dtype, const void* row_bias, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return TARDIS_ERR_SHAPE;
-    if ((M + GT - 1) / GT > 65535) return TARDIS_ERR_SHAPE;
+    if (td_gemm_refuses_rows(M)) return TARDIS_ERR_SHAPE;
     // (any M, N work on the matrix cores; small products are not worth it)
     if (dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 && is_aligned16(A) && is_aligned16(B) &&
         is_aligned16(A2) && is_aligned16(B2) && K % 8 == 0 && !gemm_force_generic()) {

@@ -1325,6 +1325,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
                              const float* cov_pn, float step, float* lo, float* hi, float* a, float* c,
                              hipStream_t s) {
     const int64_t d = desc->d, h = desc->h;
+    if (td_gemm_refuses_rows(h)) return TARDIS_ERR_SHAPE;   // (of all neurons, also where they come in chunks below)
     DevBuf zt;
     if (step <= 0.0f) {
         // The pre-activations of a chunk of neurons at a time: 64 MiB of them make one round of 256 x 256 tiles

@@ -103,6 +103,14 @@ def test_calibrate_rejects_bad_arguments_without_a_gpu():
     assert search(_desc(), step=float("nan")) == T.ERR_INVALID_ARG
 
 
+def test_calibrate_rejects_more_neurons_than_one_product_takes():
+    """Also with so many tokens that the neurons would come in chunks."""
+    p = C.c_void_p(0x4000)
+    d = _desc(h=4194241)
+    for n in (1, 32768):
+        assert T.lib().tardis_calibrate(C.byref(d), p, n, 0.9, None, p, p, p, p, None) == T.ERR_SHAPE
+
+
 def test_threshold_calls_reject_bad_arguments_without_a_gpu():
     lib = T.lib()
     p = C.c_void_p(0x4000)
