@@ -232,9 +232,9 @@ tardis_status_t td_estimate_errors(const tardis_ffn_desc* desc, const void* X, i
 tardis_status_t td_assign_thresholds(const float* err, int64_t n, float t, float t_min, float t_max, float* out,
                                      hipStream_t s);
 tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s);
-// gemm.hip:  C[m][n] = sum_k A[m][k] * B[n][k] (+ the same of A2, B2 unless null) (+ row_bias[m]); C fp32, ldc = N
-tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
-                           int64_t K, int32_t dtype, const void* row_bias, hipStream_t s);
+// gemm.hip:  C[m][n] (+)= sum_k A[m][k] * B[n][k] (+ row_bias[m]); C fp32, ldc = N
+tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
+                           int accumulate, const void* row_bias, hipStream_t s);
 bool td_gemm_refuses_rows(int64_t M);
 // the products of calls with many tokens, each with the step that follows it (see gemm.hip)
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,

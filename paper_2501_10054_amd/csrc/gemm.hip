@@ -153,6 +153,7 @@ struct GemmArgs {
     uint32_t k, k2;
     // epilogues
     float* C;                      // F32: M x N; PART: [split][M][N]
+    int accumulate;                // F32: add to C
     const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, REPAIR: per column
     bf16_t* out;                   // HIDDEN, REPAIR: M x N
     bf16_t* rest;                  // REPAIR: what the rounding of `out` to bf16 left, M x N (or null)
@@ -164,7 +165,7 @@ struct GemmArgs {
     int act;
 };
 
-// F32: C = product (+ bias).  PART: one range of K's share of C.  HIDDEN: out = sigma(product + bias).
+// F32: C = product (+ bias), or C += product.  PART: one range of K's share of C.  HIDDEN: out = sigma(product + bias).
 // REPAIR: the first pair of operands is int8 (token codes and predictor codes), the second bf16 (tokens and
 // W1): the sums of the first give the flags, those of the second z, and out = sigma(z) - (slope z + icept) at
 // the flagged places, 0 elsewhere (with `rest`: as bf16 head and bf16 remainder, 16 significant bits together).  Neither
@@ -512,13 +513,17 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
                 *reinterpret_cast<f32x4_t*>(chunk + frow * CW + (((j * 4 + fp) ^ (frow & (NB * 4 - 1))) * 4)) = v;
             }
             __builtin_amdgcn_wave_barrier();
+            auto store = [&](auto add) {
 #pragma unroll
-            for (int u = 0; u < 16 * CW / 64; ++u) {
-                const int at = u * 64 + lane, row = at / CW, col = at % CW;
-                const float v = chunk[row * CW + (((col >> 2) ^ (row & (NB * 4 - 1))) * 4) + (col & 3)];
-                const int64_t mm = mw + i * 16 + row, nn = nw + col;
-                if (mm < p.M && nn < p.N) C[mm * p.N + nn] = v;
-            }
+                for (int u = 0; u < 16 * CW / 64; ++u) {
+                    const int at = u * 64 + lane, row = at / CW, col = at % CW;
+                    const float v = chunk[row * CW + (((col >> 2) ^ (row & (NB * 4 - 1))) * 4) + (col & 3)];
+                    const int64_t mm = mw + i * 16 + row, nn = nw + col;
+                    if (mm < p.M && nn < p.N) C[mm * p.N + nn] = decltype(add)::value ? C[mm * p.N + nn] + v : v;
+                }
+            };
+            if (EPI == EPI_F32 && p.accumulate) store(std::true_type{});
+            else store(std::false_type{});
             __builtin_amdgcn_wave_barrier();
         }
     } else {
@@ -745,34 +750,30 @@ tardis_status_t td_gemm_init() {
 // more rows than the grid of the kernel for any shape counts
 bool td_gemm_refuses_rows(int64_t M) { return (M + GT - 1) / GT > 65535; }
 
-// C = A.B^T + A2.B2^T (A2, B2 null: the first product alone; both pairs have rows of K elements)
-tardis_status_t td_gemm_nt(const void* A, const void* B, const void* A2, const void* B2, float* C, int64_t M, int64_t N,
-                           int64_t K, int32_t dtype, const void* row_bias, hipStream_t s) {
+// C = A.B^T (+ row_bias), or C += A.B^T.  (A second product is added to the first one's finished sums and not summed
+// onto them: partial sums of the first may be far larger than the second.)
+tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
+                           int accumulate, const void* row_bias, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return TARDIS_ERR_SHAPE;
     if (td_gemm_refuses_rows(M)) return TARDIS_ERR_SHAPE;
     // (any M, N work on the matrix cores; small products are not worth it)
     if (dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 && is_aligned16(A) && is_aligned16(B) &&
-        is_aligned16(A2) && is_aligned16(B2) && K % 8 == 0 && !gemm_force_generic()) {
+        K % 8 == 0 && !gemm_force_generic()) {
         TD_TRY(td_gemm_init());
         GemmArgs p{};
-        p.A = bytes_of(A);
-        p.B = bytes_of(B);
-        p.A2 = A2 ? bytes_of(A2) : p.A;
-        p.B2 = B2 ? bytes_of(B2) : p.B;
+        p.A = p.A2 = bytes_of(A);
+        p.B = p.B2 = bytes_of(B);
         p.M = M;
         p.N = N;
         p.k = (uint32_t)(K * 2);
-        p.k2 = A2 ? p.k : 0u;
         p.C = C;
+        p.accumulate = accumulate;
         p.bias = static_cast<const bf16_t*>(row_bias);
         launch_tile<EPI_F32>(p, s);
+    } else if (dtype == TARDIS_BF16) {
+        launch_generic<bf16_t>(A, B, C, M, N, K, accumulate, row_bias, s);
     } else {
-        for (int part = 0; part < (A2 ? 2 : 1); ++part) {
-            if (dtype == TARDIS_BF16)
-                launch_generic<bf16_t>(part ? A2 : A, part ? B2 : B, C, M, N, K, part, part ? nullptr : row_bias, s);
-            else
-                launch_generic<float>(part ? A2 : A, part ? B2 : B, C, M, N, K, part, part ? nullptr : row_bias, s);
-        }
+        launch_generic<float>(A, B, C, M, N, K, accumulate, row_bias, s);
     }
     TD_HIP(hipGetLastError());
     return TARDIS_OK;

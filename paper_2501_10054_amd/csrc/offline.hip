@@ -1192,7 +1192,7 @@ tardis_status_t td_estimate_errors(const tardis_ffn_desc* desc, const void* X, i
     DevBuf zt, cn;
     TD_TRY(zt.alloc((size_t)h * n * 4));
     TD_TRY(cn.alloc((size_t)h * 4));
-    TD_TRY(td_gemm_nt(desc->W1, X, nullptr, nullptr, static_cast<float*>(zt.p), h, n, d, desc->dtype, desc->b1, s));
+    TD_TRY(td_gemm_nt(desc->W1, X, static_cast<float*>(zt.p), h, n, d, desc->dtype, 0, desc->b1, s));
     const dim3 cgrid((unsigned)((h + kBlock - 1) / kBlock));
     if (desc->dtype == TARDIS_BF16)
         hipLaunchKernelGGL(col_norm_kernel<bf16_t>, cgrid, dim3(kBlock), 0, s, static_cast<const bf16_t*>(desc->W2), d, h,
@@ -1291,7 +1291,8 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
             hipLaunchKernelGGL(scale_transpose_bf16_kernel, tile_grid(d, h), dim3(256), 0, s,
                                static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(work1),
                                static_cast<bf16_t*>(work2), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, work1, desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, nullptr, s));
+        TD_TRY(td_gemm_nt(desc->W2, work1, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 0, nullptr, s));
+        TD_TRY(td_gemm_nt(desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 1, nullptr, s));
         const int64_t n = d * d;
         if (Wp8)
             hipLaunchKernelGGL(wp_to_fp8_kernel, dim3((unsigned)d), dim3(kBlock), 0, s, static_cast<const float*>(acc.p),
@@ -1309,7 +1310,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
     } else {
         hipLaunchKernelGGL(scale_transpose_f32_kernel, tile_grid(d, h), dim3(256), 0, s,
                            static_cast<const float*>(desc->W1), a, static_cast<float*>(work1), h, d);
-        TD_TRY(td_gemm_nt(desc->W2, work1, nullptr, nullptr, static_cast<float*>(Wp), d, d, h, TARDIS_F32, nullptr, s));
+        TD_TRY(td_gemm_nt(desc->W2, work1, static_cast<float*>(Wp), d, d, h, TARDIS_F32, 0, nullptr, s));
         hipLaunchKernelGGL(fold_bias_terms_kernel<float>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                            static_cast<const float*>(desc->b1), a, c, static_cast<double*>(kk.p), h);
         hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)d), dim3(kBlock), 0, s,
@@ -1341,7 +1342,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
             part.W1 = static_cast<const char*>(desc->W1) + (size_t)j0 * d * es;
             part.b1 = desc->b1 ? static_cast<const char*>(desc->b1) + (size_t)j0 * es : nullptr;
             float* z = static_cast<float*>(zt.p);
-            TD_TRY(td_gemm_nt(part.W1, X, nullptr, nullptr, z, part.h, n, d, desc->dtype, part.b1, s));
+            TD_TRY(td_gemm_nt(part.W1, X, z, part.h, n, d, desc->dtype, 0, part.b1, s));
             const float* cov = cov_pn ? cov_pn + j0 : nullptr;
             if (desc->dtype == TARDIS_BF16)
                 TD_TRY(launch_calibrate<bf16_t>(&part, z, X, (int)n, coverage, cov, lo + j0, hi + j0, a + j0, c + j0, s));
@@ -1352,7 +1353,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
         return TARDIS_OK;
     }
     TD_TRY(zt.alloc((size_t)h * n * 4));
-    TD_TRY(td_gemm_nt(desc->W1, X, nullptr, nullptr, static_cast<float*>(zt.p), h, n, d, desc->dtype, desc->b1, s));
+    TD_TRY(td_gemm_nt(desc->W1, X, static_cast<float*>(zt.p), h, n, d, desc->dtype, 0, desc->b1, s));
     int npad = 2;
     while (npad < n) npad <<= 1;
     const size_t lds = (size_t)((n + 1) & ~(int64_t)1) * sizeof(double) + (size_t)npad * sizeof(float);

@@ -325,6 +325,26 @@ def test_repair_factors_are_not_rounded_to_one_bf16(d, h, n, bits, monkeypatch):
     assert rel_l2(got, want) <= 3e-3
 
 
+@pytest.mark.parametrize("d,h", [(128, 16384), (256, 4096), (64, 2048)])
+def test_fold_keeps_the_remainder_under_large_partial_sums(d, h):
+    """diag(a) W1 = +-2^(k % 3) (1 + r_j) with |r_j| < 2^-9: the heads cancel exactly over the neurons, with partial sums up
+    to 2 h, and W' is the sum of the remainders, which is far below a unit in the last place of those.  A remainder
+    is rounded to bf16 and so is W': 2^-8 of the remainders' norm and of W', against fp64."""
+    rng = np.random.default_rng(17)
+    s = np.where(np.arange(h) < h // 2, 1.0, -1.0)
+    W1 = (s[:, None] * 2.0 ** (np.arange(d) % 3)[None, :]).astype(np.float32)
+    W2 = np.ones((d, h), np.float32)
+    a = (1.0 + rng.uniform(-1, 1, h) * 2.0 ** -9 * 0.9).astype(np.float32)
+    full = lambda v: torch.full((h,), v, dtype=torch.float32, device=DEV)
+    L = T.tardis_fold(T.FFN(dev(W1, "bf16"), dev(W2, "bf16")), full(-1.0), full(1.0), torch.from_numpy(a).to(DEV), full(0.0))
+    got = host(T.tardis_get_folded(L)[0])
+    L.close()
+    r = s * (a.astype(np.float64) - 1.0)
+    scale = 2.0 ** (np.arange(d) % 3)
+    want = scale * (s * a.astype(np.float64)).sum()
+    assert np.abs(got - want).max() <= 2.0 ** -8 * (np.abs(want).max() + 4 * np.linalg.norm(r))
+
+
 def test_prompt_path_with_bias_and_relu():
     seed = synth.workload_seed(3, 11)
     layer = synth.make_layer(512, 2048, "bf16", seed, w1_std=0.05, w2_std=0.05, heavy_frac=0.01, with_bias=True)
