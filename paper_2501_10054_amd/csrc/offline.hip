@@ -487,7 +487,7 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
                         const float* __restrict__ cov_pn, int act, float* __restrict__ lo, float* __restrict__ hi,
                         float* __restrict__ a, float* __restrict__ c) {
     constexpr int NW = T / TD_WAVE;
-    static_assert(T >= 256 && kSelBins % 256 == 0, "four cells a thread in the search for the ranks' cells");
+    static_assert(NPT % 2 == 0 && T >= 256 && kSelBins % 256 == 0, "four cells a thread in the search for the ranks' cells");
     extern __shared__ float vals[];                  // npad floats, only for the sort
     __shared__ int hist[kSelBins];
     __shared__ int wave_tot[4];
@@ -507,11 +507,15 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
     for (int k = 0; k < NPT; ++k) {
         const int i = k * T + tid;
         v[k] = i < n ? z[i] : 0.0f;
-        if (i < n) {                                 // (a NaN has no cell: the histogram is left out as for an infinity)
+        if (i < n) {
             mn = fminf(mn, v[k]);
-            mx = v[k] == v[k] ? fmaxf(mx, v[k]) : INFINITY;
+            mx = fmaxf(mx, v[k]);
         }
     }
+    bool nan = false;                                // a NaN has no cell: the histogram is left out as for an infinity
+#pragma unroll
+    for (int k = 0; k < NPT; k += 2) nan |= __builtin_isunordered(v[k], v[k + 1]);
+    if (nan) mx = INFINITY;
     for (int i = tid; i < kSelBins; i += T) hist[i] = 0;
     if (tid < 2) list_n[tid] = 0;
 #pragma unroll
