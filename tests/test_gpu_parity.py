@@ -45,7 +45,7 @@ def assert_y_close(got, want, F, X, flags, dtype="bf16"):
     and, as a rounding error, uniform within its half unit: the folded product of token x is off by
     a sum of independent terms of standard deviation at most 2^-8/sqrt(3) * r_i,
     r_i = sqrt(sum_k (W'_ik x_k)^2).  (2) The paths that carry the repair factors delta_j as bf16
-    (passes of 17-64 tokens, prompts) add the same kind of sum over the token's flagged neurons,
+    (many matrix products) add the same kind of sum over the token's flagged neurons,
     q_i = sqrt(sum_j (delta_j W2_ij)^2).  Six standard deviations of (1) + (2) are allowed.
     (3) The bf16 output adds at most 2^-8 |y_i| (1.5 x 2^-8 of the checker's value allowed).
     Everything else (fp32 sums, erf) is orders below.  One wrong element - off by its own size -
@@ -223,8 +223,8 @@ def test_mid_bf16_batched_high_fallback():
 def test_batched_passes_of_64_tokens(n, coverage):
     """Up to 16 tokens: groups of 16, 8, 4 (two kernels: records, then the column-sliced down
     projection; 3, 5-7 and 9-15 tokens run as partly empty groups), 2 and 1 tokens (one kernel).
-    17 to 64: one weight stream per pass, every tile count (1, 2, 4 token tiles), the masked-dense
-    scatter.  70 and 150: the prompt path at a fraction of one tile row."""
+    17: a group and a token.  18 to 64: matrix products of one row of tiles.  70 and 150: a fraction of one
+    tile row of larger tiles."""
     w = synth.decode(d=1024, h=4096, n_cal=512, n_test=n, coverage=coverage, config=2)
     run_case(w.layer, w.X_cal, w.X_test, coverage, batched=True, check_calibrate=False)
 
@@ -243,7 +243,7 @@ def test_batched_with_bias_and_relu():
                                         (640, 1992, 129, 8)])
 def test_prompt_path_many_tokens(d, h, n, bits):
     """65 tokens and more: integer predictor sums, pre-activations, folded product and the masked
-    delta's down projection as four matrix products (ragged token counts span a partial tile);
+    delta's down projection as matrix products (ragged token counts span a partial tile);
     masks bit-exact, lists and counts as for every other path.  d = 384 and 640: odd numbers of K
     slices (3 and 5 of int8, 9 per range of the down projection); h = 1160, 1992: a ragged last
     tile column and a K of the down projection that is no multiple of the slice."""
@@ -255,13 +255,37 @@ def test_prompt_path_many_tokens(d, h, n, bits):
                                    (256, 1000, 130), (384, 4104, 333), (128, 2000, 700), (128, 1000, 2), (384, 4104, 23),
                                    (1024, 4096, 18), (512, 8200, 64), (1536, 2000, 33)])
 def test_prompt_path_tiles(d, h, n):
-    """Every tile shape of the matrix-core products at its edges: a K of one or two slices, K that is not whole
-    slices (h % 64 != 0), ragged rows and columns, words of the mask cut by the tile."""
+    """The matrix-core products at the edges of their tiles: a K of one or two slices, K that is not whole
+    slices (h % 64 != 0), ragged rows and columns, words of the mask cut by the tile.  (Tiles of 64, 128 and 256 rows
+    and 192 x 256; the others follow below.)"""
     seed = synth.workload_seed(9, 50 + n % 7)
     layer = custom_layer(d, h, "bf16", seed, 0.1, True)
     r = run_case(layer, synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL),
                  synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST), 0.93, batched=True)
     assert r["rate"] > 0
+
+
+@pytest.mark.parametrize("d,h,n", [(128, 8200, 400), (256, 8192, 590), (128, 8200, 600), (256, 8192, 890), (2048, 2048, 513),
+                                   (2048, 1000, 1025), (2048, 2048, 1600), (2048, 2000, 1600), (2048, 1000, 300)])
+def test_prompt_path_tiles_of_128_columns(d, h, n):
+    """The tiles of 192 x 128 (400, 590 tokens) and 256 x 128 (600, 890) of the up and hidden products and, with 513 tokens
+    and more, of the output product with whole and with ragged K; partial rows and columns of each.  The folded path
+    against the checker, the dense one against fp64 with its hidden activations rounded to bf16: the output's
+    rounding (2^-9) and that of fp32 sums behind a rounding that may fall on the other side (2^-9 of few)."""
+    seed = synth.workload_seed(9, 59)
+    layer = custom_layer(d, h, "bf16", seed, 0.02 if d == 2048 else 0.1, True)
+    X = synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST)
+    r = run_case(layer, synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL), X, 0.93, batched=True)
+    assert r["rate"] > 0
+    ones = torch.ones(h, dtype=torch.float32, device=DEV)
+    L = T.tardis_fold(make_ffn(layer), -ones, ones, ones, ones, max_batch=n)
+    got = host(T.tardis_dense_forward(L, dev(X, "bf16")))
+    L.close()
+    W1, W2, b1, b2 = (torch.from_numpy(np.asarray(t)).double() for t in (layer.W1, layer.W2, layer.b1, layer.b2))
+    hidden = torch.nn.functional.gelu(torch.from_numpy(X).double() @ W1.T + b1).to(torch.bfloat16).double()
+    want = (hidden @ W2.T + b2).numpy()
+    assert rel_l2(got, want) <= 3e-3
+    assert np.abs(got - want).max() <= 2.0 ** -7 * np.abs(want).max()
 
 
 def test_prompt_path_takes_tokens_at_any_address():
@@ -362,8 +386,8 @@ def test_prompt_path_in_chunks(monkeypatch):
 
 
 def test_prompt_threshold_off_takes_token_passes(monkeypatch):
-    """With the prompt path's threshold out of reach the same 300 tokens run as passes of 64 (four
-    full passes and a ragged last one)."""
+    """With the prompt path's threshold out of reach the same 300 tokens run as decode groups (18 of 16 and
+    the rest)."""
     monkeypatch.setenv("TARDIS_PREFILL_MIN", "1000000")
     w = synth.decode(d=1024, h=4096, n_cal=512, n_test=300, coverage=0.9, config=3)
     run_case(w.layer, w.X_cal, w.X_test, 0.9, batched=True, check_calibrate=False)
@@ -794,7 +818,7 @@ def test_per_neuron_coverage_and_single_calibration_token():
 
 
 def test_calibrate_many_samples_uses_large_lds():
-    # 20000 calibration tokens: the per-neuron sort needs 128 KiB of LDS (padded to 32768 samples)
+    # 20000 calibration tokens, the largest block; its sort, should it be needed, has 128 KiB of LDS (32768 samples)
     seed = synth.workload_seed(9, 3)
     layer = synth.make_layer(64, 128, "f32", seed, w1_std=0.2, w2_std=0.05)
     X_cal = synth.make_tokens(20000, 64, "f32", seed, synth.STREAM_CAL)
@@ -825,8 +849,23 @@ def test_calibrate_sample_counts_and_crowded_samples(n, kind):
         assert np.abs(a - oa).max() <= 0.1
         return
     # fp32 pre-activations (2e-6 off) against the checker's; equal samples may be split by their rounding (1/n each)
-    tol = 1e-5 * scale if kind == "normal" else 1e-5 * scale + 20.0 / n
+    tol = 1e-5 * scale + 20.0 / n if kind == "repeated" else 1e-5 * scale
     assert np.abs(a - oa).max() <= tol and np.abs(c - oc).max() <= tol
+
+
+@pytest.mark.parametrize("n", [8193, 20000, 32768])
+def test_calibrate_many_samples_with_an_outlier_are_sorted(n):
+    """One sample 10^4 times the others leaves them in one cell of the histogram: the sort of up to 32768 samples, 128 KiB
+    of LDS.  lo, hi within the fp32 pre-activations' rounding; a sample within it of an end moves a line by 1/n."""
+    seed = synth.workload_seed(9, 42)
+    layer = synth.make_layer(48, 72, "f32", seed, w1_std=0.2, w2_std=0.05, with_bias=True)
+    X = synth.make_tokens(n, 48, "f32", seed, synth.STREAM_CAL)
+    X[n // 2] *= 1e4
+    lo, hi, a, c = (t.cpu().numpy() for t in T.tardis_calibrate(make_ffn(layer), dev(X, "f32"), 0.9))
+    olo, ohi, oa, oc = O.calibrate(layer.W1, layer.b1, X, 0.9)
+    scale = max(1.0, float(np.abs(olo).max()), float(np.abs(ohi).max()))
+    assert np.abs(lo - olo).max() <= 2e-6 * scale and np.abs(hi - ohi).max() <= 2e-6 * scale
+    assert np.abs(a - oa).max() <= 1e-5 * scale + 2.0 / n and np.abs(c - oc).max() <= 1e-5 * scale + 2.0 / n
 
 
 def bitonic(z):
