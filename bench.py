@@ -69,7 +69,7 @@ def _time_us(torch, fn, reps, warm=2):
 
 def prefill_run(T, synth, torch, np, to_dev):
     """2048 (and 256) tokens x d=4096 through one layer - the prompt path: predictor sums,
-    pre-activations, folded product and masked-delta down projection as four matrix-core products -
+    pre-activations, and folded product with masked-delta down projection as matrix-core products -
     against the dense FFN as two vendor-BLAS GEMMs; also the offline calibration and fold times."""
     n = 2048
     w = synth.decode(layer=0, n_cal=4096, n_test=n, coverage=0.95, config=3)
@@ -104,7 +104,7 @@ def prefill_run(T, synth, torch, np, to_dev):
             "dense_own_us": dus_own, "dense_own_TFLOPs": (2.0 * 2 * n * D * H) / dus_own / 1e6,
             "calibrate_us": cal_us, "fold_ms_incl_alloc": fold_ms,
             "note": "fold = 2 bf16 MFMA GEMMs of %.0f GFLOP each (head + remainder of diag(a)W1); "
-                    "calibrate = 1 such GEMM + per-neuron sort/fit" % (gemm_flop / 1e9)}
+                    "calibrate = 1 such GEMM + per-neuron order statistics and fit" % (gemm_flop / 1e9)}
 
 
 def sketch_study(T, torch, ffn, cal, X64):

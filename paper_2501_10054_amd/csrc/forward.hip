@@ -6,9 +6,10 @@
 //                       y += (sigma(z_j) - (a_j z_j + c_j)) * W2[:, j]
 // plus the unmodified FFN on the same row-streaming core (the dense baseline).
 //
-// Every kernel here is bound by HBM bandwidth: each weight row is read exactly
-// once with 16-byte loads per lane, one wavefront per row, the token staged in
-// LDS, and the per-row reduction done with cross-lane shuffles.
+// One token is bound by HBM bandwidth: each weight row is read once per token (the
+// tokens of a call share rows through the caches only) with 16-byte loads per
+// lane, one wavefront per row, the token staged in LDS, and the per-row reduction
+// done with cross-lane shuffles.
 #include "common.h"
 #include "rowdot.h"
 

@@ -1,5 +1,5 @@
-// C[m][n] = sum_k A[m][k] * B[n][k]  -- both operands K-contiguous ("NT"); C fp32 (bf16 or fp32
-// operands) or exact int32 (int8 operands).
+// C[m][n] = sum_k A[m][k] * B[n][k]  -- both operands K-contiguous ("NT"); bf16 or fp32 operands and
+// fp32 sums, or int8 operands and exact int32 sums, which only feed the range test and are not stored.
 //
 // Used offline: the fold  W' = W2 . (diag(a) W1)  (Sec. "Constant Folded Matrix
 // Generation") with A = W2 (d x h) and B = (diag(a) W1)^T (d x h), and the
@@ -222,7 +222,7 @@ struct GemmTile {
     static constexpr int WN = kWavesPerTile / WM;
     static constexpr int TM = WM * NA * 16, TN = WN * NB * 16;
     static constexpr int UA = TM * SL, UB = TN * SL;      // bytes of one slice
-// one row of tiles: a row of B is read by one block, so its lines are not kept (64 tokens: 40.6 -> 38.8 us; the
+    // one row of tiles: a row of B is read by one block, so its lines are not kept (64 tokens: 40.6 -> 38.8 us; the
     // output product, whose blocks share lines between K ranges, loses by it: 31.7 -> 35.5 us)
     static constexpr bool kOnce = TM == 64 && EPI == EPI_REPAIR;
     static constexpr int LA = UA / 8192, LB = UB / 8192;                        // loads per wavefront and slice
@@ -627,9 +627,15 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 }
 
 // The tile for a product: the one whose rounds over 256 CUs cost least.  A block spends per slice either the
-// cycles of its MFMAs or those in which its share of L2 bandwidth (about 34 bytes per cycle and CU, measured
-// above) delivers the two operand slices.  `splittable`: K may be cut into 2, 4 or 8 ranges (each then adds
-// the partial tile's bytes, written and read again; at most kPartRows rows of partial sums are kept).
+// cycles of its MFMAs or those in which the two operand slices arrive, at 34 bytes per cycle and CU.  That rate is a
+// chosen number, not a measured bandwidth, and the rule's cycles only rank tiles: they stand for neither the clock under
+// load nor HBM (up / output product at 2.1 GHz by the rule, and measured, us: d = 4096, h = 16384, 2048 tokens 199 / 197,
+// 378 / 267; 333 tokens 57 / 57, 94 / 71; 64 tokens 23 / 20, 39 / 31; d = 2048, h = 8192, 23 tokens 6 / 6, 17 / 10).
+// The larger rate for slices of 256 bytes stands for what the rule does not model: with one row of tiles the weights
+// stream from HBM, which delivers longer runs faster (64 tokens, us with 256 / 128 bytes a slice: d = 4096, up
+// projection of h = 16384 38.9 / 46.2, of h = 11008 (40 tokens) 33.9 / 44.1, dense 27.4 / 29.0; d = 2048 output product 10.8 /
+// 12.1).  `splittable`: K may be cut into 2, 4 or 8 ranges (each then adds the partial tile's bytes, written and read
+// again; at most kPartRows rows of partial sums are kept).
 constexpr int64_t kPartRows = 4096;
 struct TileChoice { int shape, splits; };
 constexpr int kShapes = 10;
