@@ -717,7 +717,7 @@ def test_sketch4_zero_rows_and_zero_groups():
                                            (2048, 4096, 20, True), (4096, 2048, 5, True)])
 def test_sketch4_bf16_paths(d, h, n, batched):
     """d = 1024: the single-launch kernel on one-byte effective codes.  d = 2048, 4096: the packed
-    4-bit rows (1, 2 and 4 tokens per launch); 20 tokens: the 64-token-pass path on effective codes."""
+    4-bit rows (1, 2 and 4 tokens per launch); 20 tokens: matrix products on effective codes."""
     seed = synth.workload_seed(9, 13)
     layer = synth.make_layer(d, h, "bf16", seed, w1_std=0.03, w2_std=0.03, heavy_frac=0.01, with_bias=True)
     X_cal = synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL)
@@ -758,7 +758,7 @@ def test_degenerate_tokens_and_neurons():
 @pytest.mark.parametrize("n", [8, 40, 130])
 def test_degenerate_tokens_on_the_bf16_paths(n):
     """Zero, tiny, huge and one-hot tokens and all-zero neurons through the fused decode kernels
-    (8 tokens), a 64-token pass (40) and the prompt path (130)."""
+    (8 tokens), matrix products of one row of tiles (40) and of more (130)."""
     d, h = 1024, 2048
     seed = synth.workload_seed(9, 17)
     layer = synth.make_layer(d, h, "bf16", seed, w1_std=0.04, w2_std=0.03, heavy_frac=0.01, with_bias=True)
@@ -977,8 +977,7 @@ def test_graph_capture_and_replay_of_forward():
 
 @pytest.mark.parametrize("n", [40, 100, 300])
 def test_graph_capture_of_pass_and_prompt_paths(n):
-    """40 tokens (one 64-token pass), 100 (short-tile products that add atomically into results the
-    library zeroes itself) and 300 (square tiles, K in ranges): captured once, replayed three
+    """40 tokens (one row of tiles), 100 and 300 (larger tiles, K in ranges): captured once, replayed three
     times with eager work in between; every replay reproduces the eager call, masks bit for bit."""
     w = synth.decode(d=1024, h=4096, n_cal=256, n_test=n, coverage=0.9, config=9)
     ffn = make_ffn(w.layer)
@@ -1004,9 +1003,37 @@ def test_graph_capture_of_pass_and_prompt_paths(n):
     L.close()
 
 
+@pytest.mark.parametrize("d,h,n,dtype", [(768, 3072, 33, "bf16"), (256, 1024, 5, "f32"), (64, 256, 3, "f32")])
+def test_graph_capture_of_layers_without_decode_kernels(d, h, n, dtype):
+    """Products with the factors' remainders, three launches over all tokens (whose counters have to be zero again behind
+    each call), one block a token: replays with eager work in between give the eager call's masks and outputs."""
+    seed = synth.workload_seed(9, 81)
+    layer = custom_layer(d, h, dtype, seed, 0.1, True)
+    ffn = make_ffn(layer)
+    X = dev(synth.make_tokens(n, d, dtype, seed, synth.STREAM_TEST), dtype)
+    L = T.tardis_fold(ffn, *T.tardis_calibrate(ffn, dev(synth.make_tokens(256, d, dtype, seed, synth.STREAM_CAL), dtype), 0.9),
+                      max_batch=n)
+    y_eager = T.tardis_ffn_forward_batched(L, X).clone()
+    mask_eager = T.tardis_get_last_outliers(L, n, want_list=False)[0].clone()
+    torch.cuda.synchronize()
+    y_g = torch.zeros_like(y_eager)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        T.tardis_ffn_forward_batched(L, X, y_g)
+    for rep in range(3):
+        y_g.zero_()
+        T.tardis_ffn_forward_batched(L, torch.roll(X, 1, 0).contiguous())
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert rel_l2(host(y_g), host(y_eager)) < (2e-3 if dtype == "bf16" else 1e-6), rep      # order of atomics only
+        assert torch.equal(T.tardis_get_last_outliers(L, n, want_list=False)[0], mask_eager), rep
+    L.close()
+
+
 def test_result_does_not_depend_on_how_many_tokens_share_a_call():
-    """The same tokens through every dispatch path - single launches, groups of 2-16, a 64-token
-    pass, short and square tiles of the prompt path: the masks of a token are the same bits whatever
+    """The same tokens through every dispatch path - single launches, groups of 2-16, one row of tiles,
+    larger tiles of the prompt path: the masks of a token are the same bits whatever
     call it is part of, its output agrees to rounding (strictly per-token semantics)."""
     w = synth.decode(d=1024, h=4096, n_cal=512, n_test=300, coverage=0.9, config=3)
     ffn = make_ffn(w.layer)
@@ -1079,8 +1106,8 @@ def test_next_layer_hint_changes_nothing_but_time():
 
 
 def test_destroy_returns_the_layer_s_memory():
-    """Folding and destroying a layer many times (with every scratch area: records, 64-token
-    passes, prompt path) leaves the device's free memory where it was."""
+    """Folding and destroying a layer many times (with every scratch area: records,
+    matrix products) leaves the device's free memory where it was."""
     w = synth.decode(d=1024, h=4096, n_cal=256, n_test=128, coverage=0.9, config=9)
     ffn = make_ffn(w.layer)
     cal = T.tardis_calibrate(ffn, dev(w.X_cal, "bf16"), 0.9)
@@ -1218,7 +1245,7 @@ def test_deterministic_stack_and_refusals():
 
 def test_fixed_point_accumulators_by_knob(monkeypatch):
     """TARDIS_FIXED_POINT=1 puts the counted fixed-point accumulators under the ordinary dispatch
-    (token passes and prompts unchanged): the decode groups against the checker, single token,
+    (matrix products unchanged): the decode groups against the checker, single token,
     groups, a partly filled group, graph replay."""
     monkeypatch.setenv("TARDIS_FIXED_POINT", "1")
     w = synth.decode(d=2048, h=4096, n_cal=512, n_test=16, coverage=0.9)
@@ -1237,7 +1264,7 @@ def test_fixed_point_accumulators_by_knob(monkeypatch):
                                          (2048, 2048, "bf16", 6), (1024, 4096, "bf16", 40), (1024, 2048, "bf16", 90)])
 def test_stack_teacher_forced(d, h, dtype, n):
     """Every layer is checked on the input the GPU itself handed to it: mask bit-exact, the
-    normalised hand-over and the final output within the y tolerance.  (40 tokens: a 64-token pass
+    normalised hand-over and the final output within the y tolerance.  (40 tokens: matrix products
     per layer; 90: the prompt path, whose last kernel applies the norm.)"""
     nl = 3
     layers, oracles = [], []
