@@ -11,6 +11,7 @@
 // masked factors, [X | D] . [W' | W2]^T.
 #include <cstdlib>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -109,6 +110,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWavesPerTile = 8;
+constexpr int kNoLds = 0xc07f, kNoLoads = 0x0f70;            // s_waitcnt lgkmcnt(0), vmcnt(0)
 constexpr int kLdsBytes = 160 * 1024;
 
 // Which block computes which tile.  Blocks b, b+8, b+16, ... run on one XCD and share its L2, so
@@ -118,18 +120,32 @@ constexpr int kLdsBytes = 160 * 1024;
 // other's slices of A and B from L2 instead of fetching them from HBM again.
 struct TileMap {
     int tiles_m, tiles_n;      // tile grid of C
-    int splits;                // K ranges (1, 2, 4 or 8)
-    int gn;                    // XCD grid columns (rows = 8 / splits / gn)
+    int splits_log2;           // K ranges (1, 2, 4 or 8)
+    int gn_log2;               // XCD grid columns (rows = 8 / splits / gn)
     int rm, rn;                // tiles per XCD rectangle
-    int group;                 // tile rows walked together
+    int group;                 // tile rows walked together (fewer in the last group)
+    uint32_t inv_walk, inv_group, inv_last;   // reciprocals (see quotient) of group x rn, of group, of the last group's rows
     int slices;                // K slices per range
 };
+
+// n / d, with inv = 2^32 / d rounded down: scalar multiplications (the compiler divides on the vector unit, and a block's
+// six divisions one after another are most of a microsecond)
+uint32_t reciprocal(uint32_t d) { return d > 1 ? (uint32_t)(0x100000000ull / d) : 0xffffffffu; }
+__device__ __forceinline__ uint32_t quotient(uint32_t n, uint32_t d, uint32_t inv, uint32_t& rest) {
+    uint32_t q = __umulhi(n, inv);                          // the quotient, or one less
+    rest = n - q * d;
+    if (rest >= d) {
+        ++q;
+        rest -= d;
+    }
+    return q;
+}
 
 TileMap make_tile_map(int64_t M, int64_t N, int tile_m, int tile_n, int slices, int splits) {
     TileMap t;
     t.tiles_m = (int)((M + tile_m - 1) / tile_m);
     t.tiles_n = (int)((N + tile_n - 1) / tile_n);
-    t.splits = splits;
+    t.splits_log2 = __builtin_ctz((unsigned)splits);
     const int nx = 8 / splits;
     int best = 1 << 30, gm = nx;
     for (int cand = 1; cand <= nx; cand *= 2) {            // cand = XCD grid rows
@@ -137,12 +153,35 @@ TileMap make_tile_map(int64_t M, int64_t N, int tile_m, int tile_n, int slices, 
         const int cost = rm * rn * 4096 + rm * tile_m + rn * tile_n;   // fewest blocks, then least operand bytes
         if (cost < best) { best = cost; gm = cand; }
     }
-    t.gn = nx / gm;
+    const int gn = nx / gm;
+    t.gn_log2 = __builtin_ctz((unsigned)gn);
     t.rm = (t.tiles_m + gm - 1) / gm;
-    t.rn = (t.tiles_n + t.gn - 1) / t.gn;
+    t.rn = (t.tiles_n + gn - 1) / gn;
     t.group = t.rm < 8 ? t.rm : 8;
+    t.inv_walk = reciprocal((uint32_t)(t.group * t.rn));
+    t.inv_group = reciprocal((uint32_t)t.group);
+    t.inv_last = reciprocal((uint32_t)(t.rm - (t.rm - 1) / t.group * t.group));
     t.slices = (slices + splits - 1) / splits;
     return t;
+}
+
+// This block's tile and K range; false: none
+__device__ __forceinline__ bool place(const TileMap& t, int xcd, int local, int& tile_m, int& tile_n, int& range) {
+    range = xcd & ((1 << t.splits_log2) - 1);
+    const int xg = xcd >> t.splits_log2;
+    uint32_t r, row;
+    const int first = (int)quotient((uint32_t)local, (uint32_t)(t.group * t.rn), t.inv_walk, r) * t.group;
+    const int rows = min(t.group, t.rm - first);
+    const int col = (int)quotient(r, (uint32_t)rows, rows == t.group ? t.inv_group : t.inv_last, row);
+    tile_m = (xg >> t.gn_log2) * t.rm + first + (int)row;
+    tile_n = (xg & ((1 << t.gn_log2) - 1)) * t.rn + col;
+    return tile_m < t.tiles_m && tile_n < t.tiles_n;
+}
+
+// The slice of `len` that a block starts with
+__device__ __forceinline__ int first_slice(int xcd, int local, int len) {
+    const int at = (local & 7) + xcd * len / 8;
+    return len < 8 ? 0 : at >= len ? at - len : at;
 }
 
 // C = A.B^T (+ A2.B2^T: a second pair of operands whose K follows the first's).  Rows of A are rows of
@@ -195,13 +234,30 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t
                      ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
 }
 
-// round to nearest even, in one instruction
-__device__ __forceinline__ uint32_t to_bf16(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+// round to nearest even, two in one instruction
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
+}
 
 // (the accumulator of the int8 form holds integers)
 template <bool I8> __device__ __forceinline__ void mma16(f32x4_t& c, const td_u32x4& a, const td_u32x4& b) {
     if constexpr (I8) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+
+template <int V> using num = std::integral_constant<int, V>;
+// f(num<0>), ..., f(num<N - 1>)
+template <typename F, int... I> __device__ __forceinline__ void for_each_constant(F f, std::integer_sequence<int, I...>) { (f(num<I>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void for_constants(F f) { for_each_constant(f, std::make_integer_sequence<int, N>{}); }
+
+// v of lanes l, l^16, l^32 and l^48 or-ed together
+__device__ __forceinline__ uint32_t or_halves(uint32_t v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] | a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return b[0] | b[1];
 }
 
 // The compiler does not know how long those take.  Every use of the accumulators from here on (of their new values, for
@@ -213,6 +269,53 @@ template <int NA, int NB> __device__ __forceinline__ void fence(f32x4_t (&acc)[N
 #pragma unroll
         for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[i][j])::"memory");
     __builtin_amdgcn_sched_barrier(0);
+}
+
+// Row blocks (of 16 rows) that a wavefront stages in LDS at a time: as many as fit (beside REPAIR's three parameters per column)
+template <int EPI, int W, int WM, int NA, int NB> struct EpiRows {
+    static constexpr int kParams = EPI == EPI_REPAIR ? 3 * (W / WM) * NB * 16 * 4 : 0;
+    static constexpr int fit(int n) { return n == 1 || (NA % n == 0 && W * n * 16 * NB * 16 * 4 + kParams <= kLdsBytes) ? n : fit(n - 1); }
+    static constexpr int value = fit(NA);
+    static constexpr int kWaveBytes = value * 16 * NB * 16 * 4, kBytes = W * kWaveBytes + kParams;
+};
+
+// sigma in the epilogues, where it is evaluated for whole rows of accumulators: no branches, so that several elements are under
+// way at once.  GELU = z Phi(z): for |z| < 1 Phi = 1/2 + z S(z^2), else from Phi(-|z|) = t exp(P(t) - z^2 / 2), t = 1 / (1 + 0.4 |z|);
+// S and P are minimax fits (to 3e-10 and 3e-8) of the two functions so defined.  Root mean square error against 64 bits for z from
+// N(0, 1.6^2): 3.6e-8, of the library functions' form (td_act) 3.9e-8; below -2 it is a tenth of the latter, which cancels there.
+// Infinities and NaNs give what they gave: +inf, and NaN for -inf.
+template <int ACT> __device__ __forceinline__ float act_flat(float z) {
+    if constexpr (ACT == TARDIS_ACT_GELU_ERF) {
+        const float u = fabsf(z), w = z * z;
+        const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, u, 1.0f));
+        float s = -7.6011511e-06f, p = -0.43888903f;
+        s = fmaf(s, w, 1.13367088e-04f);
+        s = fmaf(s, w, -1.18623779e-03f);
+        s = fmaf(s, w, 9.97329503e-03f);
+        s = fmaf(s, w, -6.64903596e-02f);
+        s = fmaf(s, w, 0.398942292f);
+        p = fmaf(p, t, 1.36559796f);                        // (P and z^2 / 2 in units of log 2)
+        p = fmaf(p, t, -1.33750927f);
+        p = fmaf(p, t, 0.194332317f);
+        p = fmaf(p, t, -0.0835891962f);
+        p = fmaf(p, t, 0.504601836f);
+        p = fmaf(p, t, 1.44168389f);
+        p = fmaf(p, t, -2.64764786f);
+        const float q = t * __builtin_amdgcn_exp2f(fmaf(u * -0.721347520f, u, p));
+        return z * (u < 1.0f ? fmaf(z, s, 0.5f) : z > 0.0f ? 1.0f - q : q);
+    } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
+        // (1 + tanh v) / 2 = 1 / (1 + exp(-2 v))
+        const float v = 0.79788456080286535588f * fmaf(0.044715f * z * z, z, z);
+        return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.88539008f * v));
+    } else {
+        return td_act(z, ACT);
+    }
+}
+template <typename F> __device__ __forceinline__ void with_act(int act, F f) {
+    if (act == TARDIS_ACT_GELU_ERF) f(num<TARDIS_ACT_GELU_ERF>{});
+    else if (act == TARDIS_ACT_GELU_TANH) f(num<TARDIS_ACT_GELU_TANH>{});
+    else if (act == TARDIS_ACT_RELU) f(num<TARDIS_ACT_RELU>{});
+    else f(num<TARDIS_ACT_IDENTITY>{});
 }
 
 // RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
@@ -237,12 +340,199 @@ struct GemmTile {
     // loads that may still be in flight when slice kt+2 has to be there (see the order in the kernel)
     static constexpr int kWaitB = LA + (SB - 2) * kPer, kWaitA = (SA - 2) * kPer;
     static constexpr int kWait = kWaitB < kWaitA ? kWaitB : kWaitA;
-    static constexpr int kEpiWave = 16 * NB * 16 * (EPI == EPI_REPAIR ? 12 : 4);   // LDS of a wavefront in the epilogue
-    static constexpr int kEpiLds = kWavesPerTile * kEpiWave + (EPI == EPI_REPAIR ? 3 * TN * 4 : 0);
+    static constexpr int kEpiLds = EpiRows<EPI, kWavesPerTile, WM, NA, NB>::kBytes;
     static constexpr int kLds = kRing + kPar > kEpiLds ? kRing + kPar : kEpiLds;
     static_assert(SL % 128 == 0 && UA % 8192 == 0 && UB % 8192 == 0, "whole loads of 1 KB for 8 wavefronts");
     static_assert(SB >= 2 && SA >= 2 && kWait + kPer <= 63 && kLds <= kLdsBytes, "slice buffers");
 };
+
+// What follows the products, W wavefronts in a grid of WM rows.  Some row blocks at a time go through LDS, so that a store covers
+// whole lines of a row, and so that what is done to the elements is a loop: unrolled over the accumulators, sigma alone is
+// 100 to 200 KB of instructions, which every block fetches once (2048 x 16384 x 4096 with GELU, eight wavefronts: sigma as a loop and without branches 251 -> 228 us).
+// REPAIR: the flagged pre-activations are staged, zeros elsewhere, and every lane replaces its own by their factors, as many
+// times as the lane with the most of them has any (5 %: about 14 times for 128 elements a lane).
+template <int EPI, int W, int WM, int NA, int NB>
+__device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA][NB], const uint32_t (&bits)[NA], unsigned char* lds,
+                                            int tid, int64_t m0, int64_t n0, int ks) {
+    typedef EpiRows<EPI, W, WM, NA, NB> E;
+    constexpr int WN = W / WM, TN = WN * NB * 16, RB = E::value, CW = NB * 16, PC = CW / 4;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+    const int frow = lane & 15, fp = lane >> 4;
+    // acc[i][j][q] = C[row m0 + (wm*NA + i)*16 + lane%16][column n0 + (wn*NB + j)*16 + 4*(lane/16) + q]
+    const int64_t mw = m0 + wm * NA * 16, nw = n0 + wn * CW;         // this wavefront's corner, CW columns
+    float* chunk = reinterpret_cast<float*>(lds + wave * E::kWaveBytes);
+    [[maybe_unused]] float* par = reinterpret_cast<float*>(lds + W * E::kWaveBytes);
+    if constexpr (EPI == EPI_REPAIR) {
+        for (int c = tid; c < TN; c += W * 64) {
+            const int64_t n = n0 + c < p.N ? n0 + c : p.N - 1;
+            par[c] = td_bf16_to_f32(p.bias[n]);
+            par[TN + c] = p.slope[n];
+            par[2 * TN + c] = p.icept[n];
+        }
+        __syncthreads();
+    }
+    // (pieces of 16 bytes, rotated by the row, against bank conflicts)
+    auto place_of = [&](int row, int piece) { return row * CW + ((piece ^ (row & 15 & (PC - 1))) * 4); };
+    auto piece_of = [&](int row, int piece) { return *reinterpret_cast<const f32x4_t*>(chunk + place_of(row, piece)); };
+    for_constants<NA / RB>([&](auto batch) {
+        constexpr int first = decltype(batch)::value * RB;
+        const int64_t m1 = mw + first * 16;
+        for_constants<RB>([&](auto row_block) {
+            constexpr int u = decltype(row_block)::value, i = first + u;
+            if constexpr (EPI == EPI_REPAIR) {
+                // mask: the four lanes of a row and (where the tile holds them) two tile columns make a word of 32 bits
+                const int64_t m = mw + i * 16 + frow;
+#pragma unroll
+                for (int w = 0; w < (NB + 1) / 2; ++w) {
+                    uint32_t word = ((bits[i] >> (8 * w)) & 15u) << (4 * fp);
+                    if constexpr (NB >= 2) word |= ((bits[i] >> (8 * w + 4)) & 15u) << (4 * fp + 16);
+                    word = or_halves(word);
+                    const int64_t n = nw + w * 32;
+                    if (fp == 0 && m < p.M && n < p.N) {
+                        uint32_t* row = p.mask + (size_t)m * p.mask_words;
+                        if constexpr (NB >= 2) {
+                            row[n >> 5] = word;
+                        } else {
+                            uint16_t* half = reinterpret_cast<uint16_t*>(row) + (n >> 4);
+                            half[0] = (uint16_t)word;
+                            if (n + 16 >= p.N && ((n >> 4) & 1) == 0) half[1] = 0;   // the rest of a last word
+                        }
+                    }
+                }
+            }
+            float rb = 0.0f;
+            if constexpr (EPI == EPI_F32) {
+                const int64_t m = mw + i * 16 + frow;
+                if (p.bias && m < p.M) rb = td_bf16_to_f32(p.bias[m]);
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                f32x4_t v;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if constexpr (EPI == EPI_REPAIR) v[q] = (bits[i] >> (4 * j + q)) & 1u ? acc[i][j][q] : 0.0f;
+                    else v[q] = acc[i][j][q] + rb;
+                }
+                *reinterpret_cast<f32x4_t*>(chunk + place_of(u * 16 + frow, j * 4 + fp)) = v;
+            }
+        });
+        __builtin_amdgcn_wave_barrier();
+        if constexpr (EPI == EPI_REPAIR) {
+            // flags of this lane's RB x 4 NB elements, lowest first
+            static_assert(RB * 4 * NB <= 128, "two words of flags");
+            uint64_t now = 0, later = 0;
+            for_constants<RB>([&](auto row_block) {
+                constexpr int at = decltype(row_block)::value * 4 * NB;
+                if constexpr (at < 64) now |= (uint64_t)bits[first + decltype(row_block)::value] << at;
+                else later |= (uint64_t)bits[first + decltype(row_block)::value] << (at - 64);
+            });
+            with_act(p.act, [&](auto act) {
+                int row0 = frow;
+                while (__any((now | later) != 0)) {
+                    if (now == 0) {
+                        now = later;
+                        later = 0;
+                        row0 = 64 / (4 * NB) * 16 + frow;
+                    }
+                    if (now != 0) {
+                        const int e = __builtin_ctzll(now), piece = (e / 4 % NB) * 4 + fp;
+                        now &= now - 1;
+                        float* z = chunk + place_of(row0 + e / (4 * NB) * 16, piece) + e % 4;
+                        const int c = wn * CW + piece * 4 + e % 4;
+                        const float v = *z + par[c];
+                        *z = act_flat<decltype(act)::value>(v) - fmaf(par[TN + c], v, par[2 * TN + c]);
+                    }
+                }
+            });
+            __builtin_amdgcn_wave_barrier();
+        }
+        if constexpr (EPI == EPI_HIDDEN || EPI == EPI_REPAIR) {      // N % 8 == 0: whole 16-byte vectors
+            constexpr int RPS = 64 / (CW / 8);                       // rows at a time
+            const int64_t nn = nw + lane % (CW / 8) * 8;
+            auto rows = [&](auto store) {
+#pragma unroll 2
+                for (int row = lane / (CW / 8); row < RB * 16; row += RPS) {
+                    const f32x4_t v[2] = {piece_of(row, lane % (CW / 8) * 2), piece_of(row, lane % (CW / 8) * 2 + 1)};
+                    store(v, m1 + row < p.M && nn < p.N, (m1 + row) * p.N + nn);
+                }
+            };
+            if constexpr (EPI == EPI_HIDDEN) {
+                float bias[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) bias[q] = nn < p.N ? td_bf16_to_f32(p.bias[nn + q]) : 0.0f;
+                with_act(p.act, [&](auto act) {
+                    rows([&](const f32x4_t (&v)[2], bool in, int64_t at) {
+                        float s[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) s[q] = act_flat<decltype(act)::value>(v[q >> 2][q & 3] + bias[q]);
+                        td_u32x4 o;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) o[q] = to_bf16x2(s[2 * q], s[2 * q + 1]);
+                        if (in) *reinterpret_cast<td_u32x4*>(p.out + at) = o;
+                    });
+                });
+            } else {
+                rows([&](const f32x4_t (&v)[2], bool in, int64_t at) {
+                    td_u32x4 o;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[q] = to_bf16x2(v[q >> 1][2 * (q & 1)], v[q >> 1][2 * (q & 1) + 1]);
+                    if (in) *reinterpret_cast<td_u32x4*>(p.out + at) = o;
+                    if (p.rest) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            float rest[2] = {v[q >> 1][2 * (q & 1)] - __uint_as_float(o[q] << 16),
+                                             v[q >> 1][2 * (q & 1) + 1] - __uint_as_float(o[q] & 0xffff0000u)};
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) rest[u] = fabsf(rest[u]) < INFINITY ? rest[u] : 0.0f;   // (infinite and NaN factors are all in the head)
+                            o[q] = to_bf16x2(rest[0], rest[1]);
+                        }
+                        if (in) *reinterpret_cast<td_u32x4*>(p.rest + at) = o;
+                    }
+                });
+            }
+        } else {
+            float* C = EPI == EPI_PART ? p.C + (size_t)ks * p.M * p.N : p.C;
+            const bool add = EPI == EPI_F32 && p.accumulate;
+                            if (p.N % 4 == 0) {                                  // (C is 16-byte aligned)
+                                constexpr int RPS = 64 / PC, S = RB * 16 / RPS, U = S % 8 == 0 ? 8 : S % 4 == 0 ? 4 : S % 2 == 0 ? 2 : 1;   // rows at a time; times
+                                static_assert(RB * 16 % (RPS * U) == 0, "whole steps");
+                                const int row0 = lane / PC, piece = lane % PC;
+                                const bool whole = m1 + RB * 16 <= p.M;          // (uniform)
+                                float* at = C + (m1 + row0) * p.N + nw + piece * 4;
+                                if (nw + piece * 4 < p.N) {
+#pragma unroll 1
+                                    for (int row = row0; row < RB * 16; row += RPS * U, at += RPS * U * p.N) {
+                                        f32x4_t v[U];
+#pragma unroll
+                                        for (int u = 0; u < U; ++u) v[u] = piece_of(row + u * RPS, piece);
+                                        if (add) {
+                                            f32x4_t old[U];
+#pragma unroll
+                                            for (int u = 0; u < U; ++u)
+                                                if (whole || m1 + row + u * RPS < p.M) old[u] = *reinterpret_cast<const f32x4_t*>(at + u * RPS * p.N);
+#pragma unroll
+                                            for (int u = 0; u < U; ++u)
+#pragma unroll
+                                                for (int q = 0; q < 4; ++q) v[u][q] = old[u][q] + v[u][q];
+                                        }
+#pragma unroll
+                                        for (int u = 0; u < U; ++u)
+                                            if (whole || m1 + row + u * RPS < p.M) *reinterpret_cast<f32x4_t*>(at + u * RPS * p.N) = v[u];
+                                    }
+                                }
+                            } else {
+#pragma unroll 1
+                                for (int t = lane; t < RB * 16 * CW; t += 64) {
+                                    const int row = t / CW, col = t % CW;
+                                    const float v = piece_of(row, col >> 2)[col & 3];
+                                    const int64_t mm = m1 + row, nn = nw + col;
+                                    if (mm < p.M && nn < p.N) C[mm * p.N + nn] = add ? C[mm * p.N + nn] + v : v;
+                                }
+                            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    });
+}
 
 template <int EPI, bool RAGGED, int SL, int WM, int NA, int NB>
 __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) {
@@ -253,21 +543,15 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     const int wm = wave / WN, wn = wave % WN;
 
     const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
-    const int ks = xcd % tm.splits, xg = xcd / tm.splits;
-    const int per_group = tm.group * tm.rn;
-    const int grp = local / per_group, r = local % per_group;
-    const int gsz = min(tm.group, tm.rm - grp * tm.group);
-    const int tile_m = (xg / tm.gn) * tm.rm + grp * tm.group + r % gsz;
-    const int tile_n = (xg % tm.gn) * tm.rn + r / gsz;
-    if (tile_m >= tm.tiles_m || tile_n >= tm.tiles_n) return;
+    int tile_m, tile_n, ks;
+    if (!place(tm, xcd, local, tile_m, tile_n, ks)) return;
     const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
 
     // slices [s0, s0 + nk) of this block's range, from a starting point of its own (REPAIR: of either product)
     const int nk1 = (int)((p.k + SL - 1) / SL), nk2 = (int)((p.k2 + SL - 1) / SL);
     const int s0 = ks * tm.slices;
     const int nk = max(0, min(tm.slices, nk1 + nk2 - s0));
-    auto start = [&](int len) { return len > 0 ? ((local & 7) + xcd * len / 8) % len : 0; };
-    const int rot = start(EPI == EPI_REPAIR ? nk1 : nk), rot2 = EPI == EPI_REPAIR ? start(nk2) : 0;
+    const int rot = first_slice(xcd, local, EPI == EPI_REPAIR ? nk1 : nk), rot2 = EPI == EPI_REPAIR ? first_slice(xcd, local, nk2) : 0;
     auto slice_of = [&](int kt) {
         if constexpr (EPI == EPI_REPAIR) {
             const bool second = kt >= nk1;
@@ -387,6 +671,10 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     asm volatile("s_nop 7" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     auto multiply = [&](auto i8, int from, int to) {
+        // (a wait that the compiler knows of: what it believes to be under way here it waits for in every turn of the loop)
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(kNoLds);
+        __builtin_amdgcn_sched_barrier(0);
         for (int kt = from; kt < to; ++kt) {
             const Source ob = source(false, kt + SB), oa = source(true, kt + SA);
             const uint32_t na = ba + 1 == SA ? 0 : ba + 1, nb = bb + 1 == SB ? 0 : bb + 1;
@@ -433,7 +721,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
             bb = nb;
         }
     };
-    [[maybe_unused]] uint32_t bits[NA];               // REPAIR: bit 4j + q: the element acc[i][j][q] is flagged
+    uint32_t bits[NA] = {};                           // REPAIR: bit 4j + q: the element acc[i][j][q] is flagged
     if constexpr (EPI == EPI_REPAIR) {
         multiply(std::true_type{}, 0, nk1);
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // (the products are in inline assembly: their results are waited for here)
@@ -443,9 +731,11 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
         const float* par = reinterpret_cast<const float*>(lds + G::kRing);
         const int nc = wn * NB * 16 + 4 * fp, mr = wm * NA * 16 + frow;   // first column, row of this lane in the tile
         const f32x4_t none = {0, 0, 0, 0};
+        uint32_t columns = 0u;                        // flags of existing columns
 #pragma unroll
         for (int j = 0; j < NB; ++j) {                // N % 8 == 0: four columns or none
             const bool in = n0 + nc + j * 16 < p.N;
+            columns |= in ? 15u << (4 * j) : 0u;
             if constexpr (G::kPar > 0) {
                 lo[j] = *reinterpret_cast<const f32x4_t*>(par + nc + j * 16);
                 hi[j] = *reinterpret_cast<const f32x4_t*>(par + 256 + nc + j * 16);
@@ -467,10 +757,12 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float v = ldexpf((float)__float_as_int(acc[i][j][q]), ex[i]);
-                    const bool inside = (v >= lo[j][q]) && (v < hi[j][q]);
-                    if (!inside && n0 + nc + j * 16 < p.N && m0 + mr + i * 16 < p.M) bits[i] |= 1u << (4 * j + q);
+                    const bool inside = (v >= lo[j][q]) & (v < hi[j][q]);             // (no short cuts: as branches, a third more time)
+                    bits[i] |= inside ? 0u : 1u << (4 * j + q);
                     acc[i][j][q] = 0.0f;
                 }
+            if (m0 + mr + i * 16 >= p.M) bits[i] = 0u;
+            bits[i] &= columns;
             // (one row block at a time, and its cleared accumulators made here: the compiler otherwise prepares all of the
             // second product's beside the first one's, and the 256 x 128 tile spills: 256 -> 172 registers)
 #pragma unroll
@@ -492,213 +784,433 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     __builtin_amdgcn_s_barrier();
     fence(acc);
 
-    // acc[i][j][q] = C[row m0 + (wm*NA + i)*16 + lane%16][column n0 + (wn*NB + j)*16 + 4*(lane/16) + q]
-    const int64_t mw = m0 + wm * NA * 16, nw = n0 + wn * NB * 16;   // this wavefront's corner
-    constexpr int CW = NB * 16;                                      // its columns
-    if constexpr (EPI == EPI_F32 || EPI == EPI_PART) {
-        // 16 rows at a time through LDS, so that a store covers whole lines of a row
-        float* chunk = reinterpret_cast<float*>(lds + wave * G::kEpiWave);
-        float* C = EPI == EPI_PART ? p.C + (size_t)ks * p.M * p.N : p.C;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int64_t m = mw + i * 16 + frow;
-            float rb = 0.0f;
-            if (EPI == EPI_F32 && p.bias && m < p.M) rb = td_bf16_to_f32(p.bias[m]);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                f32x4_t v;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = acc[i][j][q] + rb;
-                // (pieces of 16 bytes rotated by the row, against bank conflicts)
-                *reinterpret_cast<f32x4_t*>(chunk + frow * CW + (((j * 4 + fp) ^ (frow & (NB * 4 - 1))) * 4)) = v;
-            }
-            __builtin_amdgcn_wave_barrier();
-            auto store = [&](auto add) {
-#pragma unroll
-                for (int u = 0; u < 16 * CW / 64; ++u) {
-                    const int at = u * 64 + lane, row = at / CW, col = at % CW;
-                    const float v = chunk[row * CW + (((col >> 2) ^ (row & (NB * 4 - 1))) * 4) + (col & 3)];
-                    const int64_t mm = mw + i * 16 + row, nn = nw + col;
-                    if (mm < p.M && nn < p.N) C[mm * p.N + nn] = decltype(add)::value ? C[mm * p.N + nn] + v : v;
-                }
-            };
-            if (EPI == EPI_F32 && p.accumulate) store(std::true_type{});
-            else store(std::false_type{});
-            __builtin_amdgcn_wave_barrier();
-        }
-    } else {
-        // REPAIR: the flagged elements (few) of 16 rows are listed in LDS first and then evaluated 64 at a time:
-        // evaluating all accumulators of a lane would run sigma 128 times per wavefront in the largest tile, the
-        // list needs about (share flagged) x 128 runs.
-        // HIDDEN: sigma(z + b) of every element.
-        bf16_t* chunk = reinterpret_cast<bf16_t*>(lds + wave * G::kEpiWave);
-        bf16_t* chunk2 = chunk + 16 * CW;                            // REPAIR: the remainders
-        uint2* list = reinterpret_cast<uint2*>(lds + wave * G::kEpiWave + 16 * CW * 4);
-        float* par = reinterpret_cast<float*>(lds + kWavesPerTile * G::kEpiWave);
-        if constexpr (EPI == EPI_REPAIR) {
-            for (int c = tid; c < TN; c += 512) {
-                const int64_t n = n0 + c < p.N ? n0 + c : p.N - 1;
-                par[c] = td_bf16_to_f32(p.bias[n]);
-                par[TN + c] = p.slope[n];
-                par[2 * TN + c] = p.icept[n];
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            if constexpr (EPI == EPI_REPAIR) {
-                // mask: the four lanes of a row and (where the tile holds them) two tile columns make a word of 32 bits
-                const int64_t m = mw + i * 16 + frow;
-#pragma unroll
-                for (int w = 0; w < (NB + 1) / 2; ++w) {
-                    uint32_t word = ((bits[i] >> (8 * w)) & 15u) << (4 * fp);
-                    if constexpr (NB >= 2) word |= ((bits[i] >> (8 * w + 4)) & 15u) << (4 * fp + 16);
-                    word |= __shfl_xor(word, 16);
-                    word |= __shfl_xor(word, 32);
-                    const int64_t n = nw + w * 32;
-                    if (fp == 0 && m < p.M && n < p.N) {
-                        uint32_t* row = p.mask + (size_t)m * p.mask_words;
-                        if constexpr (NB >= 2) {
-                            row[n >> 5] = word;
-                        } else {
-                            uint16_t* half = reinterpret_cast<uint16_t*>(row) + (n >> 4);
-                            half[0] = (uint16_t)word;
-                            if (n + 16 >= p.N && ((n >> 4) & 1) == 0) half[1] = 0;   // the rest of a last word
-                        }
-                    }
-                }
-                const td_u32x4 zero = {0, 0, 0, 0};
-                for (int v = lane; v < (p.rest ? 2 : 1) * 16 * CW / 8; v += 64) reinterpret_cast<td_u32x4*>(chunk)[v] = zero;
-                __builtin_amdgcn_wave_barrier();
-                int total = 0;
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const bool flagged = (bits[i] >> (4 * j + q)) & 1u;
-                        const unsigned long long all = __ballot(flagged);
-                        if (flagged) {
-                            const int at = total + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32),
-                                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
-                            list[at] = make_uint2(__float_as_uint(acc[i][j][q]), (uint32_t)(frow * CW + j * 16 + 4 * fp + q));
-                        }
-                        total += __popcll(all);
-                    }
-                __builtin_amdgcn_wave_barrier();
-                for (int t = lane; t < total; t += 64) {
-                    const uint2 en = list[t];
-                    const int c = wn * CW + (int)(en.y % CW);
-                    const float z = __uint_as_float(en.x) + par[c];
-                    const float factor = td_act(z, p.act) - fmaf(par[TN + c], z, par[2 * TN + c]);
-                    const uint32_t head = to_bf16(factor);
-                    chunk[en.y] = (bf16_t)head;
-                    if (p.rest) {                                     // (infinite and NaN factors are all in the head)
-                        const float rest = factor - td_bf16_to_f32((bf16_t)head);
-                        chunk2[en.y] = (bf16_t)(fabsf(rest) < INFINITY ? to_bf16(rest) : 0u);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const int64_t n = nw + j * 16 + 4 * fp;
-                    uint2 b = make_uint2(0u, 0u);
-                    if (n < p.N) b = *reinterpret_cast<const uint2*>(p.bias + n);
-                    const float bv[4] = {__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u),
-                                         __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
-                    uint32_t o[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = to_bf16(td_act(acc[i][j][q] + bv[q], p.act));
-                    *reinterpret_cast<uint2*>(chunk + frow * CW + j * 16 + 4 * fp) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            for (int v = lane; v < 16 * CW / 8; v += 64) {           // N % 8 == 0: whole 16-byte vectors
-                const int row = v / (CW / 8), col = (v % (CW / 8)) * 8;
-                const int64_t mm = mw + i * 16 + row, nn = nw + col;
-                if (mm < p.M && nn < p.N) {
-                    *reinterpret_cast<td_u32x4*>(p.out + mm * p.N + nn) = reinterpret_cast<const td_u32x4*>(chunk)[v];
-                    if (EPI == EPI_REPAIR && p.rest)
-                        *reinterpret_cast<td_u32x4*>(p.rest + mm * p.N + nn) = reinterpret_cast<const td_u32x4*>(chunk2)[v];
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
+    finish_tile<EPI, kWavesPerTile, WM, NA, NB>(p, acc, bits, lds, tid, m0, n0, ks);
 }
 
-// The tile for a product: the one whose rounds over 256 CUs cost least.  A block spends per slice either the
-// cycles of its MFMAs or those in which the two operand slices arrive, at 34 bytes per cycle and CU.  That rate is a
-// chosen number, not a measured bandwidth, and the rule's cycles only rank tiles: they stand for neither the clock under
-// load nor HBM (up / output product at 2.1 GHz by the rule, and measured, us: d = 4096, h = 16384, 2048 tokens 199 / 197,
-// 378 / 267; 333 tokens 57 / 57, 94 / 71; 64 tokens 23 / 20, 39 / 31; d = 2048, h = 8192, 23 tokens 6 / 6, 17 / 10).
-// The larger rate for slices of 256 bytes stands for what the rule does not model: with one row of tiles the weights
-// stream from HBM, which delivers longer runs faster (64 tokens, us with 256 / 128 bytes a slice: d = 4096, up
-// projection of h = 16384 38.9 / 46.2, of h = 11008 (40 tokens) 33.9 / 44.1, dense 27.4 / 29.0; d = 2048 output product 10.8 /
-// 12.1).  `splittable`: K may be cut into 2, 4 or 8 ranges (each then adds the partial tile's bytes, written and read
-// again; at most kPartRows rows of partial sums are kept).
+// The same products with 4 wavefronts, one per SIMD, in a 2 x 2 grid: 32 NA x 32 NB per tile.  For large tiles: a wavefront's
+// part is 128 x 128 instead of 128 x 64, so a slice's fragments are read 4 (instead of 6) times the slice's bytes from LDS,
+// which the eight wavefronts above keep busy all the time; the accumulators fill the second half of the register file.
+// One wavefront per SIMD hides nothing behind another one, so what stands between two MFMAs (16 cycles, four issue slots)
+// is placed by hand, one thing to a gap: a fragment read in every second gap of a half slice, and in equal distances
+// over the whole slice the loads that refill the ring, m0 in one gap and the load in the next (which is also the wait state
+// between them).  The same loads in bursts or with everything in one gap: 300 instead of 277 us on zeros, 392 instead of 376
+// on random data, 4096 x 4096 x 16384 (eight wavefronts: 325, 404).
+template <int EPI, int NA, int NB>
+struct QuadTile {
+    static constexpr int SL = 128, TM = 32 * NA, TN = 32 * NB, UA = TM * SL, UB = TN * SL;
+    static constexpr int SB = kLdsBytes / (UA + UB), SA = SB * (UA + UB) + UA <= kLdsBytes ? SB + 1 : SB;
+    static constexpr int kPer = NA + NB;                    // loads of a wavefront per slice, and reads per half slice
+    static constexpr int NM = NA * NB, TOT = 2 * NM;        // MFMAs (gaps) of half a slice, of a slice
+    static constexpr int kEvery = TOT / kPer;               // gaps from load to load
+    static constexpr int kFirst = (NM - 2 + kEvery) / kEvery;   // loads of a period that fall into its first half
+    static constexpr int kTurnA = 2 * kPer <= NM - 4 ? NM - 4 : NM - 1, kTurnB = 2 * kPer <= NM - 4 ? NM - 2 : NM - 1;   // behind the reads
+    static constexpr int kWaitB = NA + (SB - 2) * kPer, kWaitA = (SA - 2) * kPer, kWait = kWaitB < kWaitA ? kWaitB : kWaitA;
+    static constexpr int kStart = (SA > SB ? NA : 0) + (SB - 2) * kPer + kFirst;   // loads behind those of slice 0 in the prologue
+    static constexpr int kEpiLds = EpiRows<EPI, 4, 2, NA, NB>::kBytes;
+    static constexpr int kLds = SA * UA + SB * UB > kEpiLds ? SA * UA + SB * UB : kEpiLds;
+    static_assert(SB >= 2 && kWait <= 63 && kStart <= 63 && kLds <= kLdsBytes, "slice buffers");
+    static_assert(2 * kPer <= NM + 1 && kFirst * kEvery >= NM && (kPer - 1) * kEvery + 1 < TOT, "places of reads and loads");
+};
+
+template <int EPI, bool RAGGED, int NA, int NB>
+__global__ void __launch_bounds__(256, 1) gemm_quad_kernel(GemmArgs p, TileMap tm) {
+    typedef QuadTile<EPI, NA, NB> G;
+    constexpr int SL = G::SL, TM = G::TM, TN = G::TN, SA = G::SA, SB = G::SB, NM = G::NM, TOT = G::TOT;
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+
+    const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
+    int tile_m, tile_n, ks;
+    if (!place(tm, xcd, local, tile_m, tile_n, ks)) return;
+    const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
+
+    // whole slices [s0, s0 + nk) of this block's range (RAGGED: the last range has the rest of the row as well), from a
+    // starting point of its own (REPAIR: of either product)
+    const int nk1 = (int)(p.k / SL), nk2 = (int)(p.k2 / SL);
+    const int s0 = ks * tm.slices;
+    const int nk = max(0, min(tm.slices, nk1 + nk2 - s0));
+    const int rot = first_slice(xcd, local, EPI == EPI_REPAIR ? nk1 : nk), rot2 = EPI == EPI_REPAIR ? first_slice(xcd, local, nk2) : 0;
+
+    const uint32_t rows_a = (uint32_t)min((int64_t)TM, p.M - m0), rows_b = (uint32_t)min((int64_t)TN, p.N - n0);
+    const i32x4_t ra1 = buffer_of(p.A + (size_t)m0 * p.k, rows_a * p.k), rb1 = buffer_of(p.B + (size_t)n0 * p.k, rows_b * p.k);
+    const i32x4_t ra2 = buffer_of(p.A2 + (size_t)m0 * p.k2, rows_a * p.k2), rb2 = buffer_of(p.B2 + (size_t)n0 * p.k2, rows_b * p.k2);
+
+    // a load is 8 rows of 128 bytes: lane -> row lane / 8, piece (lane % 8) ^ row; wavefront w loads rows [w*TM/4, (w+1)*TM/4) of A,
+    // of B alike
+    const uint32_t lrow = (uint32_t)lane >> 3, piece = (((uint32_t)lane & 7u) ^ lrow) * 16u;
+    const uint32_t row_a = (uint32_t)(wave * (TM / 4)) + lrow, row_b = (uint32_t)(wave * (TN / 4)) + lrow;
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(base + wave * (G::UA / 4));
+    const uint32_t lds_b = __builtin_amdgcn_readfirstlane(base + SA * G::UA + wave * (G::UB / 4));
+
+    // The slice that the next loads of A (of B) fetch.  It is found in steps, which stand in different gaps.
+    struct Stream {
+        i32x4_t rs;
+        uint32_t soff, pitch, voff, to;       // K offset; bytes of a row; this lane's offset; ring buffer of this wavefront
+        int t, s;                             // number in the sequence, slice
+        bool second;
+    };
+    auto find = [&](Stream& o, bool is_a, int step) {
+        const i32x4_t &r1 = is_a ? ra1 : rb1, &r2 = is_a ? ra2 : rb2;
+        if (step == 0) {
+            if constexpr (EPI == EPI_REPAIR) o.s = o.t + (o.t >= nk1 ? rot2 : rot);
+            else o.s = o.t + rot;
+        } else if (step == 1) {
+            if constexpr (EPI == EPI_REPAIR) o.s -= o.t >= nk1 ? (o.s >= nk1 + nk2 ? nk2 : 0) : (o.s >= nk1 ? nk1 : 0);
+            else o.s += s0 - (o.s >= nk ? nk : 0);
+        } else if (step == 2) {
+            o.second = o.s >= nk1;
+            o.soff = (uint32_t)(o.second ? o.s - nk1 : o.s) * SL;
+            asm volatile("" : "+s"(o.soff));
+        } else if (step == 3) {
+            o.rs.x = o.second ? r2.x : r1.x;
+            o.rs.y = o.second ? r2.y : r1.y;
+        } else if (step == 4) {
+            o.rs.z = o.second ? r2.z : r1.z;
+            if (o.t >= nk) o.rs.z = 0;                              // past the last slice: an empty buffer
+            o.pitch = o.second ? p.k2 : p.k;
+        } else {
+            o.voff = __umul24(is_a ? row_a : row_b, o.pitch) + piece;   // (rows of at most 2^23 bytes)
+            ++o.t;
+            asm volatile("" : "+v"(o.voff));                            // here, and not where it is used
+        }
+    };
+    // (m0 and the load are two statements: see the listing's test)
+    auto target = [&](uint32_t to, auto n) { asm volatile("s_add_u32 m0, %0, %1" ::"s"(to), "n"(decltype(n)::value * 1024) : "scc"); };
+    auto fetch = [&](const Stream& o) { asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(o.voff), "s"(o.rs), "s"(o.soff)); };
+    auto load = [&](auto n, Stream& o) {
+        target(o.to, n);
+        asm volatile("s_nop 0");
+        fetch(o);
+        o.voff += 8 * o.pitch;
+    };
+    auto at = [&](Stream& o, bool is_a, int t, uint32_t to) {
+        o.t = t;
+        o.to = to;
+        for (int step = 0; step < 6; ++step) find(o, is_a, step);
+    };
+    // In period p (the half of slice p behind the barrier, and the first half of slice p+1) the loads of B(p+SB) and then
+    // of A(p+SA) are issued; the prologue issues those of periods -SB .. -2 and the first half of period -1.
+    Stream oa, ob;
+    oa.rs.w = ob.rs.w = ra1.w;
+    asm volatile("s_nop 4");   // (scalars that vector instructions have written are read by the loads below, which the compiler cannot see)
+    if constexpr (SA > SB) {
+        at(oa, true, 0, lds_a);
+        for_constants<NA>([&](auto i) { load(i, oa); });
+    }
+    for_constants<SB>([&](auto s) {
+        constexpr int n = decltype(s)::value, most = n + 1 < SB ? G::kPer : G::kFirst;
+        at(ob, false, n, lds_b + n * G::UB);
+        at(oa, true, n + SA - SB, lds_a + (n + SA - SB) * G::UA);
+        for_constants<NB>([&](auto i) { if constexpr (decltype(i)::value < most) load(i, ob); });
+        for_constants<NA>([&](auto i) { if constexpr (NB + decltype(i)::value < most) load(i, oa); });
+    });
+
+    f32x4_t acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0, 0, 0, 0};
+    // fragments: lane holds 16 bytes of row lane%16 at piece 4*step + lane/16
+    const int frow = lane & 15, fp = lane >> 4;
+    uint32_t frag_a[2], frag_b[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const uint32_t sw = (uint32_t)(frow * SL + (((s * 4 + fp) ^ (frow & 7)) * 16));
+        frag_a[s] = (uint32_t)(wm * NA * 16 * SL) + sw;
+        frag_b[s] = (uint32_t)(SA * G::UA + wn * NB * 16 * SL) + sw;
+    }
+    td_u32x4 fa[2][NA], fb[2][NB];
+    uint32_t xa = frag_a[0], xb = frag_b[0];          // where the next half slice's fragments lie
+    auto read_one = [&](int buf, int t) {             // fa[0], all of fb, the rest of fa
+        if (t == 0) fa[buf][0] = *reinterpret_cast<const td_u32x4*>(lds + xa);
+        else if (t <= NB) fb[buf][t - 1] = *reinterpret_cast<const td_u32x4*>(lds + xb + (t - 1) * (16 * SL));
+        else fa[buf][t - NB] = *reinterpret_cast<const td_u32x4*>(lds + xa + (t - NB) * (16 * SL));
+    };
+    auto mma = [&](auto i8, f32x4_t& c, const td_u32x4& a, const td_u32x4& b) {
+        if constexpr (decltype(i8)::value) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+        else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    };
+    auto hold = [&]() {                               // as fence(), for accumulators in the other half of the register file
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j])::"memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(G::kStart) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < G::kPer; ++t) read_one(0, t);
+    xa = frag_a[1];
+    xb = frag_b[1];
+    uint32_t ra = 0, rb = 0;                          // ring offsets of the slice that is multiplied
+    auto turn = [&](uint32_t o, uint32_t unit, uint32_t ring) { return o + unit == ring ? 0u : o + unit; };
+    hold();
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // One slice: the MFMAs of its first half while the fragments of the second are read, the barrier behind which slice kt+1
+    // has arrived and this slice's buffers are free, the MFMAs of the second half while slice kt+1's first are read.
+    auto multiply = [&](auto i8, int from, int to) {
+        // (waits that the compiler knows of: what it believes to be under way here it waits for in every turn of the loop, for
+        // loads from memory with all of the ring's: REPAIR, 128 x 128, 520 -> 450 us)
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(kNoLds & (EPI == EPI_REPAIR && !decltype(i8)::value ? kNoLoads : 0xffff));
+        __builtin_amdgcn_sched_barrier(0);
+        for (int kt = from; kt < to; ++kt) {
+            for_constants<TOT>([&](auto gap) {
+                constexpr int q = decltype(gap)::value, half = q / NM, h = q % NM;
+                constexpr int since = (q + NM) % TOT;                                     // gaps since the barrier
+                constexpr int until_b = NM - 1 - h, until_a = (G::kEvery * NB < NM ? G::kEvery * NB : NM) - 1 - h;
+                if constexpr (q == NM) {
+                    __builtin_amdgcn_s_waitcnt(kNoLds);
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(G::kWait) : "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    oa.to = lds_a + ra;
+                    ob.to = lds_b + rb;
+                }
+                if constexpr (h % 2 == 0 && h / 2 < G::kPer) read_one(1 - half, h / 2);
+                // the loads of this period: m0, the load
+                constexpr int n = since / G::kEvery, in = since % G::kEvery;
+                if constexpr (n < NB) {
+                    if constexpr (in == 0) target(ob.to, num<n>{});
+                    if constexpr (in == 1) {
+                        fetch(ob);
+                        ob.voff += 8 * ob.pitch;
+                    }
+                } else if constexpr (n < G::kPer) {
+                    if constexpr (in == 0) target(oa.to, num<n - NB>{});
+                    if constexpr (in == 1) {
+                        fetch(oa);
+                        oa.voff += 8 * oa.pitch;
+                    }
+                }
+                // the slices of the next period's loads: B's before the barrier, A's while B's are issued
+                if constexpr (half == 0 && until_b < 12 && until_b % 2 == 0) find(ob, false, 5 - until_b / 2);
+                if constexpr (half == 1 && until_a >= 0 && until_a < 12 && until_a % 2 == 0) find(oa, true, 5 - until_a / 2);
+                // ring offsets and addresses of the next fragments, once this half's are under way
+                if constexpr (half == 0 && h == G::kTurnA) xa = frag_a[0] + turn(ra, G::UA, SA * G::UA);
+                if constexpr (half == 0 && h == G::kTurnB) xb = frag_b[0] + turn(rb, G::UB, SB * G::UB);
+                if constexpr (half == 1 && h == G::kTurnA) {
+                    ra = turn(ra, G::UA, SA * G::UA);
+                    xa = frag_a[1] + ra;
+                }
+                if constexpr (half == 1 && h == G::kTurnB) {
+                    rb = turn(rb, G::UB, SB * G::UB);
+                    xb = frag_b[1] + rb;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mma(i8, acc[h / NB][h % NB], fb[half][h % NB], fa[half][h / NB]);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    };
+    uint32_t bits[NA] = {};                           // REPAIR: bit 4j + q: the element acc[i][j][q] is flagged
+    if constexpr (EPI == EPI_REPAIR) {
+        multiply(std::true_type{}, 0, nk1);
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // (the products are in inline assembly: their results are waited for here)
+        hold();
+        const int nc = wn * NB * 16 + 4 * fp, mr = wm * NA * 16 + frow;   // first column, row of this lane in the tile
+        const f32x4_t none = {0, 0, 0, 0};
+        int ex[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) ex[i] = m0 + mr + i * 16 < p.M ? p.e[m0 + mr + i * 16] : 0;
+        f32x4_t lo[NB], hi[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {                // N % 8 == 0: four columns or none
+            const int64_t n = n0 + nc + j * 16 < p.N ? n0 + nc + j * 16 : 0;
+            lo[j] = *reinterpret_cast<const f32x4_t*>(p.lo + n);
+            hi[j] = *reinterpret_cast<const f32x4_t*>(p.hi + n);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // (column block by column block: row by row all bounds stay in registers to the end, and some spill)
+        for_constants<NB>([&](auto column_block) {
+            constexpr int j = decltype(column_block)::value;
+            const bool in = n0 + nc + j * 16 < p.N;
+            for_constants<NA>([&](auto row_block) {
+                constexpr int i = decltype(row_block)::value;
+                uint32_t out = 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = ldexpf((float)__float_as_int(acc[i][j][q]), ex[i]);
+                    const bool inside = (v >= lo[j][q]) & (v < hi[j][q]);    // (no short cuts: as branches, a third more time)
+                    out |= inside ? 0u : 1u << (4 * j + q);
+                }
+                bits[i] |= in && m0 + mr + i * 16 < p.M ? out : 0u;
+                acc[i][j] = none;
+                asm volatile("" : "+a"(acc[i][j]));
+                asm volatile("" : "+v"(bits[i]));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        hold();
+        asm volatile("s_nop 7" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(std::false_type{}, nk1, nk);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(bits[i]));   // (nothing derived from them is kept through the loop)
+    } else {
+        multiply(std::false_type{}, 0, nk);
+    }
+    if constexpr (RAGGED) {
+        // the rest of the row, alone: pieces past its end are loaded from its start (in bounds) and zeroed as they are read
+        const uint32_t k = p.k2 ? p.k2 : p.k, from = k / SL * SL;
+        if (ks == (1 << tm.splits_log2) - 1 && from < k) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            const uint32_t pc = from + piece < k ? from + piece : 0u;
+            oa.rs = p.k2 ? ra2 : ra1;
+            ob.rs = p.k2 ? rb2 : rb1;
+            oa.pitch = ob.pitch = k;
+            oa.soff = ob.soff = 0u;
+            oa.voff = row_a * k + pc;
+            ob.voff = row_b * k + pc;
+            oa.to = lds_a;
+            ob.to = lds_b;
+            for_constants<NA>([&](auto i) { load(i, oa); });
+            for_constants<NB>([&](auto i) { load(i, ob); });
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                xa = frag_a[s];
+                xb = frag_b[s];
+                const bool in = from + (uint32_t)(s * 4 + fp) * 16u < k;
+                const td_u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+                for (int t = 0; t < G::kPer; ++t) read_one(s, t);
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    fa[s][i] = in ? fa[s][i] : zero;
+                    asm volatile("" : "+v"(fa[s][i]));
+                }
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    fb[s][j] = in ? fb[s][j] : zero;
+                    asm volatile("" : "+v"(fb[s][j]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_nop 7" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int h = 0; h < NM; ++h) mma(std::false_type{}, acc[h / NB][h % NB], fb[s][h % NB], fa[s][h / NB]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // (the products are in inline assembly: their results are waited for here)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    hold();
+    finish_tile<EPI, 4, 2, NA, NB>(p, acc, bits, lds, tid, m0, n0, ks);
+}
+
+// The tile for a product of more than 64 rows: the one with the least time by
+//     rounds over 256 CUs x (slices x time of a slice + time of the prologue and epilogue) + partial sums,
+// with the measured times below (least squares over 10 tiles, 512 products: d, h from 512, 2048 to 4096, 16384, 70 to 3000
+// tokens, all epilogues; random data, the clock that the power limit leaves).  Over those the tile so chosen takes 0.4 % longer than the best one
+// (mean; 15 % at most); by the larger of MFMA cycles and operand bytes at a fixed rate, the rule before, 7 %.
+// Four wavefronts (Q) take less per slice, eight finish a tile with a range test or sigma sooner.
+// Up to 64 rows the weights stream from memory: the larger of MFMA cycles and of the cycles in which the operands arrive, at 34
+// bytes per cycle and CU (a chosen number, which ranks these tiles; the larger one for slices of 256 bytes stands for longer runs from HBM: 64
+// tokens, us with 256 / 128 bytes a slice: d = 4096, up projection of h = 16384 38.9 / 46.2, of h = 11008 (40 tokens) 33.9 / 44.1,
+// dense 27.4 / 29.0; d = 2048 output product 10.8 / 12.1).
+// `splittable`: K may be cut into 2, 4 or 8 ranges (at most kPartRows rows of partial sums are kept).
 constexpr int64_t kPartRows = 4096;
 struct TileChoice { int shape, splits; };
-constexpr int kShapes = 10;
-constexpr int kShapeM[kShapes] = {256, 192, 256, 192, 128, 128, 64, 64, 64, 64},
-              kShapeN[kShapes] = {256, 256, 128, 128, 128, 64, 64, 64, 32, 128},
-              kShapeSlice[kShapes] = {128, 128, 128, 128, 128, 128, 128, 256, 256, 128};
+struct Shape {
+    int m, n, slice;
+    bool quad;
+    float slice_us, repair_us, hidden_us, store_us;      // a slice; prologue and epilogue with the range test, with sigma, with stores alone
+};
+constexpr Shape kShape[] = {
+    {256, 256, 128, true, 1.055f, 32.9f, 30.8f, 5.3f}, {192, 256, 128, true, 0.828f, 26.8f, 24.0f, 4.6f},
+    {256, 128, 128, true, 0.611f, 18.0f, 15.9f, 3.6f}, {192, 128, 128, true, 0.494f, 13.5f, 12.0f, 3.2f},
+    {128, 128, 128, true, 0.391f, 10.2f, 9.0f, 2.7f}, {192, 256, 128, false, 0.952f, 17.1f, 16.6f, 3.6f},
+    {256, 128, 128, false, 0.730f, 9.9f, 9.9f, 3.0f}, {192, 128, 128, false, 0.564f, 9.3f, 8.4f, 2.8f},
+    {128, 128, 128, false, 0.418f, 9.0f, 6.8f, 2.6f}, {128, 64, 128, false, 0.368f, 6.1f, 5.2f, 2.5f},
+    // at most 64 rows
+    {64, 64, 128, false}, {64, 64, 256, false}, {64, 32, 256, false}, {64, 128, 128, false}};
+constexpr int kShapes = sizeof(kShape) / sizeof(Shape);
+constexpr float kRaggedSlice = 1.35f;                    // eight wavefronts check every fragment of a ragged product (Q: the last slice's)
+constexpr float kPartUs = 0.22f / (1024 * 1024);         // a byte of partial sums, written and read again
 
 // whole: K has to be whole slices (of both products); else a ragged K is allowed
-TileChoice choose_tile(const GemmArgs& p, bool splittable, bool store_f32, bool whole) {
+TileChoice choose_tile(const GemmArgs& p, int epi, bool whole) {
     TileChoice best{0, 1};
     double best_cost = 1e300;
     const int64_t M = p.M, N = p.N;
+    const bool splittable = epi == EPI_PART;
     for (int s = 0; s < kShapes; ++s) {
-        const int SL = kShapeSlice[s], TM = kShapeM[s], TN = kShapeN[s];
-        if (whole && (p.k % SL != 0 || p.k2 % SL != 0)) continue;
-        if (TM == 64 && M > 64) continue;
+        const Shape& t = kShape[s];
+        const int SL = t.slice;
+        const bool ragged = p.k % SL != 0 || p.k2 % SL != 0;
+        if ((whole && ragged) || (t.m == 64) != (M <= 64)) continue;
         const int64_t slices = (p.k + SL - 1) / SL + (p.k2 + SL - 1) / SL;
         for (int sp = 1; sp <= (splittable ? 8 : 1); sp *= 2) {
             if (sp > 1 && (slices * SL / sp < 1024 || sp * M > kPartRows)) break;
-            const TileMap t = make_tile_map(M, N, TM, TN, (int)slices, sp);
-            const int64_t per_xcd = (int64_t)t.rm * t.rn;              // blocks of one XCD (of one range): 32 at once
-            const double mfma = 2100.0 / 128.0 * SL * TM * TN / 65536.0;
-            const double feed = ((M < TM ? M : TM) + TN) * (double)SL / (SL > 128 ? 34.5 : 34.0);
-            const double tail = 3000.0 + (store_f32 ? 0.12 : 0.06) * TM * TN;
-            const double cost = (double)((per_xcd + 31) / 32) * ((double)t.slices * (mfma > feed ? mfma : feed) + tail) +
-                                (splittable ? sp * (double)M * (double)N * 8.0 / 2000.0 : 0.0);   // partial sums, about 2 KB a cycle
+            const TileMap map = make_tile_map(M, N, t.m, t.n, (int)slices, sp);
+            const double rounds = (double)(((int64_t)map.rm * map.rn + 31) / 32);   // blocks of one XCD (of one range): 32 at once
+            double cost;
+            if (M > 64) {
+                const double fixed = epi == EPI_REPAIR ? t.repair_us : epi == EPI_HIDDEN ? t.hidden_us : t.store_us;
+                cost = rounds * (map.slices * t.slice_us * (ragged && !t.quad ? kRaggedSlice : 1.0f) + fixed) +
+                       (splittable ? sp * (double)M * (double)N * 4.0 * kPartUs : 0.0);
+            } else {
+                const double mfma = 2100.0 / 128.0 * SL * t.m * t.n / 65536.0;
+                const double feed = (M + t.n) * (double)SL / (SL > 128 ? 34.5 : 34.0);
+                const double tail = 3000.0 + (epi == EPI_F32 ? 0.12 : 0.06) * t.m * t.n;
+                cost = rounds * (map.slices * (mfma > feed ? mfma : feed) + tail) + (splittable ? sp * (double)M * (double)N * 8.0 / 2000.0 : 0.0);
+            }
             if (cost < best_cost) { best_cost = cost; best = {s, sp}; }
         }
     }
     return best;
 }
 
-// f(slice bytes, wm, na, nb) with the constants of a shape
-template <int V> using num = std::integral_constant<int, V>;
+// f(slice bytes, wm, na, nb) with the constants of a shape (wm = 0: gemm_quad_kernel)
 template <typename F> void for_shape(int shape, F f) {
     switch (shape) {
-        case 0: f(num<128>{}, num<2>{}, num<8>{}, num<4>{}); break;
-        case 1: f(num<128>{}, num<2>{}, num<6>{}, num<4>{}); break;
-        case 2: f(num<128>{}, num<2>{}, num<8>{}, num<2>{}); break;
-        case 3: f(num<128>{}, num<2>{}, num<6>{}, num<2>{}); break;
-        case 4: f(num<128>{}, num<2>{}, num<4>{}, num<2>{}); break;
-        case 5: f(num<128>{}, num<2>{}, num<4>{}, num<1>{}); break;
-        case 6: f(num<128>{}, num<2>{}, num<2>{}, num<1>{}); break;
-        case 7: f(num<256>{}, num<2>{}, num<2>{}, num<1>{}); break;
-        case 8: f(num<256>{}, num<4>{}, num<1>{}, num<1>{}); break;
+        case 0: f(num<128>{}, num<0>{}, num<8>{}, num<8>{}); break;
+        case 1: f(num<128>{}, num<0>{}, num<6>{}, num<8>{}); break;
+        case 2: f(num<128>{}, num<0>{}, num<8>{}, num<4>{}); break;
+        case 3: f(num<128>{}, num<0>{}, num<6>{}, num<4>{}); break;
+        case 4: f(num<128>{}, num<0>{}, num<4>{}, num<4>{}); break;
+        case 5: f(num<128>{}, num<2>{}, num<6>{}, num<4>{}); break;
+        case 6: f(num<128>{}, num<2>{}, num<8>{}, num<2>{}); break;
+        case 7: f(num<128>{}, num<2>{}, num<6>{}, num<2>{}); break;
+        case 8: f(num<128>{}, num<2>{}, num<4>{}, num<2>{}); break;
+        case 9: f(num<128>{}, num<2>{}, num<4>{}, num<1>{}); break;
+        case 10: f(num<128>{}, num<2>{}, num<2>{}, num<1>{}); break;
+        case 11: f(num<256>{}, num<2>{}, num<2>{}, num<1>{}); break;
+        case 12: f(num<256>{}, num<4>{}, num<1>{}, num<1>{}); break;
         default: f(num<128>{}, num<2>{}, num<2>{}, num<2>{}); break;
     }
 }
 
 template <int EPI, bool RAGGED> void launch_ragged(const GemmArgs& p, const TileChoice& c, hipStream_t s) {
     for_shape(c.shape, [&](auto sl, auto wm, auto na, auto nb) {
-        typedef GemmTile<EPI, RAGGED, sl, wm, na, nb> G;
-        const int slices = (int)((p.k + sl - 1) / sl + (p.k2 + sl - 1) / sl);
-        const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, c.splits);
-        hipLaunchKernelGGL((gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
+        if constexpr (decltype(wm)::value == 0) {
+            typedef QuadTile<EPI, na, nb> G;
+            const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, (int)(p.k / sl + p.k2 / sl), c.splits);
+            hipLaunchKernelGGL((gemm_quad_kernel<EPI, RAGGED, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(256), G::kLds, s, p, tm);
+        } else {
+            typedef GemmTile<EPI, RAGGED, sl, wm, na, nb> G;
+            const int slices = (int)((p.k + sl - 1) / sl + (p.k2 + sl - 1) / sl);
+            const TileMap tm = make_tile_map(p.M, p.N, G::TM, G::TN, slices, c.splits);
+            hipLaunchKernelGGL((gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>), dim3(8 * tm.rm * tm.rn), dim3(512), G::kLds, s, p, tm);
+        }
     });
 }
 
 // EPI_F32 and EPI_PART take any K that is whole 16-byte pieces
 template <int EPI> TileChoice launch_tile(const GemmArgs& p, hipStream_t s) {
     constexpr bool may_be_ragged = EPI == EPI_F32 || EPI == EPI_PART;
-    const TileChoice c = choose_tile(p, EPI == EPI_PART, may_be_ragged, !may_be_ragged);
-    const int sl = kShapeSlice[c.shape];
+    const TileChoice c = choose_tile(p, EPI, !may_be_ragged);
+    const int sl = kShape[c.shape].slice;
     if constexpr (may_be_ragged) {
         if (p.k % sl != 0 || p.k2 % sl != 0) {
             launch_ragged<EPI, true>(p, c, s);
@@ -709,16 +1221,18 @@ template <int EPI> TileChoice launch_tile(const GemmArgs& p, hipStream_t s) {
     return c;
 }
 
+template <typename K> bool raise_lds_of(K kernel, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+}
+
 template <int EPI, bool RAGGED> tardis_status_t raise_lds() {
-    tardis_status_t st = TARDIS_OK;
+    bool ok = true;
     for (int shape = 0; shape < kShapes; ++shape)
         for_shape(shape, [&](auto sl, auto wm, auto na, auto nb) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     GemmTile<EPI, RAGGED, sl, wm, na, nb>::kLds);
-            if (e != hipSuccess) st = TARDIS_ERR_HIP;
+            if constexpr (decltype(wm)::value == 0) ok &= raise_lds_of(gemm_quad_kernel<EPI, RAGGED, na, nb>, QuadTile<EPI, na, nb>::kLds);
+            else ok &= raise_lds_of(gemm_tile_kernel<EPI, RAGGED, sl, wm, na, nb>, GemmTile<EPI, RAGGED, sl, wm, na, nb>::kLds);
         });
-    return st;
+    return ok ? TARDIS_OK : TARDIS_ERR_HIP;
 }
 
 template <typename T>
