@@ -1,5 +1,7 @@
 // Offline steps: range selection and line fit (calibrate), constant folding,
 // predictor construction, and the layout copies the online path needs.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -416,6 +418,53 @@ __device__ __forceinline__ void sort_lds(float* vals, int npad) {
     }
 }
 
+// sigma in fp64 without branches, for the calibration's samples.  GELU = z Phi(z) from Phi(-|z|) = erfc(x) / 2, x = |z| / sqrt(2):
+// (1 + 2 x) exp(x^2) erfc(x) is a polynomial in (x - K) / (x + K) (the substitution of Shepherd and Laframboise, Math. Comp. 36,
+// 1981; K = 3.75, degree 20, the coefficients interpolate it at 400 Chebyshev points).  Against the library's erf (two
+// branches, of which a wavefront takes both): root mean square error 8.5e-17 instead of 1.6e-16 for z from -8 to 8, largest 8.9e-16 on either side.
+__device__ __forceinline__ double rcp_f64(double a) {              // a: a normal number
+    double r = __builtin_amdgcn_rcp(a);
+    r = fma(fma(-a, r, 1.0), r, r);
+    return fma(fma(-a, r, 1.0), r, r);
+}
+__device__ __forceinline__ double exp_f64(double y) {              // |y| <= 2^20: Taylor's series, 13 terms, on |r| <= log(2) / 2
+    const double n = rint(y * 1.4426950408889634074);
+    const double r = fma(n, -1.90821492927058770002e-10, fma(n, -6.93147180369123816490e-01, y));
+    constexpr double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
+                              1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
+    double s = c[12];
+#pragma unroll
+    for (int k = 11; k >= 0; --k) s = fma(s, r, c[k]);
+    return ldexp(s, (int)n);
+}
+template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
+    if constexpr (ACT == TARDIS_ACT_GELU_ERF) {
+        constexpr double K = 3.75;
+        constexpr double c[21] = {
+            1.2375126308378264, -0.14024059858550675, 0.0035854154857959016,
+            0.08227673848715551, -0.10880393015501522, 0.09230432122566992,
+            -0.05869339838179839, 0.028362276763635674, -0.009746581233908157,
+            0.001755629481119746, 0.00029372158155062665, -0.0002901662170030672,
+            5.162565962208987e-05, 2.2409881005582833e-05, -1.1399206978826016e-05,
+            -1.0082073330153207e-06, 1.6955385768824271e-06, -2.78242458762179e-08,
+            -2.1408381400078725e-07, 8.543261174054351e-09, 1.7505899450043215e-08};
+        const double x = fmin(fabs(z) * 0.70710678118654752440, 40.0);     // (erfc(40) is 0, and infinities stay what they were)
+        const double p = x + K, w = fma(2.0, x, 1.0), r = rcp_f64(p * w);
+        const double t = (x - K) * (w * r);
+        double s = c[20];
+#pragma unroll
+        for (int k = 19; k >= 0; --k) s = fma(s, t, c[k]);
+        const double half = 0.5 * s * (p * r) * exp_f64(-x * x);
+        return z * (z > 0.0 ? 1.0 - half : half);
+    } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
+        // (1 + tanh v) / 2 = 1 / (1 + exp(-2 v)); v beyond 350 is 350 (exp does not overflow, and 1e-304 is nothing to 1)
+        const double v = 0.79788456080286535588 * (z + 0.044715 * z * z * z);
+        return z * rcp_f64(1.0 + exp_f64(-2.0 * fmin(fmax(v, -350.0), 350.0)));
+    } else {
+        return td_act_f64(z, ACT);
+    }
+}
+
 // least-squares line of sigma(z) on z over the samples with lo32 <= z < hi32, and the four outputs
 __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo32, float hi32, int act, double* red,
                                               int64_t j, float* lo, float* hi, float* a, float* c) {
@@ -470,9 +519,10 @@ __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo
 // equal cells between the smallest and the largest sample finds the cells that hold them, and the few
 // samples of those cells are ranked by counting.  (A neuron whose samples crowd into one cell - an outlier
 // stretches the histogram, or most samples are equal - or that are not all finite falls back to the sort in LDS.)  The fit takes
-// sigma of every sample once, in fp64, and keeps it in registers for both of its passes.
-// What bounds it: fp64 sigma.  16384 neurons x 4096 samples: 1500 -> 430 us against a full bitonic sort in LDS
-// with sigma taken twice.
+// sigma of every sample once, in fp64.
+// What bounds it: vector instructions, about half of them for sigma (without it 59 of 107 us).  4096 neurons x 4096 samples:
+// 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 91 us with the sigma
+// above and one pass.  (A full bitonic sort in LDS and sigma taken twice: 375.)
 //
 // A sample closer to the end of a range than fp32 can tell (both are fp32 here) would count as inside or
 // outside by luck of rounding.  For those (a few of 16384 neurons) the pre-activations of the two samples
@@ -695,61 +745,59 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
     }
     const float lo32 = end[0], hi32 = end[1];
 
-    // least-squares line of sigma(z) on z over the samples with lo32 <= z < hi32
-    double g[NPT];
-    double s[3] = {0.0, 0.0, 0.0};                   // count, sum z, sum sigma
+    // least-squares line of sigma(z) on z over the samples with lo32 <= z < hi32, in one pass: sums of dz = z - pivot, of
+    // sigma and of their products.  The pivot is a sample in the range (if there is one), so equal samples have dz = 0
+    // exactly; what the subtractions of the sums lose in fp64 is far below what fp32 resolves of z.
+    const float pivot32 = stat[0] >= lo32 ? stat[0] : stat[1];
+    const double pivot = (double)pivot32;
+    double s[3] = {0.0, 0.0, 0.0}, sq[3] = {0.0, 0.0, 0.0};          // count, sum dz, sum sigma; sum dz^2, sum dz sigma
+    int inside = 0;
+    auto sums = [&](auto act_constant) {
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-        g[k] = 0.0;
-        if (k * T + tid < n && v[k] >= lo32 && v[k] < hi32) {
-            g[k] = td_act_f64((double)v[k], act);
-            s[0] += 1.0;
-            s[1] += (double)v[k];
-            s[2] += g[k];
+        for (int k = 0; k < NPT; ++k) {
+            const bool in = (k * T + tid < n) & (v[k] >= lo32) & (v[k] < hi32);
+            const double g = act_flat_f64<decltype(act_constant)::value>((double)(in ? v[k] : 0.0f));   // (sigma(0) = 0)
+            const double dz = (double)(in ? v[k] : pivot32) - pivot;
+            inside += in ? 1 : 0;
+            s[1] += dz;
+            s[2] += g;
+            sq[0] = fma(dz, dz, sq[0]);
+            sq[1] = fma(dz, g, sq[1]);
         }
-    }
-    const double ze[2] = {(double)stat[0], (double)stat[2]};
+    };
+    if (act == TARDIS_ACT_GELU_ERF) sums(std::integral_constant<int, TARDIS_ACT_GELU_ERF>{});
+    else if (act == TARDIS_ACT_GELU_TANH) sums(std::integral_constant<int, TARDIS_ACT_GELU_TANH>{});
+    else if (act == TARDIS_ACT_RELU) sums(std::integral_constant<int, TARDIS_ACT_RELU>{});
+    else sums(std::integral_constant<int, TARDIS_ACT_IDENTITY>{});
+    s[0] = (double)inside;
     if (tid == 0) {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             if (extra[q] != 0.0) {
+                const double ze = (double)stat[2 * q], dz = ze - pivot, g = td_act_f64(ze, act);
                 s[0] += extra[q];
-                s[1] += extra[q] * ze[q];
-                s[2] += extra[q] * td_act_f64(ze[q], act);
+                s[1] += extra[q] * dz;
+                s[2] += extra[q] * g;
+                sq[0] += extra[q] * dz * dz;
+                sq[1] += extra[q] * dz * g;
             }
     }
     total3(s);
+    total3(sq);
     float aj, cj;
     if (s[0] < 0.5) {
         aj = 0.0f;
         cj = (float)td_act_f64((double)lo32, act);
     } else {
-        const double zbar = s[1] / s[0], gbar = s[2] / s[0];
-        double vc[3] = {0.0, 0.0, 0.0};              // variance, covariance
-#pragma unroll
-        for (int k = 0; k < NPT; ++k)
-            if (k * T + tid < n && v[k] >= lo32 && v[k] < hi32) {
-                const double dz = (double)v[k] - zbar;
-                vc[0] += dz * dz;
-                vc[1] += dz * (g[k] - gbar);
-            }
-        if (tid == 0) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (extra[q] != 0.0) {
-                    const double dz = ze[q] - zbar;
-                    vc[0] += extra[q] * dz * dz;
-                    vc[1] += extra[q] * dz * (td_act_f64(ze[q], act) - gbar);
-                }
-        }
-        total3(vc);
-        if (s[0] < 1.5 || !(vc[0] > 0.0)) {
+        const double dbar = s[1] / s[0], gbar = s[2] / s[0];
+        const double var = sq[0] - s[1] * dbar, cov = sq[1] - s[1] * gbar;
+        if (s[0] < 1.5 || !(var > 0.0)) {
             aj = 0.0f;
             cj = (float)gbar;
         } else {
-            const double slope = vc[1] / vc[0];
+            const double slope = cov / var;
             aj = (float)slope;
-            cj = (float)(gbar - slope * zbar);
+            cj = (float)(gbar - slope * (pivot + dbar));
         }
     }
     if (tid == 0) {

@@ -1,0 +1,40 @@
+"""The calibration's one-pass fit: lines through samples far from zero and close together, equal samples, few samples,
+every activation, one to thirty-two samples a thread."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tardis_oracle as O
+from paper_2501_10054_amd import tardis as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh", "relu", "identity"])
+@pytest.mark.parametrize("n", [2, 3, 64, 1025, 4096, 9000])
+def test_lines_far_from_zero_and_equal_samples(act, n):
+    """Rows 0-7: equal samples (zero weights, biases -8 to 40): slope 0, the intercept sigma of the bias.  Rows 8-39: means
+    of -6 to 6 and deviations down to a hundredth of them.  The pre-activations are fp32 sums of 16 products and a bias: off
+    by at most 2^-21 of |z| + 1; a line through samples of deviation s moves by no more than 4 times that over s."""
+    rng = np.random.default_rng(n)
+    h, d = 40, 16
+    W1 = rng.normal(0, 1, (h, d)).astype(np.float32) * np.r_[np.zeros(8), np.geomspace(0.01, 0.5, 32)][:, None].astype(np.float32)
+    b1 = np.r_[np.linspace(-8, 40, 8), np.tile(np.linspace(-6, 6, 8), 4)].astype(np.float32)
+    X = rng.normal(0, 1, (n, d)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ffn = T.FFN(dev(W1), torch.zeros(d, h, device="cuda"), dev(b1), None, act)
+    lo, hi, a, c = (t.cpu().numpy().astype(np.float64) for t in T.tardis_calibrate(ffn, dev(X), 0.9))
+    olo, ohi, oa, oc = O.calibrate(W1, b1, X, 0.9, act)
+    z = X.astype(np.float64) @ W1.astype(np.float64).T + b1
+    off = 2.0 ** -21 * (np.abs(z).max(0) + 1)
+    assert (np.abs(lo - olo) <= off).all() and (np.abs(hi - ohi) <= off).all()
+    assert (a[:8] == 0).all() and np.abs(c[:8] - O.act(b1[:8].astype(np.float64), act)).max() <= 2.0 ** -23 * 40
+    inside = (z >= olo) & (z < ohi)
+    for j in range(8, h):
+        zi = z[inside[:, j], j]
+        near = (np.abs(z[:, j] - olo[j]) <= off[j]) | (np.abs(z[:, j] - ohi[j]) <= off[j])
+        if len(zi) < 3 or near.any():               # (a sample may fall on either side of an end)
+            continue
+        tol = 4 * off[j] / zi.std() + 2.0 ** -22
+        assert abs(a[j] - oa[j]) <= tol, (j, a[j], oa[j], tol)
+        assert abs(c[j] - oc[j]) <= tol * (np.abs(zi).max() + 1), (j, c[j], oc[j])
