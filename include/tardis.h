@@ -352,8 +352,11 @@ tardis_status_t tardis_get_last_union(tardis_handle_t L, int64_t n, uint32_t* un
 tardis_status_t tardis_get_handover(tardis_handle_t L, int64_t n, void* out, void* stream);
 
 /* Frees everything the handle owns.  The caller must have synchronised every
- * stream that used it.  NULL is accepted; a pointer that is not a live handle
- * (destroyed before, or never made here) returns TARDIS_ERR_STATE. */
+ * stream that used it.  The device memory of up to four destroyed layers, 1 GiB
+ * in all, stays with the library for the next tardis_fold of that size; it is
+ * returned to the device when an allocation of a fold fails.  NULL is accepted; a
+ * pointer that is not a live handle (destroyed before, or never made here)
+ * returns TARDIS_ERR_STATE. */
 tardis_status_t tardis_destroy(tardis_handle_t L);
 
 /* Static, NUL-terminated description of a status code (host). */

@@ -75,6 +75,8 @@ struct tardis_layer_s {
     const void* b2;  // d or null
     // owned: `memory` is the one allocation everything below lies in
     void* memory;
+    size_t memory_bytes;
+    int device;    // where it lies
     void* W2T;     // h x d, neuron-major copy of W2
     void* W2;      // d x h, copy of W2 as given (dense baseline)
     void* Wp;      // d x d folded matrix
@@ -206,6 +208,8 @@ __device__ __forceinline__ double td_act_f64(double z, int act) {
 // ---------------------------------------------------------------- internal launchers
 // (each validates nothing: the C-ABI layer in api.cpp has already done so)
 
+// api.hip: memory of destroyed layers that is kept for the next one goes back to the device; false: there was none
+bool td_give_back_memory();
 // offline.hip
 tardis_status_t td_transpose(const void* src, void* dst, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s);
 // bits = 8: Q (required).  bits = 4, 3, 2 (codes up to 7, 3, 1 in 4-bit slots): M4 (required), Q

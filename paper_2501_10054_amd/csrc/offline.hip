@@ -1200,6 +1200,7 @@ struct DevBuf {  // frees on scope exit
     }
     tardis_status_t alloc(size_t bytes) {
         hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
+        if (e == hipErrorOutOfMemory && td_give_back_memory()) e = hipMalloc(&p, bytes ? bytes : 16);
         if (e != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
