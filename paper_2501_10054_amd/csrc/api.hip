@@ -269,8 +269,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     TD_HIP(hipMemcpyAsync(L->c, c, (size_t)h * 4, hipMemcpyDeviceToDevice, s));
     // (the fold first: the two copies of W2 hold its operands until they are filled)
     TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, L->W2T, L->W2, s));
-    TD_HIP(hipMemcpyAsync(L->W2, desc->W2, (size_t)h * d * es, hipMemcpyDeviceToDevice, s));
-    TD_TRY(td_transpose(desc->W2, L->W2T, d, h, desc->dtype, s));
+    TD_TRY(td_transpose(desc->W2, L->W2T, L->W2, d, h, desc->dtype, s));
     TD_TRY(td_build_sketch(desc->W1, desc->b1, lo, hi, h, d, desc->dtype, L->sketch_bits, L->margin, L->Q, L->Q4, L->M4, L->tlo,
                            L->thi, s));
     L->stack_fused = env_int("TARDIS_STACK_FUSED", 0, 0, 2);   // 2: refuse a one-token stack the single launch cannot serve

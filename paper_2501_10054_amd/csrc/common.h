@@ -211,7 +211,8 @@ __device__ __forceinline__ double td_act_f64(double z, int act) {
 // api.hip: memory of destroyed layers that is kept for the next one goes back to the device; false: there was none
 bool td_give_back_memory();
 // offline.hip
-tardis_status_t td_transpose(const void* src, void* dst, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s);
+// dst = src transposed, copy = src
+tardis_status_t td_transpose(const void* src, void* dst, void* copy, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s);
 // bits = 8: Q (required).  bits = 4, 3, 2 (codes up to 7, 3, 1 in 4-bit slots): M4 (required), Q
 // (effective one-byte codes, optional) and Q4 (packed, optional, needs d % 32 == 0).  margin: fraction
 // of every range's width taken off at either end for the predictor's test.
@@ -238,7 +239,8 @@ tardis_status_t td_assign_thresholds(const float* err, int64_t n, float t, float
 tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s);
 // gemm.hip:  C[m][n] (+)= sum_k A[m][k] * B[n][k] (+ row_bias[m]); C fp32, ldc = N
 tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
-                           int accumulate, const void* row_bias, hipStream_t s);
+                           int accumulate, const void* row_bias, hipStream_t s, void* out16 = nullptr);
+bool td_gemm_on_matrix_cores(const void* A, const void* B, int64_t M, int64_t N, int64_t K, int32_t dtype);
 bool td_gemm_refuses_rows(int64_t M);
 // the products of calls with many tokens, each with the step that follows it (see gemm.hip)
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,

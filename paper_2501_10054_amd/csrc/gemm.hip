@@ -194,7 +194,7 @@ struct GemmArgs {
     float* C;                      // F32: M x N; PART: [split][M][N]
     int accumulate;                // F32: add to C
     const bf16_t* bias;            // F32: per row of C (or null); HIDDEN, REPAIR: per column
-    bf16_t* out;                   // HIDDEN, REPAIR: M x N
+    bf16_t* out;                   // HIDDEN, REPAIR: M x N; F32, accumulate: the sum goes here, rounded, and C stays (or null)
     bf16_t* rest;                  // REPAIR: what the rounding of `out` to bf16 left, M x N (or null)
     const float *lo, *hi;          // REPAIR: bounds of the range test per column,
     const float *slope, *icept;    //   line per column,
@@ -493,6 +493,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
         } else {
             float* C = EPI == EPI_PART ? p.C + (size_t)ks * p.M * p.N : p.C;
             const bool add = EPI == EPI_F32 && p.accumulate;
+            bf16_t* rounded = add ? p.out : nullptr;
                             if (p.N % 4 == 0) {                                  // (C is 16-byte aligned)
                                 constexpr int RPS = 64 / PC, S = RB * 16 / RPS, U = S % 8 == 0 ? 8 : S % 4 == 0 ? 4 : S % 2 == 0 ? 2 : 1;   // rows at a time; times
                                 static_assert(RB * 16 % (RPS * U) == 0, "whole steps");
@@ -517,7 +518,10 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
                                         }
 #pragma unroll
                                         for (int u = 0; u < U; ++u)
-                                            if (whole || m1 + row + u * RPS < p.M) *reinterpret_cast<f32x4_t*>(at + u * RPS * p.N) = v[u];
+                                            if (whole || m1 + row + u * RPS < p.M) {
+                                                if (rounded) *reinterpret_cast<uint2*>(rounded + (at - C) + u * RPS * p.N) = make_uint2(to_bf16x2(v[u][0], v[u][1]), to_bf16x2(v[u][2], v[u][3]));
+                                                else *reinterpret_cast<f32x4_t*>(at + u * RPS * p.N) = v[u];
+                                            }
                                     }
                                 }
                             } else {
@@ -526,7 +530,10 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
                                     const int row = t / CW, col = t % CW;
                                     const float v = piece_of(row, col >> 2)[col & 3];
                                     const int64_t mm = m1 + row, nn = nw + col;
-                                    if (mm < p.M && nn < p.N) C[mm * p.N + nn] = add ? C[mm * p.N + nn] + v : v;
+                                    if (mm >= p.M || nn >= p.N) continue;
+                                    const float sum = add ? C[mm * p.N + nn] + v : v;
+                                    if (rounded) rounded[mm * p.N + nn] = (bf16_t)to_bf16x2(sum, 0.0f);
+                                    else C[mm * p.N + nn] = sum;
                                 }
                             }
         }
@@ -1270,15 +1277,19 @@ tardis_status_t td_gemm_init() {
 // more rows than the grid of the kernel for any shape counts
 bool td_gemm_refuses_rows(int64_t M) { return (M + GT - 1) / GT > 65535; }
 
-// C = A.B^T (+ row_bias), or C += A.B^T.  (A second product is added to the first one's finished sums and not summed
+// (any M, N work on the matrix cores; small products are not worth it)
+bool td_gemm_on_matrix_cores(const void* A, const void* B, int64_t M, int64_t N, int64_t K, int32_t dtype) {
+    return dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 && is_aligned16(A) && is_aligned16(B) &&
+           K % 8 == 0 && !gemm_force_generic();
+}
+
+// C = A.B^T (+ row_bias), or C += A.B^T (or that sum rounded to bf16 into out16, C left as it was: matrix cores only).  (A second product is added to the first one's finished sums and not summed
 // onto them: partial sums of the first may be far larger than the second.)
 tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int32_t dtype,
-                           int accumulate, const void* row_bias, hipStream_t s) {
+                           int accumulate, const void* row_bias, hipStream_t s, void* out16) {
     if (M <= 0 || N <= 0 || K <= 0) return TARDIS_ERR_SHAPE;
     if (td_gemm_refuses_rows(M)) return TARDIS_ERR_SHAPE;
-    // (any M, N work on the matrix cores; small products are not worth it)
-    if (dtype == TARDIS_BF16 && M >= 32 && N >= 32 && M * N >= 128 * 128 && K >= 64 && is_aligned16(A) && is_aligned16(B) &&
-        K % 8 == 0 && !gemm_force_generic()) {
+    if (td_gemm_on_matrix_cores(A, B, M, N, K, dtype)) {
         TD_TRY(td_gemm_init());
         GemmArgs p{};
         p.A = p.A2 = bytes_of(A);
@@ -1289,6 +1300,7 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, in
         p.C = C;
         p.accumulate = accumulate;
         p.bias = static_cast<const bf16_t*>(row_bias);
+        p.out = static_cast<bf16_t*>(out16);
         launch_tile<EPI_F32>(p, s);
     } else if (dtype == TARDIS_BF16) {
         launch_generic<bf16_t>(A, B, C, M, N, K, accumulate, row_bias, s);

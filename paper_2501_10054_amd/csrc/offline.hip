@@ -32,7 +32,8 @@ transpose_kernel(const E* __restrict__ src, E* __restrict__ dst, int64_t rows, i
 // The same for 2-byte elements with rows and cols multiples of 8 and 16-byte aligned arrays: 64 x 64 tiles, 16 bytes
 // a thread on both sides (the 32 x 32 form moves 64 bytes of a row at a time).  Two source rows share a word
 // of the LDS tile; a thread collects eight of them for one destination row.
-// SPLIT: the fold's operands instead of a copy: p = a[row] * src, its bf16 head to dst and the bf16 remainder to
+// dst_lo: a straight copy of src (46 us for the transpose alone, 67 with the copy, which would otherwise read src again).
+// SPLIT: the fold's operands instead of copies: p = a[row] * src, its bf16 head to dst and the bf16 remainder to
 // dst_lo, so that the folded matrix is accumulated from ~16 significant bits instead of 8 (the paper's
 // Sec. "Precision Effects on Reordering FFN" finds bf16 intermediates visibly worse than fp32).
 // Bound: HBM.  16384 x 4096: copy 127 -> 46 us, split 217 -> 76 us (32 x 32 tiles before).
@@ -53,6 +54,7 @@ transpose16_kernel(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, bf1
             if (r + u < rows && c < cols) {
                 v[u] = *reinterpret_cast<const td_u32x4*>(src + (r + u) * cols + c);
                 if constexpr (SPLIT) s[u] = a[r + u];
+                else *reinterpret_cast<td_u32x4*>(dst_lo + (r + u) * cols + c) = v[u];
             }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -1274,18 +1276,20 @@ tardis_status_t td_fx_bounds(const tardis_layer_s* L, float* out2, hipStream_t s
     return L->dtype == TARDIS_BF16 ? fx_bounds_t<bf16_t>(L, out2, s) : fx_bounds_t<float>(L, out2, s);
 }
 
-tardis_status_t td_transpose(const void* src, void* dst, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s) {
+tardis_status_t td_transpose(const void* src, void* dst, void* copy, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s) {
     if ((rows + 31) / 32 > 65535) return TARDIS_ERR_SHAPE;
     const bool whole = rows % 8 == 0 && cols % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
     if (dtype == TARDIS_BF16 && whole)
         hipLaunchKernelGGL(transpose16_kernel<false>, tile_grid(cols, rows, 64), dim3(256), 0, s,
-                           static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), nullptr, nullptr, rows, cols);
+                           static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), static_cast<bf16_t*>(copy), nullptr, rows, cols);
     else if (dtype == TARDIS_BF16)
         hipLaunchKernelGGL(transpose_kernel<uint16_t>, tile_grid(cols, rows), dim3(256), 0, s,
                            static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst), rows, cols);
     else
         hipLaunchKernelGGL(transpose_kernel<uint32_t>, tile_grid(cols, rows), dim3(256), 0, s,
                            static_cast<const uint32_t*>(src), static_cast<uint32_t*>(dst), rows, cols);
+    if (!(dtype == TARDIS_BF16 && whole))
+        TD_HIP(hipMemcpyAsync(copy, src, (size_t)rows * cols * td_elem_size(dtype), hipMemcpyDeviceToDevice, s));
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }
@@ -1345,12 +1349,14 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
                                static_cast<const bf16_t*>(desc->W1), a, static_cast<bf16_t*>(work1),
                                static_cast<bf16_t*>(work2), h, d);
         TD_TRY(td_gemm_nt(desc->W2, work1, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 0, nullptr, s));
-        TD_TRY(td_gemm_nt(desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 1, nullptr, s));
+        // (the second product's epilogue rounds the sums; a kernel for that took 27 us and their 64 MB once more each way)
+        const bool round = !Wp8 && td_gemm_on_matrix_cores(desc->W2, work2, d, d, h, TARDIS_BF16);
+        TD_TRY(td_gemm_nt(desc->W2, work2, static_cast<float*>(acc.p), d, d, h, TARDIS_BF16, 1, nullptr, s, round ? Wp : nullptr));
         const int64_t n = d * d;
         if (Wp8)
             hipLaunchKernelGGL(wp_to_fp8_kernel, dim3((unsigned)d), dim3(kBlock), 0, s, static_cast<const float*>(acc.p),
                                d, Wp8, wp8_scale, static_cast<bf16_t*>(Wp));
-        else
+        else if (!round)
             hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                                static_cast<const float*>(acc.p), static_cast<bf16_t*>(Wp), n);
         hipLaunchKernelGGL(fold_bias_terms_kernel<bf16_t>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,

@@ -68,3 +68,27 @@ def test_fold_and_calibration_on_large_tiles(d, h, n):
     terms = np.sqrt((np.asarray(layer.W2, np.float64) ** 2 * got[2] ** 2) @ np.asarray(layer.W1, np.float64) ** 2)
     assert (np.abs(host(Wp) - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -14 * terms).all()
     L.close()
+
+
+@pytest.mark.parametrize("d,h", [(130, 136), (257, 264), (132, 520), (640, 1032), (75, 130)])
+def test_fold_rounds_in_the_second_product(d, h):
+    """Rows that are and are not whole vectors of four (and, the last one, products on the kernel for any shape): W' within
+    one rounding of the sums, and both copies of W2 (one token through the dense and through the folded layer)."""
+    seed = synth.workload_seed(9, 92)
+    layer = custom_layer(d, h, "bf16", seed, 0.1, True)
+    ffn = make_ffn(layer)
+    X = synth.make_tokens(3, d, "bf16", seed, synth.STREAM_TEST)
+    ranges = T.tardis_calibrate(ffn, dev(synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL), "bf16"), 0.9)
+    L = T.tardis_fold(ffn, *ranges, max_batch=3)
+    a = ranges[2].cpu().numpy().astype(np.float64)
+    W1, W2 = (np.asarray(t, np.float64) for t in (layer.W1, layer.W2))
+    ref, terms = (W2 * a) @ W1, np.sqrt((W2 ** 2 * a ** 2) @ W1 ** 2)
+    got = host(T.tardis_get_folded(L)[0])
+    assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -14 * terms).all()
+    F = O.build(layer.W1, layer.b1, layer.W2, layer.b2, *(t.cpu().numpy() for t in ranges))
+    want, flags = O.forward(F, X)
+    assert_y_close(host(T.tardis_ffn_forward_batched(L, dev(X, "bf16"))), want, F, X, flags)
+    z = torch.from_numpy(X).double() @ torch.from_numpy(W1).T + torch.from_numpy(np.asarray(layer.b1)).double()
+    dense = (torch.nn.functional.gelu(z) @ torch.from_numpy(W2).T).numpy() + np.asarray(layer.b2, np.float64)
+    assert rel_l2(host(T.tardis_dense_forward(L, dev(X, "bf16"))), dense) <= 1e-2
+    L.close()
