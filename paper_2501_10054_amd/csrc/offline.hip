@@ -152,34 +152,55 @@ fold_bias_terms_kernel(const T* __restrict__ b1, const float* __restrict__ a, co
     if (j < h) k[j] = (double)c[j] + (b1 ? (double)a[j] * (double)td_load<T>(b1 + j) : 0.0);
 }
 
-// b'[r] = sum_j W2[r][j] * k_j + b2[r]; one block per output row, fp64 accumulation.  Bound: HBM (W2 once, 16
-// bytes a load where rows are whole vectors): d=4096, h=16384: 92 -> 45 us.
+// b'[r] = sum_j W2[r][j] * k_j + b2[r]; one block per kBiasRows output rows, fp64 accumulation.  Bound: HBM (W2 once, 16
+// bytes a load where rows are whole vectors).  Several rows, because k (8 bytes where W2 has 2) comes from L2 for
+// every block: d=4096, h=16384: 26 us with four rows, 42 with one.
+constexpr int kBiasRows = 4;
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 fold_bias_kernel(const T* __restrict__ W2, const double* __restrict__ k, const T* __restrict__ b2, float* __restrict__ bp,
                  int64_t d, int64_t h) {
-    __shared__ double red[kBlock / TD_WAVE];
+    __shared__ double red[kBiasRows][kBlock / TD_WAVE];
     constexpr int V = 16 / (int)sizeof(T);
-    const int64_t r = blockIdx.x;
-    const T* row = W2 + r * h;
-    double acc = 0.0;
+    const int64_t r0 = (int64_t)blockIdx.x * kBiasRows;
+    const T* row[kBiasRows];                         // (past the last row: the last one once more, not stored)
+    double acc[kBiasRows];
+#pragma unroll
+    for (int i = 0; i < kBiasRows; ++i) {
+        row[i] = W2 + (r0 + i < d ? r0 + i : d - 1) * h;
+        acc[i] = 0.0;
+    }
     if (h % V == 0) {
         for (int64_t v = threadIdx.x; v < h / V; v += kBlock) {
-            const td_u32x4 w = td_load_stream16(reinterpret_cast<const td_u32x4*>(row) + v);
-            const T* wt = reinterpret_cast<const T*>(&w);
+            td_u32x4 w[kBiasRows];
 #pragma unroll
-            for (int u = 0; u < V; ++u) acc += (double)td_load<T>(wt + u) * k[v * V + u];
+            for (int i = 0; i < kBiasRows; ++i) w[i] = td_load_stream16(reinterpret_cast<const td_u32x4*>(row[i]) + v);
+            double kv[V];
+#pragma unroll
+            for (int u = 0; u < V; ++u) kv[u] = k[v * V + u];
+#pragma unroll
+            for (int i = 0; i < kBiasRows; ++i) {
+                const T* wt = reinterpret_cast<const T*>(&w[i]);
+#pragma unroll
+                for (int u = 0; u < V; ++u) acc[i] += (double)td_load<T>(wt + u) * kv[u];
+            }
         }
     } else {
-        for (int64_t j = threadIdx.x; j < h; j += kBlock) acc += (double)td_load<T>(row + j) * k[j];
+        for (int64_t j = threadIdx.x; j < h; j += kBlock)
+#pragma unroll
+            for (int i = 0; i < kBiasRows; ++i) acc[i] += (double)td_load<T>(row[i] + j) * k[j];
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = acc;
+    for (int i = 0; i < kBiasRows; ++i) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[i] += __shfl_xor(acc[i], o, 64);
+        if ((threadIdx.x & 63) == 0) red[i][threadIdx.x / 64] = acc[i];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    const int64_t r = r0 + threadIdx.x;
+    if (threadIdx.x < kBiasRows && r < d) {
         double t = 0.0;
-        for (int w = 0; w < kBlock / TD_WAVE; ++w) t += red[w];
+        for (int w = 0; w < kBlock / TD_WAVE; ++w) t += red[threadIdx.x][w];
         if (b2) t += (double)td_load<T>(b2 + r);
         bp[r] = (float)t;
     }
@@ -212,8 +233,24 @@ __device__ __forceinline__ int sketch_code(float w, double s, double inv) {
     return (int)fmin(fmax(rint(q), -127.0), 127.0);
 }
 
-// Bound: HBM (W1 once, a byte per weight out).  16384 x 4096: 140 -> 79 us (a 64-bit division per weight and
-// 2-byte loads before).
+// The codes of N weights in fp32: w * inv32 (inv32: 1 / s, rounded) is within 2^-23 of the quotient, with |quotient| <= 127
+// 1.6e-5, so where none of them is that close to a half, rint gives the integers that the exact quotients give; else false.
+// For maxima of at least kFlatMin and at most kFlatMax: inv32 is a normal number, and a NaN's code is -top here and there.
+constexpr float kFlatMin = 1e-30f, kFlatMax = 1e30f, kNearHalf = 0.5f - 4e-5f;
+template <int N> __device__ __forceinline__ bool flat_codes(const float (&w)[N], float inv32, float top, int (&code)[N]) {
+    float far = 0.0f;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float q = w[u] * inv32, n = rintf(q);
+        far = fmaxf(far, fabsf(q - n));
+        code[u] = (int)fminf(fmaxf(n, -top), top);
+    }
+    return far < kNearHalf;
+}
+
+// Bound: HBM (W1 once, a byte per weight out) and vector instructions together.  16384 x 4096: 68 us; 80 with the quotient of
+// every weight in fp64, 140 with a 64-bit division per weight and 2-byte loads.  (A wavefront per row, all its loads under
+// way at once and no barrier: 67.)
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
@@ -255,12 +292,22 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
     predictor_range((double)lo[j], (double)hi[j], (double)margin, rl, rh);
     const bool live = m > 0.0f;
     const double inv = live ? 1.0 / s : 0.0;
+    const bool flat = m >= kFlatMin && m <= kFlatMax;
+    const float inv32 = (float)inv;
     auto code = [&](float w) { return live ? sketch_code(w, s, inv) : 0; };
     auto put = [&](int64_t v, const td_u32x4& w) {
         const T* wt = reinterpret_cast<const T*>(&w);
         uint32_t o[2] = {0u, 0u};
+        float f[V];
+        int q[V];
 #pragma unroll
-        for (int u = 0; u < V; ++u) o[u >> 2] |= (uint32_t)(uint8_t)(int8_t)code(td_load<T>(wt + u)) << (8 * (u & 3));
+        for (int u = 0; u < V; ++u) f[u] = td_load<T>(wt + u);
+        if (!(flat && flat_codes(f, inv32, 127.0f, q))) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) q[u] = code(f[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) o[u >> 2] |= (uint32_t)(uint8_t)(int8_t)q[u] << (8 * (u & 3));
         int8_t* dst = Q + j * d + v * V;             // V-byte aligned: d % V == 0
         if constexpr (V == 8) *reinterpret_cast<uint2*>(dst) = make_uint2(o[0], o[1]);
         else *reinterpret_cast<uint32_t*>(dst) = o[0];
@@ -291,11 +338,25 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
 // Outputs: M4 (one byte per group); Q (optional) the effective one-byte code m*q; Q4 (optional,
 // d % 32 == 0) the packed form read by the decode kernel: group G is the 16-byte vector G of the
 // row, byte b of its dword w holds column 4w+b in the low nibble and column 16+4w+b in the high one.
+__device__ __forceinline__ void low_bit_bounds(float lo, float hi, float margin, double b, bool live, double s, float* tlo, float* thi) {
+    double rl, rh;
+    predictor_range((double)lo, (double)hi, (double)margin, rl, rh);
+    if (live) {
+        *tlo = (float)((rl - b) / s);
+        *thi = (float)((rh - b) / s);
+    } else {
+        const bool inside = (rl <= b) && (b < rh);
+        *tlo = inside ? -INFINITY : INFINITY;
+        *thi = INFINITY;
+    }
+}
+
+// (rows that are not whole groups: no packed form)
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch4_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
-               const float* __restrict__ hi, int64_t d, int ng, int8_t* __restrict__ Q, uint8_t* __restrict__ Q4,
-               uint8_t* __restrict__ M4, float* __restrict__ tlo, float* __restrict__ thi, int qmax, float margin) {
+               const float* __restrict__ hi, int64_t d, int ng, int8_t* __restrict__ Q, uint8_t* __restrict__ M4,
+                float* __restrict__ tlo, float* __restrict__ thi, int qmax, float margin) {
     extern __shared__ int gval[];                    // group maxima (bit patterns), then multipliers
     __shared__ float red[kBlock / TD_WAVE];
     const int64_t j = blockIdx.x;
@@ -331,37 +392,107 @@ sketch4_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* 
         const double q = rint((double)td_load<T>(row + k) / ((double)gval[k >> 5] * s));
         return (int)fmin(fmax(q, -(double)qmax), (double)qmax);
     };
-    if (Q4) {   // d is a multiple of 32 here
-        uint32_t* out = reinterpret_cast<uint32_t*>(Q4 + j * (d / 2));
-        for (int64_t idx = threadIdx.x; idx < d / 8; idx += kBlock) {
-            const int64_t g = idx >> 2, w = idx & 3;
+    if (Q)
+        for (int64_t k = threadIdx.x; k < d; k += kBlock) Q[j * d + k] = (int8_t)(gval[k >> 5] * code(k));
+    if (threadIdx.x == 0) low_bit_bounds(lo[j], hi[j], margin, bj, live, s, tlo + j, thi + j);
+}
+
+// The same for rows of whole groups.  Four lanes hold a group, each the eight columns of its word of the packed form, so a
+// group's maximum and multiplier stay in registers, and the codes are taken in fp32 where that decides them (flat_codes; the
+// unit of a group, m s, has a reciprocal within 2^-22, so quotients up to 105 - a group with a NaN has m = 1 - are within 3.4e-5).
+// Bound: HBM (W1 once, half a byte and where kept a byte per weight out).  16384 x 4096: 61 us; 250 with maxima by
+// LDS atomics, 2-byte loads and an fp64 division per weight; 66 with a wavefront per row.
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+sketch4_rows_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
+                    const float* __restrict__ hi, int64_t d, int8_t* __restrict__ Q, uint8_t* __restrict__ Q4,
+                    uint8_t* __restrict__ M4, float* __restrict__ tlo, float* __restrict__ thi, int qmax, float margin) {
+    __shared__ float red[kBlock / TD_WAVE];
+    constexpr int kKeep = 2;                         // words a thread keeps between the two passes
+    typedef T quad_t __attribute__((ext_vector_type(4)));
+    const int64_t j = blockIdx.x;
+    const T* row = W1 + j * d;                       // (W1 is 16-byte aligned: so is every group)
+    const int64_t words = d / 8;                     // a multiple of four: a group's lanes are all there or none
+    auto fetch = [&](int64_t idx, float (&f)[8]) {
+        const T* at = row + 32 * (idx >> 2) + 4 * (idx & 3);
+        const quad_t a = *reinterpret_cast<const quad_t*>(at), b = *reinterpret_cast<const quad_t*>(at + 16);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T x = a[u], y = b[u];
+            f[u] = td_load<T>(&x);
+            f[4 + u] = td_load<T>(&y);
+        }
+    };
+    auto group_max = [&](const float (&f)[8]) {      // non-negative floats order like their bit patterns, NaNs above all
+        int g = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) g = max(g, __float_as_int(fabsf(f[u])));
+        g = max(g, __shfl_xor(g, 1, 64));
+        return __int_as_float(max(g, __shfl_xor(g, 2, 64)));
+    };
+    float keep[kKeep][8], top[kKeep];
+    float r = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int64_t idx = i * kBlock + threadIdx.x;
+        if (idx < words) {
+            fetch(idx, keep[i]);
+            top[i] = group_max(keep[i]);
+            r = fmaxf(r, top[i]);
+        }
+    }
+    for (int64_t idx = kKeep * kBlock + threadIdx.x; idx < words; idx += kBlock) {
+        float f[8];
+        fetch(idx, f);
+        r = fmaxf(r, group_max(f));
+    }
+    r = td_wave_max(r);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = r;
+    __syncthreads();
+    r = red[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / TD_WAVE; ++w) r = fmaxf(r, red[w]);
+    const double s = (double)r / (double)(qmax * 15);
+    const bool live = r > 0.0f, flat = r >= kFlatMin && r <= kFlatMax;
+    const float inv32 = flat ? (float)(1.0 / s) : 0.0f;
+    auto put = [&](int64_t idx, const float (&f)[8], float g) {
+        int m = 1, q[8];
+        if (live) m = (int)fmin(fmax(ceil((double)g / ((double)qmax * s)), 1.0), 15.0);
+        if (!(flat && flat_codes(f, inv32 * __builtin_amdgcn_rcpf((float)m), (float)qmax, q))) {
+            const double unit = (double)m * s;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                q[u] = live ? (int)fmin(fmax(rint((double)f[u] / unit), -(double)qmax), (double)qmax) : 0;
+        }
+        if ((idx & 3) == 0) M4[j * (d / 32) + (idx >> 2)] = (uint8_t)m;
+        if (Q4) {
             uint32_t word = 0;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int64_t klo = 32 * g + 4 * w + b, khi = klo + 16;
-                const int qlo = code(klo), qhi = code(khi);
-                word |= (uint32_t)((qlo & 0xF) | ((qhi & 0xF) << 4)) << (8 * b);
-                if (Q) {
-                    Q[j * d + klo] = (int8_t)(gval[g] * qlo);
-                    Q[j * d + khi] = (int8_t)(gval[g] * qhi);
-                }
-            }
-            out[idx] = word;
+            for (int b = 0; b < 4; ++b) word |= (uint32_t)((q[b] & 0xF) | ((q[4 + b] & 0xF) << 4)) << (8 * b);
+            reinterpret_cast<uint32_t*>(Q4 + j * (d / 2))[idx] = word;
         }
-    } else if (Q) {
-        for (int64_t k = threadIdx.x; k < d; k += kBlock) Q[j * d + k] = (int8_t)(gval[k >> 5] * code(k));
+        if (Q) {
+            uint32_t o[2] = {0u, 0u};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o[u >> 2] |= (uint32_t)(uint8_t)(int8_t)(m * q[u]) << (8 * (u & 3));
+            uint32_t* dst = reinterpret_cast<uint32_t*>(Q + j * d + 32 * (idx >> 2) + 4 * (idx & 3));
+            dst[0] = o[0];
+            dst[4] = o[1];
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int64_t idx = i * kBlock + threadIdx.x;
+        if (idx < words) put(idx, keep[i], top[i]);
+    }
+    for (int64_t idx = kKeep * kBlock + threadIdx.x; idx < words; idx += kBlock) {
+        float f[8];
+        fetch(idx, f);
+        put(idx, f, group_max(f));
     }
     if (threadIdx.x == 0) {
-        double rl, rh;
-        predictor_range((double)lo[j], (double)hi[j], (double)margin, rl, rh);
-        if (live) {
-            tlo[j] = (float)((rl - bj) / s);
-            thi[j] = (float)((rh - bj) / s);
-        } else {
-            const bool inside = (rl <= bj) && (bj < rh);
-            tlo[j] = inside ? -INFINITY : INFINITY;
-            thi[j] = INFINITY;
-        }
+        const double bj = b1 ? (double)td_load<T>(b1 + j) : 0.0;
+        low_bit_bounds(lo[j], hi[j], margin, bj, live, s, tlo + j, thi + j);
     }
 }
 
@@ -1301,14 +1432,18 @@ tardis_status_t td_build_sketch(const void* W1, const void* b1, const float* lo,
         const int qmax = (1 << (bits - 1)) - 1;
         const int64_t ng = (d + 31) / 32;
         if (!M4 || (Q4 && d % 32 != 0) || ng * 4 > 64 * 1024) return TARDIS_ERR_SHAPE;
-        if (dtype == TARDIS_BF16)
-            hipLaunchKernelGGL(sketch4_kernel<bf16_t>, dim3((unsigned)h), dim3(kBlock), (size_t)ng * 4, s,
-                               static_cast<const bf16_t*>(W1), static_cast<const bf16_t*>(b1), lo, hi, d, (int)ng,
-                               Q, Q4, M4, tlo, thi, qmax, margin);
-        else
-            hipLaunchKernelGGL(sketch4_kernel<float>, dim3((unsigned)h), dim3(kBlock), (size_t)ng * 4, s,
-                               static_cast<const float*>(W1), static_cast<const float*>(b1), lo, hi, d, (int)ng,
-                               Q, Q4, M4, tlo, thi, qmax, margin);
+        auto launch = [&](auto type) {
+            typedef decltype(type) T;
+            const T *W = static_cast<const T*>(W1), *b = static_cast<const T*>(b1);
+            if (d % 32 == 0)
+                hipLaunchKernelGGL(sketch4_rows_kernel<T>, dim3((unsigned)h), dim3(kBlock), 0, s, W, b, lo, hi, d, Q, Q4, M4, tlo, thi, qmax,
+                                   margin);
+            else
+                hipLaunchKernelGGL(sketch4_kernel<T>, dim3((unsigned)h), dim3(kBlock), (size_t)ng * 4, s, W, b, lo, hi, d, (int)ng, Q, M4,
+                                   tlo, thi, qmax, margin);
+        };
+        if (dtype == TARDIS_BF16) launch(bf16_t{});
+        else launch(float{});
         TD_HIP(hipGetLastError());
         return TARDIS_OK;
     }
@@ -1361,7 +1496,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
                                static_cast<const float*>(acc.p), static_cast<bf16_t*>(Wp), n);
         hipLaunchKernelGGL(fold_bias_terms_kernel<bf16_t>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                            static_cast<const bf16_t*>(desc->b1), a, c, static_cast<double*>(kk.p), h);
-        hipLaunchKernelGGL(fold_bias_kernel<bf16_t>, dim3((unsigned)d), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL(fold_bias_kernel<bf16_t>, dim3((unsigned)((d + kBiasRows - 1) / kBiasRows)), dim3(kBlock), 0, s,
                            static_cast<const bf16_t*>(desc->W2), static_cast<const double*>(kk.p),
                            static_cast<const bf16_t*>(desc->b2), bp, d, h);
         TD_HIP(hipGetLastError());
@@ -1372,7 +1507,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
         TD_TRY(td_gemm_nt(desc->W2, work1, static_cast<float*>(Wp), d, d, h, TARDIS_F32, 0, nullptr, s));
         hipLaunchKernelGGL(fold_bias_terms_kernel<float>, dim3((unsigned)((h + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                            static_cast<const float*>(desc->b1), a, c, static_cast<double*>(kk.p), h);
-        hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)d), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL(fold_bias_kernel<float>, dim3((unsigned)((d + kBiasRows - 1) / kBiasRows)), dim3(kBlock), 0, s,
                            static_cast<const float*>(desc->W2), static_cast<const double*>(kk.p),
                            static_cast<const float*>(desc->b2), bp, d, h);
         TD_HIP(hipGetLastError());
