@@ -248,9 +248,9 @@ template <int N> __device__ __forceinline__ bool flat_codes(const float (&w)[N],
     return far < kNearHalf;
 }
 
-// Bound: HBM (W1 once, a byte per weight out) and vector instructions together.  16384 x 4096: 68 us; 80 with the quotient of
-// every weight in fp64, 140 with a 64-bit division per weight and 2-byte loads.  (A wavefront per row, all its loads under
-// way at once and no barrier: 67.)
+// Bound: HBM (W1 once, a byte per weight out) and vector instructions together.  16384 x 4096: with the quotient of
+// every weight in fp64 75 us (a few large columns) and 80 (normal weights), now 49 and 68; a 64-bit division per weight and 2-byte
+// loads: 140.  (A wavefront per row, all its loads under way at once and no barrier: 67 for normal weights.)
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
