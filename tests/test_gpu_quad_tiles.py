@@ -1,4 +1,4 @@
-"""The products with four wavefronts (large tiles): the folded and the dense path against the checker at tokens on the
+"""The products with four wavefronts (large tiles): the folded and the dense path against the oracle at tokens on the
 edges of their tiles, the fold and the calibration at partial tiles."""
 import numpy as np
 import pytest
