@@ -14,6 +14,7 @@
 #include <utility>
 
 #include "common.h"
+#include "slices.h"
 
 namespace {
 
@@ -107,7 +108,7 @@ gemm_nt_generic_kernel(const T* __restrict__ A, const T* __restrict__ B, float* 
 // through registers, which was here before: 605 us, 0.91).
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef td_i32x4 i32x4_t;
 
 constexpr int kWavesPerTile = 8;
 constexpr int kNoLds = 0xc07f, kNoLoads = 0x0f70;            // s_waitcnt lgkmcnt(0), vmcnt(0)
@@ -851,34 +852,15 @@ __global__ void __launch_bounds__(256, 1) gemm_quad_kernel(GemmArgs p, TileMap t
     const uint32_t lds_b = __builtin_amdgcn_readfirstlane(base + SA * G::UA + wave * (G::UB / 4));
 
     // The slice that the next loads of A (of B) fetch.  It is found in steps, which stand in different gaps.
-    struct Stream {
-        i32x4_t rs;
-        uint32_t soff, pitch, voff, to;       // K offset; bytes of a row; this lane's offset; ring buffer of this wavefront
-        int t, s;                             // number in the sequence, slice
-        bool second;
+    const td_slices seq{nk1, nk2, s0, nk, rot, rot2, p.k, p.k2};
+    struct Stream : td_slice_source {
+        uint32_t voff, to;                    // this lane's offset; ring buffer of this wavefront
     };
     auto find = [&](Stream& o, bool is_a, int step) {
-        const i32x4_t &r1 = is_a ? ra1 : rb1, &r2 = is_a ? ra2 : rb2;
-        if (step == 0) {
-            if constexpr (EPI == EPI_REPAIR) o.s = o.t + (o.t >= nk1 ? rot2 : rot);
-            else o.s = o.t + rot;
-        } else if (step == 1) {
-            if constexpr (EPI == EPI_REPAIR) o.s -= o.t >= nk1 ? (o.s >= nk1 + nk2 ? nk2 : 0) : (o.s >= nk1 ? nk1 : 0);
-            else o.s += s0 - (o.s >= nk ? nk : 0);
-        } else if (step == 2) {
-            o.second = o.s >= nk1;
-            o.soff = (uint32_t)(o.second ? o.s - nk1 : o.s) * SL;
-            asm volatile("" : "+s"(o.soff));
-        } else if (step == 3) {
-            o.rs.x = o.second ? r2.x : r1.x;
-            o.rs.y = o.second ? r2.y : r1.y;
-        } else if (step == 4) {
-            o.rs.z = o.second ? r2.z : r1.z;
-            if (o.t >= nk) o.rs.z = 0;                              // past the last slice: an empty buffer
-            o.pitch = o.second ? p.k2 : p.k;
-        } else {
+        td_find_slice<EPI == EPI_REPAIR, SL>(o, seq, is_a ? ra1 : rb1, is_a ? ra2 : rb2, step);
+        if (step == 2 || step == 4) asm volatile("" : "+s"(o.soff));
+        if (step == 5) {
             o.voff = __umul24(is_a ? row_a : row_b, o.pitch) + piece;   // (rows of at most 2^23 bytes)
-            ++o.t;
             asm volatile("" : "+v"(o.voff));                            // here, and not where it is used
         }
     };
@@ -894,6 +876,7 @@ __global__ void __launch_bounds__(256, 1) gemm_quad_kernel(GemmArgs p, TileMap t
     auto at = [&](Stream& o, bool is_a, int t, uint32_t to) {
         o.t = t;
         o.to = to;
+#pragma unroll
         for (int step = 0; step < 6; ++step) find(o, is_a, step);
     };
     // In period p (the half of slice p behind the barrier, and the first half of slice p+1) the loads of B(p+SB) and then
