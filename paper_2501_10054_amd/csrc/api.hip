@@ -252,6 +252,10 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     }
     if (stack_entry) mem.reserve(&L->stack_desc, sizeof(td_stack_layer_dev));
     if (L->fx) mem.reserve(&L->fx_bound, 8);
+    // (the working memory first, and always from the device: where no memory can be asked for, as while a stream is
+    // captured, the fold ends here, with nothing in the stream - also if the layer's own could be memory that is kept)
+    td_fold_work work;
+    TD_TRY(work.alloc(desc));
     TD_TRY(mem.commit(L));
 
     if (L->use_fused) {
@@ -268,7 +272,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     TD_HIP(hipMemcpyAsync(L->a, a, (size_t)h * 4, hipMemcpyDeviceToDevice, s));
     TD_HIP(hipMemcpyAsync(L->c, c, (size_t)h * 4, hipMemcpyDeviceToDevice, s));
     // (the fold first: the two copies of W2 hold its operands until they are filled)
-    TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, L->W2T, L->W2, s));
+    TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, L->W2T, L->W2, work, s));
     TD_TRY(td_transpose(desc->W2, L->W2T, L->W2, d, h, desc->dtype, s));
     TD_TRY(td_build_sketch(desc->W1, desc->b1, lo, hi, h, d, desc->dtype, L->sketch_bits, L->margin, L->Q, L->Q4, L->M4, L->tlo,
                            L->thi, s));

@@ -210,6 +210,33 @@ __device__ __forceinline__ double td_act_f64(double z, int act) {
 
 // api.hip: memory of destroyed layers that is kept for the next one goes back to the device; false: there was none
 bool td_give_back_memory();
+struct td_dev_buf {  // frees on scope exit
+    void* p = nullptr;
+    td_dev_buf() = default;
+    td_dev_buf(const td_dev_buf&) = delete;
+    td_dev_buf& operator=(const td_dev_buf&) = delete;
+    ~td_dev_buf() {
+        if (p) (void)hipFree(p);
+    }
+    tardis_status_t alloc(size_t bytes) {
+        hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
+        if (e == hipErrorOutOfMemory && td_give_back_memory()) e = hipMalloc(&p, bytes ? bytes : 16);
+        if (e != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+            return e == hipErrorOutOfMemory ? TARDIS_ERR_OOM : TARDIS_ERR_HIP;
+        }
+        return TARDIS_OK;
+    }
+};
+// working memory of td_fold (two buffers: up to 64 MiB each is what the runtime keeps for the next call)
+struct td_fold_work {
+    td_dev_buf terms, sums;
+    tardis_status_t alloc(const tardis_ffn_desc* desc) {
+        TD_TRY(terms.alloc((size_t)desc->h * 8));
+        return desc->dtype == TARDIS_BF16 ? sums.alloc((size_t)desc->d * desc->d * 4) : TARDIS_OK;
+    }
+};
 // offline.hip
 // dst = src transposed, copy = src
 tardis_status_t td_transpose(const void* src, void* dst, void* copy, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s);
@@ -226,7 +253,7 @@ tardis_status_t td_unpack_sketch4(const uint8_t* Q4, const uint8_t* M4, int64_t 
 // receives the same values as bf16
 // work1, work2: h x d elements of the layer dtype each, overwritten
 tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float* c, void* Wp, float* bp,
-                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, hipStream_t s);
+                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, const td_fold_work& work, hipStream_t s);
 // step > 0: greedy range search with that increment; step <= 0: central quantile ranges
 tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t n, float coverage,
                              const float* cov_pn, float step, float* lo, float* hi, float* a, float* c,

@@ -1326,23 +1326,6 @@ fx_bound_kernel(const T* __restrict__ Wp, const float* __restrict__ bp, int64_t 
     }
 }
 
-struct DevBuf {  // frees on scope exit
-    void* p = nullptr;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
-    tardis_status_t alloc(size_t bytes) {
-        hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
-        if (e == hipErrorOutOfMemory && td_give_back_memory()) e = hipMalloc(&p, bytes ? bytes : 16);
-        if (e != hipSuccess) {
-            p = nullptr;
-            (void)hipGetLastError();
-            return e == hipErrorOutOfMemory ? TARDIS_ERR_OOM : TARDIS_ERR_HIP;
-        }
-        return TARDIS_OK;
-    }
-};
-
 dim3 tile_grid(int64_t cols, int64_t rows, int64_t side = 32) {
     return dim3((unsigned)((cols + side - 1) / side), (unsigned)((rows + side - 1) / side));
 }
@@ -1354,7 +1337,7 @@ static tardis_status_t fx_bounds_t(const tardis_layer_s* L, float* out2, hipStre
     const int64_t d = L->d, h = L->h;
     const int chunks = 32;
     const int64_t rpc = (h + chunks - 1) / chunks;
-    DevBuf g, kk, P;
+    td_dev_buf g, kk, P;
     TD_TRY(g.alloc((size_t)h * 4));
     TD_TRY(kk.alloc((size_t)h * 4));
     TD_TRY(P.alloc((size_t)chunks * 2 * d * 4));
@@ -1375,7 +1358,7 @@ tardis_status_t td_estimate_errors(const tardis_ffn_desc* desc, const void* X, i
                                    const float* hi, const float* a, const float* c, float* err, float* err_layer,
                                    hipStream_t s) {
     const int64_t d = desc->d, h = desc->h;
-    DevBuf zt, cn;
+    td_dev_buf zt, cn;
     TD_TRY(zt.alloc((size_t)h * n * 4));
     TD_TRY(cn.alloc((size_t)h * 4));
     TD_TRY(td_gemm_nt(desc->W1, X, static_cast<float*>(zt.p), h, n, d, desc->dtype, 0, desc->b1, s));
@@ -1466,15 +1449,12 @@ tardis_status_t td_unpack_sketch4(const uint8_t* Q4, const uint8_t* M4, int64_t 
 }
 
 tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float* c, void* Wp, float* bp,
-                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, hipStream_t s) {
+                        uint8_t* Wp8, float* wp8_scale, void* work1, void* work2, const td_fold_work& work, hipStream_t s) {
     if (Wp8 && desc->dtype != TARDIS_BF16) return TARDIS_ERR_DTYPE;
     const int64_t d = desc->d, h = desc->h;
     if ((h + 31) / 32 > 65535 || (d + 31) / 32 > 65535) return TARDIS_ERR_SHAPE;
-    DevBuf kk;
-    TD_TRY(kk.alloc((size_t)h * 8));
+    const td_dev_buf &kk = work.terms, &acc = work.sums;
     if (desc->dtype == TARDIS_BF16) {
-        DevBuf acc;
-        TD_TRY(acc.alloc((size_t)d * d * 4));
         if (d % 8 == 0 && h % 8 == 0)
             hipLaunchKernelGGL(transpose16_kernel<true>, tile_grid(d, h, 64), dim3(256), 0, s,
                                static_cast<const bf16_t*>(desc->W1), static_cast<bf16_t*>(work1),
@@ -1500,7 +1480,7 @@ tardis_status_t td_fold(const tardis_ffn_desc* desc, const float* a, const float
                            static_cast<const bf16_t*>(desc->W2), static_cast<const double*>(kk.p),
                            static_cast<const bf16_t*>(desc->b2), bp, d, h);
         TD_HIP(hipGetLastError());
-        TD_HIP(hipStreamSynchronize(s));  // temporaries are freed on return
+        TD_HIP(hipStreamSynchronize(s));  // `work` is the caller's to free
     } else {
         hipLaunchKernelGGL(scale_transpose_f32_kernel, tile_grid(d, h), dim3(256), 0, s,
                            static_cast<const float*>(desc->W1), a, static_cast<float*>(work1), h, d);
@@ -1521,7 +1501,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
                              hipStream_t s) {
     const int64_t d = desc->d, h = desc->h;
     if (td_gemm_refuses_rows(h)) return TARDIS_ERR_SHAPE;   // (of all neurons, also where they come in chunks below)
-    DevBuf zt;
+    td_dev_buf zt;
     if (step <= 0.0f) {
         // The pre-activations of a chunk of neurons at a time: 64 MiB of them make one round of 256 x 256 tiles
         // over the 256 CUs, are still in the last-level cache when the fit reads them, and are the largest
@@ -1554,7 +1534,7 @@ tardis_status_t td_calibrate(const tardis_ffn_desc* desc, const void* X, int64_t
     if (lds > 48 * 1024)
         TD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(range_search_kernel),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    DevBuf capped;
+    td_dev_buf capped;
     TD_TRY(capped.alloc(sizeof(int)));
     TD_HIP(hipMemsetAsync(capped.p, 0, sizeof(int), s));
     hipLaunchKernelGGL(range_search_kernel, dim3((unsigned)h), dim3(kBlock), lds, s,
