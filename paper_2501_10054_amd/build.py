@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtardis.so")
+SIGMA_PROBE = os.path.join(OBJ, "sigma_probe.so")
 
 SOURCES = ["api.hip", "decode.hip", "forward.hip", "gemm.hip", "offline.hip", "prefill.hip", "stack.hip"]
 
@@ -53,8 +54,18 @@ def build(verbose: bool = True) -> str:
     os.replace(tmp, LIB)
     if verbose:
         print(f"built {LIB}")
+    build_sigma_probe()
     build_c_demo(verbose)
     return LIB
+
+
+def build_sigma_probe() -> str:
+    """tests/sigma_probe.hip: the library's activations on arrays, for the test that measures their error."""
+    os.makedirs(OBJ, exist_ok=True)
+    src = os.path.join(os.path.dirname(HERE), "tests", "sigma_probe.hip")
+    if os.path.exists(src):
+        _run([_hipcc(), *FLAGS, "-I" + CSRC, "-shared", src, "-o", SIGMA_PROBE])
+    return SIGMA_PROBE
 
 
 def build_c_demo(verbose: bool = True) -> str | None:

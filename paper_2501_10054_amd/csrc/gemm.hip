@@ -14,6 +14,7 @@
 #include <utility>
 
 #include "common.h"
+#include "sigma.h"
 #include "slices.h"
 
 namespace {
@@ -280,38 +281,6 @@ template <int EPI, int W, int WM, int NA, int NB> struct EpiRows {
     static constexpr int kWaveBytes = value * 16 * NB * 16 * 4, kBytes = W * kWaveBytes + kParams;
 };
 
-// sigma in the epilogues, where it is evaluated for whole rows of accumulators: no branches, so that several elements are under
-// way at once.  GELU = z Phi(z): for |z| < 1 Phi = 1/2 + z S(z^2), else from Phi(-|z|) = t exp(P(t) - z^2 / 2), t = 1 / (1 + 0.4 |z|);
-// S and P are minimax fits (to 3e-10 and 3e-8) of the two functions so defined.  Root mean square error against 64 bits for z from
-// N(0, 1.6^2): 3.6e-8, of the library functions' form (td_act) 3.9e-8; below -2 it is a tenth of the latter, which cancels there.
-// Infinities and NaNs give what they gave: +inf, and NaN for -inf.
-template <int ACT> __device__ __forceinline__ float act_flat(float z) {
-    if constexpr (ACT == TARDIS_ACT_GELU_ERF) {
-        const float u = fabsf(z), w = z * z;
-        const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, u, 1.0f));
-        float s = -7.6011511e-06f, p = -0.43888903f;
-        s = fmaf(s, w, 1.13367088e-04f);
-        s = fmaf(s, w, -1.18623779e-03f);
-        s = fmaf(s, w, 9.97329503e-03f);
-        s = fmaf(s, w, -6.64903596e-02f);
-        s = fmaf(s, w, 0.398942292f);
-        p = fmaf(p, t, 1.36559796f);                        // (P and z^2 / 2 in units of log 2)
-        p = fmaf(p, t, -1.33750927f);
-        p = fmaf(p, t, 0.194332317f);
-        p = fmaf(p, t, -0.0835891962f);
-        p = fmaf(p, t, 0.504601836f);
-        p = fmaf(p, t, 1.44168389f);
-        p = fmaf(p, t, -2.64764786f);
-        const float q = t * __builtin_amdgcn_exp2f(fmaf(u * -0.721347520f, u, p));
-        return z * (u < 1.0f ? fmaf(z, s, 0.5f) : z > 0.0f ? 1.0f - q : q);
-    } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
-        // (1 + tanh v) / 2 = 1 / (1 + exp(-2 v))
-        const float v = 0.79788456080286535588f * fmaf(0.044715f * z * z, z, z);
-        return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.88539008f * v));
-    } else {
-        return td_act(z, ACT);
-    }
-}
 template <typename F> __device__ __forceinline__ void with_act(int act, F f) {
     if (act == TARDIS_ACT_GELU_ERF) f(num<TARDIS_ACT_GELU_ERF>{});
     else if (act == TARDIS_ACT_GELU_TANH) f(num<TARDIS_ACT_GELU_TANH>{});

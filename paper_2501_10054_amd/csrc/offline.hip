@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "sigma.h"
 
 namespace {
 
@@ -548,53 +549,6 @@ __device__ __forceinline__ void sort_lds(float* vals, int npad) {
             }
             __syncthreads();
         }
-    }
-}
-
-// sigma in fp64 without branches, for the calibration's samples.  GELU = z Phi(z) from Phi(-|z|) = erfc(x) / 2, x = |z| / sqrt(2):
-// (1 + 2 x) exp(x^2) erfc(x) is a polynomial in (x - K) / (x + K) (the substitution of Shepherd and Laframboise, Math. Comp. 36,
-// 1981; K = 3.75, degree 20, the coefficients interpolate it at 400 Chebyshev points).  Against the library's erf (two
-// branches, of which a wavefront takes both): root mean square error 8.5e-17 instead of 1.6e-16 for z from -8 to 8, largest 8.9e-16 on either side.
-__device__ __forceinline__ double rcp_f64(double a) {              // a: a normal number
-    double r = __builtin_amdgcn_rcp(a);
-    r = fma(fma(-a, r, 1.0), r, r);
-    return fma(fma(-a, r, 1.0), r, r);
-}
-__device__ __forceinline__ double exp_f64(double y) {              // |y| <= 2^20: Taylor's series, 13 terms, on |r| <= log(2) / 2
-    const double n = rint(y * 1.4426950408889634074);
-    const double r = fma(n, -1.90821492927058770002e-10, fma(n, -6.93147180369123816490e-01, y));
-    constexpr double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
-                              1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
-    double s = c[12];
-#pragma unroll
-    for (int k = 11; k >= 0; --k) s = fma(s, r, c[k]);
-    return ldexp(s, (int)n);
-}
-template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
-    if constexpr (ACT == TARDIS_ACT_GELU_ERF) {
-        constexpr double K = 3.75;
-        constexpr double c[21] = {
-            1.2375126308378264, -0.14024059858550675, 0.0035854154857959016,
-            0.08227673848715551, -0.10880393015501522, 0.09230432122566992,
-            -0.05869339838179839, 0.028362276763635674, -0.009746581233908157,
-            0.001755629481119746, 0.00029372158155062665, -0.0002901662170030672,
-            5.162565962208987e-05, 2.2409881005582833e-05, -1.1399206978826016e-05,
-            -1.0082073330153207e-06, 1.6955385768824271e-06, -2.78242458762179e-08,
-            -2.1408381400078725e-07, 8.543261174054351e-09, 1.7505899450043215e-08};
-        const double x = fmin(fabs(z) * 0.70710678118654752440, 40.0);     // (erfc(40) is 0, and infinities stay what they were)
-        const double p = x + K, w = fma(2.0, x, 1.0), r = rcp_f64(p * w);
-        const double t = (x - K) * (w * r);
-        double s = c[20];
-#pragma unroll
-        for (int k = 19; k >= 0; --k) s = fma(s, t, c[k]);
-        const double half = 0.5 * s * (p * r) * exp_f64(-x * x);
-        return z * (z > 0.0 ? 1.0 - half : half);
-    } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
-        // (1 + tanh v) / 2 = 1 / (1 + exp(-2 v)); v beyond 350 is 350 (exp does not overflow, and 1e-304 is nothing to 1)
-        const double v = 0.79788456080286535588 * (z + 0.044715 * z * z * z);
-        return z * rcp_f64(1.0 + exp_f64(-2.0 * fmin(fmax(v, -350.0), 350.0)));
-    } else {
-        return td_act_f64(z, ACT);
     }
 }
 

@@ -1,0 +1,78 @@
+"""sigma without branches (sigma.h) against 64 bits, beside the library's form of it: no larger an error anywhere that
+the products' epilogues evaluate it, and infinities and NaNs as there."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_10054_amd import build as B
+
+pytestmark = pytest.mark.gpu
+ACT = {"gelu_erf": 0, "gelu_tanh": 1}
+
+
+@pytest.fixture(scope="module")
+def probe():
+    path = B.SIGMA_PROBE
+    if not os.path.exists(path):
+        B.build_sigma_probe()
+    lib = ctypes.CDLL(path)
+
+    def run(act, z):
+        z = torch.from_numpy(z).cuda()
+        flat, plain = torch.empty_like(z), torch.empty_like(z)
+        torch.cuda.synchronize()
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+        assert lib.sigma_probe(ACT[act], 8 * z.element_size(), ptr(z), ptr(flat), ptr(plain), ctypes.c_long(z.numel())) == 0
+        return flat.cpu().numpy(), plain.cpu().numpy()
+
+    return run
+
+
+def _exact32(z, act):
+    """in 64 bits, without cancellation"""
+    z = torch.from_numpy(z).double()
+    if act == "gelu_erf":
+        return (0.5 * z * torch.special.erfc(-z * 0.5 ** 0.5)).numpy()
+    v = (2 / np.pi) ** 0.5 * (z + 0.044715 * z ** 3)
+    return (z / (1 + torch.exp(-2 * v))).numpy()
+
+
+def _errors(got, want):
+    e = np.abs(got.astype(np.float64) - want)
+    return (e ** 2).mean() ** 0.5, e.max()
+
+
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh"])
+@pytest.mark.parametrize("spread", ["normal 1.6", "normal 0.5", "normal 4", "uniform 1", "uniform 8"])
+def test_32_bits(probe, act, spread):
+    rng = np.random.default_rng(len(spread) + ACT[act])
+    kind, s = spread.split()
+    z = (rng.normal(0, float(s), 1 << 21) if kind == "normal" else rng.uniform(-float(s), float(s), 1 << 21)).astype(np.float32)
+    flat, lib = probe(act, z)
+    want = _exact32(z, act)
+    (rms, most), (lib_rms, lib_most) = _errors(flat, want), _errors(lib, want)
+    print(f"{act} {spread}: rms {rms:.3g} (library {lib_rms:.3g}), largest {most:.3g} ({lib_most:.3g})")
+    assert rms <= lib_rms and most <= lib_most
+    if spread == "normal 1.6":
+        assert rms <= 4e-8
+    # of the value itself, where the library's form cancels
+    low = z < -2
+    if low.any():
+        rel = lambda got: np.sqrt((((got[low] - want[low]) / want[low]) ** 2).mean())
+        # (1 + erf z cancels more the further down z lies, and with it the library's error grows: a tenth is stated for the
+        # spread that reaches -8; half a unit of deviation reaches -2.6, where little is lost yet)
+        assert rel(flat) <= (0.1 if spread == "normal 1.6" else 1.0) * rel(lib)
+
+
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh"])
+@pytest.mark.parametrize("dtype", [np.float32])
+def test_values_at_the_ends(probe, act, dtype):
+    top = np.finfo(dtype).max
+    z = np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 30.0, 1e3, top, -30.0, -1e3, -top, 1e-30, -1e-30], dtype)
+    flat, _ = probe(act, z)
+    assert (flat[:2] == 0).all() and flat[2] == np.inf and np.isnan(flat[3]) and np.isnan(flat[4])
+    assert np.array_equal(flat[5:8], z[5:8]) and (np.abs(flat[8:11]) < 1e-30).all()
+    np.testing.assert_allclose(flat[11:], z[11:] / 2, rtol=1e-6)
