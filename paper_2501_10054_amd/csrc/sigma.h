@@ -79,9 +79,11 @@ template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
         const double half = 0.5 * s * (p * r) * exp_f64(-x * x);
         return z * (z > 0.0 ? 1.0 - half : half);
     } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
-        // (1 + tanh v) / 2 = 1 / (1 + exp(-2 v)); v beyond 350 is 350 (exp does not overflow, and 1e-304 is nothing to 1)
+        // as in 32 bits; |v| beyond 1e5 is 1e5 (where e is 0)
         const double v = 0.79788456080286535588 * (z + 0.044715 * z * z * z);
-        return z * rcp_f64(1.0 + exp_f64(-2.0 * fmin(fmax(v, -350.0), 350.0)));
+        const double e = exp_f64(fmax(-2.0 * fabs(v), -1e5));
+        const double q = e * rcp_f64(1.0 + e);
+        return z * (z > 0.0 ? 1.0 - q : q);
     } else {
         return td_act_f64(z, ACT);
     }

@@ -1,6 +1,7 @@
-"""sigma without branches (sigma.h) against 64 bits, beside the library's form of it: no larger an error anywhere that
-the products' epilogues evaluate it, and infinities and NaNs as there."""
+"""sigma without branches (sigma.h) against 64 bits and more, beside the library's form of it: no larger an error anywhere that
+the products' epilogues and the calibration evaluate it, and infinities and NaNs as there."""
 import ctypes
+import decimal
 import os
 
 import numpy as np
@@ -67,8 +68,47 @@ def test_32_bits(probe, act, spread):
         assert rel(flat) <= (0.1 if spread == "normal 1.6" else 1.0) * rel(lib)
 
 
+def _exact64(z, act):
+    """z Phi(z) in 60 digits"""
+    D = decimal.Decimal
+    with decimal.localcontext() as ctx:
+        ctx.prec = 60
+        k = (2 / D("3.14159265358979323846264338327950288419716939937510582097494459")).sqrt()
+        out = []
+        for v in z:
+            x = D(float(v))
+            if act == "gelu_erf":
+                term = total = x                      # int_0^z exp(-t^2 / 2) dt, term by term
+                n = 0
+                while abs(term) > D("1e-55"):
+                    n += 1
+                    term *= -x * x / (2 * n)
+                    total += term / (2 * n + 1)
+                out.append(x * (D("0.5") + total * k / 2))
+            else:
+                out.append(x / (1 + (-2 * k * (x + D("0.044715") * x ** 3)).exp()))
+        return out
+
+
+@pytest.mark.parametrize("act", ["gelu_tanh"])
+@pytest.mark.parametrize("spread", ["normal 1.6", "normal 0.6", "uniform 1", "uniform 8"])
+def test_64_bits(probe, act, spread):
+    rng = np.random.default_rng(7)
+    kind, s = spread.split()
+    z = rng.normal(0, float(s), 6000) if kind == "normal" else rng.uniform(-float(s), float(s), 6000)
+    flat, lib = probe(act, z)
+    want = _exact64(z, act)
+    err = lambda got: np.array([float(decimal.Decimal(float(g)) - w) for g, w in zip(got, want)])
+    e, f = err(flat), err(lib)
+    rms = lambda v: (v ** 2).mean() ** 0.5
+    print(f"{act} {spread}: rms {rms(e):.3g} (library {rms(f):.3g}), largest {np.abs(e).max():.3g} ({np.abs(f).max():.3g})")
+    assert rms(e) <= rms(f)
+    # results of 4 to 8 are 2^-50 apart, and what is rounded to half of that are two numbers: z Phi(z), and Phi(z) before it
+    assert np.abs(e).max() <= 2.0 ** -50 * 1.25
+
+
 @pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh"])
-@pytest.mark.parametrize("dtype", [np.float32])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_values_at_the_ends(probe, act, dtype):
     top = np.finfo(dtype).max
     z = np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 30.0, 1e3, top, -30.0, -1e3, -top, 1e-30, -1e-30], dtype)
