@@ -625,7 +625,7 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
                         float* __restrict__ a, float* __restrict__ c) {
     constexpr int NW = T / TD_WAVE;
     static_assert(NPT % 2 == 0 && T >= 256 && kSelBins % 256 == 0, "four cells a thread in the search for the ranks' cells");
-    extern __shared__ float vals[];                  // npad floats, only for the sort
+    extern __shared__ float vals[];                  // npad floats, for the sort and the parked samples
     __shared__ int hist[kSelBins];
     __shared__ int wave_tot[4];
     __shared__ float list[2][kSelList];
@@ -840,11 +840,22 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
     double s[3] = {0.0, 0.0, 0.0}, sq[3] = {0.0, 0.0, 0.0};          // count, sum dz, sum sigma; sum dz^2, sum dz sigma
     int inside = 0;
     auto sums = [&](auto act_constant) {
+        constexpr int ACT = decltype(act_constant)::value;
+        // (32 samples a thread beside the coefficients of this sigma are more than 128 registers: they go through LDS, each
+        // thread's own.  4096 neurons x 16384, 32768 samples: 1070, 1580 us, so 925, 1380)
+        constexpr bool kParked = NPT > 16 && ACT == TARDIS_ACT_GELU_ERF;
+        constexpr int kAtOnce = kParked ? 2 : NPT;
+        if constexpr (kParked) {
 #pragma unroll
+            for (int k = 0; k < NPT; ++k)
+                if (k * T + tid < n) vals[k * T + tid] = v[k];
+        }
+#pragma unroll kAtOnce
         for (int k = 0; k < NPT; ++k) {
-            const bool in = (k * T + tid < n) & (v[k] >= lo32) & (v[k] < hi32);
-            const double g = act_flat_f64<decltype(act_constant)::value>((double)(in ? v[k] : 0.0f));   // (sigma(0) = 0)
-            const double dz = (double)(in ? v[k] : pivot32) - pivot;
+            const float x = !kParked ? v[k] : k * T + tid < n ? vals[k * T + tid] : 0.0f;
+            const bool in = (k * T + tid < n) & (x >= lo32) & (x < hi32);
+            const double g = act_flat_f64<ACT>((double)(in ? x : 0.0f));   // (sigma(0) = 0)
+            const double dz = (double)(in ? x : pivot32) - pivot;
             inside += in ? 1 : 0;
             s[1] += dz;
             s[2] += g;

@@ -90,7 +90,7 @@ def _exact64(z, act):
         return out
 
 
-@pytest.mark.parametrize("act", ["gelu_tanh"])
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh"])
 @pytest.mark.parametrize("spread", ["normal 1.6", "normal 0.6", "uniform 1", "uniform 8"])
 def test_64_bits(probe, act, spread):
     rng = np.random.default_rng(7)
