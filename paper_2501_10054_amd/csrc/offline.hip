@@ -781,13 +781,13 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
     // (ranges that hold next to nothing have no end of their own to decide: by value)
     const bool wide = rank[1] < rank[2] && stat[2] - stat[1] > 1e-6f * fmaxf(fabsf(stat[1]), fabsf(stat[2]));
     float end[2];
-    double extra[2] = {0.0, 0.0};                    // samples (at about stat[2q]) to count in addition; may be negative
+    float cut[2];                                    // the samples inside are those with cut[0] <= v < cut[1]
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const float v0 = stat[2 * q], v1 = stat[2 * q + 1];
         const bool two = rank[2 * q + 1] != rank[2 * q];
         const float e32 = (float)((double)v0 + frac[q] * ((double)v1 - (double)v0));
-        end[q] = e32;
+        end[q] = cut[q] = e32;
         const float eps = fabsf(e32) * 2.4e-7f;      // two units in the last place
         if (!wide || (!(e32 - v0 <= eps) && !(two && v1 - e32 <= eps))) continue;   // (uniform: shared and uniform values)
         int near = 0;                                // samples in [v0, v1], and the first of either end
@@ -827,15 +827,24 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
         if (two && x0 == x1) continue;
         const double e0 = two ? fmin(x0, x1) : x0, e1 = two ? fmax(x0, x1) : x0;
         end[q] = (float)(e0 + frac[q] * (e1 - e0));
-        auto in = [&](double x) { return (q == 0 ? x >= (double)end[q] : x < (double)end[q]) ? 1.0 : 0.0; };
-        extra[q] = in(e0) - in((double)v0) + (two ? in(e1) - in((double)v1) : 0.0);
+        // (of the two samples the end lies between; no other has their values.  Are they equal here and only one of them inside, the
+        // other one is taken out by its index)
+        const int below = (e0 < (double)end[q] ? 1 : 0) + (two && e1 < (double)end[q] ? 1 : 0);
+        const bool split = two && below == 1, equal = split && v0 == v1;
+        cut[q] = below == 0 || (equal && q == 0) ? v0 : split && !equal ? v1 : nextafterf(two ? v1 : v0, INFINITY);
+        if (equal) {
+#pragma unroll
+            for (int k = 0; k < NPT; ++k)
+                if (k * T + tid == i0) v[k] = NAN;
+        }
     }
     const float lo32 = end[0], hi32 = end[1];
 
     // least-squares line of sigma(z) on z over the samples with lo32 <= z < hi32, in one pass: sums of dz = z - pivot, of
-    // sigma and of their products.  The pivot is a sample in the range (if there is one), so equal samples have dz = 0
-    // exactly; what the subtractions of the sums lose in fp64 is far below what fp32 resolves of z.
-    const float pivot32 = stat[0] >= lo32 ? stat[0] : stat[1];
+    // sigma and of their products.  The pivot is the first sample in the range (unless both next to the end are left out by its
+    // rounding), so equal samples have dz = 0 exactly; what the subtractions of the sums lose in fp64 is far below what fp32 resolves of
+    // z.  (A sample that is left out is in none of the sums: it may be far away.)
+    const float pivot32 = stat[0] >= cut[0] ? stat[0] : stat[1];
     const double pivot = (double)pivot32;
     double s[3] = {0.0, 0.0, 0.0}, sq[3] = {0.0, 0.0, 0.0};          // count, sum dz, sum sigma; sum dz^2, sum dz sigma
     int inside = 0;
@@ -853,7 +862,7 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
 #pragma unroll kAtOnce
         for (int k = 0; k < NPT; ++k) {
             const float x = !kParked ? v[k] : k * T + tid < n ? vals[k * T + tid] : 0.0f;
-            const bool in = (k * T + tid < n) & (x >= lo32) & (x < hi32);
+            const bool in = (k * T + tid < n) & (x >= cut[0]) & (x < cut[1]);
             const double g = act_flat_f64<ACT>((double)(in ? x : 0.0f));   // (sigma(0) = 0)
             const double dz = (double)(in ? x : pivot32) - pivot;
             inside += in ? 1 : 0;
@@ -868,18 +877,6 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
     else if (act == TARDIS_ACT_RELU) sums(std::integral_constant<int, TARDIS_ACT_RELU>{});
     else sums(std::integral_constant<int, TARDIS_ACT_IDENTITY>{});
     s[0] = (double)inside;
-    if (tid == 0) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (extra[q] != 0.0) {
-                const double ze = (double)stat[2 * q], dz = ze - pivot, g = td_act_f64(ze, act);
-                s[0] += extra[q];
-                s[1] += extra[q] * dz;
-                s[2] += extra[q] * g;
-                sq[0] += extra[q] * dz * dz;
-                sq[1] += extra[q] * dz * g;
-            }
-    }
     total3(s);
     total3(sq);
     float aj, cj;

@@ -38,3 +38,59 @@ def test_lines_far_from_zero_and_equal_samples(act, n):
         tol = 4 * off[j] / zi.std() + 2.0 ** -22
         assert abs(a[j] - oa[j]) <= tol, (j, a[j], oa[j], tol)
         assert abs(c[j] - oc[j]) <= tol * (np.abs(zi).max() + 1), (j, c[j], oc[j])
+
+
+@pytest.mark.parametrize("n", [300, 2000, 6000, 12000])
+def test_a_far_sample_that_the_end_leaves_out(n):
+    """Coverage 1: the smallest sample is the end itself, and where that is rounded up the sample lies outside.  It is 1000
+    away here, the others vary by 0.001: sums around it would lose eight digits of their deviations.  Pre-activations are
+    single products by one, exact, but for the far one's (-1000 - 1e-6, as fp32 -1000); the line is fp64's, rounded."""
+    rng = np.random.default_rng(n)
+    h, d = 8, 16
+    W1 = np.zeros((h, d), np.float32)
+    W1[:, :8], W1[:, 8] = np.eye(8), 1.0
+    X = np.zeros((n, d), np.float32)
+    X[:, :8] = 0.5 + 1e-3 * rng.normal(0, 1, (n, 8))
+    X[n // 3, :8], X[n // 3, 8] = -1000.0, -1e-6
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ffn = T.FFN(dev(W1), torch.zeros(d, h, device="cuda"), None, None, "gelu_erf")
+    lo, hi, a, c = (t.cpu().numpy().astype(np.float64) for t in T.tardis_calibrate(ffn, dev(X), 1.0))
+    z = X.astype(np.float64) @ W1.astype(np.float64).T
+    assert (lo == -1000.0).all() and (z.min(0) < lo).all() and (hi == z.max(0)).all()
+    for j in range(h):
+        zi = z[(z[:, j] >= lo[j]) & (z[:, j] < hi[j]), j]
+        assert len(zi) == n - 2
+        g, dz = O.act(zi, "gelu_erf"), zi - zi.mean()
+        slope = (dz * g).sum() / (dz * dz).sum()
+        # fp64 sums of deviations around a sample among them: 2^-53 of sigma over the deviation, far below one rounding to fp32
+        assert abs(a[j] - slope) <= 2.0 ** -24 * abs(slope) + 1e-11, (j, a[j] - slope)
+        assert abs(c[j] - (g.mean() - slope * zi.mean())) <= 2.0 ** -24 + 1e-11
+
+
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh", "relu", "identity"])
+@pytest.mark.parametrize("n", [300, 12000])
+def test_equal_samples_on_both_sides_of_an_end(n, act):
+    """The two smallest samples are one number in fp32 and differ in fp64; the end, between them, leaves the lower one out.  The same
+    at the upper end.  Pre-activations of the others are single products by one, exact."""
+    rng = np.random.default_rng(n)
+    h, d = 8, 16
+    W1 = np.zeros((h, d), np.float32)
+    W1[:, :8], W1[:, 8] = np.eye(8), 1.0
+    X = np.zeros((n, d), np.float32)
+    X[:, :8] = np.clip(rng.normal(0, 0.5, (n, 8)), -1.9, 1.9)
+    for at, value in ((7, -2.0), (n - 9, 2.0)):
+        X[at, :8], X[at, 8], X[at + 1, :8], X[at + 1, 8] = value, -3e-8, value, 3e-8
+    coverage = 1.0 - 0.2 / (n - 1)                   # ends a tenth of the way between the two samples
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ffn = T.FFN(dev(W1), torch.zeros(d, h, device="cuda"), None, None, act)
+    lo, hi, a, c = (t.cpu().numpy().astype(np.float64) for t in T.tardis_calibrate(ffn, dev(X), coverage))
+    z = X.astype(np.float64) @ W1.astype(np.float64).T
+    assert (lo == -2.0).all() and (hi == 2.0).all()
+    for j in range(h):
+        zi = z[(z[:, j] >= lo[j]) & (z[:, j] < hi[j]), j]
+        assert len(zi) == n - 2
+        g, dz = O.act(zi, act), zi - zi.mean()
+        slope = (dz * g).sum() / (dz * dz).sum()
+        # one rounding to fp32, and the two samples at the ends as fp32 has them: 3e-8 in n numbers of deviation 0.5
+        assert abs(a[j] - slope) <= 2.0 ** -24 * abs(slope) + 1e-8, (j, a[j] - slope)
+        assert abs(c[j] - (g.mean() - slope * zi.mean())) <= 2.0 ** -24 + 1e-8
