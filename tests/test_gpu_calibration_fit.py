@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh", "relu", "identity"])
 @pytest.mark.parametrize("n", [2, 3, 64, 1025, 4096, 9000])
 def test_lines_far_from_zero_and_equal_samples(act, n):
-    """Rows 0-7: equal samples (zero weights, biases -8 to 40): slope 0, the intercept sigma of the bias.  Rows 8-39: means
-    of -6 to 6 and deviations down to a hundredth of them.  The pre-activations are fp32 sums of 16 products and a bias: off
+    """Rows 0-7: equal samples (zero weights, biases -8 to 40): slope 0, the intercept sigma of the bias.  Rows 8-39 (from 64
+    samples on; fewer are the last test's): means of -6 to 6 and deviations down to a hundredth of them.  The pre-activations are fp32 sums of 16 products and a bias: off
     by at most 2^-21 of |z| + 1; a line through samples of deviation s moves by no more than 4 times that over s."""
     rng = np.random.default_rng(n)
     h, d = 40, 16
@@ -30,14 +30,17 @@ def test_lines_far_from_zero_and_equal_samples(act, n):
     assert (np.abs(lo - olo) <= off).all() and (np.abs(hi - ohi) <= off).all()
     assert (a[:8] == 0).all() and np.abs(c[:8] - O.act(b1[:8].astype(np.float64), act)).max() <= 2.0 ** -23 * 40
     inside = (z >= olo) & (z < ohi)
+    compared = 0
     for j in range(8, h):
         zi = z[inside[:, j], j]
         near = (np.abs(z[:, j] - olo[j]) <= off[j]) | (np.abs(z[:, j] - ohi[j]) <= off[j])
         if len(zi) < 3 or near.any():               # (a sample may fall on either side of an end)
             continue
+        compared += 1
         tol = 4 * off[j] / zi.std() + 2.0 ** -22
         assert abs(a[j] - oa[j]) <= tol, (j, a[j], oa[j], tol)
         assert abs(c[j] - oc[j]) <= tol * (np.abs(zi).max() + 1), (j, c[j], oc[j])
+    assert n < 64 or compared >= 20, compared
 
 
 @pytest.mark.parametrize("n", [300, 2000, 6000, 12000])
@@ -94,3 +97,28 @@ def test_equal_samples_on_both_sides_of_an_end(n, act):
         # one rounding to fp32, and the two samples at the ends as fp32 has them: 3e-8 in n numbers of deviation 0.5
         assert abs(a[j] - slope) <= 2.0 ** -24 * abs(slope) + 1e-8, (j, a[j] - slope)
         assert abs(c[j] - (g.mean() - slope * zi.mean())) <= 2.0 ** -24 + 1e-8
+
+
+@pytest.mark.parametrize("act", ["gelu_erf", "gelu_tanh", "relu", "identity"])
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+def test_no_one_and_two_samples_inside(n, act):
+    """Coverage 0.9 of n samples leaves n - 2 inside: no line but a constant, sigma(lo) without any and sigma(z) of one; two make the
+    line through them.  Pre-activations are single products by one, exact."""
+    rng = np.random.default_rng(10 + n)
+    h = d = 40
+    X = rng.normal(0, 1.5, (n, d)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ffn = T.FFN(dev(np.eye(h, dtype=np.float32)), torch.zeros(d, h, device="cuda"), None, None, act)
+    lo, hi, a, c = (t.cpu().numpy().astype(np.float64) for t in T.tardis_calibrate(ffn, dev(X), 0.9))
+    for j in range(h):
+        z = X[:, j].astype(np.float64)
+        zi = z[(z >= lo[j]) & (z < hi[j])]
+        assert len(zi) == max(n - 2, 0)
+        if len(zi) < 2:
+            want = 0.0, O.act(zi if len(zi) else np.array([lo[j]]), act)[0]
+        else:
+            g = O.act(zi, act)
+            slope = (g[1] - g[0]) / (zi[1] - zi[0])
+            want = slope, g.mean() - slope * zi.mean()
+        for got, w in zip((a[j], c[j]), want):
+            assert abs(got - w) <= 2.0 ** -24 * abs(w) + 1e-13 * (1 + 1 / (np.ptp(zi) if len(zi) == 2 else 1)), (j, got, w)
