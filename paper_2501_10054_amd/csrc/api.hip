@@ -39,8 +39,8 @@ tardis_status_t check_desc(const tardis_ffn_desc* desc) {
 // 1.5 to 8 ms, the fold's kernels 1.0: fold, copies of its results and destroy 5.8 -> 1.25 ms.  Bounded: at most kKeepBlocks blocks and
 // kKeepBytes in all, the oldest goes first; given back when an allocation of this library fails.  A block is
 // used again for a layer of its own size or down to three quarters of it, on its own device, and only after everything
-// that ran there has ended (tardis_destroy's caller has synchronised; hipFree would wait as well), so whatever stream
-// and thread the next fold uses.
+// that ran there has ended, so whatever stream and thread the next fold uses: the fold that takes it waits for the device
+// (tardis_destroy itself waits for nothing that a capture on another stream would not survive).
 class KeptMemory {
    public:
     // a block of at least `bytes` (*size: what it has), or null
@@ -58,13 +58,7 @@ class KeptMemory {
         return p;
     }
     void give(void* p, size_t bytes, int device) {
-        int current = 0;
-        const bool known = hipGetDevice(&current) == hipSuccess;
-        bool idle = bytes <= kKeepBytes && known && (current == device || hipSetDevice(device) == hipSuccess);
-        idle = idle && hipDeviceSynchronize() == hipSuccess;
-        if (known && current != device) (void)hipSetDevice(current);
-        if (!idle) {
-            (void)hipGetLastError();
+        if (bytes > kKeepBytes) {
             (void)hipFree(p);
             return;
         }
@@ -114,6 +108,11 @@ class Arena {
         if (n_ > kMaxParts) return TARDIS_ERR_SHAPE;
         TD_HIP(hipGetDevice(&L->device));
         void* v = g_kept.take(L->device, total_, &L->memory_bytes);
+        if (v && hipDeviceSynchronize() != hipSuccess) {   // (what a destroyed layer's caller did not wait for, as hipFree does)
+            (void)hipGetLastError();
+            g_kept.give(v, L->memory_bytes, L->device);
+            v = nullptr;
+        }
         if (!v) {
             L->memory_bytes = total_ ? total_ : 256;
             hipError_t e = hipMalloc(&v, L->memory_bytes);

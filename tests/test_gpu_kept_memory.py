@@ -80,3 +80,28 @@ def test_threads_with_streams_of_their_own():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+def test_a_layer_destroyed_during_a_capture():
+    """By the C call: Layer.close() waits for the device, which no capture survives."""
+    keep, x = _layer(1024, 4096, 7, 2)
+    gone, _ = _layer(1024, 4096, 8, 2)
+    want = T.tardis_ffn_forward_batched(keep, x).clone()
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=stream):
+        y = T.tardis_ffn_forward_batched(keep, x)
+        assert T.lib().tardis_destroy(gone.handle) == T.OK
+        gone.handle = None
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        # one token's or two tokens' sums, rounded to bf16 (see _same)
+        assert ((y.float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs() + 2.0 ** -12 * want.float().abs().max()).all()
+        again, x2 = _layer(1024, 4096, 9, 2)         # (on the memory of the destroyed one)
+        T.tardis_ffn_forward_batched(again, x2)
+        torch.cuda.synchronize()
+        again.close()
+    keep.close()

@@ -92,3 +92,24 @@ def test_a_fold_that_a_capture_refuses_leaves_nothing_in_it(hip, opts):
     st, L = hip.fold(**opts)
     assert st == T.OK and hip.lib.tardis_destroy(L) == T.OK
     assert not set(hip.events()) & {"wild-free", "wild-write"}
+
+
+def test_a_layer_destroyed_during_a_capture_does_not_spoil_it(hip):
+    """To wait for the device ends every capture in progress; whoever destroys a layer meanwhile need not know of one."""
+    layers = [hip.fold(d=512, h=2048 + 512 * k)[1] for k in range(6)]
+    hip.lib.fake_capture(1)
+    for L in layers:
+        assert hip.lib.tardis_destroy(L) == T.OK
+    hip.lib.fake_capture(0)
+    assert not hip.lib.fake_broken()
+
+
+def test_kept_memory_is_written_only_after_the_device_was_idle(hip):
+    """A caller may have left work on a layer's memory under way."""
+    L = hip.fold()[1]
+    hip.lib.tardis_destroy(L)
+    hip.events()
+    st, L = hip.fold()
+    events = hip.events()
+    assert st == T.OK and "sync" in events and events.index("sync") < min(events.index(e) for e in ("set", "copy", "launch"))
+    hip.lib.tardis_destroy(L)
