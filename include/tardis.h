@@ -352,12 +352,17 @@ tardis_status_t tardis_get_last_union(tardis_handle_t L, int64_t n, uint32_t* un
 tardis_status_t tardis_get_handover(tardis_handle_t L, int64_t n, void* out, void* stream);
 
 /* Frees everything the handle owns.  The caller must have synchronised every
- * stream that used it.  The device memory of up to four destroyed layers, 1 GiB
- * in all, stays with the library for the next tardis_fold of that size; it is
- * returned to the device when an allocation of a fold fails.  NULL is accepted; a
- * pointer that is not a live handle (destroyed before, or never made here)
+ * stream that used it.  The device memory of the layer destroyed last, up to
+ * 1 GiB, stays with the library for the next tardis_fold of that size, if at least
+ * half of the device's memory is free at this call; it is returned to the device
+ * when an allocation of the library fails, when another layer is destroyed, and
+ * by tardis_release_memory.  NULL is accepted; a pointer that is not a live handle (destroyed before, or never made here)
  * returns TARDIS_ERR_STATE. */
 tardis_status_t tardis_destroy(tardis_handle_t L);
+
+/* Returns to the device what tardis_destroy has kept (nothing to return is no
+ * error).  For a program whose other allocations need the last of the device. */
+tardis_status_t tardis_release_memory(void);
 
 /* Static, NUL-terminated description of a status code (host). */
 const char* tardis_status_string(tardis_status_t s);

@@ -35,9 +35,10 @@ tardis_status_t check_desc(const tardis_ffn_desc* desc) {
     return TARDIS_OK;
 }
 
-// Memory of destroyed layers, kept for the next fold.  Mapping and unmapping a layer (370 MB at d = 4096, h = 16384) takes
-// 1.5 to 8 ms, the fold's kernels 1.0: fold, copies of its results and destroy 5.8 -> 1.25 ms.  Bounded: at most kKeepBlocks blocks and
-// kKeepBytes in all, the oldest goes first; given back when an allocation of this library fails.  A block is
+// The memory of the layer destroyed last, kept for the next fold.  Mapping and unmapping a layer (370 MB at d = 4096, h = 16384) takes
+// 0.3 ms in a process that holds little memory and up to 9 in one that holds much, the fold's kernels 1.0.  Bounded: one block of at
+// most kKeepBytes, and none where less than half of the device's memory is free (whoever destroys a layer there may do so to have
+// room); given back when an allocation of this library fails and by tardis_release_memory.  A block is
 // used again for a layer of its own size or down to three quarters of it, on its own device, and only after everything
 // that ran there has ended, so whatever stream and thread the next fold uses: the fold that takes it waits for the device
 // (tardis_destroy itself waits for nothing that a capture on another stream would not survive).
@@ -46,53 +47,51 @@ class KeptMemory {
     // a block of at least `bytes` (*size: what it has), or null
     void* take(int device, size_t bytes, size_t* size) {
         std::lock_guard<std::mutex> guard(lock_);
-        int best = -1;
-        for (int i = 0; i < n_; ++i)
-            if (block_[i].device == device && block_[i].bytes >= bytes && block_[i].bytes / 4 * 3 <= bytes &&
-                (best < 0 || block_[i].bytes < block_[best].bytes))
-                best = i;
-        if (best < 0) return nullptr;
-        void* p = block_[best].p;
-        *size = block_[best].bytes;
-        remove(best);
-        return p;
+        if (!block_.p || block_.device != device || block_.bytes < bytes || block_.bytes / 4 * 3 > bytes) return nullptr;
+        *size = block_.bytes;
+        return swap({}).p;
     }
     void give(void* p, size_t bytes, int device) {
-        if (bytes > kKeepBytes) {
+        int current = 0;
+        size_t left = 0, total = 0;
+        const bool keep = bytes <= kKeepBytes && hipGetDevice(&current) == hipSuccess && current == device &&
+                          hipMemGetInfo(&left, &total) == hipSuccess && left >= total / 2;
+        if (!keep) {
+            (void)hipGetLastError();
             (void)hipFree(p);
             return;
         }
-        std::lock_guard<std::mutex> guard(lock_);
-        size_t total = bytes;
-        for (int i = 0; i < n_; ++i) total += block_[i].bytes;
-        while (n_ > 0 && (n_ == kKeepBlocks || total > kKeepBytes)) {
-            total -= block_[0].bytes;
-            (void)hipFree(block_[0].p);
-            remove(0);
+        Block old;
+        {
+            std::lock_guard<std::mutex> guard(lock_);
+            old = swap({p, bytes, device});
         }
-        block_[n_++] = {p, bytes, device};
+        if (old.p) (void)hipFree(old.p);
     }
-    bool give_back() {                                // everything; false: there was nothing
-        std::lock_guard<std::mutex> guard(lock_);
-        const bool any = n_ > 0;
-        while (n_ > 0) (void)hipFree(block_[--n_].p);
-        return any;
+    bool give_back() {                                // false: there was nothing
+        Block old;
+        {
+            std::lock_guard<std::mutex> guard(lock_);
+            old = swap({});
+        }
+        if (old.p) (void)hipFree(old.p);
+        return old.p != nullptr;
     }
 
    private:
-    static constexpr int kKeepBlocks = 4;
     static constexpr size_t kKeepBytes = (size_t)1 << 30;
     struct Block {
-        void* p;
-        size_t bytes;
-        int device;
+        void* p = nullptr;
+        size_t bytes = 0;
+        int device = 0;
     };
-    void remove(int i) {
-        for (--n_; i < n_; ++i) block_[i] = block_[i + 1];
+    Block swap(const Block& with) {
+        const Block old = block_;
+        block_ = with;
+        return old;
     }
     std::mutex lock_;
-    Block block_[kKeepBlocks];                        // oldest first
-    int n_ = 0;
+    Block block_;
 };
 KeptMemory g_kept;
 
@@ -532,6 +531,11 @@ tardis_status_t tardis_destroy(tardis_handle_t L) {
         if (g_live.erase(L) == 0) return TARDIS_ERR_STATE;   // not a handle of this library, or destroyed already
     }
     free_layer(L);
+    return TARDIS_OK;
+}
+
+tardis_status_t tardis_release_memory(void) {
+    (void)td_give_back_memory();
     return TARDIS_OK;
 }
 

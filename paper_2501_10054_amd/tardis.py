@@ -25,7 +25,7 @@ EXPORTS = (
     "tardis_calibrate", "tardis_calibrate_search", "tardis_estimate_errors", "tardis_assign_thresholds", "tardis_fold", "tardis_ffn_forward", "tardis_ffn_forward_batched",
     "tardis_ffn_forward_static", "tardis_stack_forward", "tardis_dense_forward", "tardis_get_folded", "tardis_get_predictor_state",
     "tardis_get_sketch_groups", "tardis_get_last_outliers", "tardis_get_last_union", "tardis_get_handover", "tardis_set_next_layer",
-    "tardis_destroy", "tardis_status_string", "tardis_version",
+    "tardis_destroy", "tardis_release_memory", "tardis_status_string", "tardis_version",
 )
 
 
@@ -75,6 +75,7 @@ def lib() -> C.CDLL:
         L.tardis_get_last_union.argtypes = [vp, i64, vp, vp, vp]
         L.tardis_get_handover.argtypes = [vp, i64, vp, vp]
         L.tardis_destroy.argtypes = [vp]
+        L.tardis_release_memory.argtypes = []
         L.tardis_status_string.argtypes = [C.c_int]
         L.tardis_status_string.restype = C.c_char_p
         L.tardis_version.argtypes = []
@@ -289,3 +290,8 @@ def tardis_get_last_union(L: Layer, n: int, want_mask: bool = False, stream=None
     um = torch.empty((L.h + 31) // 32, dtype=torch.int32, device=L.device) if want_mask else None
     _check(lib().tardis_get_last_union(L.handle, n, _ptr(um), _ptr(cnt), _stream(stream)), "tardis_get_last_union")
     return cnt, um
+
+
+def tardis_release_memory():
+    """Returns to the device the memory that the library keeps of the layer closed last (see tardis_destroy)."""
+    _check(lib().tardis_release_memory(), "tardis_release_memory")
