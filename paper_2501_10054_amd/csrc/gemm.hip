@@ -82,10 +82,11 @@ gemm_nt_generic_kernel(const T* __restrict__ A, const T* __restrict__ B, float* 
 
 
 // ------------------------------------------------------------------ MFMA (bf16 or int8)
-// One kernel for every product on the matrix cores, with the step that follows the product in its
-// epilogue.  Output tile TM x TN = (WM*NA*16) x ((8/WM)*NB*16), 8 wavefronts in a WM x (8/WM) grid, each
-// NA x NB tiles of v_mfma_f32_16x16x32_bf16 / v_mfma_i32_16x16x64_i8 (the byte geometry of the two is the
-// same: 16 bytes per lane and MFMA).  K runs in slices of 128 bytes per row.
+// Two kernels for the products on the matrix cores, with the step that follows the product in their
+// epilogue (finish_tile): gemm_tile_kernel, 8 wavefronts in a WM x (8/WM) grid, each NA x NB tiles of
+// v_mfma_f32_16x16x32_bf16 / v_mfma_i32_16x16x64_i8 (the byte geometry of the two is the same: 16 bytes per lane
+// and MFMA), so an output tile of (WM*NA*16) x ((8/WM)*NB*16); and gemm_quad_kernel, 4 wavefronts in a 2 x 2 grid, for
+// large tiles.  K runs in slices of 128 bytes per row (256 for few rows).
 //
 // What bounds it.  With real (not constant) data the chip is power limited: the clock settles where the
 // energy per MFMA and per moved byte allows (a loop of nothing but 16x16x32 MFMAs on random data runs at
@@ -105,8 +106,8 @@ gemm_nt_generic_kernel(const T* __restrict__ A, const T* __restrict__ B, float* 
 //  * blocks start at different slices (rotated within a window of 8 between the blocks of an XCD, which
 //    share lines in its L2, and by an eighth of K from XCD to XCD): with all of them at the same column of
 //    K the requests crowd onto few memory channels (zeros: 358 -> 300 us at 4096 x 4096 x 16384).
-// 4096 x 4096 x 16384 in bf16 with random data: 390 us, 1.41 PFLOP/s (one wavefront per SIMD with staging
-// through registers, which was here before: 605 us, 0.91).
+// 4096 x 4096 x 16384 in bf16 with random data (tile 256 x 256, kernel trace): 404 us with eight wavefronts, 375 with four (360 to
+// 390 from card to card), 1.47 PFLOP/s; with staging through registers 605, 0.91.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef td_i32x4 i32x4_t;
@@ -299,8 +300,8 @@ struct GemmTile {
     // output product, whose blocks share lines between K ranges, loses by it: 31.7 -> 35.5 us)
     static constexpr bool kOnce = TM == 64 && EPI == EPI_REPAIR;
     static constexpr int LA = UA / 8192, LB = UB / 8192;                        // loads per wavefront and slice
-    // REPAIR: bounds and exponents wait in LDS for the range test (the largest tile has no room and reads them then)
-    static constexpr int kPar = EPI == EPI_REPAIR && TM * TN < 256 * 256 ? 3 * 1024 : 0;
+    // REPAIR: bounds and exponents wait in LDS for the range test
+    static constexpr int kPar = EPI == EPI_REPAIR ? 3 * 1024 : 0;
     // as many slices as fit; A one ahead of B where the two do not fit equally often
     static constexpr int kRoom = kLdsBytes - kPar;
     static constexpr int SB = kRoom / (UA + UB) > 10 ? 10 : kRoom / (UA + UB);
@@ -313,6 +314,7 @@ struct GemmTile {
     static constexpr int kEpiLds = EpiRows<EPI, kWavesPerTile, WM, NA, NB>::kBytes;
     static constexpr int kLds = kRing + kPar > kEpiLds ? kRing + kPar : kEpiLds;
     static_assert(SL % 128 == 0 && UA % 8192 == 0 && UB % 8192 == 0, "whole loads of 1 KB for 8 wavefronts");
+    static_assert(TM <= 256 && TN <= 256, "a load of 1 KB for each parameter");
     static_assert(SB >= 2 && SA >= 2 && kWait + kPer <= 63 && kLds <= kLdsBytes, "slice buffers");
 };
 
@@ -464,48 +466,48 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
             float* C = EPI == EPI_PART ? p.C + (size_t)ks * p.M * p.N : p.C;
             const bool add = EPI == EPI_F32 && p.accumulate;
             bf16_t* rounded = add ? p.out : nullptr;
-                            if (p.N % 4 == 0) {                                  // (C is 16-byte aligned)
-                                constexpr int RPS = 64 / PC, S = RB * 16 / RPS, U = S % 8 == 0 ? 8 : S % 4 == 0 ? 4 : S % 2 == 0 ? 2 : 1;   // rows at a time; times
-                                static_assert(RB * 16 % (RPS * U) == 0, "whole steps");
-                                const int row0 = lane / PC, piece = lane % PC;
-                                const bool whole = m1 + RB * 16 <= p.M;          // (uniform)
-                                float* at = C + (m1 + row0) * p.N + nw + piece * 4;
-                                if (nw + piece * 4 < p.N) {
+            if (p.N % 4 == 0) {                                  // (C is 16-byte aligned)
+                constexpr int RPS = 64 / PC, S = RB * 16 / RPS, U = S % 8 == 0 ? 8 : S % 4 == 0 ? 4 : S % 2 == 0 ? 2 : 1;   // rows at a time; times
+                static_assert(RB * 16 % (RPS * U) == 0, "whole steps");
+                const int row0 = lane / PC, piece = lane % PC;
+                const bool whole = m1 + RB * 16 <= p.M;          // (uniform)
+                float* at = C + (m1 + row0) * p.N + nw + piece * 4;
+                if (nw + piece * 4 < p.N) {
 #pragma unroll 1
-                                    for (int row = row0; row < RB * 16; row += RPS * U, at += RPS * U * p.N) {
-                                        f32x4_t v[U];
+                    for (int row = row0; row < RB * 16; row += RPS * U, at += RPS * U * p.N) {
+                        f32x4_t v[U];
 #pragma unroll
-                                        for (int u = 0; u < U; ++u) v[u] = piece_of(row + u * RPS, piece);
-                                        if (add) {
-                                            f32x4_t old[U];
+                        for (int u = 0; u < U; ++u) v[u] = piece_of(row + u * RPS, piece);
+                        if (add) {
+                            f32x4_t old[U];
 #pragma unroll
-                                            for (int u = 0; u < U; ++u)
-                                                if (whole || m1 + row + u * RPS < p.M) old[u] = *reinterpret_cast<const f32x4_t*>(at + u * RPS * p.N);
+                            for (int u = 0; u < U; ++u)
+                                if (whole || m1 + row + u * RPS < p.M) old[u] = *reinterpret_cast<const f32x4_t*>(at + u * RPS * p.N);
 #pragma unroll
-                                            for (int u = 0; u < U; ++u)
+                            for (int u = 0; u < U; ++u)
 #pragma unroll
-                                                for (int q = 0; q < 4; ++q) v[u][q] = old[u][q] + v[u][q];
-                                        }
+                                for (int q = 0; q < 4; ++q) v[u][q] = old[u][q] + v[u][q];
+                        }
 #pragma unroll
-                                        for (int u = 0; u < U; ++u)
-                                            if (whole || m1 + row + u * RPS < p.M) {
-                                                if (rounded) *reinterpret_cast<uint2*>(rounded + (at - C) + u * RPS * p.N) = make_uint2(to_bf16x2(v[u][0], v[u][1]), to_bf16x2(v[u][2], v[u][3]));
-                                                else *reinterpret_cast<f32x4_t*>(at + u * RPS * p.N) = v[u];
-                                            }
-                                    }
-                                }
-                            } else {
-#pragma unroll 1
-                                for (int t = lane; t < RB * 16 * CW; t += 64) {
-                                    const int row = t / CW, col = t % CW;
-                                    const float v = piece_of(row, col >> 2)[col & 3];
-                                    const int64_t mm = m1 + row, nn = nw + col;
-                                    if (mm >= p.M || nn >= p.N) continue;
-                                    const float sum = add ? C[mm * p.N + nn] + v : v;
-                                    if (rounded) rounded[mm * p.N + nn] = (bf16_t)to_bf16x2(sum, 0.0f);
-                                    else C[mm * p.N + nn] = sum;
-                                }
+                        for (int u = 0; u < U; ++u)
+                            if (whole || m1 + row + u * RPS < p.M) {
+                                if (rounded) *reinterpret_cast<uint2*>(rounded + (at - C) + u * RPS * p.N) = make_uint2(to_bf16x2(v[u][0], v[u][1]), to_bf16x2(v[u][2], v[u][3]));
+                                else *reinterpret_cast<f32x4_t*>(at + u * RPS * p.N) = v[u];
                             }
+                    }
+                }
+            } else {
+#pragma unroll 1
+                for (int t = lane; t < RB * 16 * CW; t += 64) {
+                    const int row = t / CW, col = t % CW;
+                    const float v = piece_of(row, col >> 2)[col & 3];
+                    const int64_t mm = m1 + row, nn = nw + col;
+                    if (mm >= p.M || nn >= p.N) continue;
+                    const float sum = add ? C[mm * p.N + nn] + v : v;
+                    if (rounded) rounded[mm * p.N + nn] = (bf16_t)to_bf16x2(sum, 0.0f);
+                    else C[mm * p.N + nn] = sum;
+                }
+            }
         }
         __builtin_amdgcn_wave_barrier();
     });
@@ -613,7 +615,7 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
     constexpr int kReadEvery = NM / NR > 2 ? 2 : (NM / NR > 0 ? NM / NR : 1), kReadsPer = (NR + NM - 1) / NM;
     constexpr int kLoadEvery = NM / G::kPer > 0 ? NM / G::kPer : 1, kLoadsPer = (G::kPer + NM - 1) / NM;
 
-    if constexpr (G::kPar > 0) {
+    if constexpr (EPI == EPI_REPAIR) {
         const uint32_t at = __builtin_amdgcn_readfirstlane(
             (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + G::kRing + wave * 1024);
         if (wave == 0) load_to_lds(at, lane * 16, buffer_of(p.lo + n0, rows_b * 4), 0u);
@@ -707,25 +709,16 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
         int ex[NA];
         const float* par = reinterpret_cast<const float*>(lds + G::kRing);
         const int nc = wn * NB * 16 + 4 * fp, mr = wm * NA * 16 + frow;   // first column, row of this lane in the tile
-        const f32x4_t none = {0, 0, 0, 0};
         uint32_t columns = 0u;                        // flags of existing columns
 #pragma unroll
         for (int j = 0; j < NB; ++j) {                // N % 8 == 0: four columns or none
             const bool in = n0 + nc + j * 16 < p.N;
             columns |= in ? 15u << (4 * j) : 0u;
-            if constexpr (G::kPar > 0) {
-                lo[j] = *reinterpret_cast<const f32x4_t*>(par + nc + j * 16);
-                hi[j] = *reinterpret_cast<const f32x4_t*>(par + 256 + nc + j * 16);
-            } else {
-                lo[j] = in ? *reinterpret_cast<const f32x4_t*>(p.lo + n0 + nc + j * 16) : none;
-                hi[j] = in ? *reinterpret_cast<const f32x4_t*>(p.hi + n0 + nc + j * 16) : none;
-            }
+            lo[j] = *reinterpret_cast<const f32x4_t*>(par + nc + j * 16);
+            hi[j] = *reinterpret_cast<const f32x4_t*>(par + 256 + nc + j * 16);
         }
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            if constexpr (G::kPar > 0) ex[i] = reinterpret_cast<const int*>(par)[512 + mr + i * 16];
-            else ex[i] = m0 + mr + i * 16 < p.M ? p.e[m0 + mr + i * 16] : 0;
-        }
+        for (int i = 0; i < NA; ++i) ex[i] = reinterpret_cast<const int*>(par)[512 + mr + i * 16];
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             bits[i] = 0u;
@@ -770,8 +763,8 @@ __global__ void __launch_bounds__(512) gemm_tile_kernel(GemmArgs p, TileMap tm) 
 // One wavefront per SIMD hides nothing behind another one, so what stands between two MFMAs (16 cycles, four issue slots)
 // is placed by hand, one thing to a gap: a fragment read in every second gap of a half slice, and in equal distances
 // over the whole slice the loads that refill the ring, m0 in one gap and the load in the next (which is also the wait state
-// between them).  The same loads in bursts or with everything in one gap: 300 instead of 277 us on zeros, 392 instead of 376
-// on random data, 4096 x 4096 x 16384 (eight wavefronts: 325, 404).
+// between them).  The same loads in bursts or with everything in one gap: 392 instead of 376 us, 4096 x 4096 x 16384 on random data
+// (eight wavefronts: 404).
 template <int EPI, int NA, int NB>
 struct QuadTile {
     static constexpr int SL = 128, TM = 32 * NA, TN = 32 * NB, UA = TM * SL, UB = TN * SL;
@@ -1069,9 +1062,11 @@ __global__ void __launch_bounds__(256, 1) gemm_quad_kernel(GemmArgs p, TileMap t
 
 // The tile for a product of more than 64 rows: the one with the least time by
 //     rounds over 256 CUs x (slices x time of a slice + time of the prologue and epilogue) + partial sums,
-// with the measured times below (least squares over 10 tiles, 512 products: d, h from 512, 2048 to 4096, 16384, 70 to 3000
-// tokens, all epilogues; random data, the clock that the power limit leaves).  Over those the tile so chosen takes 0.4 % longer than the best one
-// (mean; 15 % at most); by the larger of MFMA cycles and operand bytes at a fixed rate, the rule before, 7 %.
+// with the times below (least squares over 10 tiles, 512 products: d, h from 512, 2048 to 4096, 16384, 70 to 3000 tokens, all
+// epilogues).  The slices' times are those of operands of zeros, which draw less power: 2048 x 16384 x 4096 with sigma is 197 us by the
+// rule, 193 measured on zero weights and 258 on random ones, and on random data the other large products take 1.3 to 1.4 times the
+// rule's time as well (range test 340 for 268, calibration 103 for 73, fold 375 for 275).  So the rule ranks tiles, and takes an
+// epilogue for more slices than it costs.
 // Four wavefronts (Q) take less per slice, eight finish a tile with a range test or sigma sooner.
 // Up to 64 rows the weights stream from memory: the larger of MFMA cycles and of the cycles in which the operands arrive, at 34
 // bytes per cycle and CU (a chosen number, which ranks these tiles; the larger one for slices of 256 bytes stands for longer runs from HBM: 64

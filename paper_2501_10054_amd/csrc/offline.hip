@@ -332,13 +332,7 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
     }
 }
 
-// Grouped low-bit sketch (groups of 32 consecutive columns), codes of 4, 3 or 2 bits with the
-// largest code qmax = 7, 3 or 1: group maxima g, row maximum r,
-// s = r / (qmax*15), multiplier m = ceil(g / (qmax s)) in [1, 15], code q = rint(w / (m s)) in [-qmax, qmax];
-// all in fp64, each step one IEEE operation, so every output is a function of the inputs.
-// Outputs: M4 (one byte per group); Q (optional) the effective one-byte code m*q; Q4 (optional,
-// d % 32 == 0) the packed form read by the decode kernel: group G is the 16-byte vector G of the
-// row, byte b of its dword w holds column 4w+b in the low nibble and column 16+4w+b in the high one.
+// the predictor's bounds of a neuron with a low-bit sketch, in units of s
 __device__ __forceinline__ void low_bit_bounds(float lo, float hi, float margin, double b, bool live, double s, float* tlo, float* thi) {
     double rl, rh;
     predictor_range((double)lo, (double)hi, (double)margin, rl, rh);
@@ -352,12 +346,19 @@ __device__ __forceinline__ void low_bit_bounds(float lo, float hi, float margin,
     }
 }
 
-// (rows that are not whole groups: no packed form)
+// Grouped low-bit sketch (groups of 32 consecutive columns), codes of 4, 3 or 2 bits with the
+// largest code qmax = 7, 3 or 1: group maxima g, row maximum r,
+// s = r / (qmax*15), multiplier m = ceil(g / (qmax s)) in [1, 15], code q = rint(w / (m s)) in [-qmax, qmax];
+// all in fp64, each step one IEEE operation, so every output is a function of the inputs.
+// Outputs: M4 (one byte per group); Q (optional) the effective one-byte code m*q; Q4 (optional,
+// d % 32 == 0) the packed form read by the decode kernel: group G is the 16-byte vector G of the
+// row, byte b of its dword w holds column 4w+b in the low nibble and column 16+4w+b in the high one.
+// (This kernel: rows that are not whole groups, for which there is no packed form.)
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch4_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
                const float* __restrict__ hi, int64_t d, int ng, int8_t* __restrict__ Q, uint8_t* __restrict__ M4,
-                float* __restrict__ tlo, float* __restrict__ thi, int qmax, float margin) {
+               float* __restrict__ tlo, float* __restrict__ thi, int qmax, float margin) {
     extern __shared__ int gval[];                    // group maxima (bit patterns), then multipliers
     __shared__ float red[kBlock / TD_WAVE];
     const int64_t j = blockIdx.x;
@@ -608,8 +609,8 @@ __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo
 // stretches the histogram, or most samples are equal - or that are not all finite falls back to the sort in LDS.)  The fit takes
 // sigma of every sample once, in fp64.
 // What bounds it: vector instructions, about half of them for sigma (without it 59 of 107 us).  4096 neurons x 4096 samples:
-// 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 91 us with the sigma
-// above and one pass.  (A full bitonic sort in LDS and sigma taken twice: 375.)
+// 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 89 us with the sigma of
+// sigma.h and one pass.  (A full bitonic sort in LDS and sigma taken twice: 375.)
 //
 // A sample closer to the end of a range than fp32 can tell (both are fp32 here) would count as inside or
 // outside by luck of rounding.  For those (a few of 16384 neurons) the pre-activations of the two samples
