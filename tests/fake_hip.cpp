@@ -13,7 +13,8 @@ struct State {
     char* next = reinterpret_cast<char*>((size_t)1 << 40);
     bool capturing = false, broken = false;                // a stream is being captured; a call has spoilt that
     int device = 0;
-    std::string events;
+    std::string events, launches;
+    std::map<const void*, std::string> kernels;
 } g;
 hipError_t note(const char* what) {
     std::lock_guard<std::recursive_mutex> guard(lock);
@@ -34,6 +35,12 @@ void fake_capture(int on) { g.capturing = on != 0; }
 int fake_broken() { return g.broken; }
 void fake_device(int device) { g.device = device; }
 size_t fake_used() { return g.used; }
+const char* fake_launches() {                         // names of the kernels since the last call
+    static std::string out;
+    out.swap(g.launches);
+    g.launches.clear();
+    return out.c_str();
+}
 const char* fake_events() {
     static std::string out;
     out.swap(g.events);
@@ -80,7 +87,11 @@ hipError_t hipMemsetAsync(void* p, int, size_t n, hipStream_t) {
     return note("set");
 }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return note("copy"); }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return note("launch"); }
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
+    std::lock_guard<std::recursive_mutex> guard(lock);
+    g.launches += g.kernels[kernel] + ' ';
+    return note("launch");
+}
 hipError_t hipLaunchCooperativeKernel(const void*, dim3, dim3, void**, unsigned, hipStream_t) { return note("launch"); }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
@@ -121,6 +132,6 @@ void* __hipRegisterFatBinary(const void*) {
     return handle;
 }
 void __hipUnregisterFatBinary(void*) {}
-void __hipRegisterFunction(void*, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void*, const void* kernel, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { g.kernels[kernel] = name; }
 void __hipRegisterVar(void*, void*, char*, char*, int, size_t, int, int) {}
 }

@@ -48,10 +48,10 @@ def _registers(text):
     return regs
 
 
-def _kernels(text):
-    """name -> list of (mnemonic, operands, successors' indices)"""
+def _kernels(text, kernel="gemm_tile_kernel"):
+    """name -> list of (mnemonic, operands), label -> index"""
     out = {}
-    for m in re.finditer(r"^(_ZN?\S*gemm_tile_kernel\S*):.*?\n(.*?)^\.Lfunc_end", text, re.S | re.M):
+    for m in re.finditer(rf"^(_ZN?\S*{kernel}\S*):.*?\n(.*?)^\.Lfunc_end", text, re.S | re.M):
         code, labels = [], {}
         for line in m[2].splitlines():
             line = line.split(";")[0].strip()

@@ -1,12 +1,11 @@
 """The products with four wavefronts keep their accumulators in the other half of the register file and place m0 and
 the load that uses it in different gaps between MFMAs, all in inline assembly: their listing is read here for what
 test_gemm_listing reads the other kernels' for - waits behind and before the MFMAs, m0, spills."""
-import os
 import re
 
 import pytest
 
-from test_gemm_listing import AFTER_MFMA, BEFORE_MFMA, _walk, listings  # noqa: F401
+from test_gemm_listing import AFTER_MFMA, BEFORE_MFMA, _kernels, _walk, listings  # noqa: F401
 
 
 def _registers(text):
@@ -17,24 +16,9 @@ def _registers(text):
     return regs
 
 
-def _kernels(text):
-    out = {}
-    for m in re.finditer(r"^(_ZN?\S*gemm_quad_kernel\S*):.*?\n(.*?)^\.Lfunc_end", text, re.S | re.M):
-        code, labels = [], {}
-        for line in m[2].splitlines():
-            line = line.split(";")[0].strip()
-            if re.fullmatch(r"\S+:", line):
-                labels[line[:-1]] = len(code)
-            elif line and not line.startswith("."):
-                op, _, rest = line.replace("\t", " ").partition(" ")
-                code.append((op.strip(), rest.strip()))
-        out[m[1]] = (code, labels)
-    return out
-
-
 @pytest.mark.parametrize("packed", [False, True])
 def test_results_of_matrix_instructions_are_waited_for(listings, packed):  # noqa: F811
-    kernels = _kernels(listings[packed])
+    kernels = _kernels(listings[packed], "gemm_quad_kernel")
     assert len(kernels) == 30                       # 5 tiles x (4 epilogues, two of them for ragged rows too)
     for name, (code, labels) in kernels.items():
         operands = [[_registers(p) for p in re.split(r",\s*", rest)] if rest else [] for _, rest in code]
@@ -55,7 +39,7 @@ def test_results_of_matrix_instructions_are_waited_for(listings, packed):  # noq
 
 def test_m0_belongs_to_the_loads_to_lds(listings):  # noqa: F811
     """Every load to LDS finds the m0 written for it, at least one instruction before, and nothing else uses m0."""
-    for name, (code, _) in _kernels(listings[False]).items():
+    for name, (code, _) in _kernels(listings[False], "gemm_quad_kernel").items():
         written = None
         for i, (op, rest) in enumerate(code):
             if re.search(r"\bm0\b", rest):

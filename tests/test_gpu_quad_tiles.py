@@ -12,10 +12,16 @@ from test_gpu_parity import DEV, assert_y_close, custom_layer, dev, host, make_f
 pytestmark = pytest.mark.gpu
 
 
-# up / hidden / output product (columns of the last one's K ranges): 128 x 128, 128 x 128 of eight, 128 x 128; 192 x 128 both, 256 x 256;
-# 256 x 128 both, 192 x 256; 192 x 256 both, 192 x 256; 256 x 256 both, 256 x 128
-@pytest.mark.parametrize("d,h,n,act", [(2048, 2056, 769, "gelu_erf"), (4096, 2056, 1537, "gelu_tanh"), (4096, 4104, 1500, "relu"),
-                                       (4096, 4104, 2048, "gelu_erf"), (2048, 8192, 1537, "gelu_erf")])
+# d, h, tokens: tiles of the predictor's and the hidden product, and of the two paths' output products (test_tile_choice holds the library
+# to them)
+TILES = {(2048, 2056, 769): ("128x128", "128x128 of eight", "128x128 ragged", "128x128 ragged"),
+         (4096, 2056, 1537): ("192x128", "192x128", "256x256 ragged", "256x128 ragged"),
+         (4096, 4104, 1500): ("256x128", "256x128", "192x256 ragged", "192x128 ragged"),
+         (4096, 4104, 2048): ("192x256", "192x256", "256x256 ragged", "256x128 ragged"),
+         (2048, 8192, 1537): ("256x256", "256x256", "256x128", "256x128")}
+
+
+@pytest.mark.parametrize("d,h,n,act", [(*size, act) for size, act in zip(TILES, ("gelu_erf", "gelu_tanh", "relu", "gelu_erf", "gelu_erf"))])
 def test_tokens_on_the_edges_of_large_tiles(d, h, n, act):
     """Whole and ragged K (h = 2056, 4104), partial rows and columns of tiles; every mask word, y at the first and last
     rows of tiles and in the last, partial one.  The dense path against fp64 with its hidden activations rounded
