@@ -52,7 +52,8 @@ __device__ __forceinline__ double rcp_f64(double a) {              // a: a norma
 }
 __device__ __forceinline__ double exp_f64(double y) {              // |y| <= 2^20: Taylor's series, 13 terms, on |r| <= log(2) / 2
     const double n = rint(y * 1.4426950408889634074);
-    constexpr double kHead = 0.6931471796706319, kRest = 8.893134238886677e-10;   // log(2): its first 30 bits, so that n times them is exact; the rest
+    // log(2): its first 30 bits, so that n times them is exact; the rest
+    constexpr double kHead = 0.6931471796706319, kRest = 8.893134238886677e-10;
     const double r = fma(n, -kRest, fma(n, -kHead, y));
     constexpr double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
                               1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
