@@ -15,13 +15,15 @@ pytestmark = pytest.mark.gpu
 # d, h, tokens: tiles of the predictor's and the hidden product, and of the two paths' output products (test_tile_choice holds the library
 # to them)
 TILES = {(2048, 2056, 769): ("128x128", "128x128 of eight", "128x128 ragged", "128x128 ragged"),
-         (4096, 2056, 1537): ("192x128", "192x128", "256x256 ragged", "256x128 ragged"),
-         (4096, 4104, 1500): ("256x128", "256x128", "192x256 ragged", "192x128 ragged"),
-         (4096, 4104, 2048): ("192x256", "192x256", "256x256 ragged", "256x128 ragged"),
-         (2048, 8192, 1537): ("256x256", "256x256", "256x128", "256x128")}
+         (4096, 2056, 1537): ("192x128", "192x128", "256x128 ragged", "256x128 ragged"),
+         (4096, 4104, 1500): ("256x128", "256x128", "192x128 ragged", "192x128 ragged"),
+         (4096, 4104, 2048): ("192x256", "192x256", "256x128 ragged", "256x128 ragged"),
+         (2048, 8192, 1537): ("256x256", "256x256", "256x128", "256x128"),
+         (3072, 6152, 1500): ("192x256 of eight", "192x256 of eight", "192x256 ragged", "192x256 ragged"),
+         (4096, 6152, 1537): ("192x128", "192x128", "256x256 ragged", "256x256 ragged")}
 
 
-@pytest.mark.parametrize("d,h,n,act", [(*size, act) for size, act in zip(TILES, ("gelu_erf", "gelu_tanh", "relu", "gelu_erf", "gelu_erf"))])
+@pytest.mark.parametrize("d,h,n,act", [(*size, act) for size, act in zip(TILES, ("gelu_erf", "gelu_tanh", "relu", "gelu_erf", "gelu_erf", "gelu_erf", "gelu_tanh"))])
 def test_tokens_on_the_edges_of_large_tiles(d, h, n, act):
     """Whole and ragged K (h = 2056, 4104), partial rows and columns of tiles; every mask word, y at the first and last
     rows of tiles and in the last, partial one.  The dense path against fp64 with its hidden activations rounded
