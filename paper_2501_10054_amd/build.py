@@ -16,7 +16,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtardis.so")
 SIGMA_PROBE = os.path.join(OBJ, "sigma_probe.so")
 
-SOURCES = ["api.hip", "decode.hip", "forward.hip", "gemm.hip", "offline.hip", "prefill.hip", "stack.hip"]
+SOURCES = ["api.hip", "decode.hip", "forward.hip", "gemm.hip", "offline.hip", "prefill.hip", "stack.hip", "stream.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

@@ -92,6 +92,7 @@ struct tardis_layer_s {
     float* thi;    // h
     float* a;      // h
     float* c;      // h
+    float* code_scale;     // h: the 8-bit codes are rint(weight * this) (td_code_scale); null where some row's are not
     // working memory of the online calls (sized by max_batch)
     float* yacc;       // max_batch x d fp32 accumulator
     uint32_t* mask;    // max_batch x mask_words
@@ -242,10 +243,11 @@ struct td_fold_work {
 tardis_status_t td_transpose(const void* src, void* dst, void* copy, int64_t rows, int64_t cols, int32_t dtype, hipStream_t s);
 // bits = 8: Q (required).  bits = 4, 3, 2 (codes up to 7, 3, 1 in 4-bit slots): M4 (required), Q
 // (effective one-byte codes, optional) and Q4 (packed, optional, needs d % 32 == 0).  margin: fraction
-// of every range's width taken off at either end for the predictor's test.
+// of every range's width taken off at either end for the predictor's test.  code_scale (bits = 8, bf16; or null): td_code_scale of
+// every row; no_scale (zero before) becomes 1 if some row has none.
 tardis_status_t td_build_sketch(const void* W1, const void* b1, const float* lo, const float* hi, int64_t h,
                                 int64_t d, int32_t dtype, int32_t bits, float margin, int8_t* Q, uint8_t* Q4,
-                                uint8_t* M4, float* tlo, float* thi, hipStream_t s);
+                                uint8_t* M4, float* tlo, float* thi, float* code_scale, int32_t* no_scale, hipStream_t s);
 // one-byte effective codes (multiplier * 4-bit code) from the packed 4-bit sketch
 tardis_status_t td_unpack_sketch4(const uint8_t* Q4, const uint8_t* M4, int64_t h, int64_t d, int8_t* Q,
                                   hipStream_t s);
@@ -276,6 +278,24 @@ tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const voi
 tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
                                int64_t n, int64_t d, int64_t h, hipStream_t s);
 size_t td_gemm_part_floats(int64_t n, int64_t d);
+// stream.hip: the same for up to kStreamMaxTokens tokens
+constexpr int64_t kStreamMaxTokens = 64;
+// The weights of a launch of stream_kernel and how its blocks divide them; tile = 0: not for that kernel.  (The kernel that runs before
+// it asks for what its blocks begin with: that waits in the caches when it starts, and HBM has work meanwhile.)
+struct StreamPlan {
+    const unsigned char *B, *B2;   // weights: rows of k bytes (and of k2: a second matrix whose K follows)
+    int64_t N;
+    uint32_t k, k2;
+    int tile, splits, slices;      // rows of a block; ranges of K (a power of two), slices of 256 bytes in one
+};
+constexpr int kStreamSlice = 256;
+inline int64_t stream_blocks(const StreamPlan& p) { return (p.N + p.tile - 1) / p.tile * p.splits; }
+StreamPlan td_stream_up_plan(const tardis_layer_s* L, int64_t n);
+StreamPlan td_stream_output_plan(bool folded, const void* Wp, const void* W2, int64_t n, int64_t d, int64_t h);
+tardis_status_t td_stream_repair(const tardis_layer_s* L, const StreamPlan& plan, const int8_t* XQ, const int32_t* e, const void* X,
+                                 const void* b1, uint32_t* mask, void* out, void* rest, int64_t n, const StreamPlan& next, hipStream_t s);
+tardis_status_t td_stream_output(const StreamPlan& plan, const void* X, const void* H, float* part, int* parts, int64_t n, hipStream_t s);
+tardis_status_t td_stream_init();
 tardis_status_t td_gemm_init();
 // prefill.hip
 bool td_prefill_supported(const tardis_layer_s* L);

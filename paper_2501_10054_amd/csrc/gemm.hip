@@ -10,12 +10,11 @@
 // repair factors of the flagged ones, and the folded product together with the down projection of the
 // masked factors, [X | D] . [W' | W2]^T.
 #include <cstdlib>
-#include <type_traits>
-#include <utility>
 
 #include "common.h"
 #include "sigma.h"
 #include "slices.h"
+#include "tiles.h"
 
 namespace {
 
@@ -108,13 +107,9 @@ gemm_nt_generic_kernel(const T* __restrict__ A, const T* __restrict__ B, float* 
 //    K the requests crowd onto few memory channels (zeros: 358 -> 300 us at 4096 x 4096 x 16384).
 // 4096 x 4096 x 16384 in bf16 with random data (tile 256 x 256, kernel trace): 404 us with eight wavefronts, 375 with four (360 to
 // 390 from card to card), 1.47 PFLOP/s; with staging through registers 605, 0.91.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef td_i32x4 i32x4_t;
 
 constexpr int kWavesPerTile = 8;
 constexpr int kNoLds = 0xc07f, kNoLoads = 0x0f70;            // s_waitcnt lgkmcnt(0), vmcnt(0)
-constexpr int kLdsBytes = 160 * 1024;
 
 // Which block computes which tile.  Blocks b, b+8, b+16, ... run on one XCD and share its L2, so
 // each XCD gets a rectangle of rm x rn tiles (the 8 XCDs form a gm x gn grid over the tile grid,
@@ -181,12 +176,6 @@ __device__ __forceinline__ bool place(const TileMap& t, int xcd, int local, int&
     return tile_m < t.tiles_m && tile_n < t.tiles_n;
 }
 
-// The slice of `len` that a block starts with
-__device__ __forceinline__ int first_slice(int xcd, int local, int len) {
-    const int at = (local & 7) + xcd * len / 8;
-    return len < 8 ? 0 : at >= len ? at - len : at;
-}
-
 // C = A.B^T (+ A2.B2^T: a second pair of operands whose K follows the first's).  Rows of A are rows of
 // C (M of them), rows of B columns of C (N); k, k2: bytes of a row of the first / second pair.
 struct GemmArgs {
@@ -216,53 +205,10 @@ struct GemmArgs {
 // product to the other.
 enum { EPI_F32, EPI_PART, EPI_HIDDEN, EPI_REPAIR };
 
-__device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    i32x4_t r;
-    r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r.y = __builtin_amdgcn_readfirstlane((int)((a >> 32) & 0xffffu));
-    r.z = __builtin_amdgcn_readfirstlane((int)bytes);
-    r.w = 0x00020000;
-    return r;
-}
-
-// 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
-// (m0 is set and used in the one statement.  It is a reserved register, which the compiler does not take as a clobber; it
-// uses it nowhere else in these kernels, and the listing's test holds it to that)
-template <bool ONCE = false>
-__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
-    if constexpr (ONCE)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     ::"s"(lds), "v"(voff), "s"(rs), "s"(soff));
-}
-
-// round to nearest even, two in one instruction
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
-}
-
 // (the accumulator of the int8 form holds integers)
 template <bool I8> __device__ __forceinline__ void mma16(f32x4_t& c, const td_u32x4& a, const td_u32x4& b) {
     if constexpr (I8) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-}
-
-template <int V> using num = std::integral_constant<int, V>;
-// f(num<0>), ..., f(num<N - 1>)
-template <typename F, int... I> __device__ __forceinline__ void for_each_constant(F f, std::integer_sequence<int, I...>) { (f(num<I>{}), ...); }
-template <int N, typename F> __device__ __forceinline__ void for_constants(F f) { for_each_constant(f, std::make_integer_sequence<int, N>{}); }
-
-// v of lanes l, l^16, l^32 and l^48 or-ed together
-__device__ __forceinline__ uint32_t or_halves(uint32_t v) {
-    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = a[0] | a[1];
-    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return b[0] | b[1];
 }
 
 // The compiler does not know how long those take.  Every use of the accumulators from here on (of their new values, for
@@ -283,13 +229,6 @@ template <int EPI, int W, int WM, int NA, int NB> struct EpiRows {
     static constexpr int value = fit(NA);
     static constexpr int kWaveBytes = value * 16 * NB * 16 * 4, kBytes = W * kWaveBytes + kParams;
 };
-
-template <typename F> __device__ __forceinline__ void with_act(int act, F f) {
-    if (act == TARDIS_ACT_GELU_ERF) f(num<TARDIS_ACT_GELU_ERF>{});
-    else if (act == TARDIS_ACT_GELU_TANH) f(num<TARDIS_ACT_GELU_TANH>{});
-    else if (act == TARDIS_ACT_RELU) f(num<TARDIS_ACT_RELU>{});
-    else f(num<TARDIS_ACT_IDENTITY>{});
-}
 
 // RAGGED: a row is not a whole number of slices; the pieces past its end are loaded from the row's last
 // slice start instead (in bounds) and the fragments that hold them are zeroed as they are read.

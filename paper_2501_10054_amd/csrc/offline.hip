@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "codes.h"
 #include "sigma.h"
 
 namespace {
@@ -256,7 +257,7 @@ template <typename T>
 __global__ void __launch_bounds__(kBlock)
 sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* __restrict__ lo,
               const float* __restrict__ hi, int64_t d, int8_t* __restrict__ Q, float* __restrict__ tlo,
-              float* __restrict__ thi, float margin) {
+              float* __restrict__ thi, float margin, float* __restrict__ code_scale, int32_t* __restrict__ no_scale) {
     __shared__ float red[kBlock / TD_WAVE];
     constexpr int V = 16 / (int)sizeof(T);
     constexpr int kKeep = 2;                         // vectors a thread keeps between the two passes
@@ -328,6 +329,10 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
             const bool inside = (rl <= bj) && (bj < rh);
             tlo[j] = inside ? -INFINITY : INFINITY;
             thi[j] = INFINITY;
+        }
+        if (code_scale) {
+            code_scale[j] = flat ? td_code_scale(m, code(0.5f * m)) : 0.0f;
+            if (live && !flat) *no_scale = 1;
         }
     }
 }
@@ -1373,7 +1378,7 @@ tardis_status_t td_transpose(const void* src, void* dst, void* copy, int64_t row
 
 tardis_status_t td_build_sketch(const void* W1, const void* b1, const float* lo, const float* hi, int64_t h,
                                 int64_t d, int32_t dtype, int32_t bits, float margin, int8_t* Q, uint8_t* Q4,
-                                uint8_t* M4, float* tlo, float* thi, hipStream_t s) {
+                                uint8_t* M4, float* tlo, float* thi, float* code_scale, int32_t* no_scale, hipStream_t s) {
     if (bits == 4 || bits == 3 || bits == 2) {
         const int qmax = (1 << (bits - 1)) - 1;
         const int64_t ng = (d + 31) / 32;
@@ -1396,10 +1401,10 @@ tardis_status_t td_build_sketch(const void* W1, const void* b1, const float* lo,
     if (bits != 8 || !Q) return TARDIS_ERR_INVALID_ARG;
     if (dtype == TARDIS_BF16)
         hipLaunchKernelGGL(sketch_kernel<bf16_t>, dim3((unsigned)h), dim3(kBlock), 0, s,
-                           static_cast<const bf16_t*>(W1), static_cast<const bf16_t*>(b1), lo, hi, d, Q, tlo, thi, margin);
+                           static_cast<const bf16_t*>(W1), static_cast<const bf16_t*>(b1), lo, hi, d, Q, tlo, thi, margin, code_scale, no_scale);
     else
         hipLaunchKernelGGL(sketch_kernel<float>, dim3((unsigned)h), dim3(kBlock), 0, s,
-                           static_cast<const float*>(W1), static_cast<const float*>(b1), lo, hi, d, Q, tlo, thi, margin);
+                           static_cast<const float*>(W1), static_cast<const float*>(b1), lo, hi, d, Q, tlo, thi, margin, nullptr, nullptr);
     TD_HIP(hipGetLastError());
     return TARDIS_OK;
 }

@@ -21,21 +21,38 @@
 //     Y   = [X | D] [W' | W2]^T   one product over d + h columns.
 // Calls with few tokens on some layers (fine_max_tokens) keep what the rounding of D left as well and add its product
 // with W2^T: the kernels that serve fewer tokens multiply factors of 32 bits.
+// Up to 64 tokens the products stream the weights (stream.hip) where they can, and the first two read W1 alone.
 // Neither the sums nor the pre-activations (n x h, 4 bytes each) reach memory.  Masks are bit-exact with
 // the per-token path (same integer sums, same range test).
 #include "common.h"
 #include "rowdot.h"
+#include "tiles.h"
 
 namespace {
 
 // int8 code and exponent of every token (one block per token; d % 8 == 0).  COPY: x is not 16-byte
 // aligned; an aligned copy is left for the products.
+// Blocks from `tokens` on (next.tile: the launch behind this one is a stream_kernel) ask for the weights that its blocks begin with.
 template <bool COPY>
 __global__ void __launch_bounds__(256)
 quantize_rows_kernel(const bf16_t* __restrict__ X, int d, int8_t* __restrict__ XQ, int32_t* __restrict__ E,
-                     bf16_t* __restrict__ XC) {
+                     bf16_t* __restrict__ XC, int tokens, StreamPlan next) {
     __shared__ float red[4];
     const int t = blockIdx.x;
+    if (t >= tokens) {                               // (from a multiple of 8 on: on the XCD that needs them)
+        const int block = t - (tokens + 7) / 8 * 8;
+        if (block < 0) return;
+        const StreamBlock b = stream_block(next, block);
+        uint32_t got[kWarmSlices] = {};
+#pragma unroll
+        for (int u = 0; u < kWarmSlices; ++u) {
+            const uint32_t* from = stream_warm(next, b, (int)threadIdx.x + u * 256);
+            if (from) got[u] = *from;
+        }
+#pragma unroll
+        for (int u = 0; u < kWarmSlices; ++u) asm volatile("" ::"v"(got[u]));
+        return;
+    }
     const bf16_t* x = X + (size_t)t * d;
     auto load8 = [&](int v, bf16_t (&o)[8]) {
         if constexpr (COPY) {
@@ -194,6 +211,18 @@ void finish(const PromptScratch& w, int parts, const float* bias32, const bf16_t
                        (int)d, y, aligned(y, 8) ? 1 : 0, norm_out, kRmsEps);
 }
 
+tardis_status_t output(const StreamPlan& plan, const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
+                       int64_t n, int64_t d, int64_t h, hipStream_t s) {
+    return plan.tile ? td_stream_output(plan, X, H, part, parts, n, s) : td_gemm_output(X, Wp, H, W2, part, parts, n, d, h, s);
+}
+
+// codes and exponents; the tokens as the products can read them.  next: the launch that follows, if it is a stream_kernel
+const bf16_t* quantize(const PromptScratch& w, const bf16_t* x, int64_t n, int64_t d, const StreamPlan& next, hipStream_t s) {
+    const int64_t blocks = next.tile ? (n + 7) / 8 * 8 + stream_blocks(next) : n;
+    hipLaunchKernelGGL(aligned(x, 16) ? quantize_rows_kernel<false> : quantize_rows_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x, (int)n, next);
+    return aligned(x, 16) ? x : w.x;
+}
+
 }  // namespace
 
 bool td_prefill_supported(const tardis_layer_s* L) {
@@ -212,16 +241,17 @@ static tardis_status_t prefill_chunk(tardis_layer_s* L, const bf16_t* x, int64_t
                                      bool stored, int norm_out, hipStream_t s) {
     const int64_t d = L->d, h = L->h;
     const PromptScratch w(L->pf_scratch, n, d, h, fine);
-    if (aligned(x, 16)) {
-        hipLaunchKernelGGL(quantize_rows_kernel<false>, dim3((unsigned)n), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
-    } else {
-        hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)n), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
-        x = w.x;
-    }
-    TD_TRY(td_gemm_repair(L, w.xq, w.e, x, L->b1 ? L->b1 : L->zeros_h, mask, w.hid, fine ? w.rest : nullptr, !stored, n, s));
+    const StreamPlan up = stored ? td_stream_up_plan(L, n) : StreamPlan{};
+    const StreamPlan down = td_stream_output_plan(stored, L->Wp, L->W2, n, d, h);
+    x = quantize(w, x, n, d, up, s);
+    const void* b1 = L->b1 ? L->b1 : L->zeros_h;
+    void* rest = fine ? w.rest : nullptr;
+    if (up.tile) TD_TRY(td_stream_repair(L, up, w.xq, w.e, x, b1, mask, w.hid, rest, n, down, s));
+    else TD_TRY(td_gemm_repair(L, w.xq, w.e, x, b1, mask, w.hid, rest, !stored, n, s));
     int parts = 1, more = 0;
-    TD_TRY(td_gemm_output(stored ? x : nullptr, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
-    if (fine) TD_TRY(td_gemm_output(nullptr, nullptr, w.rest, L->W2, w.part + (size_t)parts * n * d, &more, n, d, h, s));
+    TD_TRY(output(down, stored ? x : nullptr, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
+    if (fine)
+        TD_TRY(output(td_stream_output_plan(false, nullptr, L->W2, n, d, h), nullptr, nullptr, w.rest, L->W2, w.part + (size_t)parts * n * d, &more, n, d, h, s));
     parts += more;
     finish(w, parts, L->bp, nullptr, n, d, y, norm_out, s);
     TD_HIP(hipGetLastError());
@@ -251,13 +281,10 @@ tardis_status_t td_dense_prefill(tardis_layer_s* L, const void* xv, int64_t n, v
         const int64_t nc = n - t0 < L->prefill_chunk ? n - t0 : L->prefill_chunk;
         const PromptScratch w(L->pf_scratch, nc, d, h, false);
         const bf16_t* x = static_cast<const bf16_t*>(xv) + t0 * d;
-        if (!aligned(x, 16)) {
-            hipLaunchKernelGGL(quantize_rows_kernel<true>, dim3((unsigned)nc), dim3(256), 0, s, x, (int)d, w.xq, w.e, w.x);
-            x = w.x;
-        }
+        if (!aligned(x, 16)) x = quantize(w, x, nc, d, StreamPlan{}, s);
         TD_TRY(td_gemm_hidden(L, x, L->b1 ? L->b1 : L->zeros_h, w.hid, nc, s));
         int parts = 1;
-        TD_TRY(td_gemm_output(nullptr, nullptr, w.hid, L->W2, w.part, &parts, nc, d, h, s));
+        TD_TRY(output(td_stream_output_plan(false, nullptr, L->W2, nc, d, h), nullptr, nullptr, w.hid, L->W2, w.part, &parts, nc, d, h, s));
         finish(w, parts, nullptr, static_cast<const bf16_t*>(L->b2), nc, d, static_cast<bf16_t*>(yv) + t0 * d, 0, s);
     }
     TD_HIP(hipGetLastError());
