@@ -614,8 +614,9 @@ __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo
 // stretches the histogram, or most samples are equal - or that are not all finite falls back to the sort in LDS.)  The fit takes
 // sigma of every sample once, in fp64.
 // What bounds it: vector instructions, about half of them for sigma (without it 59 of 107 us).  4096 neurons x 4096 samples:
-// 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 89 us with the sigma of
-// sigma.h and one pass.  (A full bitonic sort in LDS and sigma taken twice: 375.)
+// 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 95 us with the sigma of
+// sigma.h and one pass; 81 with its constants in scalar registers, shared by two samples, and registers for five blocks a CU (left to the
+// compiler 88, with six or more blocks registers spill: 92 to 104).  (A full bitonic sort in LDS and sigma taken twice: 375.)
 //
 // A sample closer to the end of a range than fp32 can tell (both are fp32 here) would count as inside or
 // outside by luck of rounding.  For those (a few of 16384 neurons) the pre-activations of the two samples
@@ -624,7 +625,7 @@ constexpr int kSelBins = 1024;
 constexpr int kSelList = 256;
 
 template <typename E, int T, int NPT>
-__global__ void __launch_bounds__(T)
+__global__ void __launch_bounds__(T, T == 1024 ? 4 : 5)
 calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, const E* __restrict__ b1,
                         const E* __restrict__ X, int n, int npad, int64_t d, float coverage,
                         const float* __restrict__ cov_pn, int act, float* __restrict__ lo, float* __restrict__ hi,
@@ -859,23 +860,35 @@ calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, 
         // (32 samples a thread beside the coefficients of this sigma are more than 128 registers: they go through LDS, each
         // thread's own.  4096 neurons x 16384, 32768 samples: 1070, 1580 us, so 925, 1380)
         constexpr bool kParked = NPT > 16 && ACT == TARDIS_ACT_GELU_ERF;
-        constexpr int kAtOnce = kParked ? 2 : NPT;
+        constexpr int kPair = 2, kUnroll = kParked ? 1 : NPT / kPair;    // sigma of two samples at a time, side by side
         if constexpr (kParked) {
 #pragma unroll
             for (int k = 0; k < NPT; ++k)
                 if (k * T + tid < n) vals[k * T + tid] = v[k];
         }
-#pragma unroll kAtOnce
-        for (int k = 0; k < NPT; ++k) {
-            const float x = !kParked ? v[k] : k * T + tid < n ? vals[k * T + tid] : 0.0f;
-            const bool in = (k * T + tid < n) & (x >= cut[0]) & (x < cut[1]);
-            const double g = act_flat_f64<ACT>((double)(in ? x : 0.0f));   // (sigma(0) = 0)
-            const double dz = (double)(in ? x : pivot32) - pivot;
-            inside += in ? 1 : 0;
-            s[1] += dz;
-            s[2] += g;
-            sq[0] = fma(dz, dz, sq[0]);
-            sq[1] = fma(dz, g, sq[1]);
+#pragma unroll kUnroll
+        for (int k0 = 0; k0 < NPT; k0 += kPair) {
+            double g[kPair], dz[kPair];
+#pragma unroll
+            for (int u = 0; u < kPair; ++u) {
+                const int k = k0 + u;
+                const float x = !kParked ? v[k] : k * T + tid < n ? vals[k * T + tid] : 0.0f;
+                const bool in = (k * T + tid < n) & (x >= cut[0]) & (x < cut[1]);
+                g[u] = (double)(in ? x : 0.0f);                        // (sigma(0) = 0)
+                dz[u] = (double)(in ? x : pivot32) - pivot;
+                inside += in ? 1 : 0;
+            }
+            act_flat_f64<ACT>(g);
+#pragma unroll
+            for (int u = 0; u < kPair; ++u) {
+                s[1] += dz[u];
+                s[2] += g[u];
+                sq[0] = fma(dz[u], dz[u], sq[0]);
+                sq[1] = fma(dz[u], g[u], sq[1]);
+            }
+            // (the sums are taken here: put off, all of these are kept in registers)
+            asm volatile("" : "+v"(s[1]), "+v"(s[2]), "+v"(sq[0]), "+v"(sq[1]));
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     if (act == TARDIS_ACT_GELU_ERF) sums(std::integral_constant<int, TARDIS_ACT_GELU_ERF>{});

@@ -45,24 +45,42 @@ template <int ACT> __device__ __forceinline__ float act_flat(float z) {
 // 1 - 2 K / p (after the substitution of Shepherd and Laframboise, Math. Comp. 36, 1981; K = 4, degree 13, Chebyshev points for x up to
 // 4: 4e-16 of the value; less beyond that, of a value below 1e-8).  Root mean square error against 60 digits, and of the library's erf
 // in td_act_f64: 6.5e-17 and 7.5e-17 for z from N(0, 1.6^2), 2.66e-17 and 2.72e-17 from N(0, 0.6^2), 1.7e-16 and 2.0e-16 for z from -8 to 8.
+// a b + c with the constant c in scalar registers.  (Left to the compiler a step of a polynomial is two moves of c into the registers
+// that v_fmac_f64 then adds to: 126 instead of 75 vector instructions
+// for a sample's sigma and sums in the calibration's fit.)
+__device__ __forceinline__ double fma_constant(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
 __device__ __forceinline__ double rcp_f64(double a) {              // a: a normal number
     double r = __builtin_amdgcn_rcp(a);
     r = fma(fma(-a, r, 1.0), r, r);
     return fma(fma(-a, r, 1.0), r, r);
 }
-__device__ __forceinline__ double exp_f64(double y) {              // |y| <= 2^20: Taylor's series, 13 terms, on |r| <= log(2) / 2
-    const double n = rint(y * 1.4426950408889634074);
+// N values side by side, so that N steps of a polynomial share their constant
+template <int N> __device__ __forceinline__ void step_f64(double (&s)[N], const double (&x)[N], double c) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) s[u] = fma_constant(s[u], x[u], c);
+}
+template <int N> __device__ __forceinline__ void exp_f64(double (&y)[N]) {   // |y| <= 2^20: Taylor's series, 13 terms, on |r| <= log(2) / 2
     // log(2): its first 30 bits, so that n times them is exact; the rest
     constexpr double kHead = 0.6931471796706319, kRest = 8.893134238886677e-10;
-    const double r = fma(n, -kRest, fma(n, -kHead, y));
     constexpr double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
                               1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
-    double s = c[12];
+    double n[N], s[N];
 #pragma unroll
-    for (int k = 11; k >= 0; --k) s = fma(s, r, c[k]);
-    return ldexp(s, (int)n);
+    for (int u = 0; u < N; ++u) {
+        n[u] = rint(y[u] * 1.4426950408889634074);
+        y[u] = fma(n[u], -kRest, fma(n[u], -kHead, y[u]));
+        s[u] = c[12];
+    }
+#pragma unroll
+    for (int k = 11; k >= 3; --k) step_f64(s, y, c[k]);
+#pragma unroll
+    for (int u = 0; u < N; ++u) y[u] = ldexp(fma(fma(fma(s[u], y[u], 0.5), y[u], 1.0), y[u], 1.0), (int)n[u]);   // (these constants the instruction has)
 }
-template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
+template <int ACT, int N> __device__ __forceinline__ void act_flat_f64(double (&z)[N]) {
     if constexpr (ACT == TARDIS_ACT_GELU_ERF) {
         constexpr double K = 4.0, kRootHalf = 0.70710678118654752440;
         constexpr double c[14] = {                                         // (of half the function)
@@ -74,22 +92,49 @@ template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
             0.39894228040143265, -0.06649038006690387, 0.009973557009983732, -0.001187328214811527, 0.0001154346832492605,
             -9.444639861853272e-06, 6.659317805752481e-07, -4.117317843452298e-08, 2.2271240384729976e-09,
             -9.027164883791298e-11};
-        const double u = fmin(fabs(z), 60.0), w = u * u;                   // (Phi(-60) is 0, and infinities stay what they were)
-        const double r = rcp_f64(fma(u, kRootHalf, K - kRootHalf)), t = fma(-2.0 * K, r, 1.0);
-        double s = c[13], near = b[9];
+        double u[N], w[N], r[N], t[N], s[N], near[N];
 #pragma unroll
-        for (int k = 12; k >= 0; --k) s = fma(s, t, c[k]);
+        for (int i = 0; i < N; ++i) {
+            u[i] = fmin(fabs(z[i]), 60.0);                                 // (Phi(-60) is 0, and infinities stay what they were)
+            w[i] = u[i] * u[i];
+            r[i] = rcp_f64(fma_constant(u[i], kRootHalf, K - kRootHalf));
+            t[i] = fma(-2.0 * K, r[i], 1.0);
+            s[i] = c[13];
+            near[i] = b[9];
+        }
 #pragma unroll
-        for (int k = 8; k >= 0; --k) near = fma(near, w, b[k]);
-        const double half = s * r * exp_f64(-0.5 * w);
-        return z * (u < 1.0 ? fma(z, near, 0.5) : z > 0.0 ? 1.0 - half : half);
+        for (int k = 12; k >= 0; --k) step_f64(s, t, c[k]);
+#pragma unroll
+        for (int k = 8; k >= 0; --k) step_f64(near, w, b[k]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) w[i] *= -0.5;
+        exp_f64(w);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double half = s[i] * r[i] * w[i];
+            z[i] *= u[i] < 1.0 ? fma(z[i], near[i], 0.5) : z[i] > 0.0 ? 1.0 - half : half;
+        }
     } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
         // as in 32 bits; |v| beyond 1e5 is 1e5 (where e is 0)
-        const double v = 0.79788456080286535588 * (z + 0.044715 * z * z * z);
-        const double e = exp_f64(fmax(-2.0 * fabs(v), -1e5));
-        const double q = e * rcp_f64(1.0 + e);
-        return z * (z > 0.0 ? 1.0 - q : q);
+        double e[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double v = 0.79788456080286535588 * (z[i] + 0.044715 * z[i] * z[i] * z[i]);
+            e[i] = fmax(-2.0 * fabs(v), -1e5);
+        }
+        exp_f64(e);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double q = e[i] * rcp_f64(1.0 + e[i]);
+            z[i] *= z[i] > 0.0 ? 1.0 - q : q;
+        }
     } else {
-        return td_act_f64(z, ACT);
+#pragma unroll
+        for (int i = 0; i < N; ++i) z[i] = td_act_f64(z[i], ACT);
     }
+}
+template <int ACT> __device__ __forceinline__ double act_flat_f64(double z) {
+    double v[1] = {z};
+    act_flat_f64<ACT>(v);
+    return v[0];
 }
