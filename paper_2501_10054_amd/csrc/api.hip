@@ -15,8 +15,6 @@ constexpr int64_t kMaxH = 1 << 22;
 constexpr int64_t kMaxCal = 32768;        // one neuron's samples are sorted in LDS
 constexpr int64_t kMaxSearchCal = 8192;   // range search also keeps sigma of every sample there, in fp64
 constexpr int64_t kMaxBatch = 4096;
-constexpr size_t kSyncBytes = 512;           // the online calls' counters, and
-constexpr int kNoScale = 64;               // (an index of 32-bit words) whether the predictor codes of some row have no scale
 constexpr size_t kTokenLdsCap = 60 * 1024;
 
 // Live handles: a layer may name the layer that runs after it (a hint for cache warming); before
@@ -230,7 +228,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     mem.reserve(&L->hidden, nb * h * es);
     mem.reserve(&L->zeros_h, (size_t)h * es);
     mem.reserve(&L->xnext, nb * d * es);
-    mem.reserve(&L->sync, kSyncBytes);
+    mem.reserve(&L->sync, 256);
     mem.reserve(&L->yfix, yfix_bytes);
     if (L->use_fused) {
         mem.reserve(&L->rec_count, (size_t)L->dec_blocks * 4);
@@ -241,7 +239,6 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     if (byte_codes) mem.reserve(&L->Q, (size_t)h * d);
     if (packed4) mem.reserve(&L->Q4, (size_t)h * d / 2);
     if (L->sketch_bits < 8) mem.reserve(&L->M4, (size_t)h * ((d + 31) / 32));
-    if (products && L->sketch_bits == 8) mem.reserve(&L->code_scale, (size_t)h * 4);
     if (products) {
         L->prefill_chunk = env_int("TARDIS_PREFILL_CHUNK", 16384, 64, 32768);
         if (L->prefill_chunk > L->max_batch) L->prefill_chunk = (int32_t)L->max_batch;
@@ -252,6 +249,11 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
         mem.reserve(&L->wp8_scale, (size_t)d * 4);
     }
     if (stack_entry) mem.reserve(&L->stack_desc, sizeof(td_stack_layer_dev));
+    int32_t* no_scale = nullptr;                     // 1: some row's codes have no scale
+    if (products && L->sketch_bits == 8) {
+        mem.reserve(&L->code_scale, (size_t)h * 4);
+        mem.reserve(&no_scale, 4);
+    }
     if (L->fx) mem.reserve(&L->fx_bound, 8);
     // (the working memory first, and always from the device: where no memory can be asked for, as while a stream is
     // captured, the fold ends here, with nothing in the stream - also if the layer's own could be memory that is kept)
@@ -268,7 +270,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
         TD_TRY(td_stream_init());
     }
     TD_HIP(hipMemsetAsync(L->zeros_h, 0, (size_t)h * es, s));
-    TD_HIP(hipMemsetAsync(L->sync, 0, kSyncBytes, s));
+    TD_HIP(hipMemsetAsync(L->sync, 0, 256, s));
     TD_HIP(hipMemsetAsync(L->yfix, 0, yfix_bytes, s));
     TD_HIP(hipMemsetAsync(L->counts, 0, nb * 4, s));
     TD_HIP(hipMemsetAsync(L->mask, 0, nb * L->mask_words * 4, s));
@@ -278,8 +280,9 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // (the fold first: the two copies of W2 hold its operands until they are filled)
     TD_TRY(td_fold(desc, L->a, L->c, L->Wp, L->bp, L->Wp8, L->wp8_scale, L->W2T, L->W2, work, s));
     TD_TRY(td_transpose(desc->W2, L->W2T, L->W2, d, h, desc->dtype, s));
+    if (no_scale) TD_HIP(hipMemsetAsync(no_scale, 0, 4, s));
     TD_TRY(td_build_sketch(desc->W1, desc->b1, lo, hi, h, d, desc->dtype, L->sketch_bits, L->margin, L->Q, L->Q4, L->M4, L->tlo,
-                           L->thi, L->code_scale, L->sync + kNoScale, s));
+                           L->thi, L->code_scale, no_scale, s));
     L->stack_fused = env_int("TARDIS_STACK_FUSED", 0, 0, 2);   // 2: refuse a one-token stack the single launch cannot serve
     L->stack_spin_limit = env_int("TARDIS_STACK_SPIN_LIMIT", 1 << 22, 1, 1 << 30);
     if (stack_entry) {   // this layer's entry for the single-launch stack kernel
@@ -293,10 +296,10 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
         TD_HIP(hipStreamSynchronize(s));   // (hd lives on this stack frame)
     }
     if (L->fx) TD_TRY(td_fx_bounds(L, L->fx_bound, s));
-    int32_t no_scale = 0;
-    if (L->code_scale) TD_HIP(hipMemcpyAsync(&no_scale, L->sync + kNoScale, 4, hipMemcpyDeviceToHost, s));
+    int32_t without = 0;
+    if (no_scale) TD_HIP(hipMemcpyAsync(&without, no_scale, 4, hipMemcpyDeviceToHost, s));
     TD_HIP(hipStreamSynchronize(s));
-    if (no_scale) L->code_scale = nullptr;
+    if (without) L->code_scale = nullptr;
     return TARDIS_OK;
 }
 
