@@ -15,6 +15,11 @@ constexpr int64_t kMaxH = 1 << 22;
 constexpr int64_t kMaxCal = 32768;        // one neuron's samples are sorted in LDS
 constexpr int64_t kMaxSearchCal = 8192;   // range search also keeps sigma of every sample there, in fp64
 constexpr int64_t kMaxBatch = 4096;
+// 4-bit layers folded for at most this many tokens keep the packed sketch alone.  More tokens are groups of 8 and 16, which read one-byte
+// codes, and were groups of 4 and 2 without them; us at d = 4096, h = 16384, 1 / 5 / 15 % fallback, packed alone and with codes (67 MB more
+// for the layer): 5 tokens 79 / 92 / 115 and 42 / 51 / 67, 8 tokens 81 / 98 / 127 and 43 / 55 / 72, 16 tokens 162 / 197 / 253 and 55 / 73 /
+// 104; d = 2048, h = 8192, 5 %, 5, 8, 16 tokens 48, 49, 97 and 26, 28, 33.
+constexpr int64_t kPackedMaxBatch = 4;
 constexpr size_t kTokenLdsCap = 60 * 1024;
 
 // Live handles: a layer may name the layer that runs after it (a hint for cache warming); before
@@ -185,11 +190,11 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
             (d + L->dec_blocks - 1) / L->dec_blocks <= 64 && L->dec_blocks <= 65535;
     if (L->deterministic && !L->fx) return TARDIS_ERR_SHAPE;   // only the fused decode kernels have the ordered path
     // calls with at least this many tokens run as matrix products (prefill.hip).  Against decode groups at
-    // d=4096, h=16384 and 1 / 5 / 15 % fallback: 16 tokens 52 / 68 / 99 us in groups, 84 as products whatever the rate;
-    // 17 tokens (16 + 1) 73 / 93 / 129 against 84; from 18 on two full groups, 104 / 136 / 201 at 32 tokens, 85.  (d=2048: 16
-    // tokens 27 / 32 / 40 against 42; d=1024: 21 / 25 / 31 against 28.)  A layer without those kernels has only a launch
-    // sequence per token to compare with: from 2 tokens on.  (With fine factors, see below: from 19 on; 18 tokens at 5 % take 38 / 47 / 90 us in
-    // groups and 37 / 51 / 82 as products at d = 1024 / 2048 / 4096 and h = 3000 / 5000 / 11008, 19 a third group.)
+    // d=4096, h=16384 and 1 / 5 / 15 % fallback: 16 tokens 53 / 70 / 101 us in groups, 70 to 72 as products whatever the rate;
+    // 17 tokens (16 + 1) 75 / 96 / 133 against 72 (4-bit sketch 180 / 219 / 280 against 78).  d=2048: 17 tokens 42 / 48 / 58
+    // against 31; d=1024: 30 / 35 / 42 against 21.  A layer without those kernels has only a launch
+    // sequence per token to compare with: from 2 tokens on.  (With fine factors, see below: from 19 on; 18 tokens at 1 / 5 % take 33 / 38,
+    // 41 / 47, 74 / 94 us in groups and 34, 46, 73 as products at d = 1024 / 2048 / 4096 and h = 3000 / 5000 / 11008, 19 a third group.)
     const bool products = L->max_batch >= 2 && td_prefill_supported(L);   // (the dense FFN takes them from 2 tokens on)
     // 4-bit sketch: the decode kernel reads the packed form (d = 2048, 4096); every other path
     // reads one-byte effective codes, kept only where such a path can run
@@ -204,8 +209,8 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // 38 -> 52, d = 4096, h = 11008 69 -> 92 (the second product reads W2 once more).
     const bool coarse = d % 512 == 0 && d <= 8192 && h % 2048 == 0;
     L->fine_max_tokens = coarse ? 0 : packed4 ? INT32_MAX : 64;
-    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse || packed4 ? 18 : 19, 2, 1 << 20);
-    const bool byte_codes = !packed4 || (products && L->max_batch >= L->prefill_min_tokens);
+    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse ? 17 : packed4 ? 18 : 19, 2, 1 << 20);
+    const bool byte_codes = !packed4 || L->max_batch > kPackedMaxBatch;
     const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
     // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)

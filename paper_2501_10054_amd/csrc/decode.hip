@@ -1584,10 +1584,10 @@ namespace {
 tardis_status_t decode_group(tardis_layer_s* L, const DecodeScratch& ws, const void* x, void* y, float* yfold,
                              uint32_t* mask, int tokens, int n_act, int norm_out, hipStream_t s) {
     // packed 4-bit sketch (d = 2048 or 4096 only).  Groups of 8 and 16 tokens need one-byte codes
-    // (the matrix-core predictor), and with 4 tokens the unpacking already costs more vector ALU
-    // time than the halved stream saves (49 against 41 us at d = 4096, h = 16384): where the layer
-    // keeps one-byte codes as well - the same integers by definition - groups of 4 and more read those
-    if (L->Q4 && !(tokens >= 4 && L->Q && L->dec_threads == 1024)) {
+    // (the matrix-core predictor), and with 4 tokens the unpacking costs more vector ALU time than the halved stream saves at
+    // d = 4096 (h = 16384: 50 against 42 us), and less at d = 2048 (h = 8192: 24.5 against 26.0).  So where the layer keeps
+    // one-byte codes as well - the same integers by definition - those groups read them
+    if (L->Q4 && !(tokens >= (L->d >= 4096 ? 4 : 8) && L->Q && L->dec_threads == 1024)) {
         if (L->dec_threads == 512) {
             if (L->d == 2048) return launch_tb<2048, 512, 4>(L, ws, x, y, yfold, mask, tokens, n_act, norm_out, s);
             if (L->d == 4096) return launch_tb<4096, 512, 4>(L, ws, x, y, yfold, mask, tokens, n_act, norm_out, s);

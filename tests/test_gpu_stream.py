@@ -12,13 +12,13 @@ from test_gpu_parity import DEV, assert_y_close, custom_layer, dev, host, make_f
 pytestmark = pytest.mark.gpu
 
 
-def _check(layer, act, n, seed, d, h, coverage=0.85):
+def _check(layer, act, n, seed, d, h, coverage=0.85, bits=8, few=18):
     ffn = make_ffn(layer, act)
     ranges = T.tardis_calibrate(ffn, dev(synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL), "bf16"), coverage)
-    L = T.tardis_fold(ffn, *ranges, max_batch=n)
+    L = T.tardis_fold(ffn, *ranges, max_batch=n, sketch_bits=bits)
     X = synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST)
-    F = O.build(layer.W1, layer.b1, layer.W2, layer.b2, *(t.cpu().numpy() for t in ranges), act)
-    for rows in sorted({n, max(18, n - 1)}):         # (and a call that leaves rows of the scratch from the one before)
+    F = O.build(layer.W1, layer.b1, layer.W2, layer.b2, *(t.cpu().numpy() for t in ranges), act, **({} if bits == 8 else {"sketch_bits": bits}))
+    for rows in sorted({n, max(few, n - 1)}):         # (and a call that leaves rows of the scratch from the one before)
         y = T.tardis_ffn_forward_batched(L, dev(X[:rows], "bf16"))
         mask, _, _ = T.tardis_get_last_outliers(L, rows, want_list=False)
         want, flags = O.forward(F, X[:rows])
@@ -46,3 +46,12 @@ def test_rows_without_a_scale(tiny):
     layer.W1[7] *= tiny
     layer.W1[1000] *= tiny
     _check(layer, "gelu_erf", n, seed, d, h)
+
+
+@pytest.mark.parametrize("d", [2048, 4096])
+@pytest.mark.parametrize("n", [4, 5, 8, 16, 17])
+def test_packed_sketch_at_the_sizes_where_its_path_changes(d, n):
+    """4-bit layers folded for up to 4 tokens keep the packed codes alone, for more one-byte codes as well (groups of 8 and 16; 4 tokens of a
+    layer folded for 5 read either), and 17 tokens are products."""
+    seed = synth.workload_seed(9, 103)
+    _check(custom_layer(d, 2048, "bf16", seed, 0.02, True), "gelu_erf", n, seed, d, 2048, bits=4, few=1)
