@@ -212,8 +212,8 @@ tardis_status_t tardis_assign_thresholds(const float* err, int64_t n, float t, f
  * exactly as it uses the 8-bit code; tlo, thi as above with this s_j.  Storage is
  * 4 bits per weight plus one multiplier per group where the decode kernel reads the
  * packed form (bf16, d = 2048 or 4096), one byte per weight elsewhere; a layer
- * folded for more than 17 tokens per call keeps both, and its calls with 4 to 17
- * tokens read the one-byte form (same integers, faster there).
+ * folded for more than 4 tokens per call keeps both, and its calls with 5 tokens
+ * and more (d = 4096: 3 and more) read the one-byte form (same integers, faster there).
  *
  * W1, b1, b2 are BORROWED: they must stay valid and unchanged until
  * tardis_destroy (the repair step reads W1 in place).  W2 is copied into a
