@@ -273,7 +273,7 @@ bool td_gemm_on_matrix_cores(const void* A, const void* B, int64_t M, int64_t N,
 bool td_gemm_refuses_rows(int64_t M);
 // the products of calls with many tokens, each with the step that follows it (see gemm.hip)
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
-                               uint32_t* mask, void* out, void* rest, bool line, int64_t n, hipStream_t s);
+                               uint32_t* mask, void* out, void* rest, int64_t n, hipStream_t s);
 tardis_status_t td_gemm_hidden(const tardis_layer_s* L, const void* X, const void* b1, void* out, int64_t n, hipStream_t s);
 tardis_status_t td_gemm_output(const void* X, const void* Wp, const void* H, const void* W2, float* part, int* parts,
                                int64_t n, int64_t d, int64_t h, hipStream_t s);

@@ -193,16 +193,14 @@ struct GemmArgs {
     const int32_t* e;              //   exponent per row (readable to the next multiple of 16 bytes),
     uint32_t* mask;                //   flags, M x mask_words, written
     int mask_words;
-    int line;                      //   the line's product with z is part of `out`
     int act;
 };
 
 // F32: C = product (+ bias), or C += product.  PART: one range of K's share of C.  HIDDEN: out = sigma(product + bias).
 // REPAIR: the first pair of operands is int8 (token codes and predictor codes), the second bf16 (tokens and
-// W1): the sums of the first give the flags, those of the second z = product + bias, and out = sigma(z) - (slope z + icept) at
-// the flagged places, 0 elsewhere, or, with `line`, slope times the product more everywhere (with `rest`: as bf16 head and bf16
-// remainder, 16 significant bits together).  Neither the sums nor z leave the block, and the stream of slices goes on from the one
-// product to the other.
+// W1): the sums of the first give the flags, those of the second z, and out = sigma(z) - (slope z + icept) at
+// the flagged places, 0 elsewhere (with `rest`: as bf16 head and bf16 remainder, 16 significant bits together).  Neither
+// the sums nor z leave the block, and the stream of slices goes on from the one product to the other.
 enum { EPI_F32, EPI_PART, EPI_HIDDEN, EPI_REPAIR };
 
 // (the accumulator of the int8 form holds integers)
@@ -262,8 +260,8 @@ struct GemmTile {
 // What follows the products, W wavefronts in a grid of WM rows.  Some row blocks at a time go through LDS, so that a store covers
 // whole lines of a row, and so that what is done to the elements is a loop: unrolled over the accumulators, sigma alone is
 // 100 to 200 KB of instructions, which every block fetches once (2048 x 16384 x 4096 with GELU, eight wavefronts: sigma as a loop and without branches 251 -> 228 us).
-// REPAIR: the flagged pre-activations are staged, slope times the pre-activation elsewhere, and every lane replaces its own flagged ones by
-// their values, as many times as the lane with the most of them has any (5 %: about 14 times for 128 elements a lane).
+// REPAIR: the flagged pre-activations are staged, zeros elsewhere, and every lane replaces its own by their factors, as many
+// times as the lane with the most of them has any (5 %: about 14 times for 128 elements a lane).
 template <int EPI, int W, int WM, int NA, int NB>
 __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA][NB], const uint32_t (&bits)[NA], unsigned char* lds,
                                             int tid, int64_t m0, int64_t n0, int ks) {
@@ -283,16 +281,6 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
             par[2 * TN + c] = p.icept[n];
         }
         __syncthreads();
-    }
-    // REPAIR: what this lane's products are multiplied by where they are not flagged
-    [[maybe_unused]] f32x4_t line[NB];
-    if constexpr (EPI == EPI_REPAIR) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            line[j] = *reinterpret_cast<const f32x4_t*>(par + TN + wn * CW + j * 16 + fp * 4);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) line[j][q] = p.line ? line[j][q] : 0.0f;
-        }
     }
     // (pieces of 16 bytes, rotated by the row, against bank conflicts)
     auto place_of = [&](int row, int piece) { return row * CW + ((piece ^ (row & 15 & (PC - 1))) * 4); };
@@ -333,7 +321,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
                 f32x4_t v;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    if constexpr (EPI == EPI_REPAIR) v[q] = acc[i][j][q] * ((bits[i] >> (4 * j + q)) & 1u ? 1.0f : line[j][q]);
+                    if constexpr (EPI == EPI_REPAIR) v[q] = (bits[i] >> (4 * j + q)) & 1u ? acc[i][j][q] : 0.0f;
                     else v[q] = acc[i][j][q] + rb;
                 }
                 *reinterpret_cast<f32x4_t*>(chunk + place_of(u * 16 + frow, j * 4 + fp)) = v;
@@ -363,7 +351,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& p, f32x4_t (&acc)[NA
                         float* z = chunk + place_of(row0 + e / (4 * NB) * 16, piece) + e % 4;
                         const int c = wn * CW + piece * 4 + e % 4;
                         const float v = *z + par[c];
-                        *z = act_flat<decltype(act)::value>(v) - fmaf(par[TN + c], p.line ? par[c] : v, par[2 * TN + c]);
+                        *z = act_flat<decltype(act)::value>(v) - fmaf(par[TN + c], v, par[2 * TN + c]);
                     }
                 }
             });
@@ -1210,10 +1198,10 @@ tardis_status_t td_gemm_nt(const void* A, const void* B, float* C, int64_t M, in
 }
 
 // The products of calls with many tokens (bf16 layers, d % 128 == 0, h % 8 == 0, 16-byte aligned operands).
-// mask[t] = range test of Xq . Q^T (exact int32 sums), out[t] = sigma(z) - (a z + c) at its bits, else 0, z = X . W1^T + b1, and
-// (line) a (z - b1) more everywhere; rest (or null) = what `out` lost when it was rounded to bf16, in bf16
+// mask[t] = range test of Xq . Q^T (exact int32 sums), out[t] = sigma(z) - (a z + c) at its bits, else 0, z = X . W1^T + b1;
+// rest (or null) = what `out` lost when it was rounded to bf16, in bf16
 tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const int32_t* e, const void* X, const void* b1,
-                               uint32_t* mask, void* out, void* rest, bool line, int64_t n, hipStream_t s) {
+                               uint32_t* mask, void* out, void* rest, int64_t n, hipStream_t s) {
     GemmArgs p{};
     p.A = bytes_of(XQ);
     p.B = bytes_of(L->Q);
@@ -1233,7 +1221,6 @@ tardis_status_t td_gemm_repair(const tardis_layer_s* L, const int8_t* XQ, const 
     p.e = e;
     p.mask = mask;
     p.mask_words = (int)L->mask_words;
-    p.line = line ? 1 : 0;
     p.act = L->act;
     launch_tile<EPI_REPAIR>(p, s);
     TD_HIP(hipGetLastError());

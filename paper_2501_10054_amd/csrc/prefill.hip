@@ -5,20 +5,14 @@
 // gains nothing; the same per-token result is computed here from three matrix products on the
 // matrix cores, each with the step that follows it in its epilogue:
 //     ACC = Xq Q^T            exact int32 (the predictor's integer sums) -> range test -> mask words
-//     Z   = X W1^T            fp32 accumulate (the exact pre-activations less b1) -> D[t][j] = a_j Z, or, where token t flagged
-//                             neuron j, sigma(z) - (c_j + a_j b1_j), rounded to bf16
-//     Y   = D W2^T            in up to 8 ranges of h whose fp32 sums the finishing kernel adds: y = Y + b' (then the optional RMS
-//                             norm and the conversion)
-// The folded matrix has no part in it: its product with the tokens is the sum over the neurons of a_j Z W2_j, and all of Z and of
-// W2 are here anyway, so that the d columns of [X | repairs] [W' | W2]^T in front of the h need not be multiplied.  Measured
-// before and after, us: d = 4096, h = 16384, 333 tokens 152.8 -> 143.1, 2048 tokens 573 -> 549; d = 4096, h = 2056, 1537 tokens
-// 164 -> 120; d = 3072, h = 9000, 700 tokens 157 -> 141.  D's rounding takes the place of that of W' (one bf16 rounding of each
-// term of the same sum; where the terms of W' cancel it is the larger of the two, where they add up the smaller): error of y
-// against 64 bits over 10 sizes and coverages 2.16-2.25e-3 before, 2.15-2.24e-3 after, quotient 0.990 to 1.004, in the mean 0.997.
-// Not so (`stored`) for layers whose W' is kept in 8 bits, where the stored matrix defines the result, and for calls of up to 64
-// tokens, which differ by less from what the kernels for fewer tokens give if they multiply by the same W' (rounded apart:
-// 2.9e-3, below 2e-3 with the same W'): there D is 0 where nothing is flagged, sigma(z) - (a_j z + c_j) elsewhere, and
-//     Y   = [X | D] [W' | W2]^T   one product over d + h columns.
+//     Z   = X W1^T            fp32 accumulate (the exact pre-activations) -> D[t][j] = sigma(z) - (a_j z + c_j)
+//                             where token t flagged neuron j, else 0, rounded to bf16
+//     Y   = [X | D] [W' | W2]^T   one product over d + h columns, in up to 8 ranges whose fp32 sums the
+//                             finishing kernel adds: y = Y + b' (then the optional RMS norm and the conversion)
+// (The first d columns could be left out, W'x being the sum over the neurons of a_j z_j W2_j, whose factors are all here, and the
+// output product then runs over h columns: 333 tokens 153 -> 143 us, 2048 tokens 573 -> 549 at d = 4096, h = 16384.  But every
+// factor is then rounded to bf16 before the sum over the neurons, W' once behind it: where the sum is 2^-6 of its terms, y is off by
+// 15 % instead of 0.2 %, and a pre-activation beyond 32 bits makes a NaN of a y that is an ordinary number.)
 // Calls with few tokens on some layers (fine_max_tokens) keep what the rounding of D left as well and add its product
 // with W2^T: the kernels that serve fewer tokens multiply factors of 32 bits.
 // Up to 64 tokens the products stream the weights (stream.hip) where they can, and the first two read W1 alone.
@@ -175,14 +169,12 @@ finish_rows_kernel(const float* __restrict__ Y, int parts, size_t part_stride, c
     }
 }
 
-constexpr int64_t kStoredMaxTokens = 64;
-
 // Scratch of one chunk of n tokens
 struct PromptScratch {
     int8_t* xq;
     int32_t* e;
     bf16_t* x;          // aligned copy of the tokens (used when the caller's are not 16-byte aligned)
-    bf16_t* hid;        // D, or the dense hidden activations (n x h)
+    bf16_t* hid;        // repair factors D, or the dense hidden activations (n x h)
     bf16_t* rest;       // fine: remainders of D (n x h)
     float* part;        // partial sums of the output (fine: of both products)
     size_t bytes;
@@ -237,19 +229,19 @@ size_t td_prefill_scratch_bytes(const tardis_layer_s* L) {
 }
 
 // one chunk of at most L->prefill_chunk tokens (the scratch is sized for that many)
-static tardis_status_t prefill_chunk(tardis_layer_s* L, const bf16_t* x, int64_t n, bf16_t* y, uint32_t* mask, bool fine,
-                                     bool stored, int norm_out, hipStream_t s) {
+static tardis_status_t prefill_chunk(tardis_layer_s* L, const bf16_t* x, int64_t n, bf16_t* y, uint32_t* mask,
+                                     bool fine, int norm_out, hipStream_t s) {
     const int64_t d = L->d, h = L->h;
     const PromptScratch w(L->pf_scratch, n, d, h, fine);
-    const StreamPlan up = stored ? td_stream_up_plan(L, n) : StreamPlan{};
-    const StreamPlan down = td_stream_output_plan(stored, L->Wp, L->W2, n, d, h);
+    const StreamPlan up = td_stream_up_plan(L, n);
+    const StreamPlan down = td_stream_output_plan(true, L->Wp, L->W2, n, d, h);
     x = quantize(w, x, n, d, up, s);
     const void* b1 = L->b1 ? L->b1 : L->zeros_h;
     void* rest = fine ? w.rest : nullptr;
     if (up.tile) TD_TRY(td_stream_repair(L, up, w.xq, w.e, x, b1, mask, w.hid, rest, n, down, s));
-    else TD_TRY(td_gemm_repair(L, w.xq, w.e, x, b1, mask, w.hid, rest, !stored, n, s));
+    else TD_TRY(td_gemm_repair(L, w.xq, w.e, x, b1, mask, w.hid, rest, n, s));
     int parts = 1, more = 0;
-    TD_TRY(output(down, stored ? x : nullptr, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
+    TD_TRY(output(down, x, L->Wp, w.hid, L->W2, w.part, &parts, n, d, h, s));
     if (fine)
         TD_TRY(output(td_stream_output_plan(false, nullptr, L->W2, n, d, h), nullptr, nullptr, w.rest, L->W2, w.part + (size_t)parts * n * d, &more, n, d, h, s));
     parts += more;
@@ -266,8 +258,7 @@ tardis_status_t td_forward_prefill(tardis_layer_s* L, const void* xv, int64_t n,
     bf16_t* y = static_cast<bf16_t*>(yv);
     for (int64_t t0 = 0; t0 < n; t0 += L->prefill_chunk) {
         const int64_t nc = n - t0 < L->prefill_chunk ? n - t0 : L->prefill_chunk;
-        TD_TRY(prefill_chunk(L, x + t0 * L->d, nc, y + t0 * L->d, L->mask + t0 * L->mask_words, n <= L->fine_max_tokens,
-                             L->Wp8 != nullptr || n <= kStoredMaxTokens, norm_out, s));
+        TD_TRY(prefill_chunk(L, x + t0 * L->d, nc, y + t0 * L->d, L->mask + t0 * L->mask_words, n <= L->fine_max_tokens, norm_out, s));
     }
     L->last_n = n;
     return TARDIS_OK;

@@ -15,9 +15,9 @@ pytestmark = pytest.mark.gpu
 # d, h, tokens: tiles of the predictor's and the hidden product, and of the two paths' output products (test_tile_choice holds the library
 # to them)
 TILES = {(2048, 2056, 769): ("128x128", "128x128 of eight", "128x128 ragged", "128x128 ragged"),
-         (4096, 2056, 1537): ("192x128", "192x128", "256x128 ragged", "256x128 ragged"),
-         (4096, 4104, 1500): ("256x128", "256x128", "192x128 ragged", "192x128 ragged"),
-         (4096, 4104, 2048): ("192x256", "192x256", "256x128 ragged", "256x128 ragged"),
+         (4096, 2056, 1537): ("192x128", "192x128", "256x256 ragged", "256x128 ragged"),
+         (4096, 4104, 1500): ("256x128", "256x128", "192x256 ragged", "192x128 ragged"),
+         (4096, 4104, 2048): ("192x256", "192x256", "256x256 ragged", "256x128 ragged"),
          (2048, 8192, 1537): ("256x256", "256x256", "256x128", "256x128"),
          (3072, 6152, 1500): ("192x256 of eight", "192x256 of eight", "192x256 ragged", "192x256 ragged"),
          (4096, 6152, 1537): ("192x128", "192x128", "256x256 ragged", "256x256 ragged")}
