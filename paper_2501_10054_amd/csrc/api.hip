@@ -191,8 +191,9 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     if (L->deterministic && !L->fx) return TARDIS_ERR_SHAPE;   // only the fused decode kernels have the ordered path
     // calls with at least this many tokens run as matrix products (prefill.hip).  Against decode groups at
     // d=4096, h=16384 and 1 / 5 / 15 % fallback: 16 tokens 53 / 70 / 101 us in groups, 70 to 72 as products whatever the rate;
-    // 17 tokens (16 + 1) 75 / 96 / 133 against 72 (4-bit sketch 180 / 219 / 280 against 78).  d=2048: 17 tokens 42 / 48 / 58
-    // against 31; d=1024: 30 / 35 / 42 against 21.  A layer without those kernels has only a launch
+    // from 18 on two full groups, 104 / 136 / 201 at 32 tokens, 75.  17 tokens are 16 + 1, 75 / 96 / 133 (d=2048: 42 / 48 / 58, d=1024:
+    // 30 / 35 / 42) against 72 (31, 21), with factors of 32 bits that the products of `coarse` layers (see below) round to one bf16:
+    // where the factors cancel against b' that is an error of 4 % in y in place of 0.2 %.  A layer without those kernels has only a launch
     // sequence per token to compare with: from 2 tokens on.  (With fine factors, see below: from 19 on; 18 tokens at 1 / 5 % take 33 / 38,
     // 41 / 47, 74 / 94 us in groups and 34, 46, 73 as products at d = 1024 / 2048 / 4096 and h = 3000 / 5000 / 11008, 19 a third group.)
     const bool products = L->max_batch >= 2 && td_prefill_supported(L);   // (the dense FFN takes them from 2 tokens on)
@@ -209,7 +210,7 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     // 38 -> 52, d = 4096, h = 11008 69 -> 92 (the second product reads W2 once more).
     const bool coarse = d % 512 == 0 && d <= 8192 && h % 2048 == 0;
     L->fine_max_tokens = coarse ? 0 : packed4 ? INT32_MAX : 64;
-    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse ? 17 : packed4 ? 18 : 19, 2, 1 << 20);
+    L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse || packed4 ? 18 : 19, 2, 1 << 20);
     const bool byte_codes = !packed4 || L->max_batch > kPackedMaxBatch;
     const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block

@@ -51,3 +51,19 @@ def test_pre_activations_beyond_32_bits_that_nothing_flagged(n):
     assert not mask.any()
     want = 0.5 * (X @ W1.T.astype(np.float64)) @ W2.T.astype(np.float64)
     assert rel_l2(got, want) <= 1e-2
+
+
+@pytest.mark.parametrize("d,h,bits", [(1024, 4096, 8), (2048, 2048, 8), (2048, 2048, 4), (4096, 2048, 8), (4096, 2048, 4)])
+@pytest.mark.parametrize("n", [5, 16, 17])
+def test_up_to_17_tokens_have_repair_factors_of_32_bits(d, h, bits, n):
+    """Factors that have to cancel against b', as in test_repair_factors_are_not_rounded_to_one_bf16 (one bf16 a factor: 2 to 6 %), for
+    layers whose calls of more tokens round them."""
+    seed = synth.workload_seed(9, 112)
+    layer = synth.make_layer(d, h, "bf16", seed, w1_std=d ** -0.5, w2_std=0.05, heavy_frac=0.0, with_bias=False)
+    L = _layer(layer.W1, layer.W2, 0.0, 0.0, 0.0, 16.0, n, sketch_bits=bits)
+    X = synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST)
+    got = host(T.tardis_ffn_forward_batched(L, dev(X, "bf16")))
+    L.close()
+    z = torch.from_numpy(X).double() @ torch.from_numpy(layer.W1).double().T
+    want = (torch.nn.functional.gelu(z) @ torch.from_numpy(layer.W2).double().T).numpy()
+    assert rel_l2(got, want) <= 3e-3

@@ -52,6 +52,6 @@ def test_rows_without_a_scale(tiny):
 @pytest.mark.parametrize("n", [4, 5, 8, 16, 17])
 def test_packed_sketch_at_the_sizes_where_its_path_changes(d, n):
     """4-bit layers folded for up to 4 tokens keep the packed codes alone, for more one-byte codes as well (groups of 8 and 16; 4 tokens of a
-    layer folded for 5 read either), and 17 tokens are products."""
+    layer folded for 5 read either); 17 tokens are a group of 16 and one."""
     seed = synth.workload_seed(9, 103)
     _check(custom_layer(d, 2048, "bf16", seed, 0.02, True), "gelu_erf", n, seed, d, 2048, bits=4, few=1)
