@@ -51,11 +51,11 @@ class Host:
         for name in ("tardis_ffn_forward_batched", "tardis_dense_forward"):
             getattr(self.lib, name).argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
 
-    def fold(self, d=512, h=2048, max_batch=1, deterministic=0, dtype=T.BF16):
+    def fold(self, d=512, h=2048, max_batch=1, deterministic=0, dtype=T.BF16, bits=8):
         """status, handle"""
         at = lambda k: C.c_void_p((1 << 38) + (k << 30))       # (never read: nothing runs)
         desc = T.tardis_ffn_desc(d, h, dtype, 0, at(0), None, at(1), None)
-        opts = T.tardis_fold_opts(8, dtype, max_batch, deterministic, 0.0)
+        opts = T.tardis_fold_opts(bits, dtype, max_batch, deterministic, 0.0)
         out = C.c_void_p()
         return self.lib.tardis_fold(desc, at(2), at(3), at(4), at(5), opts, None, out), out
 

@@ -1,0 +1,22 @@
+"""Which codes a layer with a 4-bit sketch keeps, and which of its calls read them, from what the host code asks for and launches
+(host_runtime.py)."""
+import pytest
+
+from host_runtime import hip, host  # noqa: F401
+from paper_2501_10054_amd import tardis as T
+
+
+def _products(hip, L, n):  # noqa: F811
+    hip.launches()
+    assert hip.lib.tardis_ffn_forward_batched(L, 1 << 38, n, 1 << 37, None) == T.OK
+    return any("quantize_rows" in name for name in hip.launches())
+
+
+@pytest.mark.parametrize("max_batch", [2, 3, 4, 5, 17])
+def test_the_products_threshold_holds_for_packed_layers(hip, monkeypatch, max_batch):  # noqa: F811
+    """TARDIS_PREFILL_MIN: calls with at least that many tokens are products, whatever codes a layer keeps otherwise."""
+    monkeypatch.setenv("TARDIS_PREFILL_MIN", "2")
+    st, L = hip.fold(d=2048, h=2048, max_batch=max_batch, bits=4)
+    assert st == T.OK
+    assert all(_products(hip, L, n) for n in range(2, max_batch + 1)) and not _products(hip, L, 1)
+    hip.lib.tardis_destroy(L)
