@@ -214,6 +214,9 @@ tardis_status_t tardis_assign_thresholds(const float* err, int64_t n, float t, f
  * packed form (bf16, d = 2048 or 4096), one byte per weight elsewhere; a layer
  * folded for more than 4 tokens per call keeps both, and its calls with 5 tokens
  * and more (d = 4096: 3 and more) read the one-byte form (same integers, faster there).
+ * Folded with the environment variable TARDIS_PACKED_MAX=n, layers for up to n tokens
+ * keep the packed form alone (d x h bytes less), except where their calls run as matrix
+ * products (from 18 tokens on, see tardis_ffn_forward_batched).
  *
  * W1, b1, b2 are BORROWED: they must stay valid and unchanged until
  * tardis_destroy (the repair step reads W1 in place).  W2 is copied into a

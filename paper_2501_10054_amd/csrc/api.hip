@@ -15,11 +15,12 @@ constexpr int64_t kMaxH = 1 << 22;
 constexpr int64_t kMaxCal = 32768;        // one neuron's samples are sorted in LDS
 constexpr int64_t kMaxSearchCal = 8192;   // range search also keeps sigma of every sample there, in fp64
 constexpr int64_t kMaxBatch = 4096;
-// 4-bit layers folded for at most this many tokens, and for fewer than run as products, keep the packed sketch alone.  More tokens are groups of 8 and 16, which read one-byte
-// codes, and were groups of 4 and 2 without them; us at d = 4096, h = 16384, 1 / 5 / 15 % fallback, packed alone and with codes (67 MB more
-// for the layer): 5 tokens 79 / 92 / 115 and 42 / 51 / 67, 8 tokens 81 / 98 / 127 and 43 / 55 / 72, 16 tokens 162 / 197 / 253 and 55 / 73 /
-// 104; d = 2048, h = 8192, 5 %, 5, 8, 16 tokens 48, 49, 97 and 26, 28, 33.
-constexpr int64_t kPackedMaxBatch = 4;
+// 4-bit layers folded for at most this many tokens, and for fewer than run as products, keep the packed sketch alone.  More
+// tokens are groups of 8 and 16, which read one-byte codes (blocks of 1024 threads), and were groups of 4 and 2 without them; us at
+// d = 4096, h = 16384, 1 / 5 / 15 % fallback, packed alone and with codes (67 MB more for the layer): 5 tokens 79 / 92 / 115 and
+// 42 / 51 / 67, 8 tokens 81 / 98 / 127 and 43 / 55 / 72, 16 tokens 162 / 197 / 253 and 55 / 73 / 104; d = 2048, h = 8192, 5 %, 5, 8, 16
+// tokens 48, 49, 97 and 26, 28, 33.  Whoever wants the memory instead sets TARDIS_PACKED_MAX.
+constexpr int kPackedMaxBatch = 4;
 constexpr size_t kTokenLdsCap = 60 * 1024;
 
 // Live handles: a layer may name the layer that runs after it (a hint for cache warming); before
@@ -211,7 +212,8 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     const bool coarse = d % 512 == 0 && d <= 8192 && h % 2048 == 0;
     L->fine_max_tokens = coarse ? 0 : packed4 ? INT32_MAX : 64;
     L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse || packed4 ? 18 : 19, 2, 1 << 20);
-    const bool byte_codes = !packed4 || L->max_batch > kPackedMaxBatch || (products && L->max_batch >= L->prefill_min_tokens);
+    const bool groups_read_bytes = L->dec_threads == 1024 && L->max_batch > env_int("TARDIS_PACKED_MAX", kPackedMaxBatch, 0, 1 << 20);
+    const bool byte_codes = !packed4 || groups_read_bytes || (products && L->max_batch >= L->prefill_min_tokens);
     const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
     // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)

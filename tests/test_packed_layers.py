@@ -20,3 +20,31 @@ def test_the_products_threshold_holds_for_packed_layers(hip, monkeypatch, max_ba
     assert st == T.OK
     assert all(_products(hip, L, n) for n in range(2, max_batch + 1)) and not _products(hip, L, 1)
     hip.lib.tardis_destroy(L)
+
+
+@pytest.mark.parametrize("d", [2048, 4096])
+def test_one_byte_codes_of_packed_layers_can_be_left_out(hip, monkeypatch, d):  # noqa: F811
+    """They triple the resident sketch.  TARDIS_PACKED_MAX: layers folded for at most that many tokens keep the packed codes alone,
+    unless they can run as products."""
+    h = 4096
+
+    def memory(max_batch):
+        st, L = hip.fold(d=d, h=h, max_batch=max_batch, bits=4)
+        assert st == T.OK
+        used = hip.lib.fake_used()
+        hip.lib.tardis_destroy(L)
+        assert hip.lib.tardis_release_memory() == T.OK
+        return used
+
+    default = {n: memory(n) for n in (4, 5, 16, 18)}
+    monkeypatch.setenv("TARDIS_PACKED_MAX", "16")
+    assert [(default[n] - memory(n)) // 4096 for n in (4, 5, 16, 18)] == [0, d * h // 4096, d * h // 4096, 0]
+    monkeypatch.setenv("TARDIS_PREFILL_MIN", "1000000")
+    monkeypatch.setenv("TARDIS_PACKED_MAX", "1000000")
+    assert (default[18] - memory(18)) // 4096 == d * h // 4096
+    monkeypatch.delenv("TARDIS_PACKED_MAX")
+    monkeypatch.delenv("TARDIS_PREFILL_MIN")
+    monkeypatch.setenv("TARDIS_DECODE_THREADS", "512")     # (decode blocks of 512 threads read no one-byte codes)
+    few = memory(16)
+    monkeypatch.setenv("TARDIS_PACKED_MAX", "16")
+    assert few == memory(16)
