@@ -213,8 +213,10 @@ tardis_status_t fold_impl(const tardis_ffn_desc* desc, const float* lo, const fl
     L->fine_max_tokens = coarse ? 0 : packed4 ? INT32_MAX : 64;
     L->prefill_min_tokens = env_int("TARDIS_PREFILL_MIN", !L->use_fused ? 2 : coarse || packed4 ? 18 : 19, 2, 1 << 20);
     const bool groups_read_bytes = L->dec_threads == 1024 && L->max_batch > env_int("TARDIS_PACKED_MAX", kPackedMaxBatch, 0, 1 << 20);
-    const bool byte_codes = !packed4 || groups_read_bytes || (products && L->max_batch >= L->prefill_min_tokens);
-    const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && byte_codes;
+    const bool products_read_bytes = products && L->max_batch >= L->prefill_min_tokens;
+    const bool byte_codes = !packed4 || groups_read_bytes || products_read_bytes;
+    // (one token of a packed layer reads the packed codes, half the bytes, also where the layer has others for larger groups)
+    const bool stack_entry = L->use_fused && L->dtype == TARDIS_BF16 && (!packed4 || products_read_bytes);
     const int64_t npb = ((h + L->dec_blocks - 1) / L->dec_blocks + 31) / 32 * 32;   // neurons of a decode block
     // (at least two copies' worth: the fixed-point accumulators are 8 bytes per token and column)
     const size_t yfix_bytes = (size_t)(L->dec_copies < 2 ? 2 : L->dec_copies) * kDecodeMaxTokens * d * 4;

@@ -1,5 +1,7 @@
 """Which codes a layer with a 4-bit sketch keeps, and which of its calls read them, from what the host code asks for and launches
 (host_runtime.py)."""
+import ctypes as C
+
 import pytest
 
 from host_runtime import hip, host  # noqa: F401
@@ -38,7 +40,7 @@ def test_one_byte_codes_of_packed_layers_can_be_left_out(hip, monkeypatch, d):  
 
     default = {n: memory(n) for n in (4, 5, 16, 18)}
     monkeypatch.setenv("TARDIS_PACKED_MAX", "16")
-    assert [(default[n] - memory(n)) // 4096 for n in (4, 5, 16, 18)] == [0, d * h // 4096, d * h // 4096, 0]
+    assert [default[n] - memory(n) for n in (4, 5, 16, 18)] == [0, d * h, d * h, 0]
     monkeypatch.setenv("TARDIS_PREFILL_MIN", "1000000")
     monkeypatch.setenv("TARDIS_PACKED_MAX", "1000000")
     assert (default[18] - memory(18)) // 4096 == d * h // 4096
@@ -48,3 +50,17 @@ def test_one_byte_codes_of_packed_layers_can_be_left_out(hip, monkeypatch, d):  
     few = memory(16)
     monkeypatch.setenv("TARDIS_PACKED_MAX", "16")
     assert few == memory(16)
+
+
+@pytest.mark.parametrize("max_batch,st", [(1, T.ERR_SHAPE), (5, T.ERR_SHAPE), (17, T.ERR_SHAPE), (18, T.OK)])
+def test_single_launch_stacks_of_packed_layers(hip, monkeypatch, max_batch, st):  # noqa: F811
+    """TARDIS_STACK_FUSED=2 refuses a stack that the single launch, which reads one-byte codes, is not for: packed layers are
+    for it where they keep those for products, and one-token calls of the others read the packed codes."""
+    monkeypatch.setenv("TARDIS_STACK_FUSED", "2")
+    layers = [hip.fold(d=2048, h=2048, max_batch=max_batch, bits=4)[1] for _ in range(2)]
+    call = hip.lib.tardis_stack_forward
+    call.argtypes = [C.POINTER(C.c_void_p), C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
+    got = call((C.c_void_p * 2)(*(L.value for L in layers)), 2, 1 << 38, 1, 1 << 37, None)
+    for L in layers:
+        hip.lib.tardis_destroy(L)
+    assert got == st
