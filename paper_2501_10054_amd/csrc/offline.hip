@@ -267,10 +267,15 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
     const int64_t nv = vec ? d / V : 0;
     td_u32x4 keep[kKeep];
     float m = 0.0f;
+    bool nan = false;                                // (a NaN's stored code is -127, which no scale gives)
     auto vmax = [&](const td_u32x4& w) {
         const T* wt = reinterpret_cast<const T*>(&w);
 #pragma unroll
-        for (int u = 0; u < V; ++u) m = fmaxf(m, fabsf(td_load<T>(wt + u)));
+        for (int u = 0; u < V; ++u) {
+            const float f = td_load<T>(wt + u);
+            m = fmaxf(m, fabsf(f));
+            nan |= f != f;
+        }
     };
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) {
@@ -281,7 +286,12 @@ sketch_kernel(const T* __restrict__ W1, const T* __restrict__ b1, const float* _
         }
     }
     for (int64_t v = kKeep * kBlock + threadIdx.x; v < nv; v += kBlock) vmax(reinterpret_cast<const td_u32x4*>(row)[v]);
-    for (int64_t k = nv * V + threadIdx.x; k < d; k += kBlock) m = fmaxf(m, fabsf(td_load<T>(row + k)));
+    for (int64_t k = nv * V + threadIdx.x; k < d; k += kBlock) {
+        const float f = td_load<T>(row + k);
+        m = fmaxf(m, fabsf(f));
+        nan |= f != f;
+    }
+    if (no_scale && nan) *no_scale = 1;
     m = td_wave_max(m);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = m;
     __syncthreads();

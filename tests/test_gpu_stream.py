@@ -55,3 +55,25 @@ def test_packed_sketch_at_the_sizes_where_its_path_changes(d, n):
     layer folded for 5 read either); 17 tokens are a group of 16 and one."""
     seed = synth.workload_seed(9, 103)
     _check(custom_layer(d, 2048, "bf16", seed, 0.02, True), "gelu_erf", n, seed, d, 2048, bits=4, few=1)
+
+
+def test_rows_with_a_nan_have_the_stored_codes_on_every_path():
+    """The predictor's code of a NaN is the definition's -127 in the stored codes; masks do not depend on how many tokens a call has."""
+    d, h, n = 1024, 2048, 40
+    seed = synth.workload_seed(9, 104)
+    layer = custom_layer(d, h, "bf16", seed, 0.1, True)
+    ranges = T.tardis_calibrate(make_ffn(layer), dev(synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL), "bf16"), 0.7)
+    rng = np.random.default_rng(31)
+    rows = rng.choice(h, 64, replace=False)
+    for j in rows:
+        layer.W1[j, rng.choice(d, 8, replace=False)] = np.nan
+    L = T.tardis_fold(make_ffn(layer), *ranges, max_batch=n)
+    x = dev(synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST), "bf16")
+    T.tardis_ffn_forward_batched(L, x)
+    together = T.tardis_get_last_outliers(L, n, want_list=False)[0]
+    one = []
+    for t in range(n):
+        T.tardis_ffn_forward(L, x[t].contiguous())
+        one.append(T.tardis_get_last_outliers(L, 1, want_list=False)[0])
+    assert torch.equal(together, torch.cat(one))
+    L.close()
