@@ -385,18 +385,26 @@ tardis_status_t td_stream_init() {
     });
 }
 
-// (at every size: 512 x 2048, 20 tokens 18.7 -> 16.5 us with it, 1024 x 4096, 40 tokens 23.7 -> 21.5, 3072 x 6144, 50 tokens 43 -> 40)
+// Where one pass over W1 is the faster way to both products of the up product. A block is alone on its CU, so nothing hides its beginning and its
+// end: rows of W1 have to be long, and one round of blocks to do. us a call with gemm_tile_kernel and Q / with this, layers in turn so that
+// weights come from HBM, 20, 32, 40, 64 tokens: d = 4096, h = 10240 68 / 62, 67 / 61, 68 / 65, 73 / 69; d = 2048, h = 4096 30.5 / 28, 31 / 28.5,
+// 31 / 30.5, 32 / 32, h = 8192 35 / 33, 35 / 33, 35 / 35, 37 / 37; d = 1536, h = 12288 37 / 36, 37 / 35.5, 38 / 39, 40 / 41.5; d = 1024, h =
+// 12288 30 / 29, 31 / 30, 30 / 32, 32 / 34; d = 512, h = 4096 21 / 21, 21 / 22, 21 / 22, 22 / 22. Two full rounds: d = 4096, h = 32768 137 / 133,
+// 132 / 131, 133 / 137, 135 / 143; d = 512, h = 32768 36 / 41, 38 / 43, 38 / 47, 39 / 49; more of them, of 32 rows: d = 4096, h = 20480 98 / 103,
+// 96 / 103, 97 / 113, 103 / 120. Blocks of 32 rows that are longer than 12 KB: d = h = 6144 76 / 64, 77 / 62, 74 / 69, 80 / 76; d = h = 8192 111
+// / 114, 111 / 111, 108 / 117, 112 / 118.
 StreamPlan td_stream_up_plan(const tardis_layer_s* L, int64_t n) {
     StreamPlan w{};
-    if (n > kStreamMaxTokens || !L->code_scale) return w;
+    if (n > kStreamMaxTokens || !L->code_scale || L->d < (n <= 32 ? 1024 : 2048)) return w;
     w.B = w.B2 = bytes_of(L->W1);
     w.N = L->h;
     w.k = (uint32_t)(L->d * 2);
     w.splits = 1;
     w.slices = (int)(w.k / kStreamSlice);
     // 64 rows a block, or 32 where those leave fewer rows to the CU that has most of them
-    const int64_t wide = ((w.N + 63) / 64 + 255) / 256 * 64, narrow = ((w.N + 31) / 32 + 255) / 256 * 32;
-    w.tile = wide <= narrow ? 64 : 32;
+    const int64_t wide = (w.N + 63) / 64, narrow = (w.N + 31) / 32;
+    if (narrow <= 256 && L->d <= 6144) w.tile = 32;
+    else if (narrow > 256 && (wide <= 256 || (n <= 32 && L->d >= 3072 && wide >= 410 && wide <= 512))) w.tile = 64;
     return w;
 }
 
@@ -427,7 +435,7 @@ StreamPlan td_stream_output_plan(bool folded, const void* Wp, const void* W2, in
     return w;
 }
 
-// as td_gemm_repair without `line`; plan: td_stream_up_plan's, next: of the launch that follows
+// as td_gemm_repair; plan: td_stream_up_plan's, next: of the launch that follows
 tardis_status_t td_stream_repair(const tardis_layer_s* L, const StreamPlan& plan, const int8_t* XQ, const int32_t* e, const void* X,
                                  const void* b1, uint32_t* mask, void* out, void* rest, int64_t n, const StreamPlan& next, hipStream_t s) {
     StreamArgs p{};

@@ -1,0 +1,46 @@
+"""Which calls of up to 64 tokens stream their weights, from the kernels that the host code launches (host_runtime.py): on either side of
+the lines that the measurements beside the rules (stream.hip) draw."""
+import re
+
+import pytest
+
+from host_runtime import hip, host  # noqa: F401
+from paper_2501_10054_amd import tardis as T
+
+
+def kernels(names):
+    """matrix products of a call in their order: stream_kernel with its constants, or the other kernels' epilogue"""
+    out = []
+    for name in names:
+        m = re.search(r"stream_kernelILi(\d)ELi(\d)ELi(\d)E", name)
+        if m:
+            out.append(f"{('part', 'repair')[int(m[1])]} {16 * int(m[2])} x {16 * int(m[3])}")
+        m = re.search(r"gemm_(?:quad|tile)_kernelILi(\d)E", name)
+        if m:
+            out.append(("store", "part", "hidden", "repair")[int(m[1])])
+    return out
+
+
+def call(hip, d, h, n, dense=False, **fold):  # noqa: F811
+    st, L = hip.fold(d=d, h=h, max_batch=max(n, 64), **fold)
+    assert st == T.OK
+    hip.launches()
+    assert (hip.lib.tardis_dense_forward if dense else hip.lib.tardis_ffn_forward_batched)(L, 1 << 38, n, 1 << 37, None) == T.OK
+    got = kernels(hip.launches())
+    hip.lib.tardis_destroy(L)
+    return got
+
+
+UP = [(512, 2048, 20, "repair"), (896, 4096, 32, "repair"), (1024, 4096, 32, "repair 32 x 32"), (1024, 4096, 33, "repair"), (1920, 4096, 33, "repair"),
+      (2048, 4096, 33, "repair 64 x 32"), (1024, 8192, 20, "repair 32 x 32"), (1024, 8200, 20, "repair 32 x 64"), (1024, 16384, 20, "repair 32 x 64"),
+      (4096, 16384, 64, "repair 64 x 64"), (4096, 16392, 64, "repair"), (4096, 20480, 20, "repair"), (4096, 32768, 32, "repair 32 x 64"), (4096, 32768, 33, "repair"),
+      (2048, 32768, 20, "repair"), (4096, 40960, 20, "repair"), (6144, 8192, 64, "repair 64 x 32"), (6272, 8192, 64, "repair"), (8192, 16384, 64, "repair 64 x 64")]
+
+
+@pytest.mark.parametrize("d,h,n,want", UP)
+def test_up_products(hip, d, h, n, want):  # noqa: F811
+    assert call(hip, d, h, n)[0] == want
+
+
+def test_prompts_do_not_stream(hip):  # noqa: F811
+    assert call(hip, 4096, 16384, 65)[0] == "repair" and call(hip, 4096, 16384, 64, bits=4)[0] == "repair"
