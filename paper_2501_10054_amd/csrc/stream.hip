@@ -348,16 +348,19 @@ __global__ void __launch_bounds__(512) stream_kernel(StreamArgs p) {
     }
 }
 
-// f(token blocks, row blocks) with the constants of a tile
-template <typename F> void for_stream_tile(bool many, bool wide, F f) {
-    if (many && wide) f(num<4>{}, num<4>{});
-    else if (many) f(num<4>{}, num<2>{});
-    else if (wide) f(num<2>{}, num<4>{});
+// f(token blocks, row blocks) with the constants of a tile (output products of more than 32 tokens have 64 rows a block)
+template <int MODE, typename F> void for_stream_tile(bool many, bool wide, F f) {
+    if (many && (wide || MODE == STREAM_PART)) f(num<4>{}, num<4>{});
+    else if constexpr (MODE == STREAM_REPAIR) {
+        if (many) f(num<4>{}, num<2>{});
+        else if (wide) f(num<2>{}, num<4>{});
+        else f(num<2>{}, num<2>{});
+    } else if (wide) f(num<2>{}, num<4>{});
     else f(num<2>{}, num<2>{});
 }
 
 template <int MODE> void launch_stream(const StreamArgs& p, hipStream_t s) {
-    for_stream_tile(p.M > 32, p.w.tile == 64, [&](auto tf, auto nf) {
+    for_stream_tile<MODE>(p.M > 32, p.w.tile == 64, [&](auto tf, auto nf) {
         typedef StreamTile<MODE, tf, nf> G;
         hipLaunchKernelGGL((stream_kernel<MODE, tf, nf>), dim3((unsigned)stream_blocks(p.w)), dim3(512), G::kLds, s, p);
     });
@@ -376,11 +379,10 @@ tardis_status_t td_stream_init() {
                                       hipFuncAttributeMaxDynamicSharedMemorySize, StreamTile<decltype(mode)::value, decltype(tf)::value, decltype(nf)::value>::kLds) == hipSuccess;
         };
         for (int many = 0; many < 2; ++many)
-            for (int wide = 0; wide < 2; ++wide)
-                for_stream_tile(many, wide, [&](auto tf, auto nf) {
-                    raise(num<STREAM_PART>{}, tf, nf);
-                    raise(num<STREAM_REPAIR>{}, tf, nf);
-                });
+            for (int wide = 0; wide < 2; ++wide) {
+                for_stream_tile<STREAM_PART>(many, wide, [&](auto tf, auto nf) { raise(num<STREAM_PART>{}, tf, nf); });
+                for_stream_tile<STREAM_REPAIR>(many, wide, [&](auto tf, auto nf) { raise(num<STREAM_REPAIR>{}, tf, nf); });
+            }
         return ok ? TARDIS_OK : TARDIS_ERR_HIP;
     });
 }
@@ -408,13 +410,23 @@ StreamPlan td_stream_up_plan(const tardis_layer_s* L, int64_t n) {
     return w;
 }
 
-// Matrices of 60 MB and more.  Below that what stands around the stream counts for more, and gemm_tile_kernel has less of it.  us with
-// gemm_tile_kernel / this: dense, 20, 64 tokens: d = 2048, h = 8192 (34 MB) 24.2 / 25.4, 25.5 / 28.0; d = 3072, h = 6144 (38 MB) 26.4 /
-// 27.2, 30.4 / 31.9; d = 4096, h = 8192 (67 MB) 39.3 / 36.4, 44.1 / 39.8; d = 3072, h = 12288 (75 MB) 42.4 / 35.6, 51.2 / 46.2; d = 4096,
-// h = 16384 67.5 / 59.3, 71.5 / 65.8; folded, 60 tokens: d = 3072, h = 6144 (57 MB) 40.0 / 43.3, d = 3072, h = 12288 61.7 / 60.6.
+// Matrices of 60 MB and more (33 tokens and more: 100) and of up to 4096 rows, where a round of blocks fills the CUs. Below that what stands
+// around the stream counts for more, and gemm_tile_kernel has less of it. us with gemm_tile_kernel / this, layers in turn so that weights come
+// from HBM: dense, 20, 32, 64 tokens: d = 3072, h = 6144 (38 MB) 31 / 30, 30 / 29, 33.5 / 33; d = 4096, h = 8192 (67 MB) 39 / 38, 38 / 37, 41.5 /
+// 42; d = 3072, h = 12288 (75 MB) 42 / 38.5, 42 / 40, 49 / 47; d = 4096, h = 14336 (117 MB) 56.5 / 50, 57 / 51, 63 / 58; d = 4096, h = 16384 66 /
+// 56.5, 66 / 57, 70 / 63. Folded, 20, 32, 40, 64 tokens: d = 2048, h = 16384 (75 MB) 47.5 / 45, 46 / 44, 47 / 45, 49.5 / 48; d = 4096, h = 10240
+// (117 MB) 68 / 61.5, 67 / 59, 68 / 62, 73 / 67; d = 4096, h = 16384 82 / 77, 81 / 75, 82 / 76, 85 / 80. CUs without a block, three quarters
+// filled: d = 3072, h = 12288 (94 MB) 56 / 53, 55 / 52, 57 / 54, 62 / 60; h = 24576 87 / 86, 85 / 86, 88 / 86, 96 / 95; h = 31104 134 / 140, 133
+// / 145, 137 / 145, 146 / 160; nine sixteenths: d = 2304, h = 13824 66 / 68, 67 / 67, 68 / 71, 73 / 78. More rows: d = 5120, h = 13696 119 / 126,
+// 120 / 127, 124 / 135, 137 / 150; d = h = 8192 111 / 124, 111 / 120, 108 / 119, 112 / 126. Fewer, with many tokens: d = 1920, h = 16384, 40, 64
+// tokens 65 / 68, 67 / 70. (The loads pass the last cache by. A layer that is called again and again, with nothing between that takes its place
+// there, loses by that: d = 4096, h = 8192, dense, 20, 32 tokens 33 / 36, 33.5 / 37; d = 4096, h = 16384, 20, 32, 40, 64 tokens 72.5 / 73, 72 /
+// 72, 72 / 76, 74 / 78.)
 StreamPlan td_stream_output_plan(bool folded, const void* Wp, const void* W2, int64_t n, int64_t d, int64_t h) {
     StreamPlan w{};
-    if (n > kStreamMaxTokens || d % 128 != 0 || h % 128 != 0 || d * (h + (folded ? d : 0)) * 2 < 60000000) return w;
+    const int64_t bytes = d * (h + (folded ? d : 0)) * 2;
+    if (n > kStreamMaxTokens || d % 128 != 0 || h % 128 != 0 || d > 4096 || bytes < 60000000) return w;
+    if (n > 32 && (d < 2048 || bytes < 100000000)) return w;
     w.B = bytes_of(folded ? Wp : W2);
     w.B2 = bytes_of(W2);
     w.N = d;
@@ -424,13 +436,16 @@ StreamPlan td_stream_output_plan(bool folded, const void* Wp, const void* W2, in
     // the tile and the number of ranges with the least time: rounds over 256 CUs x (slices at the rate of HBM per CU + a launch's
     // beginning and end), and the partial sums written and read again
     double best = 1e300;
-    for (int tile = 64; tile >= 32; tile /= 2)
+    int64_t launched = 0;
+    for (int tile = 64; tile >= (n > 32 ? 64 : 32); tile /= 2)
         for (int sp = 1; sp <= 8 && (sp == 1 || slices / sp >= 4); sp *= 2) {
             const int64_t blocks = (w.N + tile - 1) / tile * sp;
             const double per = (double)((slices + sp - 1) / sp) * (double)(tile + (n > 32 ? 16 : 8)) * 256.0 / 24e3;
             const double cost = (double)((blocks + 255) / 256) * (per + 3.0) + (double)(sp * n * d) * 8.0 / 4e6;
-            if (cost < best) { best = cost; w.tile = tile; w.splits = sp; }
+            if (cost < best) { best = cost; w.tile = tile; w.splits = sp; launched = blocks; }
         }
+    const bool few = n <= 32 && bytes <= 160000000;
+    if (launched > 256 || launched < (few ? 192 : 205)) w.tile = 0;      // (three quarters, four fifths of the CUs)
     w.slices = (slices + w.splits - 1) / w.splits;
     return w;
 }

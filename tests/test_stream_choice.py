@@ -44,3 +44,18 @@ def test_up_products(hip, d, h, n, want):  # noqa: F811
 
 def test_prompts_do_not_stream(hip):  # noqa: F811
     assert call(hip, 4096, 16384, 65)[0] == "repair" and call(hip, 4096, 16384, 64, bits=4)[0] == "repair"
+
+
+# (d, h, tokens, folded: kernels of the output, dense: the same)
+OUTPUT = [(4096, 3200, 20, ["part", "part"], ["part"]), (4096, 3328, 20, ["part 32 x 64", "part"], ["part"]), (4096, 3328, 33, ["part", "part"], ["part"]),
+          (4096, 8192, 32, ["part 32 x 64"], ["part 32 x 64"]), (4096, 8192, 33, ["part 64 x 64"], ["part"]), (4096, 8320, 40, ["part 64 x 64", "part"], ["part"]),
+          (4096, 16384, 64, ["part 64 x 64"], ["part 64 x 64"]), (4096, 16392, 20, ["part", "part"], ["part"]), (4096, 16384, 65, ["part"], ["part"]),
+          (2048, 14720, 20, ["part 32 x 64", "part 32 x 64"], ["part 32 x 64"]), (4096, 12416, 40, ["part 64 x 64", "part 64 x 64"], ["part 64 x 64"]),
+          (2048, 24576, 64, ["part 64 x 64"], ["part 64 x 64"]), (1024, 28672, 20, ["part 32 x 32"], ["part"]), (1024, 30720, 32, ["part 32 x 32"], ["part 32 x 32"]),
+          (1024, 65536, 33, ["part"], ["part"]), (3072, 12288, 32, ["part 32 x 64"], ["part 32 x 64"]), (3072, 24576, 32, ["part"], ["part 32 x 64"]),
+          (3072, 16384, 33, ["part"], ["part"]), (2560, 10240, 20, ["part"], ["part"]), (5120, 20480, 20, ["part"], ["part"]), (8192, 8192, 20, ["part"], ["part"])]
+
+
+@pytest.mark.parametrize("d,h,n,folded,dense", OUTPUT)
+def test_output_products(hip, d, h, n, folded, dense):  # noqa: F811
+    assert call(hip, d, h, n)[1:] == folded and call(hip, d, h, n, dense=True)[1:] == dense
