@@ -6,6 +6,7 @@ import pytest
 
 from host_runtime import hip, host  # noqa: F401
 from paper_2501_10054_amd import tardis as T
+from test_gpu_stream import STREAMS
 
 
 def kernels(names):
@@ -59,3 +60,14 @@ OUTPUT = [(4096, 3200, 20, ["part", "part"], ["part"]), (4096, 3328, 20, ["part 
 @pytest.mark.parametrize("d,h,n,folded,dense", OUTPUT)
 def test_output_products(hip, d, h, n, folded, dense):  # noqa: F811
     assert call(hip, d, h, n)[1:] == folded and call(hip, d, h, n, dense=True)[1:] == dense
+
+
+@pytest.mark.parametrize("size", STREAMS)
+def test_kernels_of_the_gpu_tests(hip, size):  # noqa: F811
+    d, h, n = size
+    assert call(hip, d, h, n) == list(STREAMS[size][:-1]) and call(hip, d, h, n, dense=True) == ["hidden", STREAMS[size][-1]]
+
+
+def test_the_gpu_tests_reach_every_stream():
+    seen = {k for kernels_of in STREAMS.values() for k in kernels_of if " x " in k}
+    assert seen == {f"repair {m} x {n}" for m in (32, 64) for n in (32, 64)} | {"part 32 x 32", "part 32 x 64", "part 64 x 64"}
