@@ -625,8 +625,9 @@ __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo
 // sigma of every sample once, in fp64.
 // What bounds it: vector instructions, about half of them for sigma (without it 59 of 107 us).  4096 neurons x 4096 samples:
 // 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 95 us with the sigma of
-// sigma.h and one pass; 81 with its constants in scalar registers, shared by two samples, and registers for five blocks a CU (left to the
-// compiler 88, with six or more blocks registers spill: 92 to 104).  (A full bitonic sort in LDS and sigma taken twice: 375.)
+// sigma.h and one pass; 81 with its constants in scalar registers, shared by two samples, and registers for five blocks a CU (one of them
+// spills; left to the compiler 88, with six or more blocks 92 to 104).  (A full bitonic sort in LDS and sigma taken twice: 375.)
+// (Blocks of 512 threads are two a CU with 96 registers as with 128: with 96 two spill, 8192 samples, N(0, 1.6^2), 85 us either way.)
 //
 // A sample closer to the end of a range than fp32 can tell (both are fp32 here) would count as inside or
 // outside by luck of rounding.  For those (a few of 16384 neurons) the pre-activations of the two samples
@@ -635,7 +636,7 @@ constexpr int kSelBins = 1024;
 constexpr int kSelList = 256;
 
 template <typename E, int T, int NPT>
-__global__ void __launch_bounds__(T, T == 1024 ? 4 : 5)
+__global__ void __launch_bounds__(T, T == 256 ? 5 : 4)
 calibrate_neuron_kernel(const float* __restrict__ Zt, const E* __restrict__ W1, const E* __restrict__ b1,
                         const E* __restrict__ X, int n, int npad, int64_t d, float coverage,
                         const float* __restrict__ cov_pn, int act, float* __restrict__ lo, float* __restrict__ hi,
