@@ -627,7 +627,9 @@ __device__ __forceinline__ void fit_and_store(const float* vals, int n, float lo
 // 112 us with the library's erf, whose two branches a wavefront both takes, and a fit in two passes; 95 us with the sigma of
 // sigma.h and one pass; 81 with its constants in scalar registers, shared by two samples, and registers for five blocks a CU (one of them
 // spills; left to the compiler 88, with six or more blocks 92 to 104).  (A full bitonic sort in LDS and sigma taken twice: 375.)
-// (Blocks of 512 threads are two a CU with 96 registers as with 128: with 96 two spill, 8192 samples, N(0, 1.6^2), 85 us either way.)
+// Samples that all lie below 1, 4096 x 4096 with N(0, 0.23^2): 58 when only the compiler kept sigma's far form apart, 68 with both forms for
+// every pair, 52 with the far one behind a branch; 8192 samples 65, 80, 64.  (Blocks of 512 threads are two a CU with 96 registers as
+// with 128: with 96 two spill, 8192 samples, N(0, 1.6^2), 85 us either way.)
 //
 // A sample closer to the end of a range than fp32 can tell (both are fp32 here) would count as inside or
 // outside by luck of rounding.  For those (a few of 16384 neurons) the pre-activations of the two samples

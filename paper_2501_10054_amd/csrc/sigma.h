@@ -40,7 +40,7 @@ template <int ACT> __device__ __forceinline__ float act_flat(float z) {
     }
 }
 
-// sigma in fp64 without branches, for the calibration's samples.  GELU = z Phi(z): for |z| < 1 Phi = 1/2 + z S(z^2), S interpolated at
+// sigma in fp64 without divergent branches, for the calibration's samples.  GELU = z Phi(z): for |z| < 1 Phi = 1/2 + z S(z^2), S interpolated at
 // Chebyshev points, else from Phi(-|z|) = erfc(x) / 2, x = |z| / sqrt(2): with p = x - sqrt(1/2) + K, p exp(x^2) erfc(x) is a polynomial in
 // 1 - 2 K / p (after the substitution of Shepherd and Laframboise, Math. Comp. 36, 1981; K = 4, degree 13, Chebyshev points for x up to
 // 4: 4e-16 of the value; less beyond that, of a value below 1e-8).  Root mean square error against 60 digits, and of the library's erf
@@ -92,28 +92,35 @@ template <int ACT, int N> __device__ __forceinline__ void act_flat_f64(double (&
             0.39894228040143265, -0.06649038006690387, 0.009973557009983732, -0.001187328214811527, 0.0001154346832492605,
             -9.444639861853272e-06, 6.659317805752481e-07, -4.117317843452298e-08, 2.2271240384729976e-09,
             -9.027164883791298e-11};
-        double u[N], w[N], r[N], t[N], s[N], near[N];
+        double u[N], w[N], near[N], half[N];
+        bool far = false;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             u[i] = fmin(fabs(z[i]), 60.0);                                 // (Phi(-60) is 0, and infinities stay what they were)
             w[i] = u[i] * u[i];
-            r[i] = rcp_f64(fma_constant(u[i], kRootHalf, K - kRootHalf));
-            t[i] = fma(-2.0 * K, r[i], 1.0);
-            s[i] = c[13];
             near[i] = b[9];
+            half[i] = 0.0;
+            far |= u[i] >= 1.0;
         }
-#pragma unroll
-        for (int k = 12; k >= 0; --k) step_f64(s, t, c[k]);
 #pragma unroll
         for (int k = 8; k >= 0; --k) step_f64(near, w, b[k]);
+        if (__any(far)) {                                                  // (a layer's samples may all lie below 1)
+            double r[N], t[N], s[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) w[i] *= -0.5;
-        exp_f64(w);
+            for (int i = 0; i < N; ++i) {
+                r[i] = rcp_f64(fma_constant(u[i], kRootHalf, K - kRootHalf));
+                t[i] = fma(-2.0 * K, r[i], 1.0);
+                s[i] = c[13];
+                w[i] *= -0.5;
+            }
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const double half = s[i] * r[i] * w[i];
-            z[i] *= u[i] < 1.0 ? fma(z[i], near[i], 0.5) : z[i] > 0.0 ? 1.0 - half : half;
+            for (int k = 12; k >= 0; --k) step_f64(s, t, c[k]);
+            exp_f64(w);
+#pragma unroll
+            for (int i = 0; i < N; ++i) half[i] = s[i] * r[i] * w[i];
         }
+#pragma unroll
+        for (int i = 0; i < N; ++i) z[i] *= u[i] < 1.0 ? fma(z[i], near[i], 0.5) : z[i] > 0.0 ? 1.0 - half[i] : half[i];
     } else if constexpr (ACT == TARDIS_ACT_GELU_TANH) {
         // as in 32 bits; |v| beyond 1e5 is 1e5 (where e is 0)
         double e[N];
