@@ -1,4 +1,4 @@
-"""The stream that the binding passes when none is given."""
+"""The stream that the binding passes when none is given.  (Not the first of the GPU tests: the demo in C is started while nothing drives the GPU yet.)"""
 import importlib.util
 
 import pytest
