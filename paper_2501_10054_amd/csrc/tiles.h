@@ -31,7 +31,7 @@ __device__ __forceinline__ i32x4_t buffer_of(const void* p, uint32_t bytes) {
 
 // 64 x 16 bytes from rs[voff + soff] to LDS at lds + 16 * lane (past the buffer's end: nothing is fetched).
 // (m0 is set and used in the one statement.  It is a reserved register, which the compiler does not take as a clobber; it
-// uses it nowhere else in these kernels, and the listing's test holds it to that)
+// uses it nowhere else in the kernels of gemm.hip and stream.hip, and the tests of their listings hold it to that)
 template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voff, i32x4_t rs, uint32_t soff) {
     if constexpr (ONCE)

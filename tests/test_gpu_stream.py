@@ -90,6 +90,31 @@ def test_chunks_of_a_long_call_that_stream(monkeypatch):
     _check(custom_layer(d, h, "bf16", seed, 0.02, True), "gelu_erf", n, seed, d, h)
 
 
+def test_graph_capture_of_streams():
+    """Both products as streams, captured once and replayed with eager work on other tokens in between."""
+    d, h, n = 4096, 3328, 32
+    seed = synth.workload_seed(9, 107)
+    layer = custom_layer(d, h, "bf16", seed, 0.02, True)
+    ffn = make_ffn(layer)
+    L = T.tardis_fold(ffn, *T.tardis_calibrate(ffn, dev(synth.make_tokens(256, d, "bf16", seed, synth.STREAM_CAL), "bf16"), 0.85), max_batch=n)
+    x = dev(synth.make_tokens(n, d, "bf16", seed, synth.STREAM_TEST), "bf16")
+    want = T.tardis_ffn_forward_batched(L, x).clone()
+    masks = T.tardis_get_last_outliers(L, n, want_list=False)[0].clone()
+    torch.cuda.synchronize()
+    y = torch.zeros_like(want)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        T.tardis_ffn_forward_batched(L, x, y)
+    for _ in range(3):
+        y.zero_()
+        T.tardis_ffn_forward_batched(L, torch.roll(x, 1, 0).contiguous())
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(T.tardis_get_last_outliers(L, n, want_list=False)[0], masks)
+    L.close()
+
+
 @pytest.mark.parametrize("d,h,std", [(256, 1024, 0.1), (2048, 1024, 0.02)])
 @pytest.mark.parametrize("tiny", [0.0, 2.0 ** -110])
 def test_rows_without_a_scale(d, h, std, tiny):
